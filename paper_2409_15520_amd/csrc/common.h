@@ -185,12 +185,17 @@ struct MfmaGemmArgs {
 // k_splits a launch of these arguments would use given room for `partial_capacity` floats (1 = no split)
 int mfma_gemm_splits(const MfmaGemmArgs& a, size_t partial_capacity);
 bool mfma_gemm_supported(const MfmaGemmArgs& a);
+// will a dense [M, K] x [N, K]^T take the 256 x 256 tile (which fills the chip by itself)?
+bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights);
 int mfma_gemm_ce_slots(const MfmaGemmArgs& a);      // partial slots per row the launch will write (depends on the tile)
 // ce[m] = logsumexp over the slots - target logit (0 where ce_target[m] < 0)
 void launch_ce_combine(hipStream_t st, int slots, int M, const float* ce_max, const float* ce_sum, const float* ce_tlogit,
                        const int32_t* ce_target, float* ce);
 // hipSuccess, or the error of raising the kernel instance's dynamic LDS limit (then nothing was launched)
 hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a);
+// gemm_pipe.hip: the 256 x 256 tile (SwiGLU: 2 x 128 x 256) with operands fetched straight into LDS
+bool gemm_pipe_supported(const MfmaGemmArgs& a);
+hipError_t launch_gemm_pipe(hipStream_t st, const MfmaGemmArgs& a);
 
 struct MfmaLoraDownArgs {
   int T, K, rank, n_targets, rows_per_copy, rp;

@@ -9,24 +9,10 @@
 // are 8- or 16-byte accesses along the contiguous output dimension.
 #include <mutex>
 
-#include "common.h"
-#include "../../include/mpz.h"
+#include "gemm_tile.h"
 
 namespace mpz {
 namespace {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;     // 16-byte chunk in registers (native vector type)
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
-__device__ __forceinline__ bf16x8 as_frag(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-__device__ __forceinline__ float gelu_erf(float v) { return 0.5f * v * (1.0f + erff(v * 0.70710678118654752440f)); }
-// the same arithmetic as a real call: where all of a block's accumulators are live around it, inlining erff 128 times
-// would cost registers that the common path (no GELU) never needs
-__device__ __noinline__ float gelu_erf_call(float v) { return gelu_erf(v); }
 
 // Instruction interleave of one main-loop phase.  Issued as a burst, the tile's global loads occupy the address
 // path for ~16 cycles each and its LDS stores for ~8, during which the issuing wave cannot feed the matrix core:
@@ -382,224 +368,10 @@ gemm_bf16_kernel(MfmaGemmArgs a) {
       for (int i = 0; i < NI; ++i)
         acc[0][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pre_fw[j][i], pre_fx[j], acc[0][i][j], 0, 0, 0);
   } else if constexpr (!DUAL) {
-    for (int s = 0; s < a.n_seg && split == 0; ++s) {
-      const MfmaLoraSeg& sg = a.seg[s];
-      if (n0 < sg.col_begin || n0 >= sg.col_end) continue;
-      const uint16_t* tp = (const uint16_t*)sg.tp;
-      for (int ks = 0; ks < sg.rp; ks += 16) {
-        // all fragments of the step first, then its MFMAs: the block waits for L2 once per step, not once per tile
-        bf16x8 lx[NJ], lw[NJ][NI];
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          int mt = m0 + wm + j * 32;                       // first row of this MFMA tile
-          mt = mt < a.M ? mt : a.M - 32;                   // tiles past the end compute discarded values in bounds
-          const int copy = mt / a.rows_per_copy;
-          const uint16_t* bp = (const uint16_t*)sg.bp + (size_t)copy * sg.copy_stride;
-          lx[j] = as_frag(*(const u32x4*)(tp + (size_t)(mt + lrow) * sg.rp + ks + lhalf * 8));
-#pragma unroll
-          for (int i = 0; i < NI; ++i) {
-            const int n = n0 + wn + i * 32 + lrow - sg.col_begin;
-            lw[j][i] = as_frag(*(const u32x4*)(bp + (size_t)n * sg.rp + ks + lhalf * 8));
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-          for (int i = 0; i < NI; ++i)
-            acc[0][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lw[j][i], lx[j], acc[0][i][j], 0, 0, 0);
-      }
-    }
+    if (split == 0) add_low_rank<NI, NJ>(a, acc[0], m0, n0, wm, wn, lane);
   }
 
-  // Epilogue, part 1 (accumulator layout: a lane holds, for token m = lrow, features nb + g*8 + lhalf*4 + (0..3),
-  // g = 0..3, of every MFMA tile): bias, activation or gating, rotary embedding -- everything that needs no
-  // other token's data -- written back into acc[0].
-  const bool relu = !DUAL && a.act == MPZ_ACT_RELU;
-  if (!raw) {
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      int n = n0 + wn + i * 32 + g * 8 + lhalf * 4;
-      n = n < a.N ? n : 0;                                 // columns past N are never stored
-      f32x4 bg = {0.f, 0.f, 0.f, 0.f}, bu = bg;
-      if (a.bias != nullptr) {
-        bg = *(const f32x4*)(a.bias + n);
-        if (DUAL) bu = *(const f32x4*)(a.bias + a.dual_offset + n);
-      }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float v = acc[0][i][j][g * 4 + e] + bg[e];
-          if (DUAL) {
-            const float u = acc[NW - 1][i][j][g * 4 + e] + bu[e];
-            v = silu_mul_f32(v, u);                        // SiLU(gate) * up
-          } else {
-            v = (relu && !(v > 0.f)) ? 0.f : v;            // a select, not a branch per element
-          }
-          acc[0][i][j][g * 4 + e] = v;
-        }
-    }
-  }
-  if (!raw && !DUAL && a.act == MPZ_ACT_GELU_ERF) {                // rare (no workload of the paper uses it): one cold loop
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[0][i][j][e] = gelu_erf_call(acc[0][i][j][e]);
-  }
-  if constexpr (HP > 0) {
-    static_assert(!DUAL && NI >= 2 * HP && NI % (2 * HP) == 0, "a wave tile must hold whole heads");
-    if (!raw && n0 < a.rope_cols) {
-      // q / k columns: y_lo = x_lo cos - x_hi sin, y_hi = x_hi cos + x_lo sin with (lo, hi) = columns (c, c + d_head/2)
-      const int half = 32 * HP;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        int m = m0 + wm + j * 32 + lrow;
-        m = m < a.M ? m : a.M - 1;
-        const int pos = a.rope_pos != nullptr ? a.rope_pos[m % a.S] : m % a.S;
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-          if ((i / HP) % 2 != 0) continue;                  // upper halves are rotated together with their lower half
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int c = (i % HP) * 32 + g * 8 + lhalf * 4;  // column inside the lower half of the head
-            const f32x4 cs = *(const f32x4*)(a.rope_cos + (size_t)pos * half + c);
-            const f32x4 sn = *(const f32x4*)(a.rope_sin + (size_t)pos * half + c);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float lo = acc[0][i][j][g * 4 + e], hi = acc[0][i + HP][j][g * 4 + e];
-              // one rounded product, one fma: the same two operations as the stand-alone rotary kernel, so a pass
-              // that takes that kernel (tile too narrow for a whole head) gives the same bits
-              acc[0][i][j][g * 4 + e] = fmaf(lo, cs[e], -__fmul_rn(hi, sn[e]));
-              acc[0][i + HP][j][g * 4 + e] = fmaf(hi, cs[e], __fmul_rn(lo, sn[e]));
-            }
-          }
-        }
-      }
-    }
-  }
-
-  // Fused cross-entropy: the logits never leave the registers.  A lane holds NI * 16 columns of token row lrow
-  // (the other half of the row's columns sits in lane ^ 32): row maximum, sum of exponentials against it, and
-  // the target's logit if it falls into this wave tile.
-  if (a.ce_max != nullptr) {
-    constexpr float LOG2E = 1.4426950408889634f;
-    const int slot = (n0 / BN) * WGN + wave / WGM;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int m = m0 + wm + j * 32 + lrow;
-      const int tg = m < a.M ? a.ce_target[m] : -1;
-      float mx = -1e30f, tl = 0.f;
-      bool has = false;
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int n = n0 + wn + i * 32 + g * 8 + lhalf * 4 + e;
-            const float v = acc[0][i][j][g * 4 + e];
-            if (n < a.N) mx = v > mx ? v : mx;
-            if (n == tg) { tl = v; has = true; }
-          }
-      const float other = __shfl_xor(mx, 32);
-      mx = other > mx ? other : mx;
-      float sum = 0.f;
-#pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int n = n0 + wn + i * 32 + g * 8 + lhalf * 4 + e;
-            if (n < a.N) sum += __builtin_amdgcn_exp2f((acc[0][i][j][g * 4 + e] - mx) * LOG2E);
-          }
-      sum += __shfl_xor(sum, 32);
-      if (m < a.M) {
-        if (lhalf == 0) {
-          a.ce_max[(size_t)slot * a.M + m] = mx;
-          a.ce_sum[(size_t)slot * a.M + m] = sum;
-        }
-        if (has) a.ce_tlogit[m] = tl;
-      }
-    }
-    return;
-  }
-
-  // Epilogue, part 2: each wave turns its tile around in a private LDS strip, 32 tokens at a time, so that a lane
-  // ends up with 4 consecutive features of a token and consecutive lanes with consecutive features: residual reads
-  // and output stores then cover whole 128-byte lines (straight from the accumulator layout a store instruction
-  // would touch 32 token rows with 16 bytes each).
-  constexpr int EPS = TN + 4;                              // strip row stride in floats: conflict-free 16-byte columns
-  constexpr int LPR = TN / 4;                              // lanes per token row on the way out
-  float* ep = (float*)smem + wave * 32 * EPS;
-  __syncthreads();                                         // every wave is done with the operand stages
-  // With split K the raw sums of this split go out instead (fp32, no bias / activation / residual; both weight tiles
-  // of a dual launch, the second N columns to the right): partial[split][m][d N + n], row stride ldp.
-  const int nd = raw ? NW : 1;
-  const int ld = raw ? a.ldp : a.ldo;
-  float* const praw = raw ? a.partial + (size_t)split * a.M * a.ldp : nullptr;
-#pragma unroll
-  for (int d = 0; d < NW; ++d) {
-  if (d >= nd) break;
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 v = {acc[d][i][j][g * 4], acc[d][i][j][g * 4 + 1], acc[d][i][j][g * 4 + 2], acc[d][i][j][g * 4 + 3]};
-        *(f32x4*)(ep + lrow * EPS + i * 32 + g * 8 + lhalf * 4) = v;
-      }
-    // RB pieces at a time: all their residual loads are issued before the first is used (a piece past M or N reads
-    // a clamped, in-bounds address and is not stored), and the kind of output is decided outside the loops
-    constexpr int R = 32 * LPR / 64, RB = R % 8 == 0 ? 8 : 4;
-    static_assert(R % RB == 0, "pieces must deal out evenly to the batches");
-#pragma unroll
-    for (int r0 = 0; r0 < R; r0 += RB) {
-      f32x4 v[RB];
-      size_t o[RB];
-      bool ok[RB];
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        const int idx = (r0 + r) * 64 + lane, row = idx / LPR, c4 = idx % LPR;
-        const int m = m0 + wm + j * 32 + row, n = n0 + wn + c4 * 4;
-        ok[r] = m < a.M && n < a.N;
-        o[r] = (size_t)(m < a.M ? m : a.M - 1) * ld + (n < a.N ? n : 0) + (raw ? d * a.N : 0);
-        v[r] = *(const f32x4*)(ep + row * EPS + c4 * 4);
-      }
-      if (raw) {
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-          if (ok[r]) *(f32x4*)(praw + o[r]) = v[r];
-        continue;
-      }
-      if (a.residual != nullptr) {
-        f32x4 rs[RB];
-#pragma unroll
-        for (int r = 0; r < RB; ++r) rs[r] = *(const f32x4*)(a.residual + o[r]);
-#pragma unroll
-        for (int r = 0; r < RB; ++r) v[r] += rs[r];
-      }
-      if (a.out_f32) {
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-          if (ok[r]) *(f32x4*)((float*)a.out + o[r]) = v[r];
-      } else {
-#pragma unroll
-        for (int r = 0; r < RB; ++r)
-          if (ok[r]) {
-            u32x2 pk = {pack_bf16x2(v[r][0], v[r][1]), pack_bf16x2(v[r][2], v[r][3])};
-            *(u32x2*)((uint16_t*)a.out + o[r]) = pk;
-          }
-      }
-    }
-  }
-  }
+  gemm_epilogue<BN, WGN, WGM, NW, NI, NJ, HP>(a, acc, smem, m0, n0, wm, wn, wave, lane, raw, split);
 }
 
 // Measurement: what the memory system delivers to a read-only kernel whose access pattern is that of a GEMM's weight
@@ -1019,6 +791,16 @@ bool cfg_ok(const MfmaGemmArgs& a, int cfg) {
 // 64-feature tiles (twice the blocks); a dual launch has one tile shape.
 int split_tile_bn(const MfmaGemmArgs& a) { return (a.dual || a.N >= 8192 || a.K >= 8192 || a.w_scale != nullptr || a.w_absmax != nullptr) ? 128 : 64; }
 
+// Do `tiles` 256 x 256 tiles (one per CU at a time) beat the 128-wide ones?  Always from two full rounds of 256 CUs on.  Below
+// that the persistent kernel of gemm_pipe.hip wins once its last round fills five eighths of the chip: K = 4096, 128 / 192 /
+// 256 / 384 tiles: 82 / 89 / 96 / 168 us against 72 / 107 / 138 / 208 us for the same product in 128 x 128 tiles; K = 2048, 128 / 160 /
+// 256 / 320 tiles: 47 / 47 / 55 / 89 against 39 / 53 / 74 / 92.  At K = 1024 a second round no longer pays (352 tiles: 56 against
+// 55, 176 tiles: 30 against 34), at K = 768 neither does the first (192 tiles: 28 against 27).
+bool large_tiles_pay(long tiles, int K) {
+  const long rounds = (tiles + 255) / 256;
+  return tiles >= 512 || (tiles * 8 >= rounds * 256 * 5 && K >= (rounds == 1 ? 1024 : 2048));
+}
+
 int choose_cfg(const MfmaGemmArgs& a) {
   // split K (at most 256 stacked tokens): a block takes all the tokens it can (the weights are then fetched from HBM
   // once) and as few output features as the low-rank segments allow, so that there are many blocks to stream them
@@ -1030,12 +812,8 @@ int choose_cfg(const MfmaGemmArgs& a) {
   }
   const bool forced_ok = a.w_scale == nullptr || a.tile_cfg == 1 || a.tile_cfg == 6 || a.tile_cfg == 11 || a.tile_cfg == 12;   // int8: fewer instances
   if (forced_ok && known_cfg(a.tile_cfg) && cfg_ok(a, a.tile_cfg)) return a.tile_cfg;
-  // enough 256 x 256 tiles to keep 256 CUs busy for several rounds -> biggest tile; else the largest tile that
-  // still gives at least ~2 blocks per CU
-  // The L2 -> CU path feeds about 64 B/clk per CU, which a 128 x 128 tile needs in full at MFMA peak; 256 x 256
-  // halves that.  Use the big tile (8 waves of 128 x 64) once it yields two or more rounds of blocks on 256 CUs.
   const long t5 = (long)((a.N + 255) / 256) * ((a.M + 255) / 256);
-  if (t5 >= 512 && cfg_ok(a, 6)) return 6;   // BK 64 with two tiles in flight: 128 KB of loads outstanding per CU
+  if (cfg_ok(a, 6) && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, a.K)))) return 6;
   // 128 x 128 tiles that fill between one and two blocks per CU leave half the chip with twice the work of the
   // other half; 192 x 128 tiles, one per CU, balance it (N = 768 projections of the 125M-class models)
   const long t1 = (long)((a.N + 127) / 128) * ((a.M + 127) / 128), t11 = (long)((a.N + 191) / 192) * ((a.M + 127) / 128);
@@ -1082,6 +860,11 @@ __global__ void __launch_bounds__(256) ce_combine_kernel(int slots, int M, const
 }
 
 }  // namespace
+
+bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights) {
+  const long t5 = (long)((N + 255) / 256) * ((M + 255) / 256);
+  return t5 >= 512 || (bf16_weights && K % 128 == 0 && N % 8 == 0 && large_tiles_pay(t5, K));
+}
 
 int mfma_gemm_ce_slots(const MfmaGemmArgs& a0) {
   MfmaGemmArgs a = a0;
@@ -1236,12 +1019,16 @@ hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a) {
   }
   if (a.dual) {
     const long tb = (long)((a.N + 127) / 128) * ((a.M + 255) / 256);
-    if ((a.tile_cfg == 0 && tb >= 512) || a.tile_cfg == 6)                 // 2 x 128 x 256, 8 waves
+    const bool pipe = gemm_pipe_supported(a);
+    if ((a.tile_cfg == 0 && (tb >= 512 || (pipe && large_tiles_pay(tb, a.K)))) || a.tile_cfg == 6) {               // 2 x 128 x 256
+      if (pipe) return launch_gemm_pipe(st, a);
       return q8 ? launch_cfg<128, 256, 64, 2, 4, true, 0, true>(st, a) : launch_cfg<128, 256, 64, 2, 4, true>(st, a);
+    }
     return q8 ? launch_cfg<128, 128, 32, 2, 2, true, 0, true>(st, a) : launch_cfg<128, 128, 32, 2, 2, true>(st, a);
   }
   if (a.rope_cos != nullptr) {             // fused rotary epilogue: only the configurations the model path uses
     const int cfg = choose_cfg(a);
+    if (cfg == 6 && gemm_pipe_supported(a)) return launch_gemm_pipe(st, a);
     if (cfg == 6) {
       if (a.rope_dh == 64) return q8 ? launch_cfg<256, 256, 64, 2, 4, false, 1, true>(st, a) : launch_cfg<256, 256, 64, 2, 4, false, 1>(st, a);
       return q8 ? launch_cfg<256, 256, 64, 2, 4, false, 2, true>(st, a) : launch_cfg<256, 256, 64, 2, 4, false, 2>(st, a);
@@ -1257,6 +1044,7 @@ hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a) {
       default: return launch_cfg<128, 128, 64, 2, 2, false, 0, true>(st, a);
     }
   }
+  if (choose_cfg(a) == 6 && gemm_pipe_supported(a)) return launch_gemm_pipe(st, a);
   switch (choose_cfg(a)) {
     case 6: return launch_cfg<256, 256, 64, 2, 4, false>(st, a);     // 8 waves of 128 x 64, BK 64 (147 KB LDS), 128 KB in flight
     case 9: return launch_cfg<128, 64, 64, 2, 2, false>(st, a);      // 4 waves of 64 x 32: more, smaller blocks
