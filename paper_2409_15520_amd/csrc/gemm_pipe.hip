@@ -59,40 +59,52 @@ __device__ __forceinline__ void pipe_ce_partials(const MfmaGemmArgs& a, f32x4 (&
   constexpr float LOG2E = 1.4426950408889634f;
   const int l16 = lane & 15, lq = lane >> 4;
   const int slot = (n0 / BN) * WGN + wave / WGM, nl = n0 + wn + lq * 4;
+  const bool whole = n0 + wn + NI * 16 <= a.N;           // (uniform) all columns of the wave tile exist
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     __builtin_amdgcn_sched_barrier(0);
     const int m = m0 + wm + j * 16 + l16;
     const int tg = m < a.M ? a.ce_target[m] : -1;
-    float mx = -1e30f, tl = 0.f;
-    bool has = false;
+    float mx = -1e30f, sum = 0.f;
+    if (whole) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+      for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int n = nl + i * 16 + e;
-        const float v = acc[0][i][j][e];
-        mx = n < a.N && v > mx ? v : mx;
-        tl = n == tg ? v : tl;
-        has = has || n == tg;
-      }
-    float other = __shfl_xor(mx, 16);
-    mx = other > mx ? other : mx;
-    other = __shfl_xor(mx, 32);
-    mx = other > mx ? other : mx;
-    float sum = 0.f;
+        for (int e = 0; e < 4; ++e) mx = fmaxf(mx, acc[0][i][j][e]);
+    } else {
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+      for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        sum += nl + i * 16 + e < a.N ? __builtin_amdgcn_exp2f((acc[0][i][j][e] - mx) * LOG2E) : 0.f;
+        for (int e = 0; e < 4; ++e) mx = nl + i * 16 + e < a.N && acc[0][i][j][e] > mx ? acc[0][i][j][e] : mx;
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    if (whole) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum += __builtin_amdgcn_exp2f((acc[0][i][j][e] - mx) * LOG2E);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          sum += nl + i * 16 + e < a.N ? __builtin_amdgcn_exp2f((acc[0][i][j][e] - mx) * LOG2E) : 0.f;
+    }
     sum += __shfl_xor(sum, 16);
     sum += __shfl_xor(sum, 32);
-    if (m < a.M) {
-      if (lq == 0) {
-        a.ce_max[(size_t)slot * a.M + m] = mx;
-        a.ce_sum[(size_t)slot * a.M + m] = sum;
-      }
+    if (m < a.M && lq == 0) {
+      a.ce_max[(size_t)slot * a.M + m] = mx;
+      a.ce_sum[(size_t)slot * a.M + m] = sum;
+    }
+    const int rel = tg - nl;                             // the target's column among this lane's: 16 i + e
+    const bool has = rel >= 0 && rel < NI * 16 && (rel & 15) < 4;
+    if (__ballot(has) != 0) {                            // one tile in many holds a row's target
+      float tl = 0.f;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tl = rel == i * 16 + e ? acc[0][i][j][e] : tl;
       if (has) a.ce_tlogit[m] = tl;
     }
   }
@@ -133,7 +145,7 @@ struct PipeOut {
 // nothing hides an instruction here, so there are few, and no branches (the compiler spills accumulators around them):
 // outputs and residuals are buffers that start at the wave's first element and end with the matrix, so rows past M fall
 // outside, and the lanes of columns past N aim outside.
-template <bool DUAL, int EPI, bool BIAS, bool RELU, bool RES, int NW, int NI, int NJ, int BN, int WGN, int WGM, int NRS>
+template <bool DUAL, int EPI, bool BIAS, bool RELU, bool RES, int NW, int NI, int NJ, int BN, int WGN, int WGM, bool RES1, int NRS>
 __device__ __forceinline__ void pipe_epilogue(const MfmaGemmArgs& a, f32x4 (&acc)[NW][NI][NJ], u32x4 (&rs)[NRS][8], unsigned char* strip, int m0, int n0,
                                               int wm, int wn, int wave, int lane) {
   const int l16 = lane & 15, lq = lane >> 4;
@@ -152,7 +164,10 @@ __device__ __forceinline__ void pipe_epilogue(const MfmaGemmArgs& a, f32x4 (&acc
         const int hf = q / 4, j = q % 4;
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (RES) {
-          if (q == 0) out.read(rs[2], 2);
+          if (q == 0) {
+            if constexpr (!RES1) out.read(rs[1], 1);
+            out.read(rs[2], 2);
+          }
           if (q + 3 < NJ) out.read(rs[(q + 3) & 3], q + 3);
         }
         const int n = nw + hf * 64 + cc * FPC;
@@ -185,12 +200,34 @@ __device__ __forceinline__ void pipe_epilogue(const MfmaGemmArgs& a, f32x4 (&acc
           if (DUAL) bu[i] = *(const f32x4*)(a.bias + a.dual_offset + n);
         }
       }
+      // rotary tables of token tile j: cosines and sines of the lower half's features, requested one token tile ahead
+      constexpr bool ROPE = EPI == PIPE_ROPE64 || EPI == PIPE_ROPE128;
+      constexpr int HP = EPI == PIPE_ROPE128 ? 4 : 2, HALF = 16 * HP;
+      f32x4 cs[2][ROPE ? HP : 1], sn[2][ROPE ? HP : 1];
+      const float inv_s = ROPE ? 1.0f / (float)a.S : 0.f;
+      auto tables = [&](int j) {
+        int m = mw + j * 16 + l16;
+        m = m < a.M ? m : a.M - 1;
+        int p = m - (int)((float)m * inv_s) * a.S;       // m % S: m < 2^24 is exact in binary32, the quotient off by one at most
+        p = p < 0 ? p + a.S : p;
+        p = p >= a.S ? p - a.S : p;
+        if (a.rope_pos != nullptr) p = a.rope_pos[p];
+#pragma unroll
+        for (int i = 0; i < HP; ++i) {
+          cs[j & 1][i] = *(const f32x4*)(a.rope_cos + (size_t)p * HALF + i * 16 + lq * 4);
+          sn[j & 1][i] = *(const f32x4*)(a.rope_sin + (size_t)p * HALF + i * 16 + lq * 4);
+        }
+      };
+      if constexpr (ROPE) tables(0);
 #pragma unroll
       for (int j2 = 0; j2 < NJ / 2; ++j2) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const int j = j2 * 2 + h, lrow = h * 16 + l16;   // token tile, row of the strip
+          if constexpr (ROPE) {
+            if (j + 1 < NJ) tables(j + 1);
+          }
           f32x4 v[NI];
 #pragma unroll
           for (int i = 0; i < NI; ++i) {
@@ -207,24 +244,18 @@ __device__ __forceinline__ void pipe_epilogue(const MfmaGemmArgs& a, f32x4 (&acc
               for (int e = 0; e < 4; ++e) v[i][e] = v[i][e] > 0.f ? v[i][e] : 0.f;
             }
           }
-          if constexpr (EPI == PIPE_ROPE64 || EPI == PIPE_ROPE128) {
+          if constexpr (ROPE) {
             // q / k columns: y_lo = x_lo cos - x_hi sin, y_hi = x_hi cos + x_lo sin with (lo, hi) = columns (c, c + d_head/2); one
             // rounded product and one fma each, as in the stand-alone rotary kernel (same bits); v columns stay
-            constexpr int HP = EPI == PIPE_ROPE64 ? 2 : 4, half = 16 * HP;
             const bool rot = n0 < a.rope_cols;
-            int m = mw + j * 16 + l16;
-            m = m < a.M ? m : a.M - 1;
-            const int pos = a.rope_pos != nullptr ? a.rope_pos[m % a.S] : m % a.S;
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
               if ((i / HP) % 2 != 0) continue;
-              const int c = (i % HP) * 16 + lq * 4;
-              const f32x4 cs = *(const f32x4*)(a.rope_cos + (size_t)pos * half + c);
-              const f32x4 sn = *(const f32x4*)(a.rope_sin + (size_t)pos * half + c);
+              const f32x4 c = cs[j & 1][i % HP], s = sn[j & 1][i % HP];
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
                 const float lo = v[i][e], hi = v[i + HP][e];
-                const float rl = fmaf(lo, cs[e], -__fmul_rn(hi, sn[e])), rh = fmaf(hi, cs[e], __fmul_rn(lo, sn[e]));
+                const float rl = fmaf(lo, c[e], -__fmul_rn(hi, s[e])), rh = fmaf(hi, c[e], __fmul_rn(lo, s[e]));
                 v[i][e] = rot ? rl : lo;
                 v[i + HP][e] = rot ? rh : hi;
               }
@@ -451,11 +482,40 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(MfmaGemmArgs a) {
     PIN();
     const int cn0 = n0, cm0 = m0;
     const bool more = tile + PIPE_BLOCKS < nblk;
-    u32x4 rs[EPI == PIPE_F32 && (FL & 2) ? 4 : 1][8];
-    if constexpr (EPI == PIPE_F32 && (FL & 2)) {           // the residual of the first 64 tokens travels behind the K loop
+    // What the end of the tile needs and is known now travels behind the K loop: the residual of the first tokens and the
+    // low-rank operands of the first 32 or 64.  Copies are whole multiples of 32 rows, so a 32-row piece belongs to one copy;
+    // segments begin and end on tile borders.  Tiles outside every segment multiply zeros.
+    constexpr bool RES = EPI == PIPE_F32 && (FL & 2);
+    u32x4 rs[RES ? 4 : 1][8];
+    if constexpr (RES) {
       const PipeOut<4> o(a, cm0 + wm, cn0 + wn, lane);
       o.read(rs[0], 0);
-      o.read(rs[1], 1);
+      if constexpr (LR == 0) o.read(rs[1], 1);
+    }
+    u32x4 lx[LR ? NJ / 2 : 1][2], lw[LR ? NJ / 2 : 1][NI];
+    int seg = 0;
+    bool in = false;
+    const bool part = LR == 2 || lq < 2;
+    if constexpr (LR > 0) {
+      for (int s = 0; s < a.n_seg; ++s)
+        if (cn0 >= a.seg[s].col_begin && cn0 < a.seg[s].col_end) { seg = s; in = true; }
+    }
+    auto low_rank_load = [&](int j2) {                     // operands of 32 tokens
+      const MfmaLoraSeg& sg = a.seg[seg];
+      const int col = in ? cn0 + wn + l16 - sg.col_begin : l16, k8 = part ? lq * 8 : 0;
+      int mt = cm0 + wm + j2 * 32;
+      mt = mt < a.M ? mt : a.M - 32;                       // tiles past the end compute discarded values in bounds
+      const uint16_t* tr = (const uint16_t*)sg.tp + (size_t)(mt + l16) * (16 * LR) + k8;
+      const uint16_t* bp = (const uint16_t*)sg.bp + (size_t)(mt / a.rows_per_copy) * sg.copy_stride + (size_t)col * (16 * LR) + k8;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) lx[j2][j] = *(const u32x4*)(tr + j * 16 * 16 * LR);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) lw[j2][i] = *(const u32x4*)(bp + (in ? i * 16 * 16 * LR : 0));
+    };
+    if constexpr (LR > 0) {
+      low_rank_load(0);
+      if constexpr (!RES) low_rank_load(1);
+      __builtin_amdgcn_sched_barrier(0);
     }
     // the last two K-tiles fetch the next tile's first two (without a next tile: this one's again)
     if (more) place(tile + PIPE_BLOCKS, n0, m0);
@@ -476,48 +536,30 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(MfmaGemmArgs a) {
     // the matrix cores write their last results behind this; the fetches of the next tile's first two K-tiles land
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     if constexpr (LR > 0) {
-      // per-copy low-rank term: LR more K-steps, [B_hi | B_lo] of a copy against the duplicated bottleneck activations
-      // [t | t].  Copies are whole multiples of 32 rows, so a 32-row MFMA tile belongs to one copy; segments begin and end
-      // on tile borders.  Tiles outside every segment multiply zeros (no branch: see the epilogue).
-      int seg = 0;
-      bool in = false;
-      for (int s = 0; s < a.n_seg; ++s)
-        if (cn0 >= a.seg[s].col_begin && cn0 < a.seg[s].col_end) { seg = s; in = true; }
-      const MfmaLoraSeg& sg = a.seg[seg];
+      // per-copy low-rank term: one more K-step, [B_hi | B_lo] of a copy against the duplicated bottleneck activations [t | t]
+      // (rank <= 8: its upper half is zero).  The operands of the last 64 tokens travel while the first are multiplied.
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (RES) low_rank_load(1);
+      low_rank_load(2);
+      low_rank_load(3);
+      __builtin_amdgcn_sched_barrier(0);
       const u32x4 zero = {0u, 0u, 0u, 0u};
-      const int col = in ? cn0 + wn + l16 - sg.col_begin : l16;
-      const bool part = LR == 2 || lq < 2;                 // rank <= 8: the upper half of the K-step is zero
-      u32x4 lx[2][2], lw[2][NI];
-      auto low_rank_load = [&](int j2) {                   // 32 tokens: the next ones are requested before these are multiplied
-        int mt = cm0 + wm + j2 * 32;
-        mt = mt < a.M ? mt : a.M - 32;                     // tiles past the end compute discarded values in bounds
-        const int k8 = part ? lq * 8 : 0;
-        const uint16_t* tr = (const uint16_t*)sg.tp + (size_t)(mt + l16) * (16 * LR) + k8;
-        const uint16_t* bp = (const uint16_t*)sg.bp + (size_t)(mt / a.rows_per_copy) * sg.copy_stride + (size_t)col * (16 * LR) + k8;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) lx[j2 & 1][j] = *(const u32x4*)(tr + j * 16 * 16 * LR);
-#pragma unroll
-        for (int i = 0; i < NI; ++i) lw[j2 & 1][i] = *(const u32x4*)(bp + (in ? i * 16 * 16 * LR : 0));
-      };
-      low_rank_load(0);
 #pragma unroll
       for (int j2 = 0; j2 < NJ / 2; ++j2) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (j2 + 1 < NJ / 2) low_rank_load(j2 + 1);
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) lx[j2 & 1][j] = in && part ? lx[j2 & 1][j] : zero;
+        for (int j = 0; j < 2; ++j) lx[j2][j] = in && part ? lx[j2][j] : zero;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) lw[j2 & 1][i] = part ? lw[j2 & 1][i] : zero;
+        for (int i = 0; i < NI; ++i) lw[j2][i] = part ? lw[j2][i] : zero;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
           for (int i = 0; i < NI; ++i)
-            acc[0][i][j2 * 2 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(lw[j2 & 1][i]), as_frag(lx[j2 & 1][j]), acc[0][i][j2 * 2 + j], 0, 0, 0);
+            acc[0][i][j2 * 2 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(lw[j2][i]), as_frag(lx[j2][j]), acc[0][i][j2 * 2 + j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    pipe_epilogue<DUAL, EPI, (FL & 1) != 0, (FL & 2) != 0 && EPI != PIPE_F32, (FL & 2) != 0 && EPI == PIPE_F32, NW, NI, NJ, BN, WGN, WGM>(a, acc, rs, smem + 2 * STAGE + wave * 8192, cm0, cn0, wm, wn, wave, lane);
+    pipe_epilogue<DUAL, EPI, (FL & 1) != 0, (FL & 2) != 0 && EPI != PIPE_F32, (FL & 2) != 0 && EPI == PIPE_F32, NW, NI, NJ, BN, WGN, WGM, LR == 0>(a, acc, rs, smem + 2 * STAGE + wave * 8192, cm0, cn0, wm, wn, wave, lane);
     if (!more) break;
     tile += PIPE_BLOCKS;
   }
@@ -555,7 +597,8 @@ hipError_t launch_pipe_lr(hipStream_t st, const MfmaGemmArgs& a) {
 }  // namespace
 
 // bf16 weights, whole pairs of K-tiles, 16-byte output pieces that begin on 16 bytes; no GELU (erf around 256 live
-// accumulators spills); the low-rank term with one bottleneck of rank <= 16 per segment and no activation behind it.  What is
+// accumulators spills); the low-rank term with rank <= 16,
+// copies of whole 32-row pieces and no activation behind it.  What is
 // refused takes the tile of the same size in gemm_mfma.hip.
 bool gemm_pipe_supported(const MfmaGemmArgs& a) {
   if (a.w_scale != nullptr || a.w_absmax != nullptr || a.k_splits > 1 || a.K % 128 || a.act == MPZ_ACT_GELU_ERF) return false;
@@ -565,7 +608,7 @@ bool gemm_pipe_supported(const MfmaGemmArgs& a) {
   if (!a.out_f32 && a.residual != nullptr) return false;
   if (a.dual || a.rope_cos != nullptr) { if (a.out_f32) return false; }
   else if (a.act >= 0 && (a.out_f32 || a.n_seg || a.act != MPZ_ACT_RELU)) return false;
-  if (a.out_f32 && a.n_seg && a.residual == nullptr) return false;
+  if (a.n_seg && (a.rows_per_copy % 32 || a.M % 32 || (a.out_f32 && a.residual == nullptr))) return false;
   for (int s = 0; s < a.n_seg; ++s)
     if (a.seg[s].rp != a.seg[0].rp || (a.seg[s].rp != 16 && a.seg[s].rp != 32)) return false;
   return true;
