@@ -293,7 +293,8 @@ gemm_bf16_kernel(MfmaGemmArgs a) {
   bf16x8 pre_fw[PREF ? NJ : 1][PREF ? NI : 1], pre_fx[PREF ? NJ : 1];
   int pre_seg = -1;
   if constexpr (PREF) {
-    for (int s = 0; s < a.n_seg && split == 0; ++s)          // (with split K the low-rank term goes into split 0's sum)
+    // (with split K the low-rank term goes into split 0's sum; tiles of several copies: no early request)
+    for (int s = 0; s < a.n_seg && split == 0 && a.rows_per_copy % 32 == 0; ++s)
       if (n0 >= a.seg[s].col_begin && n0 < a.seg[s].col_end && a.seg[s].rp == 16) pre_seg = s;
     if (pre_seg >= 0) {
       const MfmaLoraSeg& sg = a.seg[pre_seg];
@@ -519,9 +520,11 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
   __shared__ float part[3][JT][16][64];          // partial sums of waves 1..3
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lrow = lane & 31, lhalf = lane >> 5;
   const int m0 = blockIdx.x * 32;
-  const int copy = m0 / a.rows_per_copy;
   const int R = a.n_targets * a.rank;
   const uint16_t* X = (const uint16_t*)a.x + (size_t)m0 * a.K;
+  // 32 rows of one copy, or (copies that are no multiples of 32 rows) of several: one pass per copy, each storing its rows
+  const int m_last = m0 + 31 < a.T ? m0 + 31 : a.T - 1, last_copy = m_last / a.rows_per_copy;
+  for (int copy = m0 / a.rows_per_copy; copy <= last_copy; ++copy) {
   // packed A: per copy and target [2][K / 8][rank][8] (hi part then lo part): the 16-byte pieces that the lanes of
   // a wave fetch for one MFMA operand (rank rows x 2 neighbouring chunks of 8 k) are contiguous
   const uint16_t* Ah[JT];
@@ -548,6 +551,9 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
   int grow[4], gcol[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) { int p = tid + 256 * i; grow[i] = p >> 5; gcol[i] = (p & 31) * 8; }
+  int xrow[4];                                   // the row to fetch: rows past T fetch the last one, and are not stored
+#pragma unroll
+  for (int i = 0; i < 4; ++i) xrow[i] = m0 + grow[i] < a.T ? grow[i] : m_last - m0;
   // three chunks of x in flight (registers), three LDS buffers: a K = 768 row is fetched in one go
   constexpr int PD = 3;
   u32x4 st[PD][4];
@@ -556,7 +562,7 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
   for (int p = 0; p < PD; ++p)
     if (p < nch) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) st[p][i] = *(const u32x4*)(X + (size_t)grow[i] * a.K + p * KCH + gcol[i]);
+      for (int i = 0; i < 4; ++i) st[p][i] = *(const u32x4*)(X + (size_t)xrow[i] * a.K + p * KCH + gcol[i]);
     }
   for (int ch0 = 0; ch0 < nch; ch0 += PD) {
 #pragma unroll
@@ -583,7 +589,7 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
       for (int i = 0; i < 4; ++i) *(u32x4*)(buf + grow[i] * XS + gcol[i]) = st[p][i];
       if (ch + PD < nch) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) st[p][i] = *(const u32x4*)(X + (size_t)grow[i] * a.K + (ch + PD) * KCH + gcol[i]);
+        for (int i = 0; i < 4; ++i) st[p][i] = *(const u32x4*)(X + (size_t)xrow[i] * a.K + (ch + PD) * KCH + gcol[i]);
       }
       __syncthreads();                             // chunk ch visible; its buffer was last read three chunks ago
 #pragma unroll
@@ -604,13 +610,13 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
       for (int e = 0; e < 16; ++e) part[wave - 1][t][e][lane] = acc[t][e];
   }
   __syncthreads();
-  if (wave != 0) return;
+  const int m = m0 + lrow;
+  if (wave == 0 && m < a.T && m / a.rows_per_copy == copy) {
 #pragma unroll
   for (int t = 0; t < JT; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = ((acc[t][e] + part[0][t][e][lane]) + part[1][t][e][lane]) + part[2][t][e][lane];
   // lane holds token m0 + lrow, bottleneck columns j = t*32 + g*8 + lhalf*4 + e
-  const int m = m0 + lrow;
   // (ranks are multiples of 4: the 4 consecutive columns of a lane belong to one target and go out as one 8-byte store)
 #pragma unroll
   for (int t = 0; t < JT; ++t)
@@ -629,6 +635,9 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
   if (lhalf == 0)
     for (int tgt = 0; tgt < a.n_targets; ++tgt)
       for (int c = 2 * a.rank; c < a.rp; ++c) ((uint16_t*)a.tp[tgt])[(size_t)m * a.rp + c] = 0;
+  }
+  if (copy < last_copy) __syncthreads();         // the sums of this copy are read before the next ones are written
+  }
 }
 
 // ---- pack the perturbed fp32 factors into the bf16 hi/lo operand layouts ---------------------------------
@@ -781,7 +790,6 @@ bool known_cfg(int cfg) { return cfg == 1 || cfg == 6 || (cfg >= 9 && cfg <= 13)
 bool cfg_ok(const MfmaGemmArgs& a, int cfg) {
   const int bn = tile_bn(cfg), bm = tile_bm(cfg);
   (void)bm;
-  if (a.n_seg > 0 && (a.rows_per_copy % 32 || a.M % 32)) return false;
   for (int s = 0; s < a.n_seg; ++s)
     if (a.seg[s].col_begin % bn || a.seg[s].col_end % bn) return false;
   return true;
@@ -1084,13 +1092,13 @@ void launch_mfma_probe(hipStream_t st, const void* operands, int blocks, int ite
 
 bool mfma_lora_down_supported(const MfmaLoraDownArgs& a) {
   int R = a.n_targets * a.rank;
-  return a.K % 256 == 0 && a.T % 32 == 0 && a.rows_per_copy % 32 == 0 && R <= 64 && a.rp % 8 == 0 && a.rank % 4 == 0;
+  return a.K % 256 == 0 && R <= 64 && a.rp % 8 == 0 && a.rank % 4 == 0;
 }
 
 void launch_lora_down_mfma(hipStream_t st, const MfmaLoraDownArgs& a) {
   int R = a.n_targets * a.rank;
-  if (R <= 32) lora_down_mfma_kernel<1><<<a.T / 32, 256, 0, st>>>(a);
-  else lora_down_mfma_kernel<2><<<a.T / 32, 256, 0, st>>>(a);
+  if (R <= 32) lora_down_mfma_kernel<1><<<(a.T + 31) / 32, 256, 0, st>>>(a);
+  else lora_down_mfma_kernel<2><<<(a.T + 31) / 32, 256, 0, st>>>(a);
 }
 
 void launch_pack_factors(hipStream_t st, const float* pert, int64_t P, int n_copies, const LoraLayerTable& tab,
