@@ -74,6 +74,14 @@ struct LoraSeg {              // one adapted column range of a linear
   int64_t copy_stride;
 };
 
+// fp32_kernels.hip: fp32 models on v_mfma_f64 and wave reductions; false (nothing launched): shape or alignment not taken
+struct LinearArgs;
+struct LoraDownArgs;
+bool launch_linear_f64(hipStream_t st, const LinearArgs& a);
+bool launch_lora_down_f64(hipStream_t st, const LoraDownArgs& a);
+bool launch_attention_f64(hipStream_t st, int dtype, const void* qkv, int qkv_stride, void* out, int n_seq, int S, int H, int Hkv, int dh,
+                          const int32_t* cu, int E, int rows_per_copy);
+
 struct MfmaLoraSeg {
   int32_t col_begin, col_end;   // adapted output columns, multiples of 128
   const void* tp;               // [T, rp] bf16: [t | t | 0], t = OP(s x A_c)

@@ -11,7 +11,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 // out = epilogue(x W^T) on tiles of 16 WT x 16 WT, one block per tile, its four waves a quarter of K each.  Bound by latency at
-// the sizes of the tiny models (256 x 128 x 512: 49 us -> 8 us for all its linears together) and by the fp64 matrix rate
+// the sizes of the tiny models (a whole step of 2 blocks of d = 128 over 256 rows: 485 us with the shape-agnostic kernels, 117 us
+// with those of this file; a 125M-shaped block over 768 rows: 1348 us, 363 us) and by the fp64 matrix rate
 // (72 TFLOP/s in the library) above: 768 x 2304 x 768.  Splitting K over the waves of a block, and not tiles, is what gives
 // small outputs enough wavefronts; operands come straight from L2 (a 32 x 32 tile needs 16 bytes per clock and CU).
 // MFMA layout: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16] and, of the result, D[l / 16 + 4 r][l % 16], r = 0..3.  Of
