@@ -475,11 +475,13 @@ void launch_norm(hipStream_t st, int dtype, int kind, float eps, const float* h,
 }
 
 void launch_lora_down_simple(hipStream_t st, const LoraDownArgs& a) {
+  if (launch_lora_down_f64(st, a)) return;
   int64_t total = (int64_t)a.T * a.n_targets * a.rank;
   MPZ_DISPATCH(a.dtype, (lora_down_kernel<ST><<<nblk(total, 256), 256, 0, st>>>(a)));
 }
 
 void launch_linear_simple(hipStream_t st, const LinearArgs& a) {
+  if (launch_linear_f64(st, a)) return;
   dim3 grid((a.N + 63) / 64, (a.M + 63) / 64);
   MPZ_DISPATCH(a.dtype, (linear_kernel<ST><<<grid, 256, 0, st>>>(a)));
 }
@@ -493,6 +495,7 @@ void launch_rope_convert(hipStream_t st, int dtype, const void* staging, void* o
 
 void launch_attention_simple(hipStream_t st, int dtype, const void* qkv, int qkv_stride, void* out, int n_seq, int S, int H,
                              int Hkv, int dh, const int32_t* cu, int E, int rows_per_copy) {
+  if (launch_attention_f64(st, dtype, qkv, qkv_stride, out, n_seq, S, H, Hkv, dh, cu, E, rows_per_copy)) return;
   unsigned blocks = (unsigned)((int64_t)n_seq * H * S);
   MPZ_DISPATCH(dtype, (attention_kernel<ST><<<blocks, 64, (size_t)(S + dh) * sizeof(typename Traits<ST>::AT), st>>>(
                           (const ST*)qkv, qkv_stride, (ST*)out, S, H, Hkv, dh, (float)(1.0 / sqrt((double)dh)), cu, E,
@@ -506,13 +509,11 @@ void launch_swiglu(hipStream_t st, int dtype, const void* staging, void* out, in
 
 void launch_ce_rows(hipStream_t st, int dtype, const float* logits, int64_t row_stride, int n_cols, const int32_t* target,
                     float* ce, int rows) {
-  if (launch_lora_down_f64(st, a)) return;
   if (dtype == MPZ_DTYPE_F32) ce_rows_kernel<double><<<rows, 256, 0, st>>>(logits, row_stride, n_cols, target, ce);
   else ce_rows_kernel<float><<<rows, 256, 0, st>>>(logits, row_stride, n_cols, target, ce);
 }
 
 void launch_last_pos_subset_logits(hipStream_t st, int dtype, const void* xf, const void* head, int d, int rows, int tok0,
-  if (launch_linear_f64(st, a)) return;
                                    int tok1, float* logits2) {
   MPZ_DISPATCH(dtype, (subset_logits_kernel<ST><<<rows, 64, 0, st>>>((const ST*)xf, (const ST*)head, d, tok0, tok1, logits2)));
 }
@@ -526,7 +527,6 @@ void launch_make_targets(hipStream_t st, int mode, const int32_t* tokens, const 
                          const int32_t* row_end, int tok0, int tok1, int32_t* target, int n_copies, int E, int S) {
   int64_t n = (mode == MPZ_LOSS_NEXT_TOKEN_ALL_POS) ? (int64_t)n_copies * E * S : (int64_t)n_copies * E;
   make_targets_kernel<<<nblk(n, 256), 256, 0, st>>>(mode, tokens, labels, lengths, row_end, tok0, tok1, target, n_copies, E, S);
-  if (launch_attention_f64(st, dtype, qkv, qkv_stride, out, n_seq, S, H, Hkv, dh, cu, E, rows_per_copy)) return;
 }
 
 void launch_packed_index(hipStream_t st, const int32_t* cu, int E, int rows, int32_t* row_pos, int32_t* row_end) {
