@@ -22,31 +22,11 @@
 // reads without bank conflicts; the fetch applies that order through each lane's global address.
 #include <mutex>
 
+#include "fetch.h"
 #include "gemm_tile.h"
 
 namespace mpz {
 namespace {
-
-typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
-
-// (s_nop: one wait state between the write of m0 and the fetch that reads it)
-// One wave instruction fetches 8 rows of 128 bytes (64 lanes x 16 bytes) from a raw buffer into 1 KiB of LDS at byte
-// `lds`, in lane order.  It has no destination register; its completion is counted by vmcnt.  (The builtin is not used:
-// the compiler would make every later LDS read wait for the fetch.)
-__device__ __forceinline__ void fetch_rows(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(soff), "s"(lds)
-               : "memory");
-}
-
-__device__ __forceinline__ i32x4 buffer_of(const void* p, size_t bytes) {
-  const uint64_t b = (uint64_t)p;
-  i32x4 r;
-  r[0] = (int)(uint32_t)b;
-  r[1] = (int)((uint32_t)(b >> 32) & 0xFFFFu);
-  r[2] = (int)(uint32_t)bytes;
-  r[3] = 0x00020000;
-  return r;
-}
 
 enum { PIPE_BF16 = 0, PIPE_ROPE64 = 1, PIPE_ROPE128 = 2, PIPE_F32 = 3, PIPE_CE = 4 };   // what the epilogue makes of the tile
 
@@ -601,7 +581,7 @@ hipError_t launch_pipe_lr(hipStream_t st, const MfmaGemmArgs& a) {
 // copies of whole 32-row pieces and no activation behind it.  What is
 // refused takes the tile of the same size in gemm_mfma.hip.
 bool gemm_pipe_supported(const MfmaGemmArgs& a) {
-  if (a.w_scale != nullptr || a.w_absmax != nullptr || a.k_splits > 1 || a.K % 128 || a.act == MPZ_ACT_GELU_ERF) return false;
+  if (a.w_scale != nullptr || a.w_absmax != nullptr || a.k_splits > 1 || a.K % 128 || a.act == MPZ_ACT_GELU_ERF || !fetch_aligned(a)) return false;
   if (a.ce_max != nullptr) return true;
   const int es = a.out_f32 ? 4 : 2;
   if (((uintptr_t)a.out | (uintptr_t)a.residual) & 15 || a.N * es % 16 || a.ldo * es % 16 || a.ldo > (1 << 21)) return false;

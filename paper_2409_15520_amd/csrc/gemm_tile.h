@@ -72,6 +72,39 @@ __device__ __forceinline__ void add_low_rank(const MfmaGemmArgs& a, f32x16 (&acc
   }
 }
 
+// The same on 16 x 16 tiles (v_mfma_f32_16x16x32): lane l holds features 4 (l / 16) .. + 3 of token l % 16.  Every 16-token tile
+// takes one pass per copy it holds rows of.
+template <int NI, int NJ>
+__device__ __forceinline__ void add_low_rank_16(const MfmaGemmArgs& a, f32x4 (&acc)[NI][NJ], int m0, int n0, int wm, int wn, int lane) {
+  const int l16 = lane & 15, lq = lane >> 4;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  for (int s = 0; s < a.n_seg; ++s) {
+    const MfmaLoraSeg& sg = a.seg[s];
+    if (n0 < sg.col_begin || n0 >= sg.col_end) continue;
+    for (int ks = 0; ks < sg.rp; ks += 32) {
+      const bool here = ks + lq * 8 < sg.rp;               // (rank <= 8: the upper half of the K-step is zero)
+      const int k8 = here ? ks + lq * 8 : 0;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int mt = m0 + wm + j * 16;
+        if (mt >= a.M) continue;                           // (uniform)
+        const int row = mt + l16 < a.M ? mt + l16 : a.M - 1, last = (mt + 15 < a.M ? mt + 15 : a.M - 1) / a.rows_per_copy;
+        const u32x4 xv = *(const u32x4*)((const uint16_t*)sg.tp + (size_t)row * sg.rp + k8);
+        for (int copy = mt / a.rows_per_copy; copy <= last; ++copy) {
+          const u32x4 x = here && row / a.rows_per_copy == copy ? xv : zero;
+          const uint16_t* bp = (const uint16_t*)sg.bp + (size_t)copy * sg.copy_stride + k8;
+#pragma unroll
+          for (int i = 0; i < NI; ++i) {
+            u32x4 w = *(const u32x4*)(bp + (size_t)(n0 + wn + i * 16 + l16 - sg.col_begin) * sg.rp);
+            w = here ? w : zero;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(w), as_frag(x), acc[i][j], 0, 0, 0);
+          }
+        }
+      }
+    }
+  }
+}
+
 // Fused cross-entropy: the logits never leave the registers.  A lane holds NI * 16 columns of token row lrow (the other
 // half of the row's columns sits in lane ^ 32): row maximum, sum of exponentials against it, and the target's logit if it
 // falls into this wave tile.

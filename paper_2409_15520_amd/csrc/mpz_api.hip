@@ -377,11 +377,27 @@ WeightRef weight_operand(mpz_model* m, const void* w, const float* s, int N, int
   return {dequantised(m, w, s, N, K), nullptr, nullptr, nullptr};
 }
 void set_weight(LinearArgs& a, const WeightRef& r) { a.w = r.w; a.w_scale = r.scale; a.w_codes = r.codes; a.w_absmax = r.absmax; }
+// Few stacked tokens and enough weights that every CU gets a run of K-tiles: stream them (gemm_stream.hip).  Below six K-tiles
+// of 16 KiB per CU the partial sums and the start of the stream cost more than its balance gives.
+constexpr long kStreamMinUnits = 256 * 6;
+bool plan_stream(MfmaGemmArgs& g, float* partial, size_t capacity) {
+  if (g.tile_cfg != 0 || g.ce_max != nullptr || (g.dual && g.dual_offset != g.N)) return false;
+  if (g.K < 1024 || g.K < 8 * g.M) return false;          // as ever: launches that don't split keep the one sum of every pass
+  MfmaGemmArgs b = g;
+  if (g.dual) { b.dual = 0; b.N = 2 * g.N; }              // gate | up lie back to back: one product over 2 N rows
+  if ((long)((b.N + 127) / 128) * (b.K / 64) < kStreamMinUnits) return false;
+  const int units = gemm_stream_units(b, capacity);
+  if (units == 0) return false;
+  const int slots = stream_slots(b.K / 64, units);
+  g.stream_units = units; g.k_splits = slots < 2 ? 2 : slots; g.partial = partial; g.ldp = b.N;
+  return true;
+}
 // Few stacked tokens: let k_splits blocks share an output tile (see MfmaGemmArgs).  Called once the shape and the
 // epilogue of g are filled in, before mfma_gemm_supported.
 void plan_split(const mpz_model* m, MfmaGemmArgs& g) {      // (g.w_absmax, if any, is already set: the tile depends on it)
   g.k_splits = 1; g.partial = nullptr; g.ldp = 0;
   if (m->buf.splitk == nullptr || !m->split_k) return;
+  if (plan_stream(g, m->buf.splitk, m->buf.splitk_elems)) return;
   const int ks = mfma_gemm_splits(g, m->buf.splitk_elems);
   if (ks > 1) { g.k_splits = ks; g.partial = m->buf.splitk; g.ldp = (g.dual ? 2 : 1) * g.N; }
 }
@@ -1333,8 +1349,11 @@ mpz_status mpz_debug_gemm_bf16_splitk(int32_t M, int32_t N, int32_t K, const voi
   if (K % 64 || N % 4 || M < 1 || N < 1) return fail(nullptr, MPZ_ERR_SHAPE, "shape not supported by the MFMA GEMM (K % 64, N % 4)");
   const int ks = mfma_gemm_splits(g, partial_elems);
   if (k_splits >= 2 && ks != k_splits) return fail(nullptr, MPZ_ERR_SHAPE, "mpz_debug_gemm_bf16_splitk: k_splits does not fit K or the partial buffer");
-  g.tile_cfg = ks > 1 ? 100 * ks + forced_tile : 0;
-  if (ks > 1) { g.k_splits = ks; g.partial = partial; g.ldp = (g.dual ? 2 : 1) * N; }
+  if (k_splits == 0 && forced_tile == 0 && plan_stream(g, partial, partial_elems)) {}
+  else {
+    g.tile_cfg = ks > 1 ? 100 * ks + forced_tile : 0;
+    if (ks > 1) { g.k_splits = ks; g.partial = partial; g.ldp = (g.dual ? 2 : 1) * N; }
+  }
   if (!mfma_gemm_supported(g)) return fail(nullptr, MPZ_ERR_SHAPE, "shape not supported by the MFMA GEMM");
   const hipError_t le = launch_gemm_mfma((hipStream_t)hip_stream, g);
   if (le != hipSuccess) return fail(nullptr, MPZ_ERR_DEVICE, std::string("mpz_debug_gemm_bf16_splitk: ") + hipGetErrorString(le));

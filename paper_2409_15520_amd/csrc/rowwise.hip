@@ -84,26 +84,26 @@ __global__ void __launch_bounds__(256) splitk_reduce_norm_kernel(MfmaGemmArgs a,
   }
   // the other splits, four at a time: their pieces are all requested before the first is added (they come from other
   // XCDs' blocks, a fabric round trip each), and added in split order
+  int slots[J];                                            // (a streamed GEMM: the columns of a tile have as many as blocks share it)
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+    slots[j] = a.stream_units ? stream_slots_of((tid + 256 * j) / 32, a.K / 64, a.stream_units) : a.k_splits;
   for (int s = 1; s < a.k_splits; s += 4) {
-    const int ns = a.k_splits - s < 4 ? a.k_splits - s : 4;              // block-uniform
     f32x4 t4[4][J];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (u >= ns) break;
       const f32x4* ps = (const f32x4*)(a.partial + (s + u) * plane + (size_t)row * a.ldp);
 #pragma unroll
       for (int j = 0; j < J; ++j) {
         const int c = tid + 256 * j;
-        if (c < NC) t4[u][j] = ps[c];
+        if (c < NC && s + u < slots[j]) t4[u][j] = ps[c];
       }
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (u >= ns) break;
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
       for (int j = 0; j < J; ++j)
-        if (tid + 256 * j < NC) v[j] += t4[u][j];
-    }
+        if (tid + 256 * j < NC && s + u < slots[j]) v[j] += t4[u][j];
   }
 #pragma unroll
   for (int j = 0; j < J; ++j) {

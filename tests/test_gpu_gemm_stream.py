@@ -1,0 +1,41 @@
+"""The streamed few-token GEMM (runs of K-tiles per block, partial sums per block and tile) against 64-bit products: every token
+tile (64 / 128 / 256), ragged tokens and features, tiles shared by two to nine blocks, every epilogue of the reduction."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m", [1, 33, 64, 65, 128, 129, 256])
+@pytest.mark.parametrize("n,k,act,f32,residual", [(4096, 4096, -1, True, True), (4100, 4096, -1, False, False), (1160, 11008, -1, True, False),
+                                                  (2048, 6144, 2, False, False), (6144, 2048, 0, False, False), (50000, 2112, 1, False, False)])
+def test_streamed_gemm(m, n, k, act, f32, residual):
+    import torch
+    import paper_2409_15520_amd as M
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    nw = 2 * n if act == 2 else n
+    x = torch.randn(m, k, generator=g, device="cuda").bfloat16()
+    w = (torch.randn(nw, k, generator=g, device="cuda") * 0.05).bfloat16()
+    b = torch.randn(nw, generator=g, device="cuda")
+    r = torch.randn(m, n, generator=g, device="cuda") if residual else None
+    partial = torch.empty(10 * m * nw, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    outs = []
+    for _ in range(2):
+        out = torch.full((m + 1, n), -7.0, device="cuda", dtype=torch.float32 if f32 else torch.bfloat16)
+        partial.fill_(float("nan"))                        # a slot nobody wrote would show
+        M.mpz_debug_gemm_bf16_splitk(m, n, k, x.data_ptr(), w.data_ptr(), b.data_ptr(), act, None if r is None else r.data_ptr(),
+                                     out.data_ptr(), f32, 0, partial.data_ptr(), partial.numel(), st)
+        assert bool((out[m] == -7.0).all())
+        outs.append(out[:m])
+    assert torch.equal(outs[0], outs[1])                   # the slots are added in block order, whatever finished first
+    y = x.double() @ w.double().t() + b.double()
+    if act == 2:
+        y = torch.nn.functional.silu(y[:, :n]) * y[:, n:]
+    elif act == 0:
+        y = torch.relu(y)
+    elif act == 1:
+        y = torch.nn.functional.gelu(y)
+    if r is not None:
+        y = y + r.double()
+    err = float((outs[0].double() - y).norm() / y.norm())
+    assert err < (2e-6 if f32 else 2.0 ** -8)              # fp32 sums of K products; bf16 rounding of the output
