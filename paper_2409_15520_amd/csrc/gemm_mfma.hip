@@ -782,14 +782,13 @@ hipError_t launch_cfg(hipStream_t st, const MfmaGemmArgs& a) {
   return hipSuccess;
 }
 
-// block tile of configuration cfg (1, 6, 9, 10, 11, 12, 13; see launch_gemm_mfma)
-int tile_bn(int cfg) { return (cfg == 10 || cfg == 13) ? 64 : cfg == 11 ? 192 : cfg == 6 ? 256 : 128; }
-int tile_bm(int cfg) { return (cfg == 9 || cfg == 10) ? 64 : cfg == 6 ? 256 : 128; }
-bool known_cfg(int cfg) { return cfg == 1 || cfg == 6 || (cfg >= 9 && cfg <= 13); }
+// block tile of configuration cfg (1, 6, 9, 10, 11, 12, 13, 14; see launch_gemm_mfma)
+int tile_bn(int cfg) { return cfg == 14 ? 32 : (cfg == 10 || cfg == 13) ? 64 : cfg == 11 ? 192 : cfg == 6 ? 256 : 128; }
+bool known_cfg(int cfg) { return cfg == 1 || cfg == 6 || (cfg >= 9 && cfg <= 14); }
 
 bool cfg_ok(const MfmaGemmArgs& a, int cfg) {
-  const int bn = tile_bn(cfg), bm = tile_bm(cfg);
-  (void)bm;
+  if (cfg == 14 && !gemm_ring_supported(a)) return false;
+  const int bn = tile_bn(cfg);
   for (int s = 0; s < a.n_seg; ++s)
     if (a.seg[s].col_begin % bn || a.seg[s].col_end % bn) return false;
   return true;
@@ -829,6 +828,10 @@ int choose_cfg(const MfmaGemmArgs& a) {
   // fewer 128 x 128 tiles than CUs (single-copy and single-query passes): 128 x 64 tiles, twice the blocks, and
   // 64 x 64 tiles if that is still less than one block per CU (one pass per copy on the 125M-shaped workload:
   // 8.2 -> 7.4 ms per step; 2 x 64 tokens through the 7B-shaped model: 75 -> 67 ms)
+  // 32 x 32 tiles while three blocks per CU hold them all (768 x 768 x 3072, 576 tiles: 14.9 us against 16.9 in 64 x 64 tiles;
+  // 384 x 2304 x 768, 864 tiles: 7.7 against 6.6)
+  const long t14 = (long)((a.N + 31) / 32) * ((a.M + 31) / 32);
+  if (t14 <= 768 && cfg_ok(a, 14)) return 14;
   if (t1 < 256 && a.rope_cos == nullptr && a.w_scale == nullptr && a.ce_max == nullptr && cfg_ok(a, 9))
     return (2 * t1 < 256 && cfg_ok(a, 10)) ? 10 : 9;
   // otherwise the 128 x 128 tile with 8 waves of 64 x 32 (16 waves per CU): a block of a short-K problem lives for
@@ -1058,10 +1061,11 @@ hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a) {
   switch (choose_cfg(a)) {
     case 6: return launch_cfg<256, 256, 64, 2, 4, false>(st, a);     // 8 waves of 128 x 64, BK 64 (147 KB LDS), 128 KB in flight
     case 9: return launch_cfg<128, 64, 64, 2, 2, false>(st, a);      // 4 waves of 64 x 32: more, smaller blocks
-    case 10: return launch_cfg<64, 64, 64, 2, 2, false>(st, a);      // 4 waves of 32 x 32: the smallest blocks
+    case 10: return launch_cfg<64, 64, 64, 2, 2, false>(st, a);      // 4 waves of 32 x 32: smaller still
     case 11: return launch_cfg<192, 128, 64, 2, 2, false>(st, a);    // 4 waves of 96 x 64, 92 KB LDS: 1 block per CU
     case 12: return launch_cfg<128, 128, 64, 2, 4, false>(st, a);    // 8 waves of 64 x 32: 16 waves per CU
     case 13: return launch_cfg<64, 128, 64, 2, 2, false>(st, a);     // 4 waves of 32 x 64: all of <= 128 tokens, few features
+    case 14: return launch_gemm_ring(st, a);                         // 4 waves of 16 x 16: the smallest outputs
     default: return launch_cfg<128, 128, 64, 2, 2, false>(st, a);    // 1: 4 waves of 64 x 64
   }
 }
