@@ -842,32 +842,40 @@ int choose_cfg(const MfmaGemmArgs& a) {
 
 int wave_cols(int cfg) { return (cfg == 10 || cfg == 13) ? 32 : cfg == 11 ? 96 : cfg == 6 ? 128 : 64; }   // BN / WGN of launch_gemm_mfma's table
 
-// 64 token rows per block, the slots dealt to 4 waves: logsumexp over the per-wave-tile partials (online
-// maximum / rescaled sum per thread, merged through LDS), minus the target's logit
-__global__ void __launch_bounds__(256) ce_combine_kernel(int slots, int M, const float* __restrict__ ce_max,
-                                                         const float* __restrict__ ce_sum,
-                                                         const float* __restrict__ ce_tlogit,
-                                                         const int32_t* __restrict__ ce_target, float* __restrict__ ce) {
-  __shared__ float pm[4][64], psum[4][64];
-  const int r = threadIdx.x & 63, part = threadIdx.x >> 6;
-  const int m = blockIdx.x * 64 + r;
+// 16 token rows per block, the slots dealt to 64 threads per row: logsumexp over the per-wave-tile partials (online maximum /
+// rescaled sum per thread, merged by wave shuffles and through LDS in a fixed order), minus the target's logit.  (64 rows per
+// block and four threads per row took 75 us for 512 rows of 786 slots: eight blocks walking 200 slots each.)
+__device__ __forceinline__ void ce_merge(float& mx, float& s, float omx, float os) {
+  const float hi = omx > mx ? omx : mx;
+  s = s * expf(mx - hi) + os * expf(omx - hi);
+  mx = hi;
+}
+__global__ void __launch_bounds__(1024) ce_combine_kernel(int slots, int M, const float* __restrict__ ce_max,
+                                                          const float* __restrict__ ce_sum,
+                                                          const float* __restrict__ ce_tlogit,
+                                                          const int32_t* __restrict__ ce_target, float* __restrict__ ce) {
+  __shared__ float pm[16][16], psum[16][16];
+  const int r = threadIdx.x & 15, part = threadIdx.x >> 4, wave = threadIdx.x >> 6;
+  const int m = blockIdx.x * 16 + r;
   float mx = -1e30f, s = 0.f;
   if (m < M) {
-    for (int t = part; t < slots; t += 4) {
+    for (int t = part; t < slots; t += 64) {
       const float v = ce_max[(size_t)t * M + m], sv = ce_sum[(size_t)t * M + m];
       if (v > mx) { s = s * expf(mx - v) + sv; mx = v; }
       else s += sv * expf(v - mx);
     }
   }
-  pm[part][r] = mx; psum[part][r] = s;
+#pragma unroll
+  for (int o = 16; o < 64; o <<= 1) {                    // the four threads of a row in this wave
+    const float omx = __shfl_xor(mx, o), os = __shfl_xor(s, o);
+    ce_merge(mx, s, omx, os);
+  }
+  if ((threadIdx.x & 63) < 16) { pm[wave][r] = mx; psum[wave][r] = s; }
   __syncthreads();
-  if (part != 0 || m >= M) return;
+  if (threadIdx.x >= 16 || m >= M) return;
   if (ce_target[m] < 0) { ce[m] = 0.f; return; }
-  float gm = pm[0][r];
-  for (int p = 1; p < 4; ++p) gm = pm[p][r] > gm ? pm[p][r] : gm;
-  float gs = 0.f;
-  for (int p = 0; p < 4; ++p) gs += psum[p][r] * expf(pm[p][r] - gm);
-  ce[m] = gm + logf(gs) - ce_tlogit[m];
+  for (int w = 1; w < 16; ++w) ce_merge(mx, s, pm[w][r], psum[w][r]);
+  ce[m] = mx + logf(s) - ce_tlogit[m];
 }
 
 }  // namespace
@@ -886,7 +894,7 @@ int mfma_gemm_ce_slots(const MfmaGemmArgs& a0) {
 
 void launch_ce_combine(hipStream_t st, int slots, int M, const float* ce_max, const float* ce_sum, const float* ce_tlogit,
                        const int32_t* ce_target, float* ce) {
-  ce_combine_kernel<<<(M + 63) / 64, 256, 0, st>>>(slots, M, ce_max, ce_sum, ce_tlogit, ce_target, ce);
+  ce_combine_kernel<<<(M + 15) / 16, 1024, 0, st>>>(slots, M, ce_max, ce_sum, ce_tlogit, ce_target, ce);
 }
 
 bool mfma_gemm_supported(const MfmaGemmArgs& a) {
