@@ -158,7 +158,9 @@ __global__ void __launch_bounds__(256) splitk_reduce_norm_kernel(MfmaGemmArgs a,
 // One block = 32 token rows.  Phase A is norm_rows_kernel's arithmetic (each wave takes 8 of the rows, RB at a time
 // so that their loads travel together); the bf16 row goes to global memory for the GEMM and to an LDS tile.  Phase B
 // is lora_down_mfma_kernel's arithmetic on that tile - same K split over the 4 waves, same order of the partial sums,
-// so t has the same bits - without reading x again, without chunk staging and without its launch.
+// so t has the same bits - without reading x again, without chunk staging and without its launch.  A block's life is a chain of
+// round trips to memory: gains and factors are requested with the rows (d = 768, 512 rows: 14.3 -> 11.4 us; 4096 rows beside
+// the other half's GEMMs: 24.2 -> 16.9 us).
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -174,6 +176,37 @@ __global__ void __launch_bounds__(256, NV <= 4 ? 2 : 1) norm_lora_kernel(int kin
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lrow = lane & 31, lhalf = lane >> 5;
   const int m0 = blockIdx.x * 32;
 
+  // phase B: t = scale * x (A_hi + A_lo) for the block's copy; wave w owns K-elements 256 ch + 64 w + (0..63).  Its first factors
+  // (all of them if the row is short) are requested behind the rows of phase A and travel during it
+  const int copy = m0 / a.rows_per_copy;
+  const int R = a.n_targets * a.rank;
+  const uint16_t* Ah[JT];
+  const uint16_t* Al[JT];
+  bool valid[JT];
+#pragma unroll
+  for (int t = 0; t < JT; ++t) {
+    int j = t * 32 + lrow;
+    valid[t] = j < R;
+    int jj = valid[t] ? j : 0;
+    int tgt = jj / a.rank, jr = jj % a.rank;
+    const uint16_t* base = (const uint16_t*)a.ap[tgt] + (size_t)copy * a.copy_stride;
+    Ah[t] = base + ((size_t)(wave * 8 + lhalf) * a.rank + jr) * 8;      // [2][K / 8][rank][8], as in lora_down_mfma_kernel
+    Al[t] = Ah[t] + (size_t)D * a.rank;
+  }
+  constexpr int PF = NV <= 3 && JT == 1 ? NV : 1, NS = PF == NV ? NV : 2;   // chunks requested ahead, register sets
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  u32x4 fh[NS][4][JT], fl[NS][4][JT];
+  auto request = [&](int ch) {
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4)
+#pragma unroll
+      for (int t = 0; t < JT; ++t) {
+        fh[ch % NS][s4][t] = *(const u32x4*)(Ah[t] + (size_t)(ch * 256 + s4 * 16) * a.rank);
+        fl[ch % NS][s4][t] = *(const u32x4*)(Al[t] + (size_t)(ch * 256 + s4 * 16) * a.rank);
+      }
+  };
+  f32x4 gg[NV], bb[NV];
+
   // ---- phase A: rows m0 + 8 wave + (0..7), RB at a time
 #pragma unroll 1
   for (int r0 = 0; r0 < 8; r0 += RB) {
@@ -183,6 +216,16 @@ __global__ void __launch_bounds__(256, NV <= 4 ? 2 : 1) norm_lora_kernel(int kin
       const f32x4* hr = (const f32x4*)(h + (int64_t)(m0 + wave * 8 + r0 + rr) * D);
 #pragma unroll
       for (int i = 0; i < NV; ++i) v[rr][i] = hr[i * 64 + lane];
+    }
+    if (r0 == 0) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        gg[i] = ((const f32x4*)g)[i * 64 + lane];
+        bb[i] = b != nullptr ? ((const f32x4*)b)[i * 64 + lane] : f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int c = 0; c < PF; ++c) request(c);
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int rr = 0; rr < RB; ++rr) {
@@ -204,14 +247,12 @@ __global__ void __launch_bounds__(256, NV <= 4 ? 2 : 1) norm_lora_kernel(int kin
       u32x2* lrow_p = (u32x2*)(xs + row * XS);
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
-        f32x4 gg = ((const f32x4*)g)[i * 64 + lane];
         float y[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = (v[rr][i][e] - mean) * rstd * gg[e];
+        for (int e = 0; e < 4; ++e) y[e] = (v[rr][i][e] - mean) * rstd * gg[i][e];
         if (b != nullptr) {
-          f32x4 bb = ((const f32x4*)b)[i * 64 + lane];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] += bb[e];
+          for (int e = 0; e < 4; ++e) y[e] += bb[i][e];
         }
         u32x2 pk = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
         orow[i * 64 + lane] = pk;
@@ -221,52 +262,20 @@ __global__ void __launch_bounds__(256, NV <= 4 ? 2 : 1) norm_lora_kernel(int kin
   }
   __syncthreads();
 
-  // ---- phase B: t = scale * x (A_hi + A_lo) for the block's copy; wave w owns K-elements 256 ch + 64 w + (0..63)
-  const int copy = m0 / a.rows_per_copy;
-  const int R = a.n_targets * a.rank;
-  const uint16_t* Ah[JT];
-  const uint16_t* Al[JT];
-  bool valid[JT];
-#pragma unroll
-  for (int t = 0; t < JT; ++t) {
-    int j = t * 32 + lrow;
-    valid[t] = j < R;
-    int jj = valid[t] ? j : 0;
-    int tgt = jj / a.rank, jr = jj % a.rank;
-    const uint16_t* base = (const uint16_t*)a.ap[tgt] + (size_t)copy * a.copy_stride;
-    Ah[t] = base + ((size_t)(wave * 8 + lhalf) * a.rank + jr) * 8;      // [2][K / 8][rank][8], as in lora_down_mfma_kernel
-    Al[t] = Ah[t] + (size_t)D * a.rank;
-  }
+  // ---- phase B
   f32x16 acc[JT];
 #pragma unroll
   for (int t = 0; t < JT; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  u32x4 fh[4][JT], fl[4][JT];
-#pragma unroll
-  for (int s4 = 0; s4 < 4; ++s4)
-#pragma unroll
-    for (int t = 0; t < JT; ++t) {
-      fh[s4][t] = valid[t] ? *(const u32x4*)(Ah[t] + (size_t)(s4 * 16) * a.rank) : zero;
-      fl[s4][t] = valid[t] ? *(const u32x4*)(Al[t] + (size_t)(s4 * 16) * a.rank) : zero;
-    }
 #pragma unroll
   for (int ch = 0; ch < NV; ++ch) {
     u32x4 ch_h[4][JT], ch_l[4][JT];
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4)
 #pragma unroll
-      for (int t = 0; t < JT; ++t) { ch_h[s4][t] = fh[s4][t]; ch_l[s4][t] = fl[s4][t]; }
-    if (ch + 1 < NV) {                                   // the next chunk's factors travel during this chunk's MFMAs
-#pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4)
-#pragma unroll
-        for (int t = 0; t < JT; ++t) {
-          fh[s4][t] = valid[t] ? *(const u32x4*)(Ah[t] + (size_t)((ch + 1) * 256 + s4 * 16) * a.rank) : zero;
-          fl[s4][t] = valid[t] ? *(const u32x4*)(Al[t] + (size_t)((ch + 1) * 256 + s4 * 16) * a.rank) : zero;
-        }
-    }
+      for (int t = 0; t < JT; ++t) { ch_h[s4][t] = valid[t] ? fh[ch % NS][s4][t] : zero; ch_l[s4][t] = valid[t] ? fl[ch % NS][s4][t] : zero; }
+    if (ch + PF < NV) request(ch + PF);                  // later factors travel during this chunk's MFMAs
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4) {
       const bf16x8 fx = __builtin_bit_cast(bf16x8, *(const u32x4*)(xs + lrow * XS + ch * 256 + wave * 64 + s4 * 16 + lhalf * 8));
