@@ -293,6 +293,12 @@ gemm_bf16_kernel(MfmaGemmArgs a) {
   bf16x8 pre_fw[PREF ? NJ : 1][PREF ? NI : 1], pre_fx[PREF ? NJ : 1];
   int pre_seg = -1;
   if constexpr (PREF) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      pre_fx[j] = as_frag(u32x4{0u, 0u, 0u, 0u});
+#pragma unroll
+      for (int i = 0; i < NI; ++i) pre_fw[j][i] = as_frag(u32x4{0u, 0u, 0u, 0u});
+    }
     // (with split K the low-rank term goes into split 0's sum; tiles of several copies: no early request)
     for (int s = 0; s < a.n_seg && split == 0 && a.rows_per_copy % 32 == 0; ++s)
       if (n0 >= a.seg[s].col_begin && n0 < a.seg[s].col_end && a.seg[s].rp == 16) pre_seg = s;
@@ -362,14 +368,15 @@ gemm_bf16_kernel(MfmaGemmArgs a) {
   // per-copy low-rank term: extra K-steps with the packed factor [B_hi | B_lo] of a copy against the duplicated
   // bottleneck activations [t | t].  Copies are whole multiples of 32 rows, so every 32-row MFMA tile belongs to
   // one copy (a block tile may span several); segments are aligned to the block tile.
-  if (PREF && pre_seg >= 0) {
+  if constexpr (PREF) {                                    // (zeros where nothing was requested: no branch around the accumulators)
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int i = 0; i < NI; ++i)
         acc[0][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pre_fw[j][i], pre_fx[j], acc[0][i][j], 0, 0, 0);
-  } else if constexpr (!DUAL) {
-    if (split == 0) add_low_rank<NI, NJ>(a, acc[0], m0, n0, wm, wn, lane);
+  }
+  if constexpr (!DUAL) {
+    if (split == 0 && a.n_seg > 0 && (!PREF || pre_seg < 0)) add_low_rank<NI, NJ>(a, acc[0], m0, n0, wm, wn, lane);
   }
 
   gemm_epilogue<BN, WGN, WGM, NW, NI, NJ, HP>(a, acc, smem, m0, n0, wm, wn, wave, lane, raw, split);

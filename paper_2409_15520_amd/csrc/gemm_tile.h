@@ -166,8 +166,7 @@ __device__ __forceinline__ void gemm_epilogue(const MfmaGemmArgs& a, f32x16 (&ac
   // Epilogue, part 1 (accumulator layout: a lane holds, for token m = lrow, features nb + g*8 + lhalf*4 + (0..3),
   // g = 0..3, of every MFMA tile): bias, activation or gating, rotary embedding -- everything that needs no
   // other token's data -- written back into acc[0].
-  const bool relu = !DUAL && a.act == MPZ_ACT_RELU;
-  if (!raw) {
+  if (!DUAL || !raw) {                                     // (raw sums of one weight tile: plus zero, without a branch around the accumulators)
 #pragma unroll
   for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -175,7 +174,7 @@ __device__ __forceinline__ void gemm_epilogue(const MfmaGemmArgs& a, f32x16 (&ac
       int n = n0 + wn + i * 32 + g * 8 + lhalf * 4;
       n = n < a.N ? n : 0;                                 // columns past N are never stored
       f32x4 bg = {0.f, 0.f, 0.f, 0.f}, bu = bg;
-      if (a.bias != nullptr) {
+      if (a.bias != nullptr && !raw) {
         bg = *(const f32x4*)(a.bias + n);
         if (DUAL) bu = *(const f32x4*)(a.bias + a.dual_offset + n);
       }
@@ -187,12 +186,18 @@ __device__ __forceinline__ void gemm_epilogue(const MfmaGemmArgs& a, f32x16 (&ac
           if (DUAL) {
             const float u = acc[NW - 1][i][j][g * 4 + e] + bu[e];
             v = silu_mul_f32(v, u);                        // SiLU(gate) * up
-          } else {
-            v = (relu && !(v > 0.f)) ? 0.f : v;            // a select, not a branch per element
           }
           acc[0][i][j][g * 4 + e] = v;
         }
     }
+  }
+  if (!raw && !DUAL && a.act == MPZ_ACT_RELU) {            // one uniform branch, no select where there is no ReLU
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[0][i][j][e] = !(acc[0][i][j][e] > 0.f) ? 0.f : acc[0][i][j][e];
   }
   if (!raw && !DUAL && a.act == MPZ_ACT_GELU_ERF) {                // rare (no workload of the paper uses it): one cold loop
 #pragma unroll
