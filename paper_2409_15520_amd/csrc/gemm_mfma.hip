@@ -832,6 +832,9 @@ int choose_cfg(const MfmaGemmArgs& a) {
   // other half; 192 x 128 tiles, one per CU, balance it (N = 768 projections of the 125M-class models)
   const long t1 = (long)((a.N + 127) / 128) * ((a.M + 127) / 128), t11 = (long)((a.N + 191) / 192) * ((a.M + 127) / 128);
   if (t1 > 256 && t1 < 512 && t11 <= 256 && a.N % 192 == 0 && a.K >= 1536 && a.rope_cos == nullptr && cfg_ok(a, 11)) return 11;
+  // heads of 128 columns rotated in the epilogue need a wave tile that holds one: four waves of 128 x 32 (1024 tokens of the
+  // 7B-shaped int8 model: the rotary kernel after the GEMM, 33 us, goes)
+  if (a.rope_cos != nullptr && a.rope_dh == 128 && t1 >= 256 && cfg_ok(a, 15)) return 15;
   // fewer 128 x 128 tiles than CUs (single-copy and single-query passes): 128 x 64 tiles, twice the blocks, and
   // 64 x 64 tiles if that is still less than one block per CU (one pass per copy on the 125M-shaped workload:
   // 8.2 -> 7.4 ms per step; 2 x 64 tokens through the 7B-shaped model: 75 -> 67 ms)
@@ -847,7 +850,7 @@ int choose_cfg(const MfmaGemmArgs& a) {
   return 12;
 }
 
-int wave_cols(int cfg) { return (cfg == 10 || cfg == 13) ? 32 : cfg == 11 ? 96 : cfg == 6 ? 128 : 64; }   // BN / WGN of launch_gemm_mfma's table
+int wave_cols(int cfg) { return (cfg == 10 || cfg == 13) ? 32 : cfg == 11 ? 96 : (cfg == 6 || cfg == 15) ? 128 : 64; }   // BN / WGN of launch_gemm_mfma's table
 
 // 16 token rows per block, the slots dealt to 64 threads per row: logsumexp over the per-wave-tile partials (online maximum /
 // rescaled sum per thread, merged by wave shuffles and through LDS in a fixed order), minus the target's logit.  (64 rows per
@@ -926,7 +929,7 @@ bool mfma_gemm_supported(const MfmaGemmArgs& a) {
     // the rotated column range must end on a block-tile boundary, and a wave tile must hold whole heads
     const int cfg = choose_cfg(a), bn = tile_bn(cfg), tn = wave_cols(cfg);
     if (a.dual || a.out_f32 || a.act >= 0 || a.residual != nullptr || !a.rope_sin || a.S < 1) return false;
-    if ((cfg != 6 && cfg != 1 && cfg != 12) || (a.rope_dh != 64 && a.rope_dh != 128) || a.rope_dh > tn) return false;
+    if ((cfg != 6 && cfg != 1 && cfg != 12 && cfg != 15) || (a.rope_dh != 64 && a.rope_dh != 128) || a.rope_dh > tn) return false;
     if (a.rope_cols % bn || a.rope_cols > a.N || a.N % a.rope_dh) return false;
   }
   return true;
@@ -1061,6 +1064,7 @@ hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a) {
       if (a.rope_dh == 64) return q8 ? launch_cfg<256, 256, 64, 2, 4, false, 1, true>(st, a) : launch_cfg<256, 256, 64, 2, 4, false, 1>(st, a);
       return q8 ? launch_cfg<256, 256, 64, 2, 4, false, 2, true>(st, a) : launch_cfg<256, 256, 64, 2, 4, false, 2>(st, a);
     }
+    if (cfg == 15) return q8 ? launch_cfg<128, 128, 64, 1, 4, false, 2, true>(st, a) : launch_cfg<128, 128, 64, 1, 4, false, 2>(st, a);
     if (cfg == 12) return q8 ? launch_cfg<128, 128, 64, 2, 4, false, 1, true>(st, a) : launch_cfg<128, 128, 64, 2, 4, false, 1>(st, a);
     return q8 ? launch_cfg<128, 128, 64, 2, 2, false, 1, true>(st, a) : launch_cfg<128, 128, 64, 2, 2, false, 1>(st, a);
   }
