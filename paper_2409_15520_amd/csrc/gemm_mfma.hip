@@ -10,6 +10,7 @@
 #include <mutex>
 
 #include "gemm_tile.h"
+#include "fetch.h"
 
 namespace mpz {
 namespace {
@@ -520,7 +521,7 @@ __global__ void __launch_bounds__(512, 1) mfma_probe_kernel(const uint16_t* __re
 // fragments straight from the row-major x would touch 32 rows per instruction), one chunk in flight in registers
 // while the previous one is consumed.  Inside a chunk the 4 waves split K; their partial sums meet in LDS in a
 // fixed order.  MFMA rows = bottleneck columns j of all targets that share the input x.
-template <int JT>   // number of 32-row MFMA tiles covering n_targets * r bottleneck columns
+template <int JT, bool MIXED>   // JT: number of 32-row MFMA tiles covering n_targets * r bottleneck columns; MIXED: 32 rows of several copies
 __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs a) {
   constexpr int KCH = 256, XS = KCH + 8;
   __shared__ __align__(16) uint16_t sx[3][32 * XS];
@@ -529,9 +530,9 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
   const int m0 = blockIdx.x * 32;
   const int R = a.n_targets * a.rank;
   const uint16_t* X = (const uint16_t*)a.x + (size_t)m0 * a.K;
-  // 32 rows of one copy, or (copies that are no multiples of 32 rows) of several: one pass per copy, each storing its rows
+  // MIXED (copies that are no multiples of 32 rows): one pass per copy, each storing its rows
   const int m_last = m0 + 31 < a.T ? m0 + 31 : a.T - 1, last_copy = m_last / a.rows_per_copy;
-  for (int copy = m0 / a.rows_per_copy; copy <= last_copy; ++copy) {
+  for (int copy = m0 / a.rows_per_copy;; ++copy) {
   // packed A: per copy and target [2][K / 8][rank][8] (hi part then lo part): the 16-byte pieces that the lanes of
   // a wave fetch for one MFMA operand (rank rows x 2 neighbouring chunks of 8 k) are contiguous
   const uint16_t* Ah[JT];
@@ -555,12 +556,10 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
   const u32x4 zero = {0u, 0u, 0u, 0u};
 
   // chunk staging: piece p = tid + 256 i of the 32 x 256 chunk: row p / 32, 16-byte column p % 32
-  int grow[4], gcol[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) { int p = tid + 256 * i; grow[i] = p >> 5; gcol[i] = (p & 31) * 8; }
-  int xrow[4];                                   // the row to fetch: rows past T fetch the last one, and are not stored
-#pragma unroll
-  for (int i = 0; i < 4; ++i) xrow[i] = m0 + grow[i] < a.T ? grow[i] : m_last - m0;
+  const int grow = tid >> 5, gcol = (tid & 31) * 8;       // i = 0; 8 rows further down per i
+  // (rows past T lie outside the buffer: zeros, and never stored)
+  const __amdgpu_buffer_rsrc_t rsrcX = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(X), 0, (m_last - m0 + 1) * a.K * 2, 0x00020000);
+  const int voffX = (grow * a.K + gcol) * 2;
   // three chunks of x in flight (registers), three LDS buffers: a K = 768 row is fetched in one go
   constexpr int PD = 3;
   u32x4 st[PD][4];
@@ -569,7 +568,7 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
   for (int p = 0; p < PD; ++p)
     if (p < nch) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) st[p][i] = *(const u32x4*)(X + (size_t)xrow[i] * a.K + p * KCH + gcol[i]);
+      for (int i = 0; i < 4; ++i) st[p][i] = __builtin_amdgcn_raw_buffer_load_b128(rsrcX, voffX, (i * 8 * a.K + p * KCH) * 2, 0);
     }
   for (int ch0 = 0; ch0 < nch; ch0 += PD) {
 #pragma unroll
@@ -593,10 +592,10 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
         }
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) *(u32x4*)(buf + grow[i] * XS + gcol[i]) = st[p][i];
+      for (int i = 0; i < 4; ++i) *(u32x4*)(buf + (grow + 8 * i) * XS + gcol) = st[p][i];
       if (ch + PD < nch) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) st[p][i] = *(const u32x4*)(X + (size_t)xrow[i] * a.K + (ch + PD) * KCH + gcol[i]);
+        for (int i = 0; i < 4; ++i) st[p][i] = __builtin_amdgcn_raw_buffer_load_b128(rsrcX, voffX, (i * 8 * a.K + (ch + PD) * KCH) * 2, 0);
       }
       __syncthreads();                             // chunk ch visible; its buffer was last read three chunks ago
 #pragma unroll
@@ -618,7 +617,7 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
   }
   __syncthreads();
   const int m = m0 + lrow;
-  if (wave == 0 && m < a.T && m / a.rows_per_copy == copy) {
+  if (wave == 0 && m < a.T && (!MIXED || m / a.rows_per_copy == copy)) {
 #pragma unroll
   for (int t = 0; t < JT; ++t)
 #pragma unroll
@@ -643,8 +642,103 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
     for (int tgt = 0; tgt < a.n_targets; ++tgt)
       for (int c = 2 * a.rank; c < a.rp; ++c) ((uint16_t*)a.tp[tgt])[(size_t)m * a.rp + c] = 0;
   }
-  if (copy < last_copy) __syncthreads();         // the sums of this copy are read before the next ones are written
+  if (!MIXED || copy >= last_copy) break;
+  __syncthreads();                               // the sums of this copy are read before the next ones are written
   }
+}
+
+// The same where blocks of 32 tokens leave most CUs idle (128 tokens: four blocks): a block per 32 tokens and target, x and the
+// factors fetched straight into a ring of LDS stages.  What bounds it is what one CU can fetch: K = 4096, rank 16 are 256 KB
+// of x and 256 KB of factors per block (128 tokens, two targets: 18.5 -> 11.6 us; 1024 tokens: 20.6 -> 12.5).  Every wave takes the
+// K-steps it takes above and the sums meet in the same order: the same bits.
+template <int RANK>
+__global__ void __launch_bounds__(256, 1) lora_down_ring_kernel(MfmaLoraDownArgs a) {
+  constexpr int ST = RANK == 32 ? 3 : RANK == 16 ? 4 : 5, PER = 4 + RANK / 4;      // stages; fetches of a wave per chunk
+  constexpr uint32_t XBYTES = 32 * 512, HALF = RANK * 512, STAGE = XBYTES + 2 * HALF;
+  extern __shared__ __align__(16) unsigned char lora_smem[];
+  float* part = (float*)(lora_smem + ST * STAGE);          // [3][16][64]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lrow = lane & 31, lhalf = lane >> 5;
+  const int m0 = blockIdx.x * 32, tgt = blockIdx.y, m = m0 + lrow, nch = a.K / 256;
+  const int m_last = m0 + 31 < a.T ? m0 + 31 : a.T - 1, last_copy = m_last / a.rows_per_copy;
+  const uint32_t row_b = (uint32_t)a.K * 2u;
+  const i32x4 rsrcX = buffer_of((const char*)a.x + (size_t)m0 * row_b, (size_t)(m_last - m0 + 1) * row_b);   // (rows past T: outside)
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lora_smem;
+  uint32_t voffX[4];                                       // two rows of 512 bytes per fetch, 16-byte chunk c of row r at c ^ (r % 16)
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int r = (wave * 4 + t) * 2 + (lane >> 5);
+    voffX[t] = (uint32_t)r * row_b + (uint32_t)((lane & 31) ^ (r & 15)) * 16u;
+  }
+  const bool valid = lrow < RANK;
+  const uint32_t baseX = (uint32_t)lrow * 512u, baseA = XBYTES + (uint32_t)((wave * 8 + lhalf) * RANK + (valid ? lrow : 0)) * 16u;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  for (int copy = m0 / a.rows_per_copy;; ++copy) {
+    // a chunk's factors, hi part and lo part, are RANK x 512 contiguous bytes each
+    const i32x4 rsrcA = buffer_of((const uint16_t*)a.ap[tgt] + (size_t)copy * a.copy_stride, (size_t)a.K * RANK * 4);
+    auto fetch = [&](int ch, int st) {
+      const uint32_t base = lds0 + (uint32_t)st * STAGE;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) fetch_rows<4>(rsrcX, voffX[t], (uint32_t)ch * 512u, base + (uint32_t)(wave * 4 + t) * 1024u);
+#pragma unroll
+      for (int t = 0; t < RANK / 4; ++t) {
+        const uint32_t p = (uint32_t)(wave * (RANK / 4) + t) * 1024u;                 // of the 2 HALF bytes of the chunk
+        const uint32_t soff = (uint32_t)ch * HALF + (p < HALF ? p : p - HALF + row_b * RANK);
+        fetch_rows<4>(rsrcA, (uint32_t)lane * 16u, soff, base + XBYTES + p);
+      }
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll
+    for (int t = 0; t < ST - 1; ++t)
+      if (t < nch) fetch(t, t);
+    int st = 0;
+    for (int ch = 0; ch < nch; ++ch) {
+      wait_fetched<PER, ST - 2>(nch - 1 - ch);
+      if (ch + ST - 1 < nch) fetch(ch + ST - 1, st == 0 ? ST - 1 : st - 1);
+      const unsigned char* sp = lora_smem + (uint32_t)st * STAGE;
+      st = st + 1 == ST ? 0 : st + 1;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const u32x4 x = *(const u32x4*)(sp + baseX + (uint32_t)((wave * 8 + s * 2 + lhalf) ^ (lrow & 15)) * 16u);
+        const u32x4 h = *(const u32x4*)(sp + baseA + s * 2 * RANK * 16), l = *(const u32x4*)(sp + baseA + HALF + s * 2 * RANK * 16);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(valid ? h : zero), as_frag(x), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(valid ? l : zero), as_frag(x), acc, 0, 0, 0);
+      }
+    }
+    if (wave > 0) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) part[((wave - 1) * 16 + e) * 64 + lane] = acc[e];
+    }
+    __syncthreads();                                       // the sums, and every wave is done with the stages
+    if (wave == 0 && m < a.T && m / a.rows_per_copy == copy) {
+      uint16_t* out = (uint16_t*)a.tp[tgt] + (size_t)m * a.rp;
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        acc[e] = ((acc[e] + part[e * 64 + lane]) + part[(16 + e) * 64 + lane]) + part[(32 + e) * 64 + lane];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int j = g * 8 + lhalf * 4;
+        if (j >= RANK) continue;
+        const u32x2 pk = {pack_bf16x2(acc[g * 4] * a.scale, acc[g * 4 + 1] * a.scale),
+                          pack_bf16x2(acc[g * 4 + 2] * a.scale, acc[g * 4 + 3] * a.scale)};
+        *(u32x2*)(out + j) = pk;
+        *(u32x2*)(out + RANK + j) = pk;
+      }
+      if (lhalf == 0)
+        for (int c = 2 * RANK; c < a.rp; ++c) out[c] = 0;
+    }
+    if (copy >= last_copy) break;
+    __syncthreads();                                       // the sums of this copy are read before the next ones are written
+  }
+}
+
+template <int RANK>
+void launch_lora_down_ring(hipStream_t st, const MfmaLoraDownArgs& a) {
+  constexpr int lds = (RANK == 32 ? 3 : RANK == 16 ? 4 : 5) * (32 * 512 + RANK * 1024) + 3 * 16 * 64 * 4;
+  static const hipError_t attr_status = hipFuncSetAttribute((const void*)lora_down_ring_kernel<RANK>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  (void)attr_status;                                       // (a refusal shows as the launch's error)
+  lora_down_ring_kernel<RANK><<<dim3((a.T + 31) / 32, a.n_targets), 256, lds, st>>>(a);
 }
 
 // ---- pack the perturbed fp32 factors into the bf16 hi/lo operand layouts ---------------------------------
@@ -1124,8 +1218,21 @@ bool mfma_lora_down_supported(const MfmaLoraDownArgs& a) {
 
 void launch_lora_down_mfma(hipStream_t st, const MfmaLoraDownArgs& a) {
   int R = a.n_targets * a.rank;
-  if (R <= 32) lora_down_mfma_kernel<1><<<(a.T + 31) / 32, 256, 0, st>>>(a);
-  else lora_down_mfma_kernel<2><<<(a.T + 31) / 32, 256, 0, st>>>(a);
+  const dim3 grid((a.T + 31) / 32);
+  // at most a block per CU with one target each, and enough K to fetch: 32 tokens and one target per block
+  if ((int)grid.x * a.n_targets <= 256 && a.K >= 1024 && (a.rank == 8 || a.rank == 16 || a.rank == 32)) {
+    if (a.rank == 8) launch_lora_down_ring<8>(st, a);
+    else if (a.rank == 16) launch_lora_down_ring<16>(st, a);
+    else launch_lora_down_ring<32>(st, a);
+    return;
+  }
+  if (a.rows_per_copy % 32 == 0) {
+    if (R <= 32) lora_down_mfma_kernel<1, false><<<grid, 256, 0, st>>>(a);
+    else lora_down_mfma_kernel<2, false><<<grid, 256, 0, st>>>(a);
+  } else {
+    if (R <= 32) lora_down_mfma_kernel<1, true><<<grid, 256, 0, st>>>(a);
+    else lora_down_mfma_kernel<2, true><<<grid, 256, 0, st>>>(a);
+  }
 }
 
 void launch_pack_factors(hipStream_t st, const float* pert, int64_t P, int n_copies, const LoraLayerTable& tab,
