@@ -300,13 +300,13 @@ mpz_status mpz_debug_attention(mpz_model* m, const void* qkv, int32_t n_seq, int
 
 /* Test / measurement hook: the bf16 MFMA GEMM alone, out[M, N] = act(x[M, K] w[N, K]^T + bias), all [dev], x and w bf16,
  * out bf16 or fp32 (out_f32), act = -1 (none), MPZ_ACT_RELU, MPZ_ACT_GELU_ERF, or MPZ_ACT_SWIGLU (then w has 2N rows,
- * gate then up, bias 2N, out = SiLU(gate) * up); tile_cfg 0 = chosen by shape; 1, 6, 9, 10, 11, 12 = that block-tile configuration (other numbers fall back to the choice by shape).  Errors: NULL, SHAPE (K % 64, N % 4). */
+ * gate then up, bias 2N, out = SiLU(gate) * up); tile_cfg 0 = chosen by shape; 1, 6, 9, 10, 11, 12, 14 = that block-tile configuration (other numbers fall back to the choice by shape).  Errors: NULL, SHAPE (K % 64, N % 4). */
 mpz_status mpz_debug_gemm_bf16(int32_t M, int32_t N, int32_t K, const void* x, const void* w, const float* bias,
                                int32_t act, void* out, int32_t out_f32, int32_t tile_cfg, void* hip_stream);
 /* The same GEMM through the split-K path that passes over at most 256 stacked tokens take (k_splits blocks per output
  * tile stream disjoint shares of K and leave fp32 partial sums in `partial`; a second kernel adds them in a fixed order
- * and applies bias, activation, the fp32 residual [M, N] (may be NULL) and the output type).  k_splits = 0: the count
- * the library would choose for this shape (1 = no split: the one-block kernel runs); >= 2: forced.  partial [dev]
+ * and applies bias, activation, the fp32 residual [M, N] (may be NULL) and the output type).  k_splits = 0: what
+ * the library would choose for this shape (the streamed kernel, a count, or the one-block kernel); >= 2: forced.  partial [dev]
  * fp32[partial_elems], at least k_splits * M * N (SwiGLU: 2 N) elements.  mpz_debug_gemm_splits returns the chosen
  * count.  Errors: NULL, SHAPE. */
 mpz_status mpz_debug_gemm_bf16_splitk(int32_t M, int32_t N, int32_t K, const void* x, const void* w, const float* bias,
