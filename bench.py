@@ -24,7 +24,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0       # MI355X dense bf16 MFMA
-PEAK_FP64_VECTOR_TFLOPS = 78.6  # fp32-storage models accumulate in fp64 on the vector ALUs
+PEAK_FP64_VECTOR_TFLOPS = 78.6  # fp32-storage models accumulate in fp64 (the matrix cores' fp64 peak is the same)
 PEAK_HBM_GBPS = 8000.0          # MI355X HBM3E
 HEADLINE = "c5_llama7b"
 ALL_WORKLOADS = ("c1_tiny_fp32", "c2_opt125m", "c3_opt1p3b", "c4_llama1p1b", "c5_llama7b")

@@ -358,8 +358,8 @@ mpz_status mpz_debug_hbm_read_probe(const void* buf, int64_t rows, int64_t row_b
  * Errors: NULL, SHAPE (n_elems < 64 or not a multiple of 64). */
 mpz_status mpz_debug_dequant_nf4(const void* codes, const float* absmax, void* out, int64_t n_elems, void* hip_stream);
 
-/* Test hook: simple_only != 0 routes every stage through the shape-agnostic kernels (the only path of
- * fp32 models); 0 restores the default (bf16 models use the MFMA kernels wherever a shape allows).
+/* Test hook: simple_only != 0 routes every stage through the kernels that fp32 models take (shape-agnostic
+ * for bf16 ones); 0 restores the default (bf16 models use the MFMA kernels wherever a shape allows).
  * Invalidates the perturbed copies: call mpz_regen_noise again. */
 mpz_status mpz_debug_set_kernel_path(mpz_model* m, int32_t simple_only);
 

@@ -1,8 +1,8 @@
 // Straightforward kernels for every step of the batched MP-LoRA forward pass (Section 3: one pass over
 // n = 2q stacked copies, shared W, per-copy low-rank factors).  They take any shape and both storage
 // types: fp32 storage accumulates in fp64 and rounds once per stored element, bf16 storage accumulates
-// in fp32.  The bf16 hot path replaces the GEMM / attention kernels here with MFMA kernels; these stay
-// as the fp32-model path and as the shape-agnostic fallback.
+// in fp32.  The bf16 hot path replaces the GEMM / attention kernels here with MFMA kernels, and the fp32 launchers try
+// those of fp32_kernels.hip first; these stay as the shape-agnostic fallback of both.
 #include "common.h"
 #include "../../include/mpz.h"
 
