@@ -11,8 +11,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 // out = epilogue(x W^T) on tiles of 16 WT x 16 WT, one block per tile, its four waves a quarter of K each.  Bound by latency at
-// the sizes of the tiny models (a whole step of 2 blocks of d = 128 over 256 rows: 485 us with the shape-agnostic kernels, 117 us
-// with those of this file; a 125M-shaped block over 768 rows: 1348 us, 363 us) and by the fp64 matrix rate
+// the sizes of the tiny models (a whole step of 2 blocks of d = 128 over 256 rows: 485 us with the shape-agnostic kernels, 107 us
+// with those of this file; a 125M-shaped block over 768 rows: 1346 us, 360 us) and by the fp64 matrix rate
 // (72 TFLOP/s in the library) above: 768 x 2304 x 768.  Splitting K over the waves of a block, and not tiles, is what gives
 // small outputs enough wavefronts; operands come straight from L2 (a 32 x 32 tile needs 16 bytes per clock and CU).
 // MFMA layout: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16] and, of the result, D[l / 16 + 4 r][l % 16], r = 0..3.  Of
@@ -118,75 +118,6 @@ __global__ void __launch_bounds__(256) lora_down_f64_kernel(LoraDownArgs a) {
   }
 }
 
-// Causal attention of a short sequence: a block per (sequence, head, 16 queries) with K and V in LDS, a wave per four queries.
-// Scores, probabilities and sums as in the shape-agnostic kernel (a wave per query that reads K and V from memory row by
-// row: 768 tokens, 12 heads of 64, S = 96: 51 us).
-constexpr int ATT_MAX_S = 128, ATT_QB = 16;
-__global__ void __launch_bounds__(256) attention_f64_kernel(const float* __restrict__ qkv, int qkv_stride, float* __restrict__ out, int S_grid,
-                                                            int H, int Hkv, int dh, float scale, const int32_t* __restrict__ cu, int E,
-                                                            int rows_per_copy) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int ks = dh + 1;                                   // row stride of K, V and Q: lanes that walk rows hit distinct banks
-  double* sc = (double*)smem;                              // [ATT_QB][S_grid]: scores, then probabilities
-  float* sk = (float*)(sc + ATT_QB * S_grid);              // [S_grid][ks]
-  float* sv = sk + S_grid * ks;
-  float* sq = sv + S_grid * ks;                            // [ATT_QB][ks]
-  const int qblocks = (S_grid + ATT_QB - 1) / ATT_QB;
-  const int qb = blockIdx.x % qblocks, head = (blockIdx.x / qblocks) % H;
-  const int seq = blockIdx.x / (qblocks * H);
-  int S = S_grid;
-  int64_t row0 = (int64_t)seq * S_grid;
-  if (cu != nullptr) {                                     // packed batch: S_grid is the longest sequence, this one may be shorter
-    const int e = seq % E;
-    S = cu[e + 1] - cu[e];
-    row0 = (int64_t)(seq / E) * rows_per_copy + cu[e];
-  }
-  const int q0 = qb * ATT_QB;
-  if (q0 >= S) return;                                     // block-uniform
-  const int kvh = head / (H / Hkv), d = H * dh, dkv = Hkv * dh;
-  const int nq = S - q0 < ATT_QB ? S - q0 : ATT_QB, nk = q0 + nq;
-  for (int i = threadIdx.x; i < nk * dh; i += 256) {
-    const int j = i / dh, c = i % dh;
-    const float* r = qkv + (row0 + j) * qkv_stride + d + kvh * dh + c;
-    sk[j * ks + c] = r[0];
-    sv[j * ks + c] = r[dkv];
-  }
-  for (int i = threadIdx.x; i < nq * dh; i += 256)
-    sq[(i / dh) * ks + i % dh] = qkv[(row0 + q0 + i / dh) * qkv_stride + head * dh + i % dh];
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int qi = wave; qi < nq; qi += 4) {
-    const int i = q0 + qi;
-    double* row = sc + qi * S_grid;
-    double mx = -1e30;
-    for (int j = lane; j <= i; j += 64) {
-      double dot = 0.0;
-      for (int c = 0; c < dh; ++c) dot += (double)sq[qi * ks + c] * (double)sk[j * ks + c];
-      const double s = (double)(float)dot * (double)scale;
-      row[j] = s;
-      mx = s > mx ? s : mx;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { const double v = __shfl_xor(mx, o, 64); mx = v > mx ? v : mx; }
-    double sum = 0.0;
-    for (int j = lane; j <= i; j += 64) {
-      const double p = (double)(float)exp(row[j] - mx);
-      row[j] = p;
-      sum += p;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    __builtin_amdgcn_wave_barrier();                       // (the wave's own LDS writes are read below in program order)
-    for (int c = lane; c < dh; c += 64) {
-      double acc = 0.0;
-      for (int j = 0; j <= i; ++j) acc += row[j] * (double)sv[j * ks + c];
-      out[(row0 + i) * d + head * dh + c] = (float)(acc / sum);
-    }
-  }
-}
-
-size_t attention_f64_lds(int S, int dh) { return (size_t)ATT_QB * S * 8 + (size_t)(2 * S + ATT_QB) * (dh + 1) * 4; }
-
 }  // namespace
 
 // 32 x 32 tiles once they give every CU a block, 16 x 16 below (256 x 128 x 128: 32 against 128 blocks)
@@ -204,16 +135,6 @@ bool launch_lora_down_f64(hipStream_t st, const LoraDownArgs& a) {
     if ((uintptr_t)a.Ac[t] & 15) return false;
   const int64_t items = (int64_t)a.T * a.n_targets * (a.rank / 4);
   lora_down_f64_kernel<<<(unsigned)((items + 3) / 4), 256, 0, st>>>(a);
-  return true;
-}
-
-bool launch_attention_f64(hipStream_t st, int dtype, const void* qkv, int qkv_stride, void* out, int n_seq, int S, int H, int Hkv, int dh,
-                          const int32_t* cu, int E, int rows_per_copy) {
-  const size_t lds = attention_f64_lds(S, dh);
-  if (dtype != MPZ_DTYPE_F32 || S > ATT_MAX_S || lds > 64 * 1024) return false;
-  const int qblocks = (S + ATT_QB - 1) / ATT_QB;
-  attention_f64_kernel<<<(unsigned)((int64_t)n_seq * H * qblocks), 256, lds, st>>>((const float*)qkv, qkv_stride, (float*)out, S, H, Hkv, dh,
-                                                                                  (float)(1.0 / sqrt((double)dh)), cu, E, rows_per_copy);
   return true;
 }
 

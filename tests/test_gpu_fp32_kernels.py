@@ -1,5 +1,5 @@
 """fp32 models on the 64-bit matrix instructions: parity with the oracle at the edges of the tiles (16 x 16 and 32 x 32, K by
-quarters of 16) and of the short-sequence attention (16 queries a block, S <= 128; 129 takes the general kernel).  Both sides
+quarters of 16), with K that no quarter divides and sequences of up to 129 tokens.  Both sides
 sum in binary64 and round every stored value once, so only values next to a rounding border may differ: the bar of the
 other fp32 parity tests."""
 import numpy as np
@@ -14,7 +14,7 @@ SHAPES = {
     "d36_heads_of_6": MINI_LLAMA.with_(d_model=36, n_heads=6, n_kv_heads=3, d_ffn=52, q=1, E=1, S=15, max_seq=16, lora_rank=4),
     "d20_ffn_17_general": MINI_OPT.with_(d_model=20, n_heads=2, n_kv_heads=2, d_ffn=17, q=1, E=1, S=10, lora_rank=8),
     "S128_big_tiles": MINI_OPT.with_(d_model=64, n_heads=4, n_kv_heads=4, d_ffn=260, q=2, E=2, S=128, max_seq=129, lora_rank=12),
-    "S129_general_attention": MICRO.with_(q=1, E=1, S=129, max_seq=129, lora_rank=4),
+    "S129": MICRO.with_(q=1, E=1, S=129, max_seq=129, lora_rank=4),
     "S17_heads_of_64": MINI_LLAMA.with_(d_model=128, n_heads=2, n_kv_heads=1, d_ffn=96, q=2, E=3, S=17, max_seq=32, lora_rank=64,
                                         lora_targets=("q", "o")),
 }
