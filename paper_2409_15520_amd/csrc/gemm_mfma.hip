@@ -367,8 +367,7 @@ gemm_bf16_kernel(MfmaGemmArgs a) {
   }
 
   // per-copy low-rank term: extra K-steps with the packed factor [B_hi | B_lo] of a copy against the duplicated
-  // bottleneck activations [t | t].  Copies are whole multiples of 32 rows, so every 32-row MFMA tile belongs to
-  // one copy (a block tile may span several); segments are aligned to the block tile.
+  // bottleneck activations [t | t] (a block tile may span several copies); segments are aligned to the block tile.
   if constexpr (PREF) {                                    // (zeros where nothing was requested: no branch around the accumulators)
 #pragma unroll
     for (int j = 0; j < NJ; ++j)

@@ -5,7 +5,7 @@
 //   * the work is the list of (128-feature tile, K-tile of 64) pairs, dealt to one persistent block per CU in equal
 //     contiguous runs, so no CU has a round more than another, whatever N and K (a block's run may end one tile and begin
 //     the next; a tile's sums come from as many blocks as its K-tiles fall on);
-//   * the tiles are fetched straight into a ring of LDS stages, three to five K-tiles ahead, across the tile borders of a
+//   * the tiles are fetched straight into a ring of LDS stages, two to five K-tiles ahead, across the tile borders of a
 //     run; one block barrier per K-tile;
 //   * each block leaves the raw fp32 sums of its part of a tile in its slot of the partial buffer; the reduction kernels add
 //     the slots of a tile in block order (deterministic) and apply the epilogue.
