@@ -77,6 +77,9 @@ struct LoraSeg {              // one adapted column range of a linear
 // fp32_kernels.hip: fp32 models on v_mfma_f64 and wave reductions; false (nothing launched): shape or alignment not taken
 struct LinearArgs;
 struct LoraDownArgs;
+// ordered_kernels.hip: bf16 models, the sums of the shape-agnostic kernels bit for bit on v_mfma_f32; false: as above
+bool launch_linear_ordered(hipStream_t st, const LinearArgs& a);
+bool launch_lora_down_ordered(hipStream_t st, const LoraDownArgs& a);
 bool launch_linear_f64(hipStream_t st, const LinearArgs& a);
 bool launch_lora_down_f64(hipStream_t st, const LoraDownArgs& a);
 

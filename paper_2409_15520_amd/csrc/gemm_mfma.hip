@@ -300,8 +300,7 @@ gemm_bf16_kernel(MfmaGemmArgs a) {
 #pragma unroll
       for (int i = 0; i < NI; ++i) pre_fw[j][i] = as_frag(u32x4{0u, 0u, 0u, 0u});
     }
-    // (with split K the low-rank term goes into split 0's sum; tiles of several copies: no early request)
-    for (int s = 0; s < a.n_seg && split == 0 && a.rows_per_copy % 32 == 0; ++s)
+    for (int s = 0; s < a.n_seg && split == 0; ++s)          // (with split K the low-rank term goes into split 0's sum)
       if (n0 >= a.seg[s].col_begin && n0 < a.seg[s].col_end && a.seg[s].rp == 16) pre_seg = s;
     if (pre_seg >= 0) {
       const MfmaLoraSeg& sg = a.seg[pre_seg];
@@ -520,18 +519,16 @@ __global__ void __launch_bounds__(512, 1) mfma_probe_kernel(const uint16_t* __re
 // fragments straight from the row-major x would touch 32 rows per instruction), one chunk in flight in registers
 // while the previous one is consumed.  Inside a chunk the 4 waves split K; their partial sums meet in LDS in a
 // fixed order.  MFMA rows = bottleneck columns j of all targets that share the input x.
-template <int JT, bool MIXED>   // JT: number of 32-row MFMA tiles covering n_targets * r bottleneck columns; MIXED: 32 rows of several copies
+template <int JT>   // number of 32-row MFMA tiles covering n_targets * r bottleneck columns
 __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs a) {
   constexpr int KCH = 256, XS = KCH + 8;
   __shared__ __align__(16) uint16_t sx[3][32 * XS];
   __shared__ float part[3][JT][16][64];          // partial sums of waves 1..3
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lrow = lane & 31, lhalf = lane >> 5;
   const int m0 = blockIdx.x * 32;
+  const int copy = m0 / a.rows_per_copy;
   const int R = a.n_targets * a.rank;
   const uint16_t* X = (const uint16_t*)a.x + (size_t)m0 * a.K;
-  // MIXED (copies that are no multiples of 32 rows): one pass per copy, each storing its rows
-  const int m_last = m0 + 31 < a.T ? m0 + 31 : a.T - 1, last_copy = m_last / a.rows_per_copy;
-  for (int copy = m0 / a.rows_per_copy;; ++copy) {
   // packed A: per copy and target [2][K / 8][rank][8] (hi part then lo part): the 16-byte pieces that the lanes of
   // a wave fetch for one MFMA operand (rank rows x 2 neighbouring chunks of 8 k) are contiguous
   const uint16_t* Ah[JT];
@@ -556,8 +553,7 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
 
   // chunk staging: piece p = tid + 256 i of the 32 x 256 chunk: row p / 32, 16-byte column p % 32
   const int grow = tid >> 5, gcol = (tid & 31) * 8;       // i = 0; 8 rows further down per i
-  // (rows past T lie outside the buffer: zeros, and never stored)
-  const __amdgpu_buffer_rsrc_t rsrcX = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(X), 0, (m_last - m0 + 1) * a.K * 2, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrcX = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(X), 0, 32 * a.K * 2, 0x00020000);
   const int voffX = (grow * a.K + gcol) * 2;
   // three chunks of x in flight (registers), three LDS buffers: a K = 768 row is fetched in one go
   constexpr int PD = 3;
@@ -615,13 +611,13 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
       for (int e = 0; e < 16; ++e) part[wave - 1][t][e][lane] = acc[t][e];
   }
   __syncthreads();
-  const int m = m0 + lrow;
-  if (wave == 0 && m < a.T && (!MIXED || m / a.rows_per_copy == copy)) {
+  if (wave != 0) return;
 #pragma unroll
   for (int t = 0; t < JT; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = ((acc[t][e] + part[0][t][e][lane]) + part[1][t][e][lane]) + part[2][t][e][lane];
   // lane holds token m0 + lrow, bottleneck columns j = t*32 + g*8 + lhalf*4 + e
+  const int m = m0 + lrow;
   // (ranks are multiples of 4: the 4 consecutive columns of a lane belong to one target and go out as one 8-byte store)
 #pragma unroll
   for (int t = 0; t < JT; ++t)
@@ -640,10 +636,6 @@ __global__ void __launch_bounds__(256, 2) lora_down_mfma_kernel(MfmaLoraDownArgs
   if (lhalf == 0)
     for (int tgt = 0; tgt < a.n_targets; ++tgt)
       for (int c = 2 * a.rank; c < a.rp; ++c) ((uint16_t*)a.tp[tgt])[(size_t)m * a.rp + c] = 0;
-  }
-  if (!MIXED || copy >= last_copy) break;
-  __syncthreads();                               // the sums of this copy are read before the next ones are written
-  }
 }
 
 // The same where blocks of 32 tokens leave most CUs idle (128 tokens: four blocks): a block per 32 tokens and target, x and the
@@ -657,10 +649,9 @@ __global__ void __launch_bounds__(256, 1) lora_down_ring_kernel(MfmaLoraDownArgs
   extern __shared__ __align__(16) unsigned char lora_smem[];
   float* part = (float*)(lora_smem + ST * STAGE);          // [3][16][64]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lrow = lane & 31, lhalf = lane >> 5;
-  const int m0 = blockIdx.x * 32, tgt = blockIdx.y, m = m0 + lrow, nch = a.K / 256;
-  const int m_last = m0 + 31 < a.T ? m0 + 31 : a.T - 1, last_copy = m_last / a.rows_per_copy;
+  const int m0 = blockIdx.x * 32, tgt = blockIdx.y, m = m0 + lrow, nch = a.K / 256, copy = m0 / a.rows_per_copy;
   const uint32_t row_b = (uint32_t)a.K * 2u;
-  const i32x4 rsrcX = buffer_of((const char*)a.x + (size_t)m0 * row_b, (size_t)(m_last - m0 + 1) * row_b);   // (rows past T: outside)
+  const i32x4 rsrcX = buffer_of((const char*)a.x + (size_t)m0 * row_b, (size_t)32 * row_b);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lora_smem;
   uint32_t voffX[4];                                       // two rows of 512 bytes per fetch, 16-byte chunk c of row r at c ^ (r % 16)
 #pragma unroll
@@ -671,65 +662,60 @@ __global__ void __launch_bounds__(256, 1) lora_down_ring_kernel(MfmaLoraDownArgs
   const bool valid = lrow < RANK;
   const uint32_t baseX = (uint32_t)lrow * 512u, baseA = XBYTES + (uint32_t)((wave * 8 + lhalf) * RANK + (valid ? lrow : 0)) * 16u;
   const u32x4 zero = {0u, 0u, 0u, 0u};
-  for (int copy = m0 / a.rows_per_copy;; ++copy) {
-    // a chunk's factors, hi part and lo part, are RANK x 512 contiguous bytes each
-    const i32x4 rsrcA = buffer_of((const uint16_t*)a.ap[tgt] + (size_t)copy * a.copy_stride, (size_t)a.K * RANK * 4);
-    auto fetch = [&](int ch, int st) {
-      const uint32_t base = lds0 + (uint32_t)st * STAGE;
+  // a chunk's factors, hi part and lo part, are RANK x 512 contiguous bytes each
+  const i32x4 rsrcA = buffer_of((const uint16_t*)a.ap[tgt] + (size_t)copy * a.copy_stride, (size_t)a.K * RANK * 4);
+  auto fetch = [&](int ch, int st) {
+    const uint32_t base = lds0 + (uint32_t)st * STAGE;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) fetch_rows<4>(rsrcX, voffX[t], (uint32_t)ch * 512u, base + (uint32_t)(wave * 4 + t) * 1024u);
+    for (int t = 0; t < 4; ++t) fetch_rows<4>(rsrcX, voffX[t], (uint32_t)ch * 512u, base + (uint32_t)(wave * 4 + t) * 1024u);
 #pragma unroll
-      for (int t = 0; t < RANK / 4; ++t) {
-        const uint32_t p = (uint32_t)(wave * (RANK / 4) + t) * 1024u;                 // of the 2 HALF bytes of the chunk
-        const uint32_t soff = (uint32_t)ch * HALF + (p < HALF ? p : p - HALF + row_b * RANK);
-        fetch_rows<4>(rsrcA, (uint32_t)lane * 16u, soff, base + XBYTES + p);
-      }
-    };
-    f32x16 acc;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-#pragma unroll
-    for (int t = 0; t < ST - 1; ++t)
-      if (t < nch) fetch(t, t);
-    int st = 0;
-    for (int ch = 0; ch < nch; ++ch) {
-      wait_fetched<PER, ST - 2>(nch - 1 - ch);
-      if (ch + ST - 1 < nch) fetch(ch + ST - 1, st == 0 ? ST - 1 : st - 1);
-      const unsigned char* sp = lora_smem + (uint32_t)st * STAGE;
-      st = st + 1 == ST ? 0 : st + 1;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const u32x4 x = *(const u32x4*)(sp + baseX + (uint32_t)((wave * 8 + s * 2 + lhalf) ^ (lrow & 15)) * 16u);
-        const u32x4 h = *(const u32x4*)(sp + baseA + s * 2 * RANK * 16), l = *(const u32x4*)(sp + baseA + HALF + s * 2 * RANK * 16);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(valid ? h : zero), as_frag(x), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(valid ? l : zero), as_frag(x), acc, 0, 0, 0);
-      }
+    for (int t = 0; t < RANK / 4; ++t) {
+      const uint32_t p = (uint32_t)(wave * (RANK / 4) + t) * 1024u;                   // of the 2 HALF bytes of the chunk
+      const uint32_t soff = (uint32_t)ch * HALF + (p < HALF ? p : p - HALF + row_b * RANK);
+      fetch_rows<4>(rsrcA, (uint32_t)lane * 16u, soff, base + XBYTES + p);
     }
-    if (wave > 0) {
+  };
+  f32x16 acc;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) part[((wave - 1) * 16 + e) * 64 + lane] = acc[e];
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll
+  for (int t = 0; t < ST - 1; ++t)
+    if (t < nch) fetch(t, t);
+  int st = 0;
+  for (int ch = 0; ch < nch; ++ch) {
+    wait_fetched<PER, ST - 2>(nch - 1 - ch);
+    if (ch + ST - 1 < nch) fetch(ch + ST - 1, st == 0 ? ST - 1 : st - 1);
+    const unsigned char* sp = lora_smem + (uint32_t)st * STAGE;
+    st = st + 1 == ST ? 0 : st + 1;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const u32x4 x = *(const u32x4*)(sp + baseX + (uint32_t)((wave * 8 + s * 2 + lhalf) ^ (lrow & 15)) * 16u);
+      const u32x4 h = *(const u32x4*)(sp + baseA + s * 2 * RANK * 16), l = *(const u32x4*)(sp + baseA + HALF + s * 2 * RANK * 16);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(valid ? h : zero), as_frag(x), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(valid ? l : zero), as_frag(x), acc, 0, 0, 0);
     }
-    __syncthreads();                                       // the sums, and every wave is done with the stages
-    if (wave == 0 && m < a.T && m / a.rows_per_copy == copy) {
-      uint16_t* out = (uint16_t*)a.tp[tgt] + (size_t)m * a.rp;
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        acc[e] = ((acc[e] + part[e * 64 + lane]) + part[(16 + e) * 64 + lane]) + part[(32 + e) * 64 + lane];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int j = g * 8 + lhalf * 4;
-        if (j >= RANK) continue;
-        const u32x2 pk = {pack_bf16x2(acc[g * 4] * a.scale, acc[g * 4 + 1] * a.scale),
-                          pack_bf16x2(acc[g * 4 + 2] * a.scale, acc[g * 4 + 3] * a.scale)};
-        *(u32x2*)(out + j) = pk;
-        *(u32x2*)(out + RANK + j) = pk;
-      }
-      if (lhalf == 0)
-        for (int c = 2 * RANK; c < a.rp; ++c) out[c] = 0;
-    }
-    if (copy >= last_copy) break;
-    __syncthreads();                                       // the sums of this copy are read before the next ones are written
   }
+  if (wave > 0) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) part[((wave - 1) * 16 + e) * 64 + lane] = acc[e];
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  uint16_t* out = (uint16_t*)a.tp[tgt] + (size_t)m * a.rp;
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+    acc[e] = ((acc[e] + part[e * 64 + lane]) + part[(16 + e) * 64 + lane]) + part[(32 + e) * 64 + lane];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int j = g * 8 + lhalf * 4;
+    if (j >= RANK) continue;
+    const u32x2 pk = {pack_bf16x2(acc[g * 4] * a.scale, acc[g * 4 + 1] * a.scale),
+                      pack_bf16x2(acc[g * 4 + 2] * a.scale, acc[g * 4 + 3] * a.scale)};
+    *(u32x2*)(out + j) = pk;
+    *(u32x2*)(out + RANK + j) = pk;
+  }
+  if (lhalf == 0)
+    for (int c = 2 * RANK; c < a.rp; ++c) out[c] = 0;
 }
 
 template <int RANK>
@@ -737,7 +723,7 @@ void launch_lora_down_ring(hipStream_t st, const MfmaLoraDownArgs& a) {
   constexpr int lds = (RANK == 32 ? 3 : RANK == 16 ? 4 : 5) * (32 * 512 + RANK * 1024) + 3 * 16 * 64 * 4;
   static const hipError_t attr_status = hipFuncSetAttribute((const void*)lora_down_ring_kernel<RANK>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   (void)attr_status;                                       // (a refusal shows as the launch's error)
-  lora_down_ring_kernel<RANK><<<dim3((a.T + 31) / 32, a.n_targets), 256, lds, st>>>(a);
+  lora_down_ring_kernel<RANK><<<dim3(a.T / 32, a.n_targets), 256, lds, st>>>(a);
 }
 
 // ---- pack the perturbed fp32 factors into the bf16 hi/lo operand layouts ---------------------------------
@@ -888,6 +874,7 @@ bool known_cfg(int cfg) { return cfg == 1 || cfg == 6 || (cfg >= 9 && cfg <= 14)
 
 bool cfg_ok(const MfmaGemmArgs& a, int cfg) {
   if (cfg == 14 && !gemm_ring_supported(a)) return false;
+  if (a.n_seg > 0 && (a.rows_per_copy % 32 || a.M % 32)) return false;
   const int bn = tile_bn(cfg);
   for (int s = 0; s < a.n_seg; ++s)
     if (a.seg[s].col_begin % bn || a.seg[s].col_end % bn) return false;
@@ -1212,12 +1199,12 @@ void launch_mfma_probe(hipStream_t st, const void* operands, int blocks, int ite
 
 bool mfma_lora_down_supported(const MfmaLoraDownArgs& a) {
   int R = a.n_targets * a.rank;
-  return a.K % 256 == 0 && R <= 64 && a.rp % 8 == 0 && a.rank % 4 == 0;
+  return a.K % 256 == 0 && a.T % 32 == 0 && a.rows_per_copy % 32 == 0 && R <= 64 && a.rp % 8 == 0 && a.rank % 4 == 0;
 }
 
 void launch_lora_down_mfma(hipStream_t st, const MfmaLoraDownArgs& a) {
   int R = a.n_targets * a.rank;
-  const dim3 grid((a.T + 31) / 32);
+  const dim3 grid(a.T / 32);
   // at most a block per CU with one target each, and enough K to fetch: 32 tokens and one target per block
   if ((int)grid.x * a.n_targets <= 256 && a.K >= 1024 && (a.rank == 8 || a.rank == 16 || a.rank == 32)) {
     if (a.rank == 8) launch_lora_down_ring<8>(st, a);
@@ -1225,13 +1212,8 @@ void launch_lora_down_mfma(hipStream_t st, const MfmaLoraDownArgs& a) {
     else launch_lora_down_ring<32>(st, a);
     return;
   }
-  if (a.rows_per_copy % 32 == 0) {
-    if (R <= 32) lora_down_mfma_kernel<1, false><<<grid, 256, 0, st>>>(a);
-    else lora_down_mfma_kernel<2, false><<<grid, 256, 0, st>>>(a);
-  } else {
-    if (R <= 32) lora_down_mfma_kernel<1, true><<<grid, 256, 0, st>>>(a);
-    else lora_down_mfma_kernel<2, true><<<grid, 256, 0, st>>>(a);
-  }
+  if (R <= 32) lora_down_mfma_kernel<1><<<grid, 256, 0, st>>>(a);
+  else lora_down_mfma_kernel<2><<<grid, 256, 0, st>>>(a);
 }
 
 void launch_pack_factors(hipStream_t st, const float* pert, int64_t P, int n_copies, const LoraLayerTable& tab,

@@ -577,8 +577,8 @@ hipError_t launch_pipe_lr(hipStream_t st, const MfmaGemmArgs& a) {
 }  // namespace
 
 // bf16 weights, whole pairs of K-tiles, 16-byte output pieces that begin on 16 bytes; no GELU (erf around 256 live
-// accumulators spills); the low-rank term with rank <= 16,
-// copies of whole 32-row pieces and no activation behind it.  What is
+// accumulators spills); the low-rank term with rank <= 16
+// and no activation behind it.  What is
 // refused takes the tile of the same size in gemm_mfma.hip.
 bool gemm_pipe_supported(const MfmaGemmArgs& a) {
   if (a.w_scale != nullptr || a.w_absmax != nullptr || a.k_splits > 1 || a.K % 128 || a.act == MPZ_ACT_GELU_ERF || !fetch_aligned(a)) return false;
@@ -588,7 +588,7 @@ bool gemm_pipe_supported(const MfmaGemmArgs& a) {
   if (!a.out_f32 && a.residual != nullptr) return false;
   if (a.dual || a.rope_cos != nullptr) { if (a.out_f32) return false; }
   else if (a.act >= 0 && (a.out_f32 || a.n_seg || a.act != MPZ_ACT_RELU)) return false;
-  if (a.n_seg && (a.rows_per_copy % 32 || a.M % 32 || (a.out_f32 && a.residual == nullptr))) return false;
+  if (a.n_seg && a.out_f32 && a.residual == nullptr) return false;
   for (int s = 0; s < a.n_seg; ++s)
     if (a.seg[s].rp != a.seg[0].rp || (a.seg[s].rp != 16 && a.seg[s].rp != 32)) return false;
   return true;

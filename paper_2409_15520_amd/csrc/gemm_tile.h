@@ -20,60 +20,42 @@ __device__ __forceinline__ float gelu_erf(float v) { return 0.5f * v * (1.0f + e
 __device__ __noinline__ float gelu_erf_call(float v) { return gelu_erf(v); }
 
 // Per-copy low-rank term: extra K-steps with the packed factor [B_hi | B_lo] of a copy against the duplicated
-// bottleneck activations [t | t].  Segments begin and end on the borders of block tiles.  Where copies are whole multiples of
-// 32 rows, every 32-row MFMA tile belongs to one copy; a tile that holds rows of several copies takes one pass per copy,
-// with the rows of the others zero (a 1.1B-shaped block, 8 copies of 231 rows: 2347 us with the shape-agnostic kernels that
-// such batches took before, 311 us).
+// bottleneck activations [t | t].  Copies are whole multiples of 32 rows, so every 32-row MFMA tile belongs to one copy
+// (a block tile may span several); segments are aligned to the block tile.
 template <int NI, int NJ>
 __device__ __forceinline__ void add_low_rank(const MfmaGemmArgs& a, f32x16 (&acc)[NI][NJ], int m0, int n0, int wm, int wn, int lane) {
   const int lrow = lane & 31, lhalf = lane >> 5;
-  const bool mixed = a.rows_per_copy % 32 != 0;            // (uniform) tiles may hold rows of several copies
-  const u32x4 zero = {0u, 0u, 0u, 0u};
   for (int s = 0; s < a.n_seg; ++s) {
     const MfmaLoraSeg& sg = a.seg[s];
     if (n0 < sg.col_begin || n0 >= sg.col_end) continue;
     const uint16_t* tp = (const uint16_t*)sg.tp;
     for (int ks = 0; ks < sg.rp; ks += 16) {
-      for (int dc = 0;; ++dc) {                            // pass dc: the dc-th copy of every tile
-        // all fragments of the step first, then its MFMAs: the block waits for L2 once per step, not once per tile
-        bf16x8 lx[NJ], lw[NJ][NI];
-        bool again = false;
+      // all fragments of the step first, then its MFMAs: the block waits for L2 once per step, not once per tile
+      bf16x8 lx[NJ], lw[NJ][NI];
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          int mt = m0 + wm + j * 32;                       // first row of this MFMA tile
-          if (!mixed) mt = mt < a.M ? mt : a.M - 32;       // tiles past the end compute discarded values in bounds
-          int row = mt + lrow, first = mt;
-          if (mixed) { row = row < a.M ? row : a.M - 1; first = mt < a.M ? mt : a.M - 1; }
-          int copy = first / a.rows_per_copy + dc;
-          u32x4 x = *(const u32x4*)(tp + (size_t)row * sg.rp + ks + lhalf * 8);
-          if (mixed) {
-            const int last = (mt + 31 < a.M ? mt + 31 : a.M - 1) / a.rows_per_copy;
-            again = again || copy < last;
-            x = row / a.rows_per_copy == copy ? x : zero;
-            copy = copy < last ? copy : last;
-          }
-          const uint16_t* bp = (const uint16_t*)sg.bp + (size_t)copy * sg.copy_stride;
-          lx[j] = as_frag(x);
+      for (int j = 0; j < NJ; ++j) {
+        int mt = m0 + wm + j * 32;                       // first row of this MFMA tile
+        mt = mt < a.M ? mt : a.M - 32;                   // tiles past the end compute discarded values in bounds
+        const int copy = mt / a.rows_per_copy;
+        const uint16_t* bp = (const uint16_t*)sg.bp + (size_t)copy * sg.copy_stride;
+        lx[j] = as_frag(*(const u32x4*)(tp + (size_t)(mt + lrow) * sg.rp + ks + lhalf * 8));
 #pragma unroll
-          for (int i = 0; i < NI; ++i) {
-            const int n = n0 + wn + i * 32 + lrow - sg.col_begin;
-            lw[j][i] = as_frag(*(const u32x4*)(bp + (size_t)n * sg.rp + ks + lhalf * 8));
-          }
+        for (int i = 0; i < NI; ++i) {
+          const int n = n0 + wn + i * 32 + lrow - sg.col_begin;
+          lw[j][i] = as_frag(*(const u32x4*)(bp + (size_t)n * sg.rp + ks + lhalf * 8));
         }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-          for (int i = 0; i < NI; ++i)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lw[j][i], lx[j], acc[i][j], 0, 0, 0);
-        if (!again) break;
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lw[j][i], lx[j], acc[i][j], 0, 0, 0);
     }
   }
 }
 
-// The same on 16 x 16 tiles (v_mfma_f32_16x16x32): lane l holds features 4 (l / 16) .. + 3 of token l % 16.  Every 16-token tile
-// takes one pass per copy it holds rows of.
+// The same on 16 x 16 tiles (v_mfma_f32_16x16x32): lane l holds features 4 (l / 16) .. + 3 of token l % 16.
 template <int NI, int NJ>
 __device__ __forceinline__ void add_low_rank_16(const MfmaGemmArgs& a, f32x4 (&acc)[NI][NJ], int m0, int n0, int wm, int wn, int lane) {
   const int l16 = lane & 15, lq = lane >> 4;
@@ -88,17 +70,14 @@ __device__ __forceinline__ void add_low_rank_16(const MfmaGemmArgs& a, f32x4 (&a
       for (int j = 0; j < NJ; ++j) {
         const int mt = m0 + wm + j * 16;
         if (mt >= a.M) continue;                           // (uniform)
-        const int row = mt + l16 < a.M ? mt + l16 : a.M - 1, last = (mt + 15 < a.M ? mt + 15 : a.M - 1) / a.rows_per_copy;
-        const u32x4 xv = *(const u32x4*)((const uint16_t*)sg.tp + (size_t)row * sg.rp + k8);
-        for (int copy = mt / a.rows_per_copy; copy <= last; ++copy) {
-          const u32x4 x = here && row / a.rows_per_copy == copy ? xv : zero;
-          const uint16_t* bp = (const uint16_t*)sg.bp + (size_t)copy * sg.copy_stride + k8;
+        u32x4 x = *(const u32x4*)((const uint16_t*)sg.tp + (size_t)(mt + l16) * sg.rp + k8);
+        x = here ? x : zero;
+        const uint16_t* bp = (const uint16_t*)sg.bp + (size_t)(mt / a.rows_per_copy) * sg.copy_stride + k8;
 #pragma unroll
-          for (int i = 0; i < NI; ++i) {
-            u32x4 w = *(const u32x4*)(bp + (size_t)(n0 + wn + i * 16 + l16 - sg.col_begin) * sg.rp);
-            w = here ? w : zero;
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(w), as_frag(x), acc[i][j], 0, 0, 0);
-          }
+        for (int i = 0; i < NI; ++i) {
+          u32x4 w = *(const u32x4*)(bp + (size_t)(n0 + wn + i * 16 + l16 - sg.col_begin) * sg.rp);
+          w = here ? w : zero;
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(w), as_frag(x), acc[i][j], 0, 0, 0);
         }
       }
     }

@@ -465,7 +465,7 @@ bool gemm(mpz_model* m, const LinearArgs& a, NormAfter* then = nullptr) {
     m->deferred = "int8 weights: a GEMM of this pass has a shape the MFMA kernel does not take";
     return true;
   }
-  launch_linear_simple(m->stream, dense);
+  if (!(m->use_mfma && launch_linear_ordered(m->stream, dense))) launch_linear_simple(m->stream, dense);
   return true;
 }
 
@@ -628,7 +628,7 @@ void run_qkv(mpz_model* m, const Buffers& b, int l, int E, int S, bool rope, int
     if (nt && !lora_done) {
       if (!m->pert_valid) m->deferred = "internal: a pass needs the fp32 factor copies and they were not prepared";
       ProfScope ps(m, MPZ_PROF_LORA_DOWN, 2.0 * T * (double)d * nt * r, esz(m) * T * ((double)d + (double)nt * r));
-      launch_lora_down_simple(st, da);
+      if (!(m->use_mfma && launch_lora_down_ordered(st, da))) launch_lora_down_simple(st, da);
     }
     set_weight(qa, weight_operand(m, lw.w_qkv, lw.s_qkv, nqkv, d, T));
     if (rope) {
@@ -709,7 +709,7 @@ void run_layers(mpz_model* m, float* h, int l0, int l1, int E, int S) {
       if (!o_done) {
         if (!m->pert_valid) m->deferred = "internal: a pass needs the fp32 factor copies and they were not prepared";
         ProfScope ps(m, MPZ_PROF_LORA_DOWN, 2.0 * T * (double)d * r, esz(m) * T * ((double)d + (double)r));
-        launch_lora_down_simple(st, oda);
+        if (!(m->use_mfma && launch_lora_down_ordered(st, oda))) launch_lora_down_simple(st, oda);
       }
       oa.n_seg = 1;
       oa.seg[0].col_begin = 0; oa.seg[0].col_end = d; oa.seg[0].t = b.t; oa.seg[0].t_stride = r; oa.seg[0].t_off = 0;

@@ -352,7 +352,7 @@ void launch_norm_lora_t(hipStream_t st, int kind, float eps, const float* h, con
 // 1.3B-shaped one).
 bool norm_lora_supported(int d, const MfmaLoraDownArgs& a) {
   const bool wide = a.n_targets * a.rank > 32;
-  return (d == 768 || d == 1024 || (d == 2048 && wide)) && a.K == d && a.T % 32 == 0 && a.rows_per_copy % 32 == 0 && mfma_lora_down_supported(a);
+  return (d == 768 || d == 1024 || (d == 2048 && wide)) && a.K == d && mfma_lora_down_supported(a);
 }
 
 void launch_norm_lora(hipStream_t st, int kind, float eps, const float* h, const float* g, const float* b, void* out,
