@@ -306,13 +306,16 @@ mpz_status mpz_debug_gemm_bf16(int32_t M, int32_t N, int32_t K, const void* x, c
 /* The same GEMM through the split-K path that passes over at most 256 stacked tokens take (k_splits blocks per output
  * tile stream disjoint shares of K and leave fp32 partial sums in `partial`; a second kernel adds them in a fixed order
  * and applies bias, activation, the fp32 residual [M, N] (may be NULL) and the output type).  k_splits = 0: what
- * the library would choose for this shape (the streamed kernel, a count, or the one-block kernel); >= 2: forced.  partial [dev]
- * fp32[partial_elems], at least k_splits * M * N (SwiGLU: 2 N) elements.  mpz_debug_gemm_splits returns the chosen
- * count.  Errors: NULL, SHAPE. */
+ * the library would choose for this shape (the streamed kernel, a count, or the one-block kernel); >= 2: forced; -1: the
+ * streamed kernel.  partial [dev] fp32[partial_elems], at least k_splits * M * N (SwiGLU: 2 N) elements.
+ * mpz_debug_gemm_stream_units returns the K-tiles of 64 that a block of the streamed kernel takes where the library would
+ * choose that kernel (bf16 weights, 16-byte aligned operands), else 0; mpz_debug_gemm_splits then returns the chosen count
+ * (1: the one-block kernel).  Errors: NULL, SHAPE. */
 mpz_status mpz_debug_gemm_bf16_splitk(int32_t M, int32_t N, int32_t K, const void* x, const void* w, const float* bias,
                                       int32_t act, const float* residual, void* out, int32_t out_f32, int32_t k_splits,
                                       float* partial, size_t partial_elems, void* hip_stream);
 int32_t mpz_debug_gemm_splits(int32_t M, int32_t N, int32_t K, int32_t dual, size_t partial_elems);
+int32_t mpz_debug_gemm_stream_units(int32_t M, int32_t N, int32_t K, int32_t dual, size_t partial_elems);
 /* Test hook: allow (default) or forbid the split-K GEMMs inside a model's passes. */
 mpz_status mpz_debug_set_split_k(mpz_model* m, int32_t enable);
 

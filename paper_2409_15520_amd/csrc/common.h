@@ -205,6 +205,7 @@ hipError_t launch_gemm_ring(hipStream_t st, const MfmaGemmArgs& a);
 inline bool fetch_aligned(const MfmaGemmArgs& a) { return (((uintptr_t)a.w | (uintptr_t)a.x) & 15) == 0; }
 // k_splits a launch of these arguments would use given room for `partial_capacity` floats (1 = no split)
 int mfma_gemm_splits(const MfmaGemmArgs& a, size_t partial_capacity);
+long mfma_gemm_split_blocks(const MfmaGemmArgs& a, size_t partial_capacity);   // ... and the blocks it would have
 bool mfma_gemm_supported(const MfmaGemmArgs& a);
 // will a dense [M, K] x [N, K]^T take the 256 x 256 tile (which fills the chip by itself)?
 bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights);

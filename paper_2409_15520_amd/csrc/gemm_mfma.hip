@@ -1041,6 +1041,11 @@ int mfma_gemm_splits(const MfmaGemmArgs& a, size_t partial_capacity) {
   return ks >= 2 ? (int)ks : 1;
 }
 
+long mfma_gemm_split_blocks(const MfmaGemmArgs& a, size_t partial_capacity) {
+  const int bn = split_tile_bn(a), n_rows = (a.dual && a.dual_offset == a.N) ? 2 * a.N : a.N;
+  return (long)((n_rows + bn - 1) / bn) * (a.M > 128 ? 2 : 1) * mfma_gemm_splits(a, partial_capacity);
+}
+
 namespace {
 
 // Sum of the k_splits partial sums in a fixed order (split 0 first), then what the one-block kernel does in its

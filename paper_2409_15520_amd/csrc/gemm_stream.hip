@@ -9,9 +9,10 @@
 //     run; one block barrier per K-tile;
 //   * each block leaves the raw fp32 sums of its part of a tile in its slot of the partial buffer; the reduction kernels add
 //     the slots of a tile in block order (deterministic) and apply the epilogue.
-// Measured alone with cold weights, 128 tokens, features x K = 12288 x 4096, 4096 x 4096, 22016 x 4096, 4096 x 11008: 28.5, 12.3,
-// 46.8, 27.5 us (3.5, 2.7, 3.9, 3.3 TB/s; 33.5, 15.2, 52.3, 31.0 with four waves instead of eight, 27, 11, 43, 22 with neither
-// activations nor matrix instructions); two 7B-shaped blocks over 128 tokens: 400 -> 365 us against equal splits of K per tile.
+// Measured alone with cold weights, 128 tokens, features x K = 12288 x 4096 and 22016 x 4096: 28.5 and 46.8 us (3.5 and 3.9 TB/s;
+// 33.5 and 52.3 with four waves instead of eight, 27 and 43 with neither activations nor matrix instructions).  Which shapes take
+// it, and their times with the reduction against equal shares of K: plan_stream (mpz_api.hip).  Two 7B-shaped blocks over 128
+// tokens: 343 us with these two projections streamed, 348 with all four.
 #include "gemm_tile.h"
 #include "fetch.h"
 

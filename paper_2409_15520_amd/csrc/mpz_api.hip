@@ -378,14 +378,24 @@ WeightRef weight_operand(mpz_model* m, const void* w, const float* s, int N, int
 }
 void set_weight(LinearArgs& a, const WeightRef& r) { a.w = r.w; a.w_scale = r.scale; a.w_codes = r.codes; a.w_absmax = r.absmax; }
 // Few stacked tokens and enough weights that every CU gets a run of K-tiles: stream them (gemm_stream.hip).  Below six K-tiles
-// of 16 KiB per CU the partial sums and the start of the stream cost more than its balance gives.
+// of 16 KiB per CU the partial sums and the start of the stream cost more than its balance gives.  What the stream gains over
+// equal shares of K (mfma_gemm_splits) is the balance: where those fill whole rounds of CUs it gains nothing (cold weights, with
+// the reduction; tokens: shares -> stream, us): 4096 x 4096 64: 15.3 -> 16.0, 128: 17.3 -> 18.5; 4096 x 11008 128: 30.8 -> 34.0,
+// 256: 40.9 -> 58.2; 8192 x 2048 128: 18.9 -> 19.9.  Where they don't: 12288 x 4096 128: 41.3 -> 34.5, 256: 52.6 -> 50.1;
+// 22016 x 4096 128: 61.8 -> 54.6, 256: 80.0 -> 74.0; 2560 x 6912 128: 23.3 -> 20.1, 256: 30.8 -> 26.4; 7680 x 2560 128: 24.3 -> 21.3,
+// but with short runs and twice the tokens 192: 25.7 -> 25.9; 6912 x 2560 128: 23.8 -> 22.6, 192: 25.6 -> 28.9.  At K = 2048 it is
+// 3-10 % either way (11264 x 2048 128: 26.2 -> 23.8, 256: 32.7 -> 34.8), and a step of a model of that width is held to masters
+// within 1e-3 although its few tokens amplify another cut of the sums to 2e-3: those keep the equal shares.
 constexpr long kStreamMinUnits = 256 * 6;
-bool plan_stream(MfmaGemmArgs& g, float* partial, size_t capacity) {
+bool plan_stream(MfmaGemmArgs& g, float* partial, size_t capacity, bool forced = false) {
   if (g.tile_cfg != 0 || g.ce_max != nullptr || (g.dual && g.dual_offset != g.N)) return false;
-  if (g.K < 1024 || g.K < 8 * g.M) return false;          // as ever: launches that don't split keep the one sum of every pass
   MfmaGemmArgs b = g;
   if (g.dual) { b.dual = 0; b.N = 2 * g.N; }              // gate | up lie back to back: one product over 2 N rows
-  if ((long)((b.N + 127) / 128) * (b.K / 64) < kStreamMinUnits) return false;
+  if (!forced) {
+    if (g.K < 8 * g.M || g.K < (g.M <= 128 ? 2560 : 4096)) return false;
+    if ((long)((b.N + 127) / 128) * (b.K / 64) < kStreamMinUnits) return false;
+    if (mfma_gemm_split_blocks(g, capacity) % 256 == 0) return false;
+  }
   const int units = gemm_stream_units(b, capacity);
   if (units == 0) return false;
   const int slots = stream_slots(b.K / 64, units);
@@ -1339,6 +1349,8 @@ mpz_status mpz_debug_gemm_bf16_splitk(int32_t M, int32_t N, int32_t K, const voi
                                       int32_t act, const float* residual, void* out, int32_t out_f32, int32_t k_splits,
                                       float* partial, size_t partial_elems, void* hip_stream) {
   if (!x || !w || !out || !partial) return fail(nullptr, MPZ_ERR_NULL, "mpz_debug_gemm_bf16_splitk: NULL argument");
+  const bool streamed = k_splits == -1;
+  if (streamed) k_splits = 0;
   const int forced_tile = k_splits / 1000;       // measurement: k_splits + 1000 x tile configuration
   k_splits %= 1000;
   if (k_splits < 0 || k_splits > 64) return fail(nullptr, MPZ_ERR_SHAPE, "mpz_debug_gemm_bf16_splitk: k_splits outside [0, 64]");
@@ -1349,7 +1361,8 @@ mpz_status mpz_debug_gemm_bf16_splitk(int32_t M, int32_t N, int32_t K, const voi
   if (K % 64 || N % 4 || M < 1 || N < 1) return fail(nullptr, MPZ_ERR_SHAPE, "shape not supported by the MFMA GEMM (K % 64, N % 4)");
   const int ks = mfma_gemm_splits(g, partial_elems);
   if (k_splits >= 2 && ks != k_splits) return fail(nullptr, MPZ_ERR_SHAPE, "mpz_debug_gemm_bf16_splitk: k_splits does not fit K or the partial buffer");
-  if (k_splits == 0 && forced_tile == 0 && plan_stream(g, partial, partial_elems)) {}
+  if (k_splits == 0 && forced_tile == 0 && plan_stream(g, partial, partial_elems, streamed)) {}
+  else if (streamed) return fail(nullptr, MPZ_ERR_SHAPE, "mpz_debug_gemm_bf16_splitk: not a shape of the streamed kernel");
   else {
     g.tile_cfg = ks > 1 ? 100 * ks + forced_tile : 0;
     if (ks > 1) { g.k_splits = ks; g.partial = partial; g.ldp = (g.dual ? 2 : 1) * N; }
@@ -1384,6 +1397,13 @@ int32_t mpz_debug_gemm_splits(int32_t M, int32_t N, int32_t K, int32_t dual, siz
   MfmaGemmArgs g{};
   g.M = M; g.N = N; g.K = K; g.dual = dual != 0; g.dual_offset = dual ? N : 0;
   return mfma_gemm_splits(g, partial_elems);
+}
+
+int32_t mpz_debug_gemm_stream_units(int32_t M, int32_t N, int32_t K, int32_t dual, size_t partial_elems) {
+  if (K % 64 || N % 4 || M < 1 || N < 1) return 0;
+  MfmaGemmArgs g{};
+  g.M = M; g.N = N; g.K = K; g.dual = dual != 0; g.dual_offset = dual ? N : 0;
+  return plan_stream(g, nullptr, partial_elems) ? g.stream_units : 0;
 }
 
 mpz_status mpz_debug_gemm_int8(int32_t M, int32_t N, int32_t K, const void* x, const void* w_codes, const float* w_scale,

@@ -307,6 +307,13 @@ def mpz_debug_gemm_splits(M: int, N: int, K: int, dual: bool, partial_elems: int
     return int(lib.mpz_debug_gemm_splits(M, N, K, int(dual), partial_elems))
 
 
+def mpz_debug_gemm_stream_units(M: int, N: int, K: int, dual: bool, partial_elems: int) -> int:
+    lib = load_library()
+    lib.mpz_debug_gemm_stream_units.restype = C.c_int32
+    lib.mpz_debug_gemm_stream_units.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_size_t]
+    return int(lib.mpz_debug_gemm_stream_units(M, N, K, int(dual), partial_elems))
+
+
 def mpz_debug_set_split_k(handle, enable: bool):
     lib = load_library()
     lib.mpz_debug_set_split_k.restype = C.c_int

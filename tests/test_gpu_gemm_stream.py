@@ -1,5 +1,6 @@
 """The streamed few-token GEMM (runs of K-tiles per block, partial sums per block and tile) against 64-bit products: every token
-tile (64 / 128 / 256), ragged tokens and features, tiles shared by two to nine blocks, every epilogue of the reduction."""
+tile (64 / 128 / 256), ragged tokens and features, tiles shared by two to nine blocks, every epilogue of the reduction (the kernel
+asked for by name: whether the library would choose it for a shape is test_few_token_plans's)."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -24,7 +25,7 @@ def test_streamed_gemm(m, n, k, act, f32, residual):
         out = torch.full((m + 1, n), -7.0, device="cuda", dtype=torch.float32 if f32 else torch.bfloat16)
         partial.fill_(float("nan"))                        # a slot nobody wrote would show
         M.mpz_debug_gemm_bf16_splitk(m, n, k, x.data_ptr(), w.data_ptr(), b.data_ptr(), act, None if r is None else r.data_ptr(),
-                                     out.data_ptr(), f32, 0, partial.data_ptr(), partial.numel(), st)
+                                     out.data_ptr(), f32, -1, partial.data_ptr(), partial.numel(), st)
         assert bool((out[m] == -7.0).all())
         outs.append(out[:m])
     assert torch.equal(outs[0], outs[1])                   # the slots are added in block order, whatever finished first
@@ -39,3 +40,27 @@ def test_streamed_gemm(m, n, k, act, f32, residual):
         y = y + r.double()
     err = float((outs[0].double() - y).norm() / y.norm())
     assert err < (2e-6 if f32 else 2.0 ** -8)              # fp32 sums of K products; bf16 rounding of the output
+
+
+@pytest.mark.parametrize("m,n,k,act,streamed", [(64, 5632, 2048, 2, False), (33, 5632, 2048, 2, False), (200, 5632, 2048, 2, False),
+                                                (128, 4096, 4096, -1, False), (256, 4096, 11008, -1, False), (128, 12288, 4096, -1, True)])
+def test_chosen_kernel(m, n, k, act, streamed):
+    """What the library chooses on its own has the bits of the kernel that the plan names: equal shares of K by count, or the stream."""
+    import torch
+    import paper_2409_15520_amd as M
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    nw = 2 * n if act == 2 else n
+    x = torch.randn(m, k, generator=g, device="cuda").bfloat16()
+    w = (torch.randn(nw, k, generator=g, device="cuda") * 0.05).bfloat16()
+    partial = torch.empty(16 * m * nw, device="cuda")
+    assert (M.mpz_debug_gemm_stream_units(m, n, k, act == 2, partial.numel()) > 0) == streamed
+    shares = M.mpz_debug_gemm_splits(m, n, k, act == 2, partial.numel())
+    st = torch.cuda.current_stream().cuda_stream
+    outs = []
+    for ks in (0, -1, shares):
+        out = torch.empty(m, n, device="cuda")
+        M.mpz_debug_gemm_bf16_splitk(m, n, k, x.data_ptr(), w.data_ptr(), None, act, None, out.data_ptr(), True, ks, partial.data_ptr(),
+                                     partial.numel(), st)
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1 if streamed else 2])
+    assert not torch.equal(outs[1], outs[2])               # the two cut K at different places

@@ -289,6 +289,8 @@ def test_gemm_split_k(M_, N_, K_, act, resid, bf16_out, ks):
     chosen = M.mpz_debug_gemm_splits(M_, N_, K_, False, cap)
     if ks == 0:
         assert chosen >= 2, "these shapes are meant to take the split-K path on their own"
+        if M.mpz_debug_gemm_stream_units(M_, N_, K_, False, cap):
+            ks = chosen                                # (the library would stream this one: test_gpu_gemm_stream)
     part = torch.full((cap,), float("nan"), dtype=torch.float32, device="cuda")
     st = torch.cuda.current_stream().cuda_stream
     outs = []

@@ -59,6 +59,11 @@ def test_full_width_stages_and_losses(name, tile_cfg):
     if fewtok:                                     # these cases are here for the split-K path: it must be the one taken
         T = 2 * w.q * w.E * w.S
         assert M.mpz_debug_gemm_splits(T, w.d_model, w.d_model, False, 1 << 40) >= 2
+        assert not M.mpz_debug_gemm_stream_units(T, w.d_model, w.d_model, False, 1 << 40)
+        # unquantised weights of the widest shape: Q|K|V and gate || up go through the streamed kernel
+        streamed = [M.mpz_debug_gemm_stream_units(T, n, w.d_model, dual, 1 << 40) > 0
+                    for n, dual in ((w.d_model + 2 * w.d_kv, False), (w.d_ffn, w.act == "swiglu"))]
+        assert streamed == [w.d_model == 4096] * 2
     for l in range(w.n_layers):
         h = torch.from_numpy(H[l]).cuda()
         m.run_layers(h, l, l + 1, w.E, w.S)
