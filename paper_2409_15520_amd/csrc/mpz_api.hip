@@ -407,8 +407,11 @@ bool plan_stream(MfmaGemmArgs& g, float* partial, size_t capacity, bool forced =
 void plan_split(const mpz_model* m, MfmaGemmArgs& g) {      // (g.w_absmax, if any, is already set: the tile depends on it)
   g.k_splits = 1; g.partial = nullptr; g.ldp = 0;
   if (m->buf.splitk == nullptr || !m->split_k) return;
-  if (plan_stream(g, m->buf.splitk, m->buf.splitk_elems)) return;
-  const int ks = mfma_gemm_splits(g, m->buf.splitk_elems);
+  // the room that a pass of just these tokens has: a larger buffer would allow shorter runs, and the cuts of K (so the bits) must
+  // not depend on what the handle was initialised for, or on whose scratch the pass runs in
+  const size_t own = splitk_capacity(&m->cfg, g.M), room = own < m->buf.splitk_elems ? own : m->buf.splitk_elems;
+  if (plan_stream(g, m->buf.splitk, room)) return;
+  const int ks = mfma_gemm_splits(g, room);
   if (ks > 1) { g.k_splits = ks; g.partial = m->buf.splitk; g.ldp = (g.dual ? 2 : 1) * g.N; }
 }
 

@@ -64,3 +64,29 @@ def test_chosen_kernel(m, n, k, act, streamed):
         outs.append(out)
     assert torch.equal(outs[0], outs[1 if streamed else 2])
     assert not torch.equal(outs[1], outs[2])               # the two cut K at different places
+
+
+def test_cuts_of_k_do_not_depend_on_the_room():
+    """A narrow projection of long K whose runs the partial-sum buffer limits: the same losses bit for bit from a handle made for
+    just this batch, one made for more, and the library's own scratch."""
+    import numpy as np
+    import torch
+    import paper_2409_15520_amd as M
+    import workloads as W
+    w = W.Workload(name="room", n_layers=3, d_model=960, n_heads=15, n_kv_heads=15, d_ffn=16384, vocab=512, max_seq=64, act="relu",
+                   norm="layernorm", pos="learned", has_bias=True, tie_embeddings=True, dtype="bf16", lora_rank=8,
+                   lora_targets=("q", "v"), loss_mode="next_token_all_pos", q=1, E=1, S=32, steps=1, eps=1e-2)
+    assert M.mpz_debug_gemm_stream_units(64, 960, 16384, False, 4096 * 960) != M.mpz_debug_gemm_stream_units(64, 960, 16384, False, 1024 * 960)
+    frozen, masters = W.make_frozen_weights(w, 1), W.make_lora_masters(w, 2, b_std=0.05)
+    tok = torch.from_numpy(W.make_tokens(w, 3)).cuda()
+    losses = []
+    for E_max in (1, 16):
+        m = M.ZoModel(w, frozen, masters, E_max=E_max)
+        m.regen_noise(5, 0)
+        losses.append(m.forward_perturbed(tok).cpu().numpy().copy())
+        out = torch.zeros(2, device="cuda")
+        M.mpz_forward_perturbed_noalloc(m.handle, tok.data_ptr(), None, 1, 32, out.data_ptr())
+        losses.append(out.cpu().numpy().copy())
+    assert np.isfinite(losses[0]).all()
+    for l in losses[1:]:
+        assert np.array_equal(l.view(np.uint32), losses[0].view(np.uint32)), losses
