@@ -95,26 +95,26 @@ __global__ void __launch_bounds__(256) linear_f64_kernel(LinearArgs a) {
 // thread per column walk K alone: 768 rows, K = 768, 16 columns 85 us)
 __global__ void __launch_bounds__(256) lora_down_f64_kernel(LoraDownArgs a) {
   const int groups = a.rank / 4, R = a.n_targets * a.rank;
-  const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int per_row = a.n_targets * groups;
-  if (item >= (int64_t)a.T * per_row) return;
-  const int m = (int)(item / per_row), g = (int)(item % per_row), tgt = g / groups, j0 = (g % groups) * 4, lane = threadIdx.x & 63;
-  const float* A = a.Ac[tgt] + (int64_t)(m / a.rows_per_copy) * a.copy_stride + j0;
-  const float* x = (const float*)a.x + (int64_t)m * a.K;
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int k = lane; k < a.K; k += 64) {
-    const f32x4 av = *(const f32x4*)(A + (int64_t)k * a.rank);
-    const double xv = (double)x[k];
+  for (int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); item < (int64_t)a.T * per_row; item += (int64_t)gridDim.x * 4) {
+    const int m = (int)(item / per_row), g = (int)(item % per_row), tgt = g / groups, j0 = (g % groups) * 4, lane = threadIdx.x & 63;
+    const float* A = a.Ac[tgt] + (int64_t)(m / a.rows_per_copy) * a.copy_stride + j0;
+    const float* x = (const float*)a.x + (int64_t)m * a.K;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k = lane; k < a.K; k += 64) {
+      const f32x4 av = *(const f32x4*)(A + (int64_t)k * a.rank);
+      const double xv = (double)x[k];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] += xv * (double)av[e];
-  }
+      for (int e = 0; e < 4; ++e) s[e] += xv * (double)av[e];
+    }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
+    for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] += __shfl_xor(s[e], o, 64);
-  if (lane < 4) {
-    const double v = lane == 0 ? s[0] : lane == 1 ? s[1] : lane == 2 ? s[2] : s[3];
-    ((float*)a.t)[(int64_t)m * R + tgt * a.rank + j0 + lane] = (float)(v * (double)a.scale);
+      for (int e = 0; e < 4; ++e) s[e] += __shfl_xor(s[e], o, 64);
+    if (lane < 4) {
+      const double v = lane == 0 ? s[0] : lane == 1 ? s[1] : lane == 2 ? s[2] : s[3];
+      ((float*)a.t)[(int64_t)m * R + tgt * a.rank + j0 + lane] = (float)(v * (double)a.scale);
+    }
   }
 }
 
@@ -134,7 +134,8 @@ bool launch_lora_down_f64(hipStream_t st, const LoraDownArgs& a) {
   for (int t = 0; t < a.n_targets; ++t)
     if ((uintptr_t)a.Ac[t] & 15) return false;
   const int64_t items = (int64_t)a.T * a.n_targets * (a.rank / 4);
-  lora_down_f64_kernel<<<(unsigned)((items + 3) / 4), 256, 0, st>>>(a);
+  const int64_t blocks = (items + 3) / 4, most = UINT32_MAX / 256;   // (a launch holds fewer than 2^32 threads; the waves walk the rest)
+  lora_down_f64_kernel<<<(unsigned)(blocks < most ? blocks : most), 256, 0, st>>>(a);
   return true;
 }
 

@@ -492,7 +492,8 @@ void launch_embed(hipStream_t st, int dtype, const int32_t* tokens, const void* 
                   const int32_t* row_pos, float* h,
                   int n_copies, int E, int S, int d) {
   unsigned rows = (unsigned)((int64_t)n_copies * E * S);
-  if (d % 4 == 0 && (((uintptr_t)emb | (uintptr_t)pos_emb | (uintptr_t)h) & 15) == 0) {
+  // (256 threads a row: a launch holds fewer than 2^32 threads, so 2^24 rows take the kernel of 128)
+  if (d % 4 == 0 && rows <= UINT32_MAX / 256 && (((uintptr_t)emb | (uintptr_t)pos_emb | (uintptr_t)h) & 15) == 0) {
     const dim3 grid(rows, (unsigned)((d / 4 + 255) / 256));
     MPZ_DISPATCH(dtype, (embed_vec_kernel<ST><<<grid, 256, 0, st>>>(tokens, (const ST*)emb, (const ST*)pos_emb, row_pos, h, E, S, d)));
     return;

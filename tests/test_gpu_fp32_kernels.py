@@ -28,3 +28,42 @@ def test_fp32_shapes(name):
     assert np.abs(Lg - Lo).max() <= 1e-6 * np.abs(Lo).max()
     assert rel_err(Gg[0], Go[0]) <= 1e-4
     assert rel_err(Mg, Mo) <= 1e-3
+
+
+def test_bottleneck_of_more_waves_than_a_launch_holds():
+    """Rank 64 on Q, K and V from 1.4 M stacked tokens on: 2^32 threads at a wave per row and four columns.  A sequence's rows do not
+    depend on how many others there are."""
+    import torch
+    import paper_2409_15520_amd as M
+    import workloads as W
+    big = 5500
+    w = W.Workload(name="wide", n_layers=1, d_model=32, n_heads=2, n_kv_heads=2, d_ffn=32, vocab=64, max_seq=128, act="relu",
+                   norm="layernorm", pos="learned", has_bias=True, tie_embeddings=True, dtype="f32", lora_rank=64,
+                   lora_targets=("q", "k", "v"), loss_mode="next_token_all_pos", q=1, E=big, S=128, steps=1, eps=1e-2)
+    assert 2 * big * 128 * 3 * 64 // 4 * 64 >= 2 ** 32
+    frozen, masters = W.make_frozen_weights(w, 1), W.make_lora_masters(w, 2, b_std=0.05)
+    tokens = torch.from_numpy(W.make_tokens(w, 3)).cuda()
+    outs = []
+    for first, E in ((0, big), (0, 3), (big - 3, 3)):
+        m = M.ZoModel(w.with_(E=E), frozen, masters)
+        m.regen_noise(5, 0)
+        outs.append(m.run_layers(m.embed(tokens[first:first + E].contiguous()), 0, 1, E, 128).reshape(2, E, 128, -1).clone())
+        m.close()
+    assert torch.equal(outs[0][:, :3], outs[1]) and torch.equal(outs[0][:, -3:], outs[2])
+
+
+def test_embedding_of_the_largest_batch():
+    """2^24 stacked tokens, the most a handle takes."""
+    import torch
+    import paper_2409_15520_amd as M
+    import workloads as W
+    w = W.Workload(name="most", n_layers=1, d_model=4, n_heads=1, n_kv_heads=1, d_ffn=4, vocab=64, max_seq=512, act="relu",
+                   norm="layernorm", pos="learned", has_bias=True, tie_embeddings=True, dtype="f32", lora_rank=4,
+                   lora_targets=("q",), loss_mode="last_pos_label_subset", q=1, E=1 << 14, S=512, steps=1, eps=1e-2)
+    frozen = W.make_frozen_weights(w, 1)
+    tokens = torch.from_numpy(W.make_tokens(w, 3)).cuda()
+    m = M.ZoModel(w, frozen, W.make_lora_masters(w, 2))
+    m.regen_noise(5, 0)
+    h = m.embed(tokens).reshape(2, w.E, w.S, 4)
+    want = torch.from_numpy(frozen["emb"]).cuda()[tokens.long()] + torch.from_numpy(frozen["pos_emb"]).cuda()[None, :w.S]
+    assert torch.equal(h[0], want) and torch.equal(h[1], want)
