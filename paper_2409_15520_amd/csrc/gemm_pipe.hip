@@ -582,7 +582,7 @@ hipError_t launch_pipe_lr(hipStream_t st, const MfmaGemmArgs& a) {
 // refused takes the tile of the same size in gemm_mfma.hip.
 bool gemm_pipe_supported(const MfmaGemmArgs& a) {
   if (a.w_scale != nullptr || a.w_absmax != nullptr || a.k_splits > 1 || a.K % 128 || a.act == MPZ_ACT_GELU_ERF || !fetch_aligned(a)) return false;
-  if (a.ce_max != nullptr) return true;
+  if (a.ce_max != nullptr) return a.bias == nullptr && a.n_seg == 0 && a.act < 0;   // (its epilogue takes the products as the logits)
   const int es = a.out_f32 ? 4 : 2;
   if (((uintptr_t)a.out | (uintptr_t)a.residual) & 15 || a.N * es % 16 || a.ldo * es % 16 || a.ldo > (1 << 21)) return false;
   if (!a.out_f32 && a.residual != nullptr) return false;
