@@ -386,8 +386,9 @@ mpz_status mpz_debug_set_fused_norm_lora(mpz_model* m, int32_t enable);
  * kernel.  Same bits either way.  Invalidates the perturbed copies: call mpz_regen_noise again. */
 mpz_status mpz_debug_set_fused_perturb_pack(mpz_model* m, int32_t enable);
 
-/* Test hook: force one block-tile configuration (1, 6, 9, 10, 11 or 12; 0 = chosen by shape) for every MFMA GEMM of the model's
- * passes, so that small test shapes can exercise the configurations large workloads select.  Errors: NULL, CONFIG. */
+/* Test hook: force one block-tile configuration (1, 6, 9, 10, 11, 12 or 15; 0 = chosen by shape) for every MFMA GEMM of the
+ * model's passes that has it (15: rotated heads of 128), so that small test shapes can exercise the configurations large
+ * workloads select.  Errors: NULL, CONFIG. */
 mpz_status mpz_debug_set_tile_config(mpz_model* m, int32_t tile_cfg);
 
 /* Measurement hook: between _begin and _end every kernel launch of the three hot-path calls is bracketed by HIP

@@ -868,9 +868,11 @@ hipError_t launch_cfg(hipStream_t st, const MfmaGemmArgs& a) {
   return hipSuccess;
 }
 
-// block tile of configuration cfg (1, 6, 9, 10, 11, 12, 13, 14; see launch_gemm_mfma)
+// block tile of configuration cfg (1, 6, 9 .. 15; see launch_gemm_mfma)
 int tile_bn(int cfg) { return cfg == 14 ? 32 : (cfg == 10 || cfg == 13) ? 64 : cfg == 11 ? 192 : cfg == 6 ? 256 : 128; }
-bool known_cfg(int cfg) { return cfg == 1 || cfg == 6 || (cfg >= 9 && cfg <= 14); }
+bool known_cfg(const MfmaGemmArgs& a, int cfg) {
+  return cfg == 1 || cfg == 6 || (cfg >= 9 && cfg <= 14) || (cfg == 15 && a.rope_cos != nullptr && a.rope_dh == 128);
+}
 
 bool cfg_ok(const MfmaGemmArgs& a, int cfg) {
   if (cfg == 14 && !gemm_ring_supported(a)) return false;
@@ -904,8 +906,8 @@ int choose_cfg(const MfmaGemmArgs& a) {
     if (split_tile_bn(a) == 128 || !cfg_ok(a, 13)) return a.M <= 64 ? 9 : 1;     // 128 features x 64 or 128 tokens
     return a.M <= 64 ? 10 : 13;                                                   // 64 features x 64 or 128 tokens
   }
-  const bool forced_ok = a.w_scale == nullptr || a.tile_cfg == 1 || a.tile_cfg == 6 || a.tile_cfg == 11 || a.tile_cfg == 12;   // int8: fewer instances
-  if (forced_ok && known_cfg(a.tile_cfg) && cfg_ok(a, a.tile_cfg)) return a.tile_cfg;
+  const bool forced_ok = a.w_scale == nullptr || a.tile_cfg == 1 || a.tile_cfg == 6 || a.tile_cfg == 11 || a.tile_cfg == 12 || a.tile_cfg == 15;   // int8: fewer instances
+  if (forced_ok && known_cfg(a, a.tile_cfg) && cfg_ok(a, a.tile_cfg)) return a.tile_cfg;
   const long t5 = (long)((a.N + 255) / 256) * ((a.M + 255) / 256);
   if (cfg_ok(a, 6) && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, a.K)))) return 6;
   // 128 x 128 tiles that fill between one and two blocks per CU leave half the chip with twice the work of the

@@ -1493,8 +1493,8 @@ mpz_status mpz_debug_set_fused_perturb_pack(mpz_model* m, int32_t enable) {
 
 mpz_status mpz_debug_set_tile_config(mpz_model* m, int32_t tile_cfg) {
   if (!m) return fail(nullptr, MPZ_ERR_NULL, "mpz_debug_set_tile_config: NULL model");
-  if (!(tile_cfg == 0 || tile_cfg == 1 || tile_cfg == 6 || (tile_cfg >= 9 && tile_cfg <= 12)))
-    return fail(m, MPZ_ERR_CONFIG, "tile configuration must be 0 (by shape), 1, 6, 9, 10, 11 or 12");
+  if (!(tile_cfg == 0 || tile_cfg == 1 || tile_cfg == 6 || (tile_cfg >= 9 && tile_cfg <= 12) || tile_cfg == 15))
+    return fail(m, MPZ_ERR_CONFIG, "tile configuration must be 0 (by shape), 1, 6, 9, 10, 11, 12 or 15");
   m->force_tile_cfg = tile_cfg;
   return MPZ_OK;
 }
