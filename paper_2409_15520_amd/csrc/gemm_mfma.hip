@@ -671,7 +671,7 @@ __global__ void __launch_bounds__(256, 1) lora_down_ring_kernel(MfmaLoraDownArgs
 #pragma unroll
     for (int t = 0; t < RANK / 4; ++t) {
       const uint32_t p = (uint32_t)(wave * (RANK / 4) + t) * 1024u;                   // of the 2 HALF bytes of the chunk
-      const uint32_t soff = (uint32_t)ch * HALF + (p < HALF ? p : p - HALF + row_b * RANK);
+      const uint32_t soff = __builtin_amdgcn_readfirstlane((uint32_t)ch * HALF + (p < HALF ? p : p - HALF + row_b * RANK));
       fetch_rows<4>(rsrcA, (uint32_t)lane * 16u, soff, base + XBYTES + p);
     }
   };
