@@ -81,3 +81,25 @@ def test_int8_weights_refuse_odd_copies():
     with pytest.raises(M.MpzError) as e:
         m.run_layers(h, 0, 1, 1, 33)
     assert e.value.status == 3                             # MPZ_ERR_SHAPE
+
+
+# few tokens: the linears without adapters split K (or, 4-bit, look their codes up) whatever the rows of a copy; the adapted ones
+# don't.  Another order of the same fp32 sums: bf16 flips through one block, 4e-3 at most as measured for whole copies
+@pytest.mark.parametrize("q,E,S,quant", [(1, 1, 33, "none"), (2, 1, 21, "none"), (8, 1, 5, "nf4"), (1, 3, 33, "nf4")])
+def test_few_tokens_of_odd_copies(q, E, S, quant):
+    import torch
+    import paper_2409_15520_amd as M
+    w = _workload(True, 2048, 16, 4, 16, q, E, S, "qkvo", quant).with_(d_ffn=5632)
+    T = 2 * q * E * S
+    assert T % 32 and M.mpz_debug_gemm_splits(T, 5632, 2048, True, 1 << 40) >= 2 and M.mpz_debug_gemm_splits(T, 2048, 5632, False, 1 << 40) >= 2
+    m = M.ZoModel(w, W.make_frozen_weights(w, 1), W.make_lora_masters(w, 2, b_std=0.05))
+    m.regen_noise(5, 0)
+    tokens = torch.from_numpy(W.make_tokens(w, 3)).cuda()
+    outs = []
+    for split in (True, False):
+        M.mpz_debug_set_split_k(m.handle, split)
+        outs.append(m.run_layers(m.embed(tokens), 0, 1, E, S).clone())
+    assert torch.isfinite(outs[0]).all()
+    err = float((outs[0] - outs[1]).norm() / outs[1].norm())
+    print(f"\nodd few tokens q {q} E {E} S {S} {quant}: {err:.2e}")
+    assert 0 < err < 8e-3
