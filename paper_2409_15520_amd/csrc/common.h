@@ -174,7 +174,8 @@ struct MfmaGemmArgs {
   int act;                      // -1 none, MPZ_ACT_RELU, MPZ_ACT_GELU_ERF (ignored when dual: SiLU(gate) * up)
   const float* residual;        // [M, ldo] fp32 or null
   int out_f32; void* out; int ldo;
-  int tile_cfg;                 // 0 = choose by shape; 1, 6, 9, 10, 11, 12 force that tile configuration (tests)
+  int tile_cfg;                 // 0 = choose by shape; 1, 6, 9 .. 15 force that tile configuration (tests; 13: split K only, 14: what
+                                // gemm_ring_supported takes, 15: rotated heads of 128)
   // fused rotary embedding (bf16 output only): columns [0, rope_cols) are heads of width rope_dh rotated by the
   // position m % S with tables [max_seq, rope_dh / 2]; packed batches: position rope_pos[m % S] (S = rows per copy)
   const float* rope_cos; const float* rope_sin; int rope_cols, rope_dh, S;

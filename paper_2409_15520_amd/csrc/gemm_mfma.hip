@@ -321,7 +321,6 @@ gemm_bf16_kernel(MfmaGemmArgs a) {
 
   constexpr int NM = NW * NI * NJ, NF = NW * NI + NJ, NV = NW * LW + LX, KS = BK / 16;
   // Tile kt+1 sits in one register set (in flight or landed) while tile kt+2 is fetched into the other: a load
-  // Tile kt+1 sits in one register set (in flight or landed) while tile kt+2 is fetched into the other: a load
   // has two MFMA phases to arrive before its LDS store needs it.  Loads past the last tile fall outside the
   // buffers (zeros); what they put into the idle LDS stage is never read.
   {
@@ -846,8 +845,9 @@ __global__ void __launch_bounds__(256) pack_factors_vec_kernel(const float* __re
 
 // ---- tile configurations ----------------------------------------------------------------------------
 // The numbered configurations (BN x BM x BK, waves) are listed where they are instantiated, in launch_gemm_mfma;
-// choose_cfg picks among 6 (256 x 256 x 64, 8 waves: large problems), 12 and 1 (128 x 128 x 64 with 8 or 4 waves),
-// 11 (192 x 128 x 64), 9 and 10 (128 x 64 and 64 x 64: problems with fewer tiles than CUs).  LDS = stages x (BN + BM) x (BK + 8) x 2 bytes, or the epilogue strips if those are larger.
+// choose_cfg picks among 6 (256 x 256 x 64: large problems; gemm_pipe.hip, or 8 waves here), 12 and 1 (128 x 128 x 64 with 8 or 4
+// waves), 15 (the same with 4 waves of 128 x 32: rotated heads of 128), 11 (192 x 128 x 64), 9 and 10 (128 x 64 and 64 x 64: problems
+// with fewer tiles than CUs), 14 (32 x 32 x 128: gemm_ring.hip) and, splitting K, 13 (64 x 128 x 64).  LDS = stages x (BN + BM) x (BK + 8) x 2 bytes, or the epilogue strips if those are larger.
 template <int BN, int BM, int BK, int WGN, int WGM, bool DUAL, int HP = 0, int WQ = 0>
 hipError_t launch_cfg(hipStream_t st, const MfmaGemmArgs& a) {
   constexpr size_t lds_stages = (size_t)2 * ((DUAL ? 2 : 1) * BN + BM) * (BK + 8) * 2;
@@ -888,7 +888,7 @@ bool cfg_ok(const MfmaGemmArgs& a, int cfg) {
 int split_tile_bn(const MfmaGemmArgs& a) { return (a.dual || a.N >= 8192 || a.K >= 8192 || a.w_scale != nullptr || a.w_absmax != nullptr) ? 128 : 64; }
 
 // Do `tiles` 256 x 256 tiles (one per CU at a time) beat the 128-wide ones?  Always from two full rounds of 256 CUs on.  Below
-// that the persistent kernel of gemm_pipe.hip wins once its last round fills five eighths of the chip: K = 4096, 128 / 192 /
+// that the persistent kernel of gemm_pipe.hip wins once its rounds together are five eighths full (two rounds: from 320 tiles): K = 4096, 128 / 192 /
 // 256 / 384 tiles: 82 / 89 / 96 / 168 us against 72 / 107 / 138 / 208 us for the same product in 128 x 128 tiles; K = 2048, 128 / 160 /
 // 256 / 320 tiles: 47 / 47 / 55 / 89 against 39 / 53 / 74 / 92.  At K = 1024 a second round no longer pays (352 tiles: 56 against
 // 55, 176 tiles: 30 against 34), at K = 768 neither does the first (192 tiles: 28 against 27).

@@ -566,7 +566,8 @@ void norm(mpz_model* m, const float* h, int64_t h_row_stride, const float* g, co
 
 void run_embed(mpz_model* m, const int32_t* tokens, int E, int S, float* h) {
   const mpz_config& c = m->cfg;
-  ProfScope ps(m, MPZ_PROF_EMBED, 0.0, (double)m->nc * E * S * (double)c.d_model * (4.0 + esz(m)));
+  // every copy reads the same embedding rows: they come from memory once
+  ProfScope ps(m, MPZ_PROF_EMBED, 0.0, (double)E * S * (double)c.d_model * (m->nc * 4.0 + (c.pos == MPZ_POS_ROPE ? 1.0 : 2.0) * esz(m)));
   launch_embed(m->stream, c.dtype, tokens, m->w.emb, c.pos == MPZ_POS_ROPE ? nullptr : m->w.pos_emb,
                m->pk.cu ? m->buf.row_pos : nullptr, h, m->nc, E, S, c.d_model);
 }
