@@ -1212,8 +1212,9 @@ bool mfma_lora_down_supported(const MfmaLoraDownArgs& a) {
 void launch_lora_down_mfma(hipStream_t st, const MfmaLoraDownArgs& a) {
   int R = a.n_targets * a.rank;
   const dim3 grid(a.T / 32);
-  // at most a block per CU with one target each, and enough K to fetch: 32 tokens and one target per block
-  if ((int)grid.x * a.n_targets <= 256 && a.K >= 1024 && (a.rank == 8 || a.rank == 16 || a.rank == 32)) {
+  // at most a block per CU with one target each, and enough K to fetch: 32 tokens and one target per block (rows that begin on 16
+  // bytes: they go straight into LDS in such pieces)
+  if ((int)grid.x * a.n_targets <= 256 && a.K >= 1024 && ((uintptr_t)a.x & 15) == 0 && (a.rank == 8 || a.rank == 16 || a.rank == 32)) {
     if (a.rank == 8) launch_lora_down_ring<8>(st, a);
     else if (a.rank == 16) launch_lora_down_ring<16>(st, a);
     else launch_lora_down_ring<32>(st, a);

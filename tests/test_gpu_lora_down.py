@@ -29,3 +29,23 @@ def test_few_tokens_equal_many(rank, d, S):
         outs.append(h[:, 0].clone())
     assert torch.isfinite(outs[0]).all()
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("rank,S", [(16, 32), (8, 64)])
+def test_rows_that_begin_between_pieces(rank, S):
+    """Operand rows that begin on 8 bytes but not on 16 keep the kernels that fetch through registers: the same bits."""
+    import torch
+    import paper_2409_15520_amd as M
+    w = W.Workload(name="shift", n_layers=1, d_model=1024, n_heads=16, n_kv_heads=16, d_ffn=256, vocab=500, max_seq=64, act="relu",
+                   norm="layernorm", pos="learned", has_bias=True, tie_embeddings=False, dtype="bf16", lora_rank=rank,
+                   lora_targets=("q", "v"), loss_mode="next_token_all_pos", q=1, E=1, S=S, steps=1, eps=1e-2)
+    m = M.ZoModel(w, W.make_frozen_weights(w, 1), W.make_lora_masters(w, 2, b_std=0.05))
+    m.regen_noise(5, 0)
+    T = 2 * S
+    x = torch.randn(T * 1024 + 4, generator=torch.Generator(device="cuda").manual_seed(rank), device="cuda").bfloat16()
+    outs = []
+    for buf in (x[4:], x[4:].clone()):
+        out = torch.empty(T, 3072, device="cuda")
+        M.mpz_debug_qkv_projection(m.handle, buf.data_ptr(), 0, 1, S, out.data_ptr())
+        outs.append(out)
+    assert x[4:].data_ptr() % 16 == 8 and torch.equal(outs[0], outs[1])
