@@ -6,9 +6,10 @@
 // which reads half as many LDS bytes again per MFMA); everything below is there to keep the loop at that rate and to
 // take the edges of a tile off the clock.  v_mfma_f32_16x16x32_bf16 gives the bits of two v_mfma_f32_32x32x16_bf16 in a row
 // and draws less power: the same kernel built on the 32 x 32 shape is 10-12 % slower (48.7 against 54.6 us per round of 256
-// tiles at K = 2048).  Measured against the register-staged 8-wave tile it replaces (bf16 out, M x N x K): 8192 x 12288 x 4096
-// 655 -> 545 us (1510 TFLOP/s), 8192 x 4096 x 11008 556 -> 485, 65536 x 2560 x 2048 587 -> 491, SwiGLU 65536 x 5632 x 2048
-// 2426 -> 2105, 32768 x 8192 x 2048 with ReLU 975 -> 805; with the fp32 residual 65536 x 2048 x 2048 600 -> 487.
+// tiles at K = 2048).  Measured in turn with the register-staged 8-wave tile it replaces, one box (bf16 out, M x N x K; boxes differ
+// by 5 %): 8192 x 12288 x 4096 718 -> 640 us (1290 TFLOP/s), 8192 x 4096 x 4096 221 -> 191, 8192 x 4096 x 11008 560 -> 491 (1500),
+// 32768 x 8192 x 2048 953 -> 798, 65536 x 2560 x 2048 580 -> 502; on another box SwiGLU 65536 x 5632 x 2048 2426 -> 2105 and, with
+// the fp32 residual, 65536 x 2048 x 2048 600 -> 487.
 //   * A K-tile (64) is four pieces of 128 rows x 128 bytes: weights W0, W1 and tokens X0, X1, each wave owning 64 rows of
 //     every piece.  Two LDS stages of four pieces; a piece's slot is free as soon as its fragments are in registers, so
 //     a fetch has one and a half K-tiles to arrive, without registers to stage it.

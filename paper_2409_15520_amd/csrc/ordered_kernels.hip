@@ -7,7 +7,7 @@
 // a step's masters are held to.
 // Bound by the fp32 matrix rate (256 FLOP per clock and CU, a sixteenth of bf16) and, few tokens, by the chain: K / 2 dependent
 // instructions of 64 clocks.  A 1.1B-shaped block, 8 copies of 231 rows, adapters on all four projections: 2157 us with the
-// shape-agnostic kernels, 622 us with these (1848 x 2560 x 2048: 222 us, 87 TFLOP/s; the bottleneck of three targets 30 us).
+// shape-agnostic kernels, 637 us with these (1848 x 2560 x 2048: 222 us, 87 TFLOP/s; the bottleneck of three targets 30 us).
 #include "common.h"
 #include "fetch.h"
 #include "../../include/mpz.h"
