@@ -33,7 +33,8 @@ enum { PIPE_BF16 = 0, PIPE_ROPE64 = 1, PIPE_ROPE128 = 2, PIPE_F32 = 3, PIPE_CE =
 
 // Fused cross-entropy: the logits never leave the registers.  A lane holds 4 NI columns of a token row (lanes l, l ^ 16,
 // l ^ 32 and l ^ 48 share the row): row maximum, sum of exponentials against it, and the target's logit if it falls into
-// this wave tile.
+// this wave tile.  Two sweeps over all rows instead of one row after the other, so that the shuffles of the eight token tiles travel
+// together and the targets are requested at once (33792 x 32000 x 2048: 3581 -> 3519 us, 65536 x 32000 x 2048: 6577 -> 6551).
 template <int BN, int WGN, int WGM, int NW, int NI, int NJ>
 __device__ __forceinline__ void pipe_ce_partials(const MfmaGemmArgs& a, f32x4 (&acc)[NW][NI][NJ], int m0, int n0, int wm, int wn,
                                                  int wave, int lane) {
@@ -41,44 +42,49 @@ __device__ __forceinline__ void pipe_ce_partials(const MfmaGemmArgs& a, f32x4 (&
   const int l16 = lane & 15, lq = lane >> 4;
   const int slot = (n0 / BN) * WGN + wave / WGM, nl = n0 + wn + lq * 4;
   const bool whole = n0 + wn + NI * 16 <= a.N;           // (uniform) all columns of the wave tile exist
+  const int mr = m0 + wm + l16;
+  int tg[NJ];
+  float mx[NJ], sum[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) tg[j] = mr + j * 16 < a.M ? a.ce_target[mr + j * 16] : -1;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     __builtin_amdgcn_sched_barrier(0);
-    const int m = m0 + wm + j * 16 + l16;
-    const int tg = m < a.M ? a.ce_target[m] : -1;
-    float mx = -1e30f, sum = 0.f;
+    mx[j] = -1e30f;
     if (whole) {
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) mx = fmaxf(mx, acc[0][i][j][e]);
+        for (int e = 0; e < 4; ++e) mx[j] = fmaxf(mx[j], acc[0][i][j][e]);
     } else {
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) mx = nl + i * 16 + e < a.N && acc[0][i][j][e] > mx ? acc[0][i][j][e] : mx;
+        for (int e = 0; e < 4; ++e) mx[j] = nl + i * 16 + e < a.N && acc[0][i][j][e] > mx[j] ? acc[0][i][j][e] : mx[j];
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 16));
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 32));
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    __builtin_amdgcn_sched_barrier(0);
+    sum[j] = 0.f;
     if (whole) {
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum += __builtin_amdgcn_exp2f((acc[0][i][j][e] - mx) * LOG2E);
+        for (int e = 0; e < 4; ++e) sum[j] += __builtin_amdgcn_exp2f((acc[0][i][j][e] - mx[j]) * LOG2E);
     } else {
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          sum += nl + i * 16 + e < a.N ? __builtin_amdgcn_exp2f((acc[0][i][j][e] - mx) * LOG2E) : 0.f;
+          sum[j] += nl + i * 16 + e < a.N ? __builtin_amdgcn_exp2f((acc[0][i][j][e] - mx[j]) * LOG2E) : 0.f;
     }
-    sum += __shfl_xor(sum, 16);
-    sum += __shfl_xor(sum, 32);
-    if (m < a.M && lq == 0) {
-      a.ce_max[(size_t)slot * a.M + m] = mx;
-      a.ce_sum[(size_t)slot * a.M + m] = sum;
-    }
-    const int rel = tg - nl;                             // the target's column among this lane's: 16 i + e
+    const int rel = tg[j] - nl;                          // the target's column among this lane's: 16 i + e
     const bool has = rel >= 0 && rel < NI * 16 && (rel & 15) < 4;
     if (__ballot(has) != 0) {                            // one tile in many holds a row's target
       float tl = 0.f;
@@ -86,9 +92,20 @@ __device__ __forceinline__ void pipe_ce_partials(const MfmaGemmArgs& a, f32x4 (&
       for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) tl = rel == i * 16 + e ? acc[0][i][j][e] : tl;
-      if (has) a.ce_tlogit[m] = tl;
+      if (has) a.ce_tlogit[mr + j * 16] = tl;
     }
   }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) sum[j] += __shfl_xor(sum[j], 16);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) sum[j] += __shfl_xor(sum[j], 32);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+    if (mr + j * 16 < a.M && lq == 0) {
+      a.ce_max[(size_t)slot * a.M + mr + j * 16] = mx[j];
+      a.ce_sum[(size_t)slot * a.M + mr + j * 16] = sum[j];
+    }
 }
 
 // The part of the output (and of the residual, of the same shape) that belongs to a wave, as a buffer that starts at the
@@ -123,8 +140,8 @@ struct PipeOut {
 // features n0 + wn + 16 i + 4 (lane / 16) + (0..3) of MFMA tile (i, j).  32 tokens at a time go through the wave's own
 // 8 KiB strip (16-byte chunk c of row r at c ^ (r % 16)), so that residual reads and output stores cover whole 256-byte
 // pieces of a row with 16 bytes per lane; bf16 outputs are rounded before they enter the strip.  With one wave per SIMD
-// nothing hides an instruction here, so there are few, and no branches (the compiler spills accumulators around them; 26 of the 31
-// instances still spill 3 to 33 registers between the K loop and the stores, none inside the loop):
+// nothing hides an instruction here, so there are few, and no branches (the compiler spills accumulators around them; 19 of the 31
+// instances still spill 3 to 27 registers between the K loop and the stores, none inside the loop):
 // outputs and residuals are buffers that start at the wave's first element and end with the matrix, so rows past M fall
 // outside, and the lanes of columns past N aim outside.
 template <bool DUAL, int EPI, bool BIAS, bool RELU, bool RES, int NW, int NI, int NJ, int BN, int WGN, int WGM, bool RES1, int NRS>
@@ -182,10 +199,10 @@ __device__ __forceinline__ void pipe_epilogue(const MfmaGemmArgs& a, f32x4 (&acc
           if (DUAL) bu[i] = *(const f32x4*)(a.bias + a.dual_offset + n);
         }
       }
-      // rotary tables of token tile j: cosines and sines of the lower half's features, requested one token tile ahead
+      // rotary tables of token tile j: cosines and sines of the lower half's features, requested one or two token tiles ahead
       constexpr bool ROPE = EPI == PIPE_ROPE64 || EPI == PIPE_ROPE128;
-      constexpr int HP = EPI == PIPE_ROPE128 ? 4 : 2, HALF = 16 * HP;
-      f32x4 cs[2][ROPE ? HP : 1], sn[2][ROPE ? HP : 1];
+      constexpr int HP = EPI == PIPE_ROPE128 ? 4 : 2, HALF = 16 * HP, TD = HP == 2 ? 3 : 2;
+      f32x4 cs[TD][ROPE ? HP : 1], sn[TD][ROPE ? HP : 1];
       const float inv_s = ROPE ? 1.0f / (float)a.S : 0.f;
       auto tables = [&](int j) {
         int m = mw + j * 16 + l16;
@@ -196,11 +213,14 @@ __device__ __forceinline__ void pipe_epilogue(const MfmaGemmArgs& a, f32x4 (&acc
         if (a.rope_pos != nullptr) p = a.rope_pos[p];
 #pragma unroll
         for (int i = 0; i < HP; ++i) {
-          cs[j & 1][i] = *(const f32x4*)(a.rope_cos + (size_t)p * HALF + i * 16 + lq * 4);
-          sn[j & 1][i] = *(const f32x4*)(a.rope_sin + (size_t)p * HALF + i * 16 + lq * 4);
+          cs[j % TD][i] = *(const f32x4*)(a.rope_cos + (size_t)p * HALF + i * 16 + lq * 4);
+          sn[j % TD][i] = *(const f32x4*)(a.rope_sin + (size_t)p * HALF + i * 16 + lq * 4);
         }
       };
-      if constexpr (ROPE) tables(0);
+      if constexpr (ROPE) {
+#pragma unroll
+        for (int j = 0; j < TD - 1; ++j) tables(j);
+      }
 #pragma unroll
       for (int j2 = 0; j2 < NJ / 2; ++j2) {
         __builtin_amdgcn_sched_barrier(0);
@@ -208,7 +228,7 @@ __device__ __forceinline__ void pipe_epilogue(const MfmaGemmArgs& a, f32x4 (&acc
         for (int h = 0; h < 2; ++h) {
           const int j = j2 * 2 + h, lrow = h * 16 + l16;   // token tile, row of the strip
           if constexpr (ROPE) {
-            if (j + 1 < NJ) tables(j + 1);
+            if (j + TD - 1 < NJ) tables(j + TD - 1);
           }
           f32x4 v[NI];
 #pragma unroll
@@ -233,7 +253,7 @@ __device__ __forceinline__ void pipe_epilogue(const MfmaGemmArgs& a, f32x4 (&acc
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
               if ((i / HP) % 2 != 0) continue;
-              const f32x4 c = cs[j & 1][i % HP], s = sn[j & 1][i % HP];
+              const f32x4 c = cs[j % TD][i % HP], s = sn[j % TD][i % HP];
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
                 const float lo = v[i][e], hi = v[i + HP][e];
@@ -464,9 +484,12 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(MfmaGemmArgs a) {
     PIN();
     const int cn0 = n0, cm0 = m0;
     const bool more = tile + PIPE_BLOCKS < nblk;
-    // What the end of the tile needs and is known now travels behind the K loop: the residual of the first tokens and the
-    // low-rank operands of the first 32 or 64.  Copies are whole multiples of 32 rows, so a 32-row piece belongs to one copy;
-    // segments begin and end on tile borders.  Tiles outside every segment multiply zeros.
+    // What the end of the tile needs and is known now travels behind the K loop: the residual of the first tokens, the
+    // bottleneck activations of all the wave's tokens and the factor of the first ones' copy.  Copies are whole multiples of 32
+    // rows, so a 32-row piece belongs to one copy, and the wave's 128 rows mostly do: only where a copy ends inside are the next
+    // pieces' factors requested behind the loop, each under the matrix instructions of the piece before.  Segments begin and end
+    // on tile borders; tiles outside every segment multiply zeros.  (With the factors of every 32 rows fetched as if of another copy,
+    // half of them behind the loop: 65536 x 2560 x 2048 rotated 588 us, now 554; 65536 x 2048 x 2048 with residual 542 / 509.)
     constexpr bool RES = EPI == PIPE_F32 && (FL & 2);
     u32x4 rs[RES ? 4 : 1][8];
     if constexpr (RES) {
@@ -474,29 +497,35 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(MfmaGemmArgs a) {
       o.read(rs[0], 0);
       if constexpr (LR == 0) o.read(rs[1], 1);
     }
-    u32x4 lx[LR ? NJ / 2 : 1][2], lw[LR ? NJ / 2 : 1][NI];
+    u32x4 lx[LR ? NJ / 2 : 1][2], lw[2][NI];
     int seg = 0;
-    bool in = false;
+    bool in = false, one = true;                           // one: the wave's 128 tokens belong to one copy
     const bool part = LR == 2 || lq < 2;
+    auto first_row = [&](int j2) {                         // tiles past the end compute discarded values in bounds
+      const int mt = cm0 + wm + j2 * 32;
+      return mt < a.M ? mt : a.M - 32;
+    };
     if constexpr (LR > 0) {
       for (int s = 0; s < a.n_seg; ++s)
         if (cn0 >= a.seg[s].col_begin && cn0 < a.seg[s].col_end) { seg = s; in = true; }
+      one = first_row(0) / a.rows_per_copy == first_row(NJ / 2 - 1) / a.rows_per_copy;
     }
-    auto low_rank_load = [&](int j2) {                     // operands of 32 tokens
-      const MfmaLoraSeg& sg = a.seg[seg];
-      const int col = in ? cn0 + wn + l16 - sg.col_begin : l16, k8 = part ? lq * 8 : 0;
-      int mt = cm0 + wm + j2 * 32;
-      mt = mt < a.M ? mt : a.M - 32;                       // tiles past the end compute discarded values in bounds
-      const uint16_t* tr = (const uint16_t*)sg.tp + (size_t)(mt + l16) * (16 * LR) + k8;
-      const uint16_t* bp = (const uint16_t*)sg.bp + (size_t)(mt / a.rows_per_copy) * sg.copy_stride + (size_t)col * (16 * LR) + k8;
+    auto low_rank_x = [&](int j2) {                        // operands of 32 tokens
+      const uint16_t* tr = (const uint16_t*)a.seg[seg].tp + (size_t)(first_row(j2) + l16) * (16 * LR) + (part ? lq * 8 : 0);
 #pragma unroll
       for (int j = 0; j < 2; ++j) lx[j2][j] = *(const u32x4*)(tr + j * 16 * 16 * LR);
+    };
+    auto low_rank_w = [&](int j2) {                        // and the factor of their copy
+      const MfmaLoraSeg& sg = a.seg[seg];
+      const int col = in ? cn0 + wn + l16 - sg.col_begin : l16;
+      const uint16_t* bp = (const uint16_t*)sg.bp + (size_t)(first_row(j2) / a.rows_per_copy) * sg.copy_stride + (size_t)col * (16 * LR) + (part ? lq * 8 : 0);
 #pragma unroll
-      for (int i = 0; i < NI; ++i) lw[j2][i] = *(const u32x4*)(bp + (in ? i * 16 * 16 * LR : 0));
+      for (int i = 0; i < NI; ++i) lw[j2 & 1][i] = *(const u32x4*)(bp + (in ? i * 16 * 16 * LR : 0));
     };
     if constexpr (LR > 0) {
-      low_rank_load(0);
-      if constexpr (!RES) low_rank_load(1);
+#pragma unroll
+      for (int j2 = 0; j2 < NJ / 2; ++j2) low_rank_x(j2);
+      low_rank_w(0);
       __builtin_amdgcn_sched_barrier(0);
     }
     // the last two K-tiles fetch the next tile's first two (without a next tile: this one's again)
@@ -519,25 +548,29 @@ __global__ void __launch_bounds__(256, 1) gemm_pipe_kernel(MfmaGemmArgs a) {
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     if constexpr (LR > 0) {
       // per-copy low-rank term: one more K-step, [B_hi | B_lo] of a copy against the duplicated bottleneck activations [t | t]
-      // (rank <= 8: its upper half is zero).  The operands of the last 64 tokens travel while the first are multiplied.
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (RES) low_rank_load(1);
-      low_rank_load(2);
-      low_rank_load(3);
+      // (rank <= 8: its upper half is zero)
       __builtin_amdgcn_sched_barrier(0);
       const u32x4 zero = {0u, 0u, 0u, 0u};
+      if (!one) {
+        low_rank_w(1);
+      } else {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) lw[1][i] = lw[0][i];
+      }
 #pragma unroll
       for (int j2 = 0; j2 < NJ / 2; ++j2) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < 2; ++j) lx[j2][j] = in && part ? lx[j2][j] : zero;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) lw[j2][i] = part ? lw[j2][i] : zero;
+        for (int i = 0; i < NI; ++i) lw[j2 & 1][i] = part ? lw[j2 & 1][i] : zero;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
           for (int i = 0; i < NI; ++i)
-            acc[0][i][j2 * 2 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(lw[j2][i]), as_frag(lx[j2][j]), acc[0][i][j2 * 2 + j], 0, 0, 0);
+            acc[0][i][j2 * 2 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(lw[j2 & 1][i]), as_frag(lx[j2][j]), acc[0][i][j2 * 2 + j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
+        if (j2 + 2 < NJ / 2 && !one) low_rank_w(j2 + 2);
       }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
