@@ -323,7 +323,8 @@ mpz_status mpz_debug_set_split_k(mpz_model* m, int32_t enable);
  * 256 stacked tokens does with weight_quant = NF4): w_codes [dev] [N, K / 2] bytes (SwiGLU: [2N, K / 2], gate rows then up
  * rows; two codes per byte, low nibble first), w_absmax [dev] [N or 2N, K / 64] fp32, 16- and 4-byte aligned; the other
  * arguments as mpz_debug_gemm_bf16_splitk with 2 <= k_splits <= 64.  The result has the bits of mpz_debug_dequant_nf4
- * followed by mpz_debug_gemm_bf16_splitk with the same k_splits.  Errors: NULL, SHAPE, DEVICE. */
+ * followed by mpz_debug_gemm_bf16_splitk with the same k_splits.  k_splits = -1: the streamed kernel, which takes projections
+ * with many weights (operands 16-byte aligned).  Errors: NULL, SHAPE, DEVICE. */
 mpz_status mpz_debug_gemm_nf4_splitk(int32_t M, int32_t N, int32_t K, const void* x, const void* w_codes, const float* w_absmax,
                                      const float* bias, int32_t act, const float* residual, void* out, int32_t out_f32,
                                      int32_t k_splits, float* partial, size_t partial_elems, void* hip_stream);

@@ -191,15 +191,19 @@ struct MfmaGemmArgs {
   // (launch_gemm_mfma does both).  0 or 1: off.  defer_reduce: launch_gemm_mfma leaves the reduction to the caller
   // (launch_splitk_reduce_norm: the reduction in one kernel with the pre-norm that follows the projection).
   int k_splits; float* partial; int ldp; int defer_reduce;
-  // stream_units > 0 (with k_splits > 1): gemm_stream.hip instead - every block takes stream_units K-tiles of the list of
-  // (128-feature tile, K-tile) pairs, and the sums of a tile's columns lie in as many slots of `partial` as blocks share it
-  int stream_units;
+  // stream_units > 0 (with k_splits > 1): gemm_stream.hip or gemm_codes.hip instead - every block takes stream_units K-tiles of the
+  // list of (feature tile, K-tile) pairs, and the sums of a tile's columns lie in as many slots of `partial` as blocks share it
+  int stream_units, stream_bn;  // (stream_bn: features of such a tile)
 };
 // blocks that share a tile of nk K-tiles: the tile's own, and the most any tile has
 __host__ __device__ inline int stream_slots_of(int tile, int nk, int units) { return ((tile + 1) * nk - 1) / units - tile * nk / units + 1; }
 __host__ __device__ inline int stream_slots(int nk, int units) { return nk % units == 0 ? nk / units : (nk + units - 2) / units + 1; }
 int gemm_stream_units(const MfmaGemmArgs& a, size_t capacity);
 hipError_t launch_gemm_stream(hipStream_t st, const MfmaGemmArgs& a);
+bool gemm_codes_supported(const MfmaGemmArgs& a);                            // gemm_codes.hip: 4-bit weights, few tokens
+int gemm_codes_units(const MfmaGemmArgs& a, size_t capacity);
+constexpr int kCodesTile = 256;                          // features of its tile
+hipError_t launch_gemm_codes(hipStream_t st, const MfmaGemmArgs& a);
 bool gemm_ring_supported(const MfmaGemmArgs& a);                             // gemm_ring.hip: 32 x 32 tiles, bf16 weights
 hipError_t launch_gemm_ring(hipStream_t st, const MfmaGemmArgs& a);
 // operands that may be fetched straight into LDS, 16 bytes at a time

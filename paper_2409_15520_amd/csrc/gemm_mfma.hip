@@ -1063,7 +1063,7 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(MfmaGemmArgs a) {
   auto sum4 = [&](int col) {
     const float* p = a.partial + (size_t)m * a.ldp + col;
     f32x4 v = *(const f32x4*)p;
-    const int slots = a.stream_units ? stream_slots_of(col / 128, a.K / 64, a.stream_units) : a.k_splits;
+    const int slots = a.stream_units ? stream_slots_of(col / a.stream_bn, a.K / 64, a.stream_units) : a.k_splits;
     for (int s = 1; s < slots; ++s) v += *(const f32x4*)(p + s * plane);
     return v;
   };
@@ -1119,7 +1119,7 @@ hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a) {
     // kernel's raw layout), on the BK = 64 tile that fetches whole 128-byte lines
     MfmaGemmArgs b = a;
     if (a.dual && a.dual_offset == a.N) { b.dual = 0; b.N = 2 * a.N; }
-    if (a.stream_units > 0) e = launch_gemm_stream(st, b);
+    if (a.stream_units > 0) e = a.w_absmax != nullptr ? launch_gemm_codes(st, b) : launch_gemm_stream(st, b);
     else if (b.dual) e = q8 ? launch_cfg<128, 128, 32, 2, 2, true, 0, true>(st, a) : launch_cfg<128, 128, 32, 2, 2, true>(st, a);
     else if (a.w_absmax != nullptr)          // 4-bit codes looked up in the operand load: the two 128-feature tiles
       e = choose_cfg(b) == 9 ? launch_cfg<128, 64, 64, 2, 2, false, 0, 2>(st, b) : launch_cfg<128, 128, 64, 2, 2, false, 0, 2>(st, b);

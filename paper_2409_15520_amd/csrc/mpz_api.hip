@@ -391,6 +391,19 @@ bool plan_stream(MfmaGemmArgs& g, float* partial, size_t capacity, bool forced =
   if (g.tile_cfg != 0 || g.ce_max != nullptr || (g.dual && g.dual_offset != g.N)) return false;
   MfmaGemmArgs b = g;
   if (g.dual) { b.dual = 0; b.N = 2 * g.N; }              // gate | up lie back to back: one product over 2 N rows
+  if (g.w_absmax != nullptr) {
+    // 4-bit weights: gemm_codes.hip from twelve K-tiles of 256 features per CU on, sixteen up to 128 tokens.  Below, its partial sums
+    // (one of 256 features per CU at least) cost more than looking every weight up once saves; shares of K looked up in
+    // gemm_bf16_kernel -> here, us with the reduction: 12288 x 4096 64: 28 -> 32, 128: 38 -> 40, 192: 57 -> 46, 256: 60 -> 56;
+    // 22016 x 4096 64: 49 -> 42, 256: 93 -> 80; 4096 x 11008 (eleven) 128: 36 -> 39, 256: 51 -> 64; 11264 x 2048 (six) 192: 38 -> 43
+    if (!gemm_codes_supported(b)) return false;
+    if (!forced && (long)((b.N + kCodesTile - 1) / kCodesTile) * (b.K / 64) < 256 * (b.M <= 128 ? 16 : 12)) return false;
+    const int units = gemm_codes_units(b, capacity);
+    if (units == 0) return false;
+    const int slots = stream_slots(b.K / 64, units);
+    g.stream_units = units; g.stream_bn = kCodesTile; g.k_splits = slots < 2 ? 2 : slots; g.partial = partial; g.ldp = b.N;
+    return true;
+  }
   if (!forced) {
     if (g.K < 8 * g.M || g.K < (g.M <= 128 ? 2560 : 4096)) return false;
     if ((long)((b.N + 127) / 128) * (b.K / 64) < kStreamMinUnits) return false;
@@ -399,7 +412,7 @@ bool plan_stream(MfmaGemmArgs& g, float* partial, size_t capacity, bool forced =
   const int units = gemm_stream_units(b, capacity);
   if (units == 0) return false;
   const int slots = stream_slots(b.K / 64, units);
-  g.stream_units = units; g.k_splits = slots < 2 ? 2 : slots; g.partial = partial; g.ldp = b.N;
+  g.stream_units = units; g.stream_bn = 128; g.k_splits = slots < 2 ? 2 : slots; g.partial = partial; g.ldp = b.N;
   return true;
 }
 // Few stacked tokens: let k_splits blocks share an output tile (see MfmaGemmArgs).  Called once the shape and the
@@ -1382,15 +1395,19 @@ mpz_status mpz_debug_gemm_nf4_splitk(int32_t M, int32_t N, int32_t K, const void
                                      const float* bias, int32_t act, const float* residual, void* out, int32_t out_f32,
                                      int32_t k_splits, float* partial, size_t partial_elems, void* hip_stream) {
   if (!x || !w_codes || !w_absmax || !out || !partial) return fail(nullptr, MPZ_ERR_NULL, "mpz_debug_gemm_nf4_splitk: NULL argument");
-  if (k_splits < 2 || k_splits > 64) return fail(nullptr, MPZ_ERR_SHAPE, "mpz_debug_gemm_nf4_splitk: k_splits outside [2, 64]");
+  if (k_splits != -1 && (k_splits < 2 || k_splits > 64)) return fail(nullptr, MPZ_ERR_SHAPE, "mpz_debug_gemm_nf4_splitk: k_splits outside [2, 64]");
   if (K % 64 || N % 4 || M < 1 || N < 1) return fail(nullptr, MPZ_ERR_SHAPE, "shape not supported by the MFMA GEMM (K % 64, N % 4)");
   MfmaGemmArgs g{};
   g.M = M; g.N = N; g.K = K; g.x = x; g.w = w_codes; g.w_absmax = w_absmax; g.w_rows = N; g.bias = bias; g.rows_per_copy = M; g.act = act;
-  g.residual = residual; g.out_f32 = out_f32; g.out = out; g.ldo = N; g.tile_cfg = 100 * k_splits;
+  g.residual = residual; g.out_f32 = out_f32; g.out = out; g.ldo = N; g.tile_cfg = k_splits > 0 ? 100 * k_splits : 0;
   if (act == MPZ_ACT_SWIGLU) { g.dual = 1; g.dual_offset = N; g.w_rows = 2 * N; g.act = -1; }
-  if (mfma_gemm_splits(g, partial_elems) != k_splits)
-    return fail(nullptr, MPZ_ERR_SHAPE, "mpz_debug_gemm_nf4_splitk: k_splits does not fit K or the partial buffer");
-  g.k_splits = k_splits; g.partial = partial; g.ldp = (g.dual ? 2 : 1) * N;
+  if (k_splits == -1) {
+    if (!plan_stream(g, partial, partial_elems, true)) return fail(nullptr, MPZ_ERR_SHAPE, "mpz_debug_gemm_nf4_splitk: not a shape of the streamed kernel");
+  } else {
+    if (mfma_gemm_splits(g, partial_elems) != k_splits)
+      return fail(nullptr, MPZ_ERR_SHAPE, "mpz_debug_gemm_nf4_splitk: k_splits does not fit K or the partial buffer");
+    g.k_splits = k_splits; g.partial = partial; g.ldp = (g.dual ? 2 : 1) * N;
+  }
   if (!mfma_gemm_supported(g)) return fail(nullptr, MPZ_ERR_SHAPE, "shape or alignment not supported by the MFMA GEMM");
   const hipError_t le = launch_gemm_mfma((hipStream_t)hip_stream, g);
   if (le != hipSuccess) return fail(nullptr, MPZ_ERR_DEVICE, std::string("mpz_debug_gemm_nf4_splitk: ") + hipGetErrorString(le));

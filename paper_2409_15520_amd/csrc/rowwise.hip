@@ -88,7 +88,7 @@ __global__ void __launch_bounds__(256) splitk_reduce_norm_kernel(MfmaGemmArgs a,
   int slots[J];                                            // (a streamed GEMM: the columns of a tile have as many as blocks share it)
 #pragma unroll
   for (int j = 0; j < J; ++j)
-    slots[j] = a.stream_units ? stream_slots_of((tid + 256 * j) / 32, a.K / 64, a.stream_units) : a.k_splits;
+    slots[j] = a.stream_units ? stream_slots_of((tid + 256 * j) * 4 / a.stream_bn, a.K / 64, a.stream_units) : a.k_splits;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   f32x4 add[J], res[J], gg[J], bb[J];
 #pragma unroll
