@@ -5,9 +5,12 @@
 // and subnormal operands: every bit of 1024 chains of 512).  The bf16 matrix instructions add in another order; on such
 // batches a step's two-point differences (small copies: few tokens, so little averages out) moved by more than the 1e-3 that
 // a step's masters are held to.
-// Bound by the fp32 matrix rate (256 FLOP per clock and CU, a sixteenth of bf16) and, few tokens, by the chain: K / 2 dependent
-// instructions of 64 clocks.  A 1.1B-shaped block, 8 copies of 231 rows, adapters on all four projections: 2157 us with the
-// shape-agnostic kernels, 637 us with these (1848 x 2560 x 2048: 222 us, 87 TFLOP/s; the bottleneck of three targets 30 us).
+// Bound by the fp32 matrix instructions, which run on the vector lanes (256 FLOP per clock and CU, a sixteenth of bf16; no other
+// vector instruction runs beside them, on any wave of the SIMD: loops of theirs with one v_perm each, one in turn / eight in turn,
+// reach 104 / 129 TFLOP/s with one wave per SIMD, 115 / 133 with four, 155 without).  So the operands of a step are widened together,
+// addresses are constants, and the next step's operands are read before.  1848 x 2560 x 2048: 222 -> 199 us (one instruction of
+// 32 x 32 x 2 and its two v_perm in turn: 87 TFLOP/s); a 1.1B-shaped block, 8 copies of 231 rows, adapters on all four
+// projections: 2157 us with the shape-agnostic kernels, 631 -> 567 us with these.
 #include "common.h"
 #include "fetch.h"
 #include "../../include/mpz.h"
@@ -28,16 +31,15 @@ __device__ __forceinline__ void factors(float& a, float& b) {
   b = hb + __uint_as_float(l & 0xFFFF0000u);
 }
 
-// out = epilogue(x W^T): a block of four waves, 32 tokens x 32 features each; K-tiles of 64 go straight into a ring of three LDS
-// stages.  (Operands read by each wave for itself, a piece of 32 rows per instruction: 338 us a launch against 204, the two
-// adapted projections of that block together.)  Both halves of a wave read the same eight k of a row: the lower half takes the even ones, the
-// upper half the odd ones, which is the order in which the instruction adds.  MFMA layout: lane l holds A[l % 32][l / 32],
-// B[l / 32][l % 32] and, of the result, D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32], r = 0..15: rows are tokens, columns features.
-__global__ void __launch_bounds__(256) linear_ordered_kernel(LinearArgs a) {
-  constexpr int BK = 64, ST = 3, PER = 4;                  // k per stage, stages, fetches of a wave per stage (8 rows of 128 bytes each)
-  constexpr uint32_t HALF_STAGE = 64 * BK * 2, STAGE = 2 * HALF_STAGE;
-  __shared__ __align__(16) unsigned char smem[ST * STAGE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
+// out = epilogue(x W^T): a block of four waves, each 16 NT tokens x 16 NT features; K-tiles of 64 go straight into a ring of ST LDS
+// stages.  MFMA layout (16x16x4): lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and, of the result, D[4 (l / 16) + r][l % 16],
+// r = 0..3: rows are features, columns tokens.  The four lanes of a row read the same eight k and take the ones of their quarter.
+template <int NT, int ST>
+__global__ void __launch_bounds__(256) linear_ordered_kernel(LinearArgs a, int vec) {
+  constexpr int BK = 64, BT = 32 * NT, PER = BT / 16;      // k per stage; rows of either operand; fetches of a wave per stage (8 rows of 128 bytes each)
+  constexpr uint32_t HALF_STAGE = BT * BK * 2, STAGE = 2 * HALF_STAGE;
+  __shared__ __align__(128) unsigned char smem[ST * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, lq = lane >> 4;
   // XCD-aware tile order, groups of 8 token tiles per feature tile: see gemm_bf16_kernel
   const int tiles_n = gridDim.x, tiles_m = gridDim.y, nblk = tiles_n * tiles_m;
   int pid = blockIdx.y * tiles_n + blockIdx.x;
@@ -49,14 +51,14 @@ __global__ void __launch_bounds__(256) linear_ordered_kernel(LinearArgs a) {
   const int group = pid / (GM * tiles_n), first_m = group * GM;
   const int gsz = tiles_m - first_m < GM ? tiles_m - first_m : GM;
   const int rr = pid - group * GM * tiles_n;
-  const int bm = (first_m + rr % gsz) * 64, bn = rr / gsz * 64;
-  const int m0 = bm + (wave >> 1) * 32, n0 = bn + (wave & 1) * 32;
+  const int bm = (first_m + rr % gsz) * BT, bn = rr / gsz * BT;
+  const int m0 = bm + (wave >> 1) * 16 * NT, n0 = bn + (wave & 1) * 16 * NT;
 
   // buffers hold the tile's rows: rows past M or N fall outside (zeros), and their results are not stored.  Waves 0 and 1 fetch the
   // token rows, 2 and 3 the weight rows; 16-byte chunk c of row r lies at c ^ ((r / 2) % 8)
   const size_t row_b = (size_t)a.K * 2;
   const bool weights = wave >= 2;
-  const int r_first = weights ? bn : bm, r_end = weights ? a.N : a.M, left = r_end - r_first < 64 ? r_end - r_first : 64;
+  const int r_first = weights ? bn : bm, r_end = weights ? a.N : a.M, left = r_end - r_first < BT ? r_end - r_first : BT;
   const i32x4 rsrc = buffer_of((const char*)(weights ? a.w : a.x) + (size_t)r_first * row_b, (size_t)left * row_b);
   uint32_t voff[PER];
 #pragma unroll
@@ -69,127 +71,239 @@ __global__ void __launch_bounds__(256) linear_ordered_kernel(LinearArgs a) {
 #pragma unroll
     for (int t = 0; t < PER; ++t) fetch_rows<4>(rsrc, voff[t], (uint32_t)kt * (BK * 2), lds0 + (uint32_t)st * STAGE + (uint32_t)t * 1024u);
   };
-  const uint32_t sw = (uint32_t)((l32 >> 1) & 7) * 16u;
-  const uint32_t baseX = (uint32_t)((wave >> 1) * 32 + l32) * 128u, baseW = HALF_STAGE + (uint32_t)((wave & 1) * 32 + l32) * 128u;
-  const uint32_t sel = half ? 0x07060c0cu : 0x05040c0cu;   // of two bf16 the one of this half's k, as fp32
-  auto take = [&](uint32_t two) { return __uint_as_float(__builtin_amdgcn_perm(two, 0u, sel)); };
-
-  f32x16 acc;
+  const uint32_t sel = 0x00000c0cu | (uint32_t)(2 * lq) << 16 | (uint32_t)(2 * lq + 1) << 24;    // element lq of four bf16, as fp32
+  auto take = [&](uint32_t lo, uint32_t hi) { return __uint_as_float(__builtin_amdgcn_perm(hi, lo, sel)); };
+  const unsigned char* px[8];                              // this lane's piece of each eight k of its first row, in stage 0
+  const unsigned char* pw[8];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  for (int c = 0; c < 8; ++c) {
+    const uint32_t o = (uint32_t)l16 * 128u + ((uint32_t)c * 16u ^ ((uint32_t)((l16 >> 1) & 7) * 16u));
+    px[c] = smem + (wave >> 1) * 16 * NT * 128 + o;
+    pw[c] = smem + HALF_STAGE + (wave & 1) * 16 * NT * 128 + o;
+  }
+
+  f32x4 acc[NT][NT];                                       // [features][tokens]
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int nk = a.K / BK;
 #pragma unroll
   for (int t = 0; t < ST - 1; ++t)
     if (t < nk) fetch(t, t);
-  int st = 0;
-  for (int kt = 0; kt < nk; ++kt) {
-    // K-tile kt has landed for the whole block, and every wave is done with the stage that the next fetch overwrites
-    wait_fetched<PER, ST - 2>(nk - 1 - kt);
-    if (kt + ST - 1 < nk) fetch(kt + ST - 1, st == 0 ? ST - 1 : st - 1);
-    const unsigned char* sp = smem + (uint32_t)st * STAGE;
-    st = st + 1 == ST ? 0 : st + 1;
+  for (int k0 = 0; k0 < nk; k0 += ST)
 #pragma unroll
-    for (int c = 0; c < BK / 8; ++c) {
-      const u32x4 x = *(const u32x4*)(sp + baseX + ((uint32_t)c * 16u ^ sw)), w = *(const u32x4*)(sp + baseW + ((uint32_t)c * 16u ^ sw));
+    for (int st = 0; st < ST; ++st) {                      // (the stage is a constant: no address arithmetic, see above)
+      const int kt = k0 + st;
+      if (kt >= nk) break;                                 // (uniform)
+      // K-tile kt has landed for the whole block, and every wave is done with the stage that the next fetch overwrites
+      wait_fetched<PER, ST - 2>(nk - 1 - kt);
+      if (kt + ST - 1 < nk) fetch(kt + ST - 1, (st + ST - 1) % ST);
+      u32x4 x[2][NT], w[2][NT];
+      auto read = [&](int c) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(take(x[e]), take(w[e]), acc, 0, 0, 0);
-    }
-  }
-  if (m0 >= a.M || n0 >= a.N) return;                      // (no barriers below)
-  const int mrow = m0 + l32 < a.M ? m0 + l32 : a.M - 1;
-  const int n = n0 + l32;
-
-  // per-copy low-rank term: a chain of its own over the rank, for every copy that has rows in the tile; its sum goes to the
-  // rows of that copy alone (a result row depends on its own row of t only)
-  const int last_row = m0 + 31 < a.M ? m0 + 31 : a.M - 1;
-  const int first_copy = m0 / a.rows_per_copy, last_copy = last_row / a.rows_per_copy;
-  for (int s = 0; s < a.n_seg; ++s) {
-    const LoraSeg& sg = a.seg[s];
-    if (n0 + 31 < sg.col_begin || n0 >= sg.col_end) continue;
-    const int kout = sg.col_end - sg.col_begin;
-    const bool in = n >= sg.col_begin && n < sg.col_end;
-    const bf16_t* t = (const bf16_t*)sg.t + (int64_t)mrow * sg.t_stride + sg.t_off;
-    for (int copy = first_copy; copy <= last_copy; ++copy) {
-      const float* B = sg.Bc + (int64_t)copy * sg.copy_stride + (in ? n - sg.col_begin : 0);
-      f32x16 dl;
+        for (int j = 0; j < NT; ++j) {
+          x[c & 1][j] = *(const u32x4*)(px[c] + st * STAGE + j * 2048);
+          w[c & 1][j] = *(const u32x4*)(pw[c] + st * STAGE + j * 2048);
+        }
+      };
+      read(0);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) dl[e] = 0.f;
-      for (int r = half; r < a.rank + half; r += 4) {      // (ranks are multiples of 4)
-        float b0 = B[(int64_t)r * kout], b1 = B[(int64_t)(r + 2) * kout];
-        factors(b0, b1);
-        dl = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_to_f32(t[r]), b0, dl, 0, 0, 0);
-        dl = __builtin_amdgcn_mfma_f32_32x32x2f32(bf16_to_f32(t[r + 2]), b1, dl, 0, 0, 0);
-      }
+      for (int c = 0; c < BK / 8; ++c) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (c + 1 < BK / 8) read(c + 1);
+        float fx[2][NT], fw[2][NT];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = m0 + 8 * (e / 4) + 4 * half + e % 4;
-        acc[e] = in && m / a.rows_per_copy == copy ? acc[e] + dl[e] : acc[e];
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int j = 0; j < NT; ++j) {
+            fx[e][j] = take(x[c & 1][j][2 * e], x[c & 1][j][2 * e + 1]);
+            fw[e][j] = take(w[c & 1][j][2 * e], w[c & 1][j][2 * e + 1]);
+          }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[e][i], fx[e][j], acc[i][j], 0, 0, 0);
       }
     }
-  }
-
-  if (n >= a.N) return;
-  const float bias = a.bias != nullptr ? a.bias[n] : 0.f;
+  // (no barriers below)
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int m = m0 + 8 * (e / 4) + 4 * half + e % 4;
-    if (m >= a.M) continue;
-    float v = acc[e];
-    if (a.bias != nullptr) v += bias;
-    if (a.act == MPZ_ACT_RELU) v = v > 0.f ? v : 0.f;
-    const int64_t o = (int64_t)m * a.N + n;
-    if (a.residual != nullptr) v += a.residual[o];
-    if (a.out_kind == 0) ((bf16_t*)a.out)[o] = f32_to_bf16(v);
-    else ((float*)a.out)[o] = v;                           // (bf16 models stage in fp32)
+  for (int j = 0; j < NT; ++j) {
+    const int mj = m0 + j * 16, m = mj + l16, mrow = m < a.M ? m : a.M - 1;
+    if (mj >= a.M) continue;                               // (uniform)
+    // per-copy low-rank term: a chain of its own over the rank, for every copy that has rows in the tile; its sum goes to the
+    // rows of that copy alone (a result column depends on its own row of t only)
+    const int last_row = mj + 15 < a.M ? mj + 15 : a.M - 1;
+    const int first_copy = mj / a.rows_per_copy, last_copy = last_row / a.rows_per_copy;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int ni = n0 + i * 16;
+      if (ni >= a.N) continue;                             // (uniform)
+      for (int s = 0; s < a.n_seg; ++s) {
+        const LoraSeg& sg = a.seg[s];
+        if (ni + 15 < sg.col_begin || ni >= sg.col_end) continue;
+        const int kout = sg.col_end - sg.col_begin, col = ni + l16;
+        const bool in = col >= sg.col_begin && col < sg.col_end;
+        const bf16_t* t = (const bf16_t*)sg.t + (int64_t)mrow * sg.t_stride + sg.t_off;
+        for (int copy = first_copy; copy <= last_copy; ++copy) {
+          const float* B = sg.Bc + (int64_t)copy * sg.copy_stride + (in ? col - sg.col_begin : 0);
+          f32x4 dl = {0.f, 0.f, 0.f, 0.f};
+          for (int r = lq; r < a.rank + lq; r += 4) {      // (ranks are multiples of 4)
+            float b0 = B[(int64_t)r * kout], none = 0.f;
+            factors(b0, none);
+            dl = __builtin_amdgcn_mfma_f32_16x16x4f32(b0, bf16_to_f32(t[r]), dl, 0, 0, 0);
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int n = ni + 4 * lq + e;
+            acc[i][j][e] = n >= sg.col_begin && n < sg.col_end && m / a.rows_per_copy == copy ? acc[i][j][e] + dl[e] : acc[i][j][e];
+          }
+        }
+      }
+      const int n = ni + 4 * lq;
+      if (m >= a.M || n >= a.N) continue;
+      const int64_t o = (int64_t)m * a.N + n;
+      f32x4 v = acc[i][j];
+      if (vec) {                                           // N a multiple of 4, pointers on 16 bytes
+        if (a.bias != nullptr) v += *(const f32x4*)(a.bias + n);
+        if (a.act == MPZ_ACT_RELU) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+        }
+        if (a.residual != nullptr) v += *(const f32x4*)(a.residual + o);
+        if (a.out_kind == 0) {
+          uint32_t lo = (uint32_t)f32_to_bf16(v[0]).bits | (uint32_t)f32_to_bf16(v[1]).bits << 16;
+          uint32_t hi = (uint32_t)f32_to_bf16(v[2]).bits | (uint32_t)f32_to_bf16(v[3]).bits << 16;
+          *(uint64_t*)((bf16_t*)a.out + o) = (uint64_t)hi << 32 | lo;
+        } else {
+          *(f32x4*)((float*)a.out + o) = v;                // (bf16 models stage in fp32)
+        }
+        continue;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (n + e >= a.N) continue;
+        float y = v[e];
+        if (a.bias != nullptr) y += a.bias[n + e];
+        if (a.act == MPZ_ACT_RELU) y = y > 0.f ? y : 0.f;
+        if (a.residual != nullptr) y += a.residual[o + e];
+        if (a.out_kind == 0) ((bf16_t*)a.out)[o + e] = f32_to_bf16(y);
+        else ((float*)a.out)[o + e] = y;
+      }
+    }
   }
 }
 
-// LoRA bottleneck t = bf16(scale * x A_c): a wave per 16 rows of one copy and 16 bottleneck columns.  Bound by the latency of its
-// chain: K / 4 dependent instructions of 32 clocks.  Lane l holds x[l % 16][k = l / 16] and A[k = l / 16][column l % 16] of every
-// four k and, of the result, D[4 (l / 16) + r][l % 16], r = 0..3.
-__global__ void __launch_bounds__(64) lora_down_ordered_kernel(LoraDownArgs a, int tiles_per_copy, int col_tiles) {
-  constexpr int CH = 4, AHEAD = 6;                         // pieces of 8 k in a register set, sets in flight
-  const int lane = threadIdx.x, l16 = lane & 15, lq = lane >> 4, R = a.n_targets * a.rank;
-  const int col_tile = blockIdx.x % col_tiles, rest = blockIdx.x / col_tiles;
-  const int copy = rest / tiles_per_copy, r0 = rest % tiles_per_copy * 16;   // first row inside the copy
-  const int row = r0 + l16 < a.rows_per_copy ? r0 + l16 : a.rows_per_copy - 1;
-  const u32x4* px = (const u32x4*)((const uint16_t*)a.x + (int64_t)(copy * (int64_t)a.rows_per_copy + row) * a.K);
-  const int j = col_tile * 16 + l16, jj = j < R ? j : R - 1;
-  const float* A = a.Ac[jj / a.rank] + (int64_t)copy * a.copy_stride + (int64_t)lq * a.rank + jj % a.rank;
-  const uint32_t sel = 0x00000c0cu | (uint32_t)(2 * lq) << 16 | (uint32_t)(2 * lq + 1) << 24;    // element lq of four bf16
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  const int chunks = a.K / (8 * CH);
-  u32x4 rx[AHEAD][CH];
-  float rf[AHEAD][2 * CH];
-  auto request = [&](u32x4 (&x)[CH], float (&f)[2 * CH], int c) {
-    c = c < chunks ? c : chunks - 1;                       // (past the end: the last piece again, never multiplied)
+// LoRA bottleneck t = bf16(scale * x A_c): a block of four waves per 64 rows of one copy and 16 columns of one target, a wave per 16
+// rows; K-tiles of 64 (64 rows of x, 64 x 16 of the factor) go straight into a ring of LDS stages.  The factor's values become
+// what the contraction sees one K-tile ahead, in place, a quarter by each wave.  Bound by the chain: K / 4 dependent instructions
+// of 32 clocks, and vector instructions do not run beside it (1848 rows, K = 2048: 29 -> 21 us; a wave
+// per 16 rows with both operands from memory, converting the factor for itself, waited for its requests).  Lane l holds x[l % 16][k = l / 16] and
+// A[k = l / 16][column l % 16] of every four k and, of the result, D[4 (l / 16) + r][l % 16], r = 0..3.
+template <int BK, int ST>
+__global__ void __launch_bounds__(256) lora_down_ordered_kernel(LoraDownArgs a, int tiles_per_copy, int col_tiles) {
+  constexpr int FX = BK / 32, FA = BK / 64, PER = FX + FA;                     // fetches of a wave per stage: of x, of the factor
+  constexpr uint32_t CPR = BK / 8, RPF = 64 / CPR;                             // 16-byte chunks of a row, rows of a fetch
+  constexpr uint32_t XBYTES = 64 * BK * 2, STAGE = XBYTES + BK * 64;
+  extern __shared__ __align__(16) unsigned char lora_smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, lq = lane >> 4;
+  const int cols = a.n_targets * col_tiles, col_tile = blockIdx.x % cols, rest = blockIdx.x / cols;
+  const int target = col_tile / col_tiles, c0 = col_tile % col_tiles * 16;
+  const int copy = rest / tiles_per_copy, r0 = rest % tiles_per_copy * 64;     // first row inside the copy
+  const size_t row_b = (size_t)a.K * 2;
+  const int rows = a.rows_per_copy - r0 < 64 ? a.rows_per_copy - r0 : 64;      // rows past the copy read zeros and are not stored
+  const i32x4 rsrcX = buffer_of((const char*)a.x + ((size_t)copy * a.rows_per_copy + r0) * row_b, (size_t)rows * row_b);
+  const i32x4 rsrcA = buffer_of(a.Ac[target] + (int64_t)copy * a.copy_stride + c0, ((size_t)a.K * a.rank - c0) * 4);
+  const uint32_t row_a = (uint32_t)a.rank * 4u;
+  auto swizzle = [](uint32_t row) { return BK == 64 ? row >> 1 & 7u : row & 15u; };          // chunk c of a row lies at c ^ this
+  uint32_t voffX[FX];
 #pragma unroll
-    for (int i = 0; i < CH; ++i) x[i] = px[c * CH + i];
+  for (int t = 0; t < FX; ++t) {
+    const uint32_t row = (uint32_t)(wave * FX + t) * RPF + lane / CPR;
+    voffX[t] = row * (uint32_t)row_b + ((lane % CPR) ^ swizzle(row)) * 16u;
+  }
+  const uint32_t voffA = (uint32_t)(wave * 16 + (lane >> 2)) * row_a + (uint32_t)(lane & 3) * 16u;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lora_smem;
+  auto fetch = [&](int kt, int st) {
+    const uint32_t base = lds0 + (uint32_t)st * STAGE;
 #pragma unroll
-    for (int i = 0; i < 2 * CH; ++i) f[i] = A[(int64_t)(c * 8 * CH + 4 * i) * a.rank];
+    for (int t = 0; t < FX; ++t) fetch_rows<4>(rsrcX, voffX[t], (uint32_t)kt * (BK * 2), base + (uint32_t)(wave * FX + t) * 1024u);
+#pragma unroll
+    for (int t = 0; t < FA; ++t)
+      fetch_rows<4>(rsrcA, voffA, (uint32_t)(kt * BK + t * 64) * row_a, base + XBYTES + (uint32_t)(t * 4 + wave) * 1024u);
   };
+  auto convert = [&](int st) {
 #pragma unroll
-  for (int u = 0; u < AHEAD; ++u) request(rx[u], rf[u], u);
-  for (int c0 = 0; c0 < chunks; c0 += AHEAD)
-#pragma unroll
-    for (int u = 0; u < AHEAD; ++u) {
-      if (c0 + u >= chunks) break;                         // (uniform)
-#pragma unroll
-      for (int i = 0; i < 2 * CH; i += 2) factors(rf[u][i], rf[u][i + 1]);
-#pragma unroll
-      for (int i = 0; i < 2 * CH; ++i) {
-        const float x = __uint_as_float(__builtin_amdgcn_perm(rx[u][i / 2][i % 2 * 2 + 1], rx[u][i / 2][i % 2 * 2], sel));
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, rf[u][i], acc, 0, 0, 0);
-      }
-      request(rx[u], rf[u], c0 + u + AHEAD);
-      __builtin_amdgcn_sched_barrier(0);
+    for (int t = 0; t < FA; ++t) {
+      f32x4* p = (f32x4*)(lora_smem + (uint32_t)st * STAGE + XBYTES) + t * 256 + tid;
+      f32x4 v = *p;
+      float f[4] = {v[0], v[1], v[2], v[3]};
+      factors(f[0], f[1]);
+      factors(f[2], f[3]);
+      *p = f32x4{f[0], f[1], f[2], f[3]};
     }
-  if (j >= R) return;
+  };
+  const uint32_t sel = 0x00000c0cu | (uint32_t)(2 * lq) << 16 | (uint32_t)(2 * lq + 1) << 24;    // element lq of four bf16
+  const uint32_t baseX = (uint32_t)(wave * 16 + l16) * (BK * 2), sw = swizzle(l16) * 16u, baseA = XBYTES + (uint32_t)(lq * 16 + l16) * 4u;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  const int nk = a.K / BK;
+#pragma unroll
+  for (int t = 0; t < ST - 1; ++t)
+    if (t < nk) fetch(t, t);
+  wait_fetched<PER, ST - 2>(nk - 1);
+  convert(0);
+  int st = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    // K-tile kt + 1 has landed, the factor of kt is converted (its writes are awaited with the fetches), and every wave is done with
+    // the stage that the next fetch overwrites
+    wait_fetched<PER, ST - 3>(nk - 2 - kt);
+    if (kt + ST - 1 < nk) fetch(kt + ST - 1, st == 0 ? ST - 1 : st - 1);
+    const unsigned char* sp = lora_smem + (uint32_t)st * STAGE;
+    st = st + 1 == ST ? 0 : st + 1;
+    u32x4 x[2][8];
+    float f[2][16];
+    auto read = [&](int h) {                               // 64 k
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        x[h & 1][c] = *(const u32x4*)(sp + baseX + ((uint32_t)(h * 8 + c) * 16u ^ sw));
+#pragma unroll
+        for (int e = 0; e < 2; ++e) f[h & 1][2 * c + e] = *(const float*)(sp + baseA + (h * 16 + 2 * c + e) * 256);
+      }
+    };
+    read(0);
+    if (kt + 1 < nk) convert(st);
+#pragma unroll
+    for (int h = 0; h < BK / 64; ++h) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (h + 1 < BK / 64) read(h + 1);
+      float fx[16];
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) fx[2 * c + e] = __uint_as_float(__builtin_amdgcn_perm(x[h & 1][c][2 * e + 1], x[h & 1][c][2 * e], sel));
+      __builtin_amdgcn_sched_barrier(0);                   // (the chain without vector instructions between its links)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fx[i], f[h & 1][i], acc, 0, 0, 0);
+    }
+  }
+  const int jr = c0 + l16, R = a.n_targets * a.rank;
+  if (jr >= a.rank) return;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int rc = r0 + 4 * lq + r;
-    if (rc < a.rows_per_copy) ((bf16_t*)a.t)[(copy * (int64_t)a.rows_per_copy + rc) * R + j] = f32_to_bf16(acc[r] * a.scale);
+    const int rc = r0 + wave * 16 + 4 * lq + r;
+    if (rc < a.rows_per_copy) ((bf16_t*)a.t)[(copy * (int64_t)a.rows_per_copy + rc) * R + target * a.rank + jr] = f32_to_bf16(acc[r] * a.scale);
   }
+}
+
+template <int BK, int ST>
+void launch_down(hipStream_t st, const LoraDownArgs& a, unsigned blocks, int tiles, int cols) {
+  constexpr int lds = ST * (64 * BK * 2 + BK * 64);
+  static const hipError_t attr_status = hipFuncSetAttribute((const void*)lora_down_ordered_kernel<BK, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  (void)attr_status;                                       // (a refusal shows as the launch's error)
+  lora_down_ordered_kernel<BK, ST><<<blocks, 256, lds, st>>>(a, tiles, cols);
 }
 
 }  // namespace
@@ -198,16 +312,27 @@ __global__ void __launch_bounds__(64) lora_down_ordered_kernel(LoraDownArgs a, i
 // other surroundings)
 bool launch_linear_ordered(hipStream_t st, const LinearArgs& a) {
   if (a.dtype != MPZ_DTYPE_BF16 || a.K % 64 || a.K < 64 || a.K >= 1 << 24 || a.act == MPZ_ACT_GELU_ERF || (((uintptr_t)a.x | (uintptr_t)a.w) & 15)) return false;
-  linear_ordered_kernel<<<dim3((a.N + 63) / 64, (a.M + 63) / 64), 256, 0, st>>>(a);
+  const int vec = a.N % 4 == 0 && (((uintptr_t)a.out | (uintptr_t)a.residual | (uintptr_t)a.bias) & 15) == 0;
+  const long small = (long)((a.N + 31) / 32) * ((a.M + 31) / 32);
+  const dim3 g32((a.N + 31) / 32, (a.M + 31) / 32), g64((a.N + 63) / 64, (a.M + 63) / 64);
+  // up to two tiles of 64 x 64 per CU's worth of rows and columns, 16 x 16 per wave: a quarter of the chain per wave, four times the
+  // waves (154 rows, Q|K|V and O of the 1.1B shape: 136 -> 60 us, 100 in the larger tiles; 3696 rows of the 125M shape: 217 / 206)
+  if (small <= 2048) linear_ordered_kernel<1, 3><<<g32, 256, 0, st>>>(a, vec);
+  else linear_ordered_kernel<2, 2><<<g64, 256, 0, st>>>(a, vec);
   return true;
 }
 
 bool launch_lora_down_ordered(hipStream_t st, const LoraDownArgs& a) {
-  if (a.dtype != MPZ_DTYPE_BF16 || a.K % 32 || a.K < 32 || ((uintptr_t)a.x & 15) || a.T % a.rows_per_copy) return false;
-  const int tiles = (a.rows_per_copy + 15) / 16, cols = (a.n_targets * a.rank + 15) / 16;
-  const int64_t blocks = (int64_t)(a.T / a.rows_per_copy) * tiles * cols;
-  if (blocks * 64 > (int64_t)UINT32_MAX) return false;
-  lora_down_ordered_kernel<<<(unsigned)blocks, 64, 0, st>>>(a, tiles, cols);
+  if (a.dtype != MPZ_DTYPE_BF16 || a.K % 64 || a.K < 64 || a.rank % 4 || a.copy_stride % 4 || ((uintptr_t)a.x & 15) || a.T % a.rows_per_copy) return false;
+  if ((size_t)a.K * a.rank * 4 >= (size_t)1 << 31 || (size_t)a.K * 128 >= (size_t)1 << 31) return false;
+  for (int t = 0; t < a.n_targets; ++t)
+    if ((uintptr_t)a.Ac[t] & 15) return false;
+  const int tiles = (a.rows_per_copy + 63) / 64, cols = (a.rank + 15) / 16;
+  const int64_t blocks = (int64_t)(a.T / a.rows_per_copy) * tiles * cols * a.n_targets;
+  if (blocks * 256 > (int64_t)UINT32_MAX) return false;
+  // few blocks: twice the bytes in flight and half the barriers (a block has the CU to itself)
+  if (blocks <= 256 && a.K % 128 == 0) launch_down<128, 6>(st, a, (unsigned)blocks, tiles, cols);
+  else launch_down<64, 6>(st, a, (unsigned)blocks, tiles, cols);
   return true;
 }
 

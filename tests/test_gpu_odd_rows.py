@@ -44,6 +44,13 @@ def test_projection_has_the_bits_of_the_shape_agnostic_kernels(d, heads, kv, ran
     assert not torch.equal(y[0], y[1])                     # every copy has factors of its own
 
 
+# enough rows and columns for the larger wave tile, which ends inside rows, columns and segments (1120 columns, segments from 1088 and
+# 1104); many blocks of the bottleneck, whole pairs of its K-tiles and not
+@pytest.mark.parametrize("d,heads,q,E,S,rank", [(1088, 68, 4, 3, 81, 16), (1088, 68, 16, 1, 77, 20), (512, 8, 16, 7, 33, 24)])
+def test_many_rows_have_the_bits_of_the_shape_agnostic_kernels(d, heads, q, E, S, rank):
+    test_projection_has_the_bits_of_the_shape_agnostic_kernels(d, heads, 1, rank, q, E, S, "qkv")
+
+
 # a block whose every other part takes the same kernels either way (d = 320, heads of 32) and whose feed-forward adds exact
 # zeros: norm, q/k/v with rotary staging or not, attention, output projection with residual; 4-bit weights once per pass
 @pytest.mark.parametrize("llama,rank,q,E,S,quant", [(True, 16, 4, 3, 77, "none"), (False, 8, 4, 3, 77, "none"), (True, 32, 2, 3, 33, "none"),
