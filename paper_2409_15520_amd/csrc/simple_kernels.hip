@@ -252,6 +252,40 @@ __global__ void __launch_bounds__(256) rope_convert_kernel(const typename Traits
   Tr::store(out, idx, v);
 }
 
+// The same for bf16 models, eight columns per thread: four of a head's lower half and their four partners, in 16- and 8-byte
+// pieces.  The same two operations per element.  (1848 rows of 2560: 15.8 us with a thread, a 64-bit division and two reads of the
+// row per element.)
+__global__ void __launch_bounds__(256) rope_convert_vec_kernel(const float* __restrict__ stg, bf16_t* __restrict__ out, uint32_t items,
+                                                               uint32_t per_row, uint32_t S, int n_cols, uint32_t d_head, uint32_t n_rot_heads,
+                                                               const float* __restrict__ cos_tab, const float* __restrict__ sin_tab,
+                                                               const int32_t* __restrict__ row_pos) {
+  const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
+  if (idx >= items) return;
+  const uint32_t row = idx / per_row, item = idx % per_row, half = d_head / 2, head = item / (half / 4), i = item % (half / 4) * 4;
+  const int64_t o = (int64_t)row * n_cols + head * d_head + i;
+  const float4 lo = *(const float4*)(stg + o), hi = *(const float4*)(stg + o + half);
+  float l[4] = {lo.x, lo.y, lo.z, lo.w}, h[4] = {hi.x, hi.y, hi.z, hi.w};
+  if (head < n_rot_heads) {
+    uint32_t p = row % S;
+    if (row_pos != nullptr) p = (uint32_t)row_pos[p];
+    const float4 c4 = *(const float4*)(cos_tab + (size_t)p * half + i), s4 = *(const float4*)(sin_tab + (size_t)p * half + i);
+    const float c[4] = {c4.x, c4.y, c4.z, c4.w}, s[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = l[e], y = h[e];
+      l[e] = fmaf(x, c[e], -__fmul_rn(y, s[e]));
+      h[e] = fmaf(y, c[e], __fmul_rn(x, s[e]));
+    }
+  }
+  auto put = [&](int64_t at, const float* v) {
+    ushort4 r;
+    r.x = f32_to_bf16(v[0]).bits; r.y = f32_to_bf16(v[1]).bits; r.z = f32_to_bf16(v[2]).bits; r.w = f32_to_bf16(v[3]).bits;
+    *(ushort4*)(out + at) = r;
+  };
+  put(o, l);
+  put(o + half, h);
+}
+
 // ---- causal attention, one wave per (sequence, head, query position) --------------------------------
 template <typename ST>
 __global__ void __launch_bounds__(64) attention_kernel(const ST* __restrict__ qkv, int qkv_stride, ST* __restrict__ out,
@@ -521,6 +555,14 @@ void launch_linear_simple(hipStream_t st, const LinearArgs& a) {
 void launch_rope_convert(hipStream_t st, int dtype, const void* staging, void* out, int T, int S, int n_cols, int d_head,
                          int n_rot_heads, const float* cos_tab, const float* sin_tab, const int32_t* row_pos) {
   int64_t total = (int64_t)T * n_cols;
+  // whole groups of four in a half head, 16-byte pieces, 32-bit indices
+  if (dtype == MPZ_DTYPE_BF16 && d_head % 8 == 0 && n_cols % d_head == 0 && total / 8 < (int64_t)UINT32_MAX - 256 &&
+      (((uintptr_t)staging | (uintptr_t)cos_tab | (uintptr_t)sin_tab) & 15) == 0 && ((uintptr_t)out & 7) == 0) {
+    const uint32_t items = (uint32_t)(total / 8);
+    rope_convert_vec_kernel<<<nblk(items, 256), 256, 0, st>>>((const float*)staging, (bf16_t*)out, items, (uint32_t)(n_cols / 8), (uint32_t)S, n_cols,
+                                                              (uint32_t)d_head, (uint32_t)n_rot_heads, cos_tab, sin_tab, row_pos);
+    return;
+  }
   MPZ_DISPATCH(dtype, (rope_convert_kernel<ST><<<nblk(total, 256), 256, 0, st>>>(
                           (const typename Traits<ST>::AT*)staging, (ST*)out, total, S, n_cols, d_head, n_rot_heads, cos_tab, sin_tab, row_pos)));
 }
