@@ -82,6 +82,8 @@ bool launch_linear_ordered(hipStream_t st, const LinearArgs& a);
 bool launch_lora_down_ordered(hipStream_t st, const LoraDownArgs& a);
 bool launch_linear_f64(hipStream_t st, const LinearArgs& a);
 bool launch_lora_down_f64(hipStream_t st, const LoraDownArgs& a);
+bool launch_attention_f64(hipStream_t st, const float* qkv, int qkv_stride, float* out, int n_seq, int S, int H, int Hkv, int dh, const int32_t* cu,
+                          int E, int rows_per_copy);
 
 struct MfmaLoraSeg {
   int32_t col_begin, col_end;   // adapted output columns, multiples of 128

@@ -569,6 +569,7 @@ void launch_rope_convert(hipStream_t st, int dtype, const void* staging, void* o
 
 void launch_attention_simple(hipStream_t st, int dtype, const void* qkv, int qkv_stride, void* out, int n_seq, int S, int H,
                              int Hkv, int dh, const int32_t* cu, int E, int rows_per_copy) {
+  if (dtype == MPZ_DTYPE_F32 && launch_attention_f64(st, (const float*)qkv, qkv_stride, (float*)out, n_seq, S, H, Hkv, dh, cu, E, rows_per_copy)) return;
   unsigned blocks = (unsigned)((int64_t)n_seq * H * S);
   MPZ_DISPATCH(dtype, (attention_kernel<ST><<<blocks, 64, (size_t)(S + dh) * sizeof(typename Traits<ST>::AT), st>>>(
                           (const ST*)qkv, qkv_stride, (ST*)out, S, H, Hkv, dh, (float)(1.0 / sqrt((double)dh)), cu, E,
