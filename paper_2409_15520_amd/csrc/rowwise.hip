@@ -2,6 +2,8 @@
 // bf16 GEMM operand.  One 64-lane wave owns one token row, the row lives in registers (d / 64 floats per lane),
 // statistics are two-pass in fp32 with wave-level reductions only; every access is 16 B (loads) or 8 B (stores)
 // per lane and contiguous across the wave.
+#include <type_traits>
+
 #include "common.h"
 #include "../../include/mpz.h"
 
@@ -11,9 +13,23 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
+// Sum over the wave: lanes 32, 16, 8, 4, 2, 1 apart are added in turn (the two halves and the odd and even rows of 16 change places;
+// inside a row, whose values then repeat every 8, 4, 2 lanes, a rotation by as many meets the same partner).  All on the vector
+// lanes: the same six additions through LDS shuffles, 700 clocks a sum, were half of the kernels below on few rows.
 __device__ __forceinline__ float wave_sum_f32(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  const uint32_t u = __float_as_uint(v);
+  const auto halves = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  v = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
+  const uint32_t w = __float_as_uint(v);
+  const auto rows = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+  v = __uint_as_float(rows[0]) + __uint_as_float(rows[1]);
+  auto rotated = [](float x, auto n) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x120 + decltype(n)::value, 0xF, 0xF, false));
+  };
+  v += rotated(v, std::integral_constant<int, 8>{});
+  v += rotated(v, std::integral_constant<int, 4>{});
+  v += rotated(v, std::integral_constant<int, 2>{});
+  v += rotated(v, std::integral_constant<int, 1>{});
   return v;
 }
 
