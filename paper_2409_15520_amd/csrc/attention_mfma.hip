@@ -32,7 +32,9 @@ constexpr int QB = 128;   // queries per block
 // MINB = blocks per CU the register allocation is held to: 2 leaves 134 registers (3 waves per SIMD), 4 squeezes the
 // same code into 128 (4 waves per SIMD, no spills), which pays once a block streams several key chunks (S = 512:
 // 11.9 -> 11.1 ms per step on the 1.1B-shaped workload) and costs 3 % at S = 256, where a block lives for two.
-template <int DH, int KC, int MINB>
+// ONE: no sequence is longer than a chunk (the launcher knows); the scores of pass 1 stay in registers and pass 2 takes them from
+// there instead of computing them again (4 sequences of 128, 12 heads of 64: 5.9 -> 5.1 us; 2 of 64, 32 heads of 128: 7.5 -> 5.5).
+template <int DH, int KC, int MINB, bool ONE>
 __global__ void __launch_bounds__(256, MINB) attention_mfma_kernel(const uint16_t* __restrict__ qkv, int qkv_stride,
                                                              uint16_t* __restrict__ out, int S_grid, int H, int Hkv,
                                                              float scale, const int32_t* __restrict__ cu, int E,
@@ -91,7 +93,7 @@ __global__ void __launch_bounds__(256, MINB) attention_mfma_kernel(const uint16_
   }
 
   const int last_q_block = (qb * QB + QB - 1 < S ? qb * QB + QB - 1 : S - 1);
-  const int n_chunks = last_q_block / KC + 1;     // key chunks any query of the block can see
+  const int n_chunks = ONE ? 1 : last_q_block / KC + 1;     // key chunks any query of the block can see
   const int wave_last_q = q0 + 31;
   constexpr int CPR = DH / 8;                     // 16-byte chunks per key row
 
@@ -154,6 +156,7 @@ __global__ void __launch_bounds__(256, MINB) attention_mfma_kernel(const uint16_
 
   // ---- pass 1: exact row maximum ----
   float mx = -1e30f;
+  f32x16 kept[ONE ? KC / 32 : 1];                 // ONE: the scores of the only chunk, for pass 2
   MPZ_FETCH_K(0)
   if (n_chunks == 1) { MPZ_FETCH_V(0) }
   for (int c = 0; c < n_chunks; ++c) {
@@ -168,7 +171,7 @@ __global__ void __launch_bounds__(256, MINB) attention_mfma_kernel(const uint16_
     for (int t = 0; t < KC / 32; ++t) {
       int kt0 = c * KC + t * 32;
       if (kt0 > wave_last_q) continue;            // tile entirely in this wave's future
-      f32x16 sc;
+      f32x16& sc = kept[ONE ? t : 0];
       MPZ_SCORE_TILE(t, kt0, sc)
 #pragma unroll
       for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sc[e]);
@@ -198,8 +201,8 @@ __global__ void __launch_bounds__(256, MINB) attention_mfma_kernel(const uint16_
     for (int t = 0; t < KC / 32; ++t) {
       int kt0 = c * KC + t * 32;
       if (kt0 > wave_last_q) continue;
-      f32x16 sc;
-      MPZ_SCORE_TILE(t, kt0, sc)
+      f32x16& sc = kept[ONE ? t : 0];
+      if constexpr (!ONE) MPZ_SCORE_TILE(t, kt0, sc)
       uint32_t pw[8];                             // 16 probabilities as bf16 pairs
 #pragma unroll
       for (int e = 0; e < 16; e += 2) {
@@ -258,11 +261,15 @@ void launch_attention_mfma(hipStream_t st, const void* qkv, int qkv_stride, void
   const unsigned blocks = (unsigned)((size_t)n_seq * H * qblocks);
   const float scale = (float)(1.0 / sqrt((double)dh));
   if (dh == 64 && S > 256)
-    attention_mfma_kernel<64, 128, 4><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
+    attention_mfma_kernel<64, 128, 4, false><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
+  else if (dh == 64 && S > 128)
+    attention_mfma_kernel<64, 128, 2, false><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
   else if (dh == 64)
-    attention_mfma_kernel<64, 128, 2><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
+    attention_mfma_kernel<64, 128, 2, true><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
+  else if (S > 64)
+    attention_mfma_kernel<128, 64, 2, false><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
   else
-    attention_mfma_kernel<128, 64, 2><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
+    attention_mfma_kernel<128, 64, 2, true><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
 }
 
 }  // namespace mpz
