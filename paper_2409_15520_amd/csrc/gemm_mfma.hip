@@ -897,6 +897,12 @@ bool large_tiles_pay(long tiles, int K) {
   return tiles >= 512 || (tiles * 8 >= rounds * 256 * 5 && K >= (rounds == 1 ? 1024 : 2048));
 }
 
+// The same question for int8 weights, whose 256 x 256 tile is the register-staged one of this file: one and two part-filled rounds
+// pay from the same fill on (K = 4096, 128 / 192 / 256 / 288 / 384 tiles: 92 / 104 / 118 / 194 / 205 us against 78 / 116 / 150 / 179 / 222 in
+// 128 x 128 tiles; K = 2048, 128 / 160 / 256 / 384: 53 / 53 / 67 / 115 against 42 / 58 / 81 / 119; gate and up together, K = 4096, 172 / 344
+// tiles: 94 / 191 against 119 / 212).  Measured from K = 2048 on.
+bool int8_large_tiles_pay(long tiles, int K) { return K >= 2048 && large_tiles_pay(tiles, K); }
+
 int choose_cfg(const MfmaGemmArgs& a) {
   // split K (at most 256 stacked tokens): a block takes all the tokens it can (the weights are then fetched from HBM
   // once) and as few output features as the low-rank segments allow, so that there are many blocks to stream them
@@ -909,7 +915,7 @@ int choose_cfg(const MfmaGemmArgs& a) {
   const bool forced_ok = a.w_scale == nullptr || a.tile_cfg == 1 || a.tile_cfg == 6 || a.tile_cfg == 11 || a.tile_cfg == 12 || a.tile_cfg == 15;   // int8: fewer instances
   if (forced_ok && known_cfg(a, a.tile_cfg) && cfg_ok(a, a.tile_cfg)) return a.tile_cfg;
   const long t5 = (long)((a.N + 255) / 256) * ((a.M + 255) / 256);
-  if (cfg_ok(a, 6) && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, a.K)))) return 6;
+  if (cfg_ok(a, 6) && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, a.K)) || (a.w_scale != nullptr && int8_large_tiles_pay(t5, a.K)))) return 6;
   // 128 x 128 tiles that fill between one and two blocks per CU leave half the chip with twice the work of the
   // other half; 192 x 128 tiles, one per CU, balance it (N = 768 projections of the 125M-class models)
   const long t1 = (long)((a.N + 127) / 128) * ((a.M + 127) / 128), t11 = (long)((a.N + 191) / 192) * ((a.M + 127) / 128);
@@ -972,9 +978,9 @@ __global__ void __launch_bounds__(1024) ce_combine_kernel(int slots, int M, cons
 
 }  // namespace
 
-bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights) {
+bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights, bool int8_weights) {
   const long t5 = (long)((N + 255) / 256) * ((M + 255) / 256);
-  return t5 >= 512 || (bf16_weights && K % 128 == 0 && N % 8 == 0 && large_tiles_pay(t5, K));
+  return t5 >= 512 || (bf16_weights && K % 128 == 0 && N % 8 == 0 && large_tiles_pay(t5, K)) || (int8_weights && int8_large_tiles_pay(t5, K));
 }
 
 int mfma_gemm_ce_slots(const MfmaGemmArgs& a0) {
@@ -1140,7 +1146,7 @@ hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a) {
   if (a.dual) {
     const long tb = (long)((a.N + 127) / 128) * ((a.M + 255) / 256);
     const bool pipe = gemm_pipe_supported(a);
-    if ((a.tile_cfg == 0 && (tb >= 512 || (pipe && large_tiles_pay(tb, a.K)))) || a.tile_cfg == 6) {               // 2 x 128 x 256
+    if ((a.tile_cfg == 0 && (tb >= 512 || (pipe && large_tiles_pay(tb, a.K)) || (q8 && int8_large_tiles_pay(tb, a.K)))) || a.tile_cfg == 6) {               // 2 x 128 x 256
       if (pipe) return launch_gemm_pipe(st, a);
       return q8 ? launch_cfg<128, 256, 64, 2, 4, true, 0, true>(st, a) : launch_cfg<128, 256, 64, 2, 4, true>(st, a);
     }

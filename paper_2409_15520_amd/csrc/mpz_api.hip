@@ -1043,7 +1043,7 @@ bool use_two_halves(mpz_model* m, int E, int S) {
   const long T = (long)n * E * S;
   if (m->split_k && m->buf.splitk != nullptr && T / 2 <= 256) return false;  // so is the split-K partial-sum buffer
   const int nqkv = c.d_model + 2 * c.n_kv_heads * (c.d_model / c.n_heads);
-  if (T <= INT32_MAX && mfma_gemm_large_tiles((int)T, nqkv, c.d_model, c.weight_quant == MPZ_WEIGHT_QUANT_NONE)) return false;   // large problems fill the chip alone
+  if (T <= INT32_MAX && mfma_gemm_large_tiles((int)T, nqkv, c.d_model, c.weight_quant == MPZ_WEIGHT_QUANT_NONE, c.weight_quant == MPZ_WEIGHT_QUANT_INT8)) return false;   // large problems fill the chip alone
   if (!m->stream2) {
     if (hipStreamCreateWithFlags(&m->stream2, hipStreamNonBlocking) != hipSuccess) { m->stream2 = nullptr; (void)hipGetLastError(); return false; }
     if (hipEventCreateWithFlags(&m->ev_fork, hipEventDisableTiming) != hipSuccess ||
