@@ -888,20 +888,23 @@ bool cfg_ok(const MfmaGemmArgs& a, int cfg) {
 int split_tile_bn(const MfmaGemmArgs& a) { return (a.dual || a.N >= 8192 || a.K >= 8192 || a.w_scale != nullptr || a.w_absmax != nullptr) ? 128 : 64; }
 
 // Do `tiles` 256 x 256 tiles (one per CU at a time) beat the 128-wide ones?  Always from two full rounds of 256 CUs on.  Below
-// that the persistent kernel of gemm_pipe.hip wins once its rounds together are five eighths full (two rounds: from 320 tiles): K = 4096, 128 / 192 /
-// 256 / 384 tiles: 82 / 89 / 96 / 168 us against 72 / 107 / 138 / 208 us for the same product in 128 x 128 tiles; K = 2048, 128 / 160 /
-// 256 / 320 tiles: 47 / 47 / 55 / 89 against 39 / 53 / 74 / 92.  At K = 1024 a second round no longer pays (352 tiles: 56 against
-// 55, 176 tiles: 30 against 34), at K = 768 neither does the first (192 tiles: 28 against 27).
+// that the persistent kernel of gemm_pipe.hip wins once one round is nine sixteenths full, two rounds together five eighths: K = 4096,
+// 128 / 144 / 192 / 256 / 384 tiles: 82 / 80 / 89 / 96 / 168 us against 72 / 90 / 107 / 138 / 208 us for the same product in 128 x 128 tiles;
+// K = 2048, 128 / 144 / 160 / 256 / 320: 47 / 45 / 47 / 55 / 89 against 39 / 49 / 53 / 74 / 92.  At K = 1024 a second round no longer pays
+// (352 tiles: 56 against 55, 176 tiles: 30 against 34), at K = 768 neither does the first (192 tiles: 28 against 27).
 bool large_tiles_pay(long tiles, int K) {
   const long rounds = (tiles + 255) / 256;
-  return tiles >= 512 || (tiles * 8 >= rounds * 256 * 5 && K >= (rounds == 1 ? 1024 : 2048));
+  return tiles >= 512 || (tiles * 16 >= rounds * 256 * (rounds == 1 ? 9 : 10) && K >= (rounds == 1 ? 1024 : 2048));
 }
+// Gate and up together (2 x 128 features per tile), whose small tile fetches half lines: from half a round on (768 x 5632 x 2048, 132
+// tiles: 56 -> 44 us; 1536 x 2816 x 1024, 132: 33 -> 28; 768 x 11008 x 4096, 258: 179 -> 163; 512 x 5632 x 2048, 88: no gain)
+bool large_dual_tiles_pay(long tiles, int K) { return tiles >= 512 || (tiles >= 128 && K >= (tiles <= 256 ? 1024 : 2048)); }
 
 // The same question for int8 weights, whose 256 x 256 tile is the register-staged one of this file: one and two part-filled rounds
 // pay from the same fill on (K = 4096, 128 / 192 / 256 / 288 / 384 tiles: 92 / 104 / 118 / 194 / 205 us against 78 / 116 / 150 / 179 / 222 in
 // 128 x 128 tiles; K = 2048, 128 / 160 / 256 / 384: 53 / 53 / 67 / 115 against 42 / 58 / 81 / 119; gate and up together, K = 4096, 172 / 344
 // tiles: 94 / 191 against 119 / 212).  Measured from K = 2048 on.
-bool int8_large_tiles_pay(long tiles, int K) { return K >= 2048 && large_tiles_pay(tiles, K); }
+bool int8_large_tiles_pay(long tiles, int K) { return tiles >= 512 || (tiles * 8 >= (tiles + 255) / 256 * 256 * 5 && K >= 2048); }
 
 int choose_cfg(const MfmaGemmArgs& a) {
   // split K (at most 256 stacked tokens): a block takes all the tokens it can (the weights are then fetched from HBM
@@ -917,21 +920,26 @@ int choose_cfg(const MfmaGemmArgs& a) {
   const long t5 = (long)((a.N + 255) / 256) * ((a.M + 255) / 256);
   if (cfg_ok(a, 6) && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, a.K)) || (a.w_scale != nullptr && int8_large_tiles_pay(t5, a.K)))) return 6;
   // 128 x 128 tiles that fill between one and two blocks per CU leave half the chip with twice the work of the
-  // other half; 192 x 128 tiles, one per CU, balance it (N = 768 projections of the 125M-class models)
+  // other half; 192 x 128 tiles, one per CU, balance it (N = 768 projections of the 125M-class models; 2048 x 2560 with K = 2048 / 2560 /
+  // 6912: 33 / 41 / 97 -> 29 / 35 / 75 us, the last column of tiles a third used)
   const long t1 = (long)((a.N + 127) / 128) * ((a.M + 127) / 128), t11 = (long)((a.N + 191) / 192) * ((a.M + 127) / 128);
-  if (t1 > 256 && t1 < 512 && t11 <= 256 && a.N % 192 == 0 && a.K >= 1536 && a.rope_cos == nullptr && cfg_ok(a, 11)) return 11;
+  const bool plain = a.rope_cos == nullptr && a.w_scale == nullptr && a.ce_max == nullptr;
+  if (t1 > 256 && t1 < 512 && t11 <= 256 && a.K >= 1536 && a.rope_cos == nullptr && (a.N % 192 == 0 || plain) && cfg_ok(a, 11)) return 11;
   // heads of 128 columns rotated in the epilogue need a wave tile that holds one: four waves of 128 x 32 (1024 tokens of the
   // 7B-shaped int8 model: the rotary kernel after the GEMM, 33 us, goes)
   if (a.rope_cos != nullptr && a.rope_dh == 128 && t1 >= 256 && cfg_ok(a, 15)) return 15;
   // fewer 128 x 128 tiles than CUs (single-copy and single-query passes): 128 x 64 tiles, twice the blocks, and
   // 64 x 64 tiles if that is still less than one block per CU (one pass per copy on the 125M-shaped workload:
-  // 8.2 -> 7.4 ms per step; 2 x 64 tokens through the 7B-shaped model: 75 -> 67 ms)
+  // 8.2 -> 7.4 ms per step; 2 x 64 tokens through the 7B-shaped model: 75 -> 67 ms), unless K is long (96 and 120 tiles, K = 8192 and 6912:
+  // 51 and 44 us against 44 and 41 in 128 x 64).  From 144 tiles on the whole ones are ahead again, a CU each instead of two halves on some
+  // (768 x 4096 x 11008, 192 tiles: 101 -> 81 us; 1024 x 2560 x 2048, 160: 22 -> 19; 3072 x 768 x 3072, 144: 31 -> 25).
   // 32 x 32 tiles while three blocks per CU hold them all (768 x 768 x 3072, 576 tiles: 14.9 us against 16.9 in 64 x 64 tiles;
-  // 384 x 2304 x 768, 864 tiles: 7.7 against 6.6)
+  // 384 x 2304 x 768, 864 tiles: 7.7 against 6.6), two per CU for wide outputs (288 x 2048 x 2048, 576 tiles: 12.3 against 9.9; 288 x 2560 x
+  // 6912, 720: 35 against 32)
   const long t14 = (long)((a.N + 31) / 32) * ((a.M + 31) / 32);
-  if (t14 <= 768 && cfg_ok(a, 14)) return 14;
-  if (t1 < 256 && a.rope_cos == nullptr && a.w_scale == nullptr && a.ce_max == nullptr && cfg_ok(a, 9))
-    return (2 * t1 < 256 && cfg_ok(a, 10)) ? 10 : 9;
+  if (t14 <= (a.N >= 2048 ? 512 : 768) && cfg_ok(a, 14)) return 14;
+  if (t1 < 144 && plain && cfg_ok(a, 9))
+    return ((t1 < 96 || (t1 < 128 && a.K < 4096)) && cfg_ok(a, 10)) ? 10 : 9;
   // otherwise the 128 x 128 tile with 8 waves of 64 x 32 (16 waves per CU): a block of a short-K problem lives for
   // a dozen K-tiles, and what hides its first loads and last stores is other waves (10 % over 4 waves of 64 x 64
   // at K = 768, equal at long K)
@@ -1146,7 +1154,7 @@ hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a) {
   if (a.dual) {
     const long tb = (long)((a.N + 127) / 128) * ((a.M + 255) / 256);
     const bool pipe = gemm_pipe_supported(a);
-    if ((a.tile_cfg == 0 && (tb >= 512 || (pipe && large_tiles_pay(tb, a.K)) || (q8 && int8_large_tiles_pay(tb, a.K)))) || a.tile_cfg == 6) {               // 2 x 128 x 256
+    if ((a.tile_cfg == 0 && (tb >= 512 || (pipe && large_dual_tiles_pay(tb, a.K)) || (q8 && int8_large_tiles_pay(tb, a.K)))) || a.tile_cfg == 6) {               // 2 x 128 x 256
       if (pipe) return launch_gemm_pipe(st, a);
       return q8 ? launch_cfg<128, 256, 64, 2, 4, true, 0, true>(st, a) : launch_cfg<128, 256, 64, 2, 4, true>(st, a);
     }

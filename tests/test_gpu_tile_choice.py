@@ -1,0 +1,28 @@
+"""The tile that a mid-size bf16 pass chooses: the bits of the forced 128 x 128 tiles where 192-wide tiles end in a part column, where gate and
+up take the 256-wide tile from half a round, where whole 128 x 128 tiles replace halves, and where 64 x 64 ones replace the ring."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("heads,ffn,q,E,S,rank,targets", [(40, 2816, 4, 2, 128, 16, "qv"),       # 192-wide tiles, 64 of 192 features in the last
+                                                          (16, 5632, 4, 1, 96, 16, "qvo"),       # gate and up: 132 tiles
+                                                          (32, 5632, 5, 1, 109, 8, "qv"),        # 144 whole tiles, the last rows a part
+                                                          (32, 4096, 3, 1, 48, 16, "qkvo")])     # 576 tiles of 32 x 32: 64 x 64 ones
+def test_block_has_the_bits_of_whole_tiles(heads, ffn, q, E, S, rank, targets):
+    import torch
+    import workloads as W
+    import paper_2409_15520_amd as M
+    w = W.Workload(name="mid", n_layers=1, d_model=64 * heads, n_heads=heads, n_kv_heads=heads // 2, d_ffn=ffn, vocab=600, max_seq=256,
+                   act="swiglu", norm="rmsnorm", pos="rope", has_bias=False, tie_embeddings=False, dtype="bf16", lora_rank=rank,
+                   lora_targets=tuple(targets), loss_mode="next_token_all_pos", q=q, E=E, S=S, steps=1, eps=1e-2)
+    frozen = W.make_frozen_weights(w, 1)
+    masters = W.make_lora_masters(w, 2, b_std=0.05)
+    tokens = torch.from_numpy(W.make_tokens(w, 3)).cuda()
+    hs = []
+    for cfg in (0, 12, 1):
+        m = M.ZoModel(w, frozen, masters)
+        M.mpz_debug_set_tile_config(m.handle, cfg)
+        m.regen_noise(5, 0)
+        hs.append(m.run_layers(m.embed(tokens), 0, 1, E, S).clone())
+    assert torch.equal(hs[0], hs[1]) and torch.equal(hs[0], hs[2])
