@@ -368,9 +368,10 @@ mpz_status mpz_debug_dequant_nf4(const void* codes, const float* absmax, void* o
 mpz_status mpz_debug_set_kernel_path(mpz_model* m, int32_t simple_only);
 
 /* Test hook: allow (default) or forbid the two-halves schedule of mpz_forward_perturbed: for small models (every
- * GEMM on the 128-wide tiles, label-subset loss) the pass is issued as two halves of q copies each on the caller's
- * stream and on an internal second stream of the same priority, forked from and joined to the caller's stream by
- * events, so that the halves' kernels overlap.  Losses are bit-identical either way. */
+ * GEMM on the 128-wide tiles, label-subset loss, d_model < 2048) and some thousand stacked tokens the pass is issued
+ * as two halves of q copies each on the caller's stream and on an internal second stream of the same priority, forked
+ * from and joined to the caller's stream by events, so that the halves' kernels overlap.  Losses are bit-identical
+ * either way. */
 mpz_status mpz_debug_set_two_halves(mpz_model* m, int32_t enable);
 /* Number of streams the last mpz_forward_perturbed was issued on: 2 with the two-halves schedule, 1 without, 0
  * before the first pass (or for a NULL handle). */

@@ -1041,11 +1041,11 @@ bool use_two_halves(mpz_model* m, int E, int S) {
   if (c.weight_quant == MPZ_WEIGHT_QUANT_NF4) return false;                  // so is the dequantised-weight buffer
   if (((n / 2) * E * S) % 32) return false;
   const long T = (long)n * E * S;
-  if (m->split_k && m->buf.splitk != nullptr && T / 2 <= 256) return false;  // so is the split-K partial-sum buffer
   // Twice the launches, each of half the work: that pays once a launch is long enough to hide the next one's, and while blocks are short
   // (12 layers, one pass / two halves, us; d = 768, 3072 / 5120 / 6144 / 8192 tokens: 1270 / 1726 / 2101 / 2567 against 1358 / 1753 / 1998 /
   // 2334; d = 1024, 2688 / 3072 / 4224: 1603 / 1847 / 2300 against 1755 / 1769 / 2036; d = 1536, 1536 / 3072: 2335 / 3072 against
-  // 2467 / 2984; d = 2048, 2560 / 3072: 3414 / 4171 against 3777 / 4327)
+  // 2467 / 2984; d = 2048, 2560 / 3072: 3414 / 4171 against 3777 / 4327).  A half has more than the 256 tokens that split K, whose
+  // partial-sum buffer the halves would share.
   if (c.d_model >= 2048 || T < 3072 || (double)T * c.d_model * c.d_model < 3.0 * (1 << 30)) return false;
   const int nqkv = c.d_model + 2 * c.n_kv_heads * (c.d_model / c.n_heads);
   if (T <= INT32_MAX && mfma_gemm_large_tiles((int)T, nqkv, c.d_model, c.weight_quant == MPZ_WEIGHT_QUANT_NONE, c.weight_quant == MPZ_WEIGHT_QUANT_INT8)) return false;   // large problems fill the chip alone

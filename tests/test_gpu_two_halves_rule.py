@@ -1,0 +1,29 @@
+"""Which passes run as two halves on two streams: the tokens and widths on either side of the rule, with the bits of the pass on one stream."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("heads,q,E,S,streams", [(16, 8, 2, 96, 2),      # 1024 wide, 3072 tokens: the first that does
+                                                 (16, 8, 1, 188, 1),     # 3008 tokens
+                                                 (12, 8, 2, 170, 1),     # 768 wide, 5440 tokens: below 3 x 2^30
+                                                 (12, 8, 2, 172, 2),     # 5504
+                                                 (16, 9, 2, 128, 2),     # 4608 tokens: 144 tiles of 256 x 256 for Q|K|V
+                                                 (16, 10, 2, 128, 1),    # 160
+                                                 (32, 8, 2, 96, 1)])     # 2048 wide
+def test_streams_and_bits(heads, q, E, S, streams):
+    import torch
+    import workloads as W
+    import paper_2409_15520_amd as M
+    w = W.Workload(name="halves", n_layers=1, d_model=64 * heads, n_heads=heads, n_kv_heads=heads if heads == 12 else heads // 2,
+                   d_ffn=1024, vocab=600, max_seq=256, act="swiglu", norm="rmsnorm", pos="rope", has_bias=False, tie_embeddings=False,
+                   dtype="bf16", lora_rank=8, lora_targets=("q", "v"), loss_mode="last_pos_label_subset", q=q, E=E, S=S, steps=1, eps=1e-2)
+    m = M.ZoModel(w, W.make_frozen_weights(w, 1), W.make_lora_masters(w, 2, b_std=0.05))
+    tokens, labels = torch.from_numpy(W.make_tokens(w, 3)).cuda(), torch.from_numpy(W.make_labels(w, 3)).cuda()
+    m.regen_noise(5, 0)
+    got = m.forward_perturbed(tokens, labels).clone()
+    assert M.mpz_debug_last_pass_streams(m.handle) == streams
+    M.mpz_debug_set_two_halves(m.handle, False)
+    one = m.forward_perturbed(tokens, labels).clone()
+    assert M.mpz_debug_last_pass_streams(m.handle) == 1
+    assert torch.equal(got.view(torch.int32), one.view(torch.int32))
