@@ -202,7 +202,8 @@ __global__ void __launch_bounds__(256) linear_ordered_kernel(LinearArgs a, int v
 // what the contraction sees one K-tile ahead, in place, a quarter by each wave.  Bound by the chain: K / 4 dependent instructions
 // of 32 clocks, and vector instructions do not run beside it (1848 rows, K = 2048: 29 -> 21 us; a wave
 // per 16 rows with both operands from memory, converting the factor for itself, waited for its requests).  Lane l holds x[l % 16][k = l / 16] and
-// A[k = l / 16][column l % 16] of every four k and, of the result, D[4 (l / 16) + r][l % 16], r = 0..3.
+// A[k = l / 16][column l % 16] of every four k and, of the result, D[4 (l / 16) + r][l % 16], r = 0..3.  K is a multiple of 32: of a
+// last K-tile that is half outside, the chain takes the half inside (what lies behind it in the stage is never multiplied).
 template <int BK, int ST>
 __global__ void __launch_bounds__(256) lora_down_ordered_kernel(LoraDownArgs a, int tiles_per_copy, int col_tiles) {
   constexpr int FX = BK / 32, FA = BK / 64, PER = FX + FA;                     // fetches of a wave per stage: of x, of the factor
@@ -249,7 +250,8 @@ __global__ void __launch_bounds__(256) lora_down_ordered_kernel(LoraDownArgs a, 
   const uint32_t sel = 0x00000c0cu | (uint32_t)(2 * lq) << 16 | (uint32_t)(2 * lq + 1) << 24;    // element lq of four bf16
   const uint32_t baseX = (uint32_t)(wave * 16 + l16) * (BK * 2), sw = swizzle(l16) * 16u, baseA = XBYTES + (uint32_t)(lq * 16 + l16) * 4u;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  const int nk = a.K / BK;
+  const int nk = (a.K + BK - 1) / BK;
+  const bool half = BK == 64 && a.K % BK != 0;             // the last K-tile has 32 k
 #pragma unroll
   for (int t = 0; t < ST - 1; ++t)
     if (t < nk) fetch(t, t);
@@ -286,7 +288,10 @@ __global__ void __launch_bounds__(256) lora_down_ordered_kernel(LoraDownArgs a, 
         for (int e = 0; e < 2; ++e) fx[2 * c + e] = __uint_as_float(__builtin_amdgcn_perm(x[h & 1][c][2 * e + 1], x[h & 1][c][2 * e], sel));
       __builtin_amdgcn_sched_barrier(0);                   // (the chain without vector instructions between its links)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fx[i], f[h & 1][i], acc, 0, 0, 0);
+      for (int i = 0; i < 8; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fx[i], f[h & 1][i], acc, 0, 0, 0);
+      if (half && kt + 1 == nk) break;                     // (uniform)
+#pragma unroll
+      for (int i = 8; i < 16; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fx[i], f[h & 1][i], acc, 0, 0, 0);
     }
   }
   const int jr = c0 + l16, R = a.n_targets * a.rank;
@@ -322,14 +327,21 @@ bool launch_linear_ordered(hipStream_t st, const LinearArgs& a) {
   return true;
 }
 
-bool launch_lora_down_ordered(hipStream_t st, const LoraDownArgs& a) {
-  if (a.dtype != MPZ_DTYPE_BF16 || a.K % 64 || a.K < 64 || a.rank % 4 || a.copy_stride % 4 || ((uintptr_t)a.x & 15) || a.T % a.rows_per_copy) return false;
-  if ((size_t)a.K * a.rank * 4 >= (size_t)1 << 31 || (size_t)a.K * 128 >= (size_t)1 << 31) return false;
+// whole pieces of 32 k (bf16 models of any such width take their bottleneck here, 32 modulo 64 among them: widths of 96 / 352 / 1312
+// with the shape-agnostic kernel, a whole block of 1848 tokens took 4 - 10 / 14 - 24 / 8 - 15 % longer)
+int64_t lora_down_ordered_blocks(const LoraDownArgs& a) {
+  if (a.dtype != MPZ_DTYPE_BF16 || a.K % 32 || a.K < 32 || a.rank % 4 || a.copy_stride % 4 || ((uintptr_t)a.x & 15) || a.T % a.rows_per_copy) return 0;
+  if ((size_t)a.K * a.rank * 4 >= (size_t)1 << 31 || (size_t)a.K * 128 >= (size_t)1 << 31) return 0;
   for (int t = 0; t < a.n_targets; ++t)
-    if ((uintptr_t)a.Ac[t] & 15) return false;
+    if ((uintptr_t)a.Ac[t] & 15) return 0;
+  const int64_t blocks = (int64_t)(a.T / a.rows_per_copy) * ((a.rows_per_copy + 63) / 64) * ((a.rank + 15) / 16) * a.n_targets;
+  return blocks * 256 > (int64_t)UINT32_MAX ? 0 : blocks;
+}
+
+bool launch_lora_down_ordered(hipStream_t st, const LoraDownArgs& a) {
+  const int64_t blocks = lora_down_ordered_blocks(a);
+  if (blocks == 0) return false;
   const int tiles = (a.rows_per_copy + 63) / 64, cols = (a.rank + 15) / 16;
-  const int64_t blocks = (int64_t)(a.T / a.rows_per_copy) * tiles * cols * a.n_targets;
-  if (blocks * 256 > (int64_t)UINT32_MAX) return false;
   // few blocks: twice the bytes in flight and half the barriers (a block has the CU to itself)
   if (blocks <= 256 && a.K % 128 == 0) launch_down<128, 6>(st, a, (unsigned)blocks, tiles, cols);
   else launch_down<64, 6>(st, a, (unsigned)blocks, tiles, cols);

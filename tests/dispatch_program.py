@@ -1,0 +1,55 @@
+"""The library's own dispatch rules, asked from a small host program (no GPU): ask() takes lines of a query's name and its numbers and
+returns one integer per line."""
+import functools
+import os
+import subprocess
+import tempfile
+
+import paper_2409_15520_amd as M
+from paper_2409_15520_amd import build
+
+PROGRAM = r"""
+#include "common.h"
+#include "../../include/mpz.h"
+#include <cstdio>
+#include <cstring>
+using namespace mpz;
+int main() {
+  char what[64];
+  while (scanf("%63s", what) == 1) {
+    if (!strcmp(what, "lora_down_ordered")) {            // K, rank, targets, rows per copy, copies
+      LoraDownArgs a{};
+      int copies;
+      if (scanf("%d %d %d %d %d", &a.K, &a.rank, &a.n_targets, &a.rows_per_copy, &copies) != 5) return 1;
+      a.dtype = MPZ_DTYPE_BF16; a.T = copies * a.rows_per_copy; a.x = (const void*)4096; a.copy_stride = 16LL * a.K * a.rank;
+      for (int t = 0; t < a.n_targets; ++t) a.Ac[t] = (const float*)4096 + 2LL * t * a.K * a.rank;
+      printf("%lld\n", (long long)lora_down_ordered_blocks(a));
+    } else return 1;
+  }
+  return 0;
+}
+"""
+
+
+_DIR = tempfile.TemporaryDirectory()
+
+
+@functools.lru_cache(maxsize=None)
+def _program():
+    M.load_library()
+    src, obj, exe = (os.path.join(_DIR.name, n) for n in ("rules.hip", "rules.o", "rules"))
+    with open(src, "w") as f:
+        f.write(PROGRAM)
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    rocm = os.path.join(os.path.dirname(os.path.realpath(hipcc)), "..", "lib")
+    subprocess.run([hipcc, "--offload-host-only", "-O0", "-fPIC", "-std=c++17", "-I", build.CSRC, "-c", src, "-o", obj], check=True,
+                   capture_output=True)
+    subprocess.run(["g++", obj, "-o", exe, build.LIB, "-L", rocm, "-lamdhip64", f"-Wl,-rpath,{build.PKG}", f"-Wl,-rpath,{rocm}"],
+                   check=True, capture_output=True)
+    return exe
+
+
+def ask(lines):
+    out = subprocess.run([_program()], input="\n".join(lines) + "\n", check=True, capture_output=True, text=True).stdout.split()
+    assert len(out) == len(lines)
+    return [int(v) for v in out]

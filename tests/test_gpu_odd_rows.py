@@ -51,6 +51,13 @@ def test_many_rows_have_the_bits_of_the_shape_agnostic_kernels(d, heads, q, E, S
     test_projection_has_the_bits_of_the_shape_agnostic_kernels(d, heads, 1, rank, q, E, S, "qkv")
 
 
+# widths of 32 modulo 64: a bottleneck whose last K-tile is half outside (one K-tile and many), its last rows those of the operand
+@pytest.mark.parametrize("d,heads,kv,rank,q,E,S,targets", [(32, 2, 1, 4, 2, 1, 33, "qkv"), (96, 4, 4, 8, 4, 3, 77, "qv"), (96, 4, 2, 20, 2, 1, 33, "qkv"),
+                                                           (288, 4, 4, 16, 2, 1, 5, "qv"), (352, 8, 2, 8, 2, 3, 45, "qkv"), (1312, 8, 8, 16, 2, 1, 99, "q")])
+def test_widths_of_half_a_k_tile_have_the_bits_of_the_shape_agnostic_kernels(d, heads, kv, rank, q, E, S, targets):
+    test_projection_has_the_bits_of_the_shape_agnostic_kernels(d, heads, kv, rank, q, E, S, targets)
+
+
 # a block whose every other part takes the same kernels either way (d = 320, heads of 32) and whose feed-forward adds exact
 # zeros: norm, q/k/v with rotary staging or not, attention, output projection with residual; 4-bit weights once per pass
 @pytest.mark.parametrize("llama,rank,q,E,S,quant", [(True, 16, 4, 3, 77, "none"), (False, 8, 4, 3, 77, "none"), (True, 32, 2, 3, 33, "none"),
