@@ -197,27 +197,27 @@ __global__ void __launch_bounds__(256) linear_ordered_kernel(LinearArgs a, int v
   }
 }
 
-// LoRA bottleneck t = bf16(scale * x A_c): a block of four waves per 64 rows of one copy and 16 columns of one target, a wave per 16
-// rows; K-tiles of 64 (64 rows of x, 64 x 16 of the factor) go straight into a ring of LDS stages.  The factor's values become
+// LoRA bottleneck t = bf16(scale * x A_c): a block of four waves per 64 rows of one copy and 16 columns, a wave per 16 rows.  The columns
+// are those of all targets side by side, so ranks below 16 share a tile (a lane fetches four columns, which are one target's); K-tiles of 64 (64 rows of x, 64 x 16 of the factor) go straight into a ring of LDS stages.  The factor's values become
 // what the contraction sees one K-tile ahead, in place, a quarter by each wave.  Bound by the chain: K / 4 dependent instructions
 // of 32 clocks, and vector instructions do not run beside it (1848 rows, K = 2048: 29 -> 21 us; a wave
 // per 16 rows with both operands from memory, converting the factor for itself, waited for its requests).  Lane l holds x[l % 16][k = l / 16] and
 // A[k = l / 16][column l % 16] of every four k and, of the result, D[4 (l / 16) + r][l % 16], r = 0..3.  K is a multiple of 32: of a
 // last K-tile that is half outside, the chain takes the half inside (what lies behind it in the stage is never multiplied).
+struct DownFactors { const float* first; uint32_t bytes, off[4]; };           // the targets' factors of a copy as one buffer
 template <int BK, int ST>
-__global__ void __launch_bounds__(256) lora_down_ordered_kernel(LoraDownArgs a, int tiles_per_copy, int col_tiles) {
+__global__ void __launch_bounds__(256) lora_down_ordered_kernel(LoraDownArgs a, DownFactors fa, int tiles_per_copy, int col_tiles) {
   constexpr int FX = BK / 32, FA = BK / 64, PER = FX + FA;                     // fetches of a wave per stage: of x, of the factor
   constexpr uint32_t CPR = BK / 8, RPF = 64 / CPR;                             // 16-byte chunks of a row, rows of a fetch
   constexpr uint32_t XBYTES = 64 * BK * 2, STAGE = XBYTES + BK * 64;
   extern __shared__ __align__(16) unsigned char lora_smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, lq = lane >> 4;
-  const int cols = a.n_targets * col_tiles, col_tile = blockIdx.x % cols, rest = blockIdx.x / cols;
-  const int target = col_tile / col_tiles, c0 = col_tile % col_tiles * 16;
+  const int c0 = blockIdx.x % col_tiles * 16, rest = blockIdx.x / col_tiles, R = a.n_targets * a.rank;
   const int copy = rest / tiles_per_copy, r0 = rest % tiles_per_copy * 64;     // first row inside the copy
   const size_t row_b = (size_t)a.K * 2;
   const int rows = a.rows_per_copy - r0 < 64 ? a.rows_per_copy - r0 : 64;      // rows past the copy read zeros and are not stored
   const i32x4 rsrcX = buffer_of((const char*)a.x + ((size_t)copy * a.rows_per_copy + r0) * row_b, (size_t)rows * row_b);
-  const i32x4 rsrcA = buffer_of(a.Ac[target] + (int64_t)copy * a.copy_stride + c0, ((size_t)a.K * a.rank - c0) * 4);
+  const i32x4 rsrcA = buffer_of(fa.first + (int64_t)copy * a.copy_stride, fa.bytes);
   const uint32_t row_a = (uint32_t)a.rank * 4u;
   auto swizzle = [](uint32_t row) { return BK == 64 ? row >> 1 & 7u : row & 15u; };          // chunk c of a row lies at c ^ this
   uint32_t voffX[FX];
@@ -226,7 +226,11 @@ __global__ void __launch_bounds__(256) lora_down_ordered_kernel(LoraDownArgs a, 
     const uint32_t row = (uint32_t)(wave * FX + t) * RPF + lane / CPR;
     voffX[t] = row * (uint32_t)row_b + ((lane % CPR) ^ swizzle(row)) * 16u;
   }
-  const uint32_t voffA = (uint32_t)(wave * 16 + (lane >> 2)) * row_a + (uint32_t)(lane & 3) * 16u;
+  const int j = c0 + (lane & 3) * 4;                       // the first of this lane's four columns; past the last one: aimed outside (zeros)
+  uint32_t voffA = 0x80000000u;
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    if (j >= t * a.rank && j < (t + 1) * a.rank && j < R) voffA = fa.off[t] + (uint32_t)(wave * 16 + (lane >> 2)) * row_a + (uint32_t)(j - t * a.rank) * 4u;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lora_smem;
   auto fetch = [&](int kt, int st) {
     const uint32_t base = lds0 + (uint32_t)st * STAGE;
@@ -294,21 +298,20 @@ __global__ void __launch_bounds__(256) lora_down_ordered_kernel(LoraDownArgs a, 
       for (int i = 8; i < 16; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fx[i], f[h & 1][i], acc, 0, 0, 0);
     }
   }
-  const int jr = c0 + l16, R = a.n_targets * a.rank;
-  if (jr >= a.rank) return;
+  if (c0 + l16 >= R) return;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int rc = r0 + wave * 16 + 4 * lq + r;
-    if (rc < a.rows_per_copy) ((bf16_t*)a.t)[(copy * (int64_t)a.rows_per_copy + rc) * R + target * a.rank + jr] = f32_to_bf16(acc[r] * a.scale);
+    if (rc < a.rows_per_copy) ((bf16_t*)a.t)[(copy * (int64_t)a.rows_per_copy + rc) * R + c0 + l16] = f32_to_bf16(acc[r] * a.scale);
   }
 }
 
 template <int BK, int ST>
-void launch_down(hipStream_t st, const LoraDownArgs& a, unsigned blocks, int tiles, int cols) {
+void launch_down(hipStream_t st, const LoraDownArgs& a, const DownFactors& fa, unsigned blocks, int tiles, int cols) {
   constexpr int lds = ST * (64 * BK * 2 + BK * 64);
   static const hipError_t attr_status = hipFuncSetAttribute((const void*)lora_down_ordered_kernel<BK, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   (void)attr_status;                                       // (a refusal shows as the launch's error)
-  lora_down_ordered_kernel<BK, ST><<<blocks, 256, lds, st>>>(a, tiles, cols);
+  lora_down_ordered_kernel<BK, ST><<<blocks, 256, lds, st>>>(a, fa, tiles, cols);
 }
 
 }  // namespace
@@ -331,20 +334,32 @@ bool launch_linear_ordered(hipStream_t st, const LinearArgs& a) {
 // with the shape-agnostic kernel, a whole block of 1848 tokens took 4 - 10 / 14 - 24 / 8 - 15 % longer)
 int64_t lora_down_ordered_blocks(const LoraDownArgs& a) {
   if (a.dtype != MPZ_DTYPE_BF16 || a.K % 32 || a.K < 32 || a.rank % 4 || a.copy_stride % 4 || ((uintptr_t)a.x & 15) || a.T % a.rows_per_copy) return 0;
-  if ((size_t)a.K * a.rank * 4 >= (size_t)1 << 31 || (size_t)a.K * 128 >= (size_t)1 << 31) return 0;
-  for (int t = 0; t < a.n_targets; ++t)
-    if ((uintptr_t)a.Ac[t] & 15) return 0;
-  const int64_t blocks = (int64_t)(a.T / a.rows_per_copy) * ((a.rows_per_copy + 63) / 64) * ((a.rank + 15) / 16) * a.n_targets;
+  if ((size_t)a.K * 128 >= (size_t)1 << 31) return 0;
+  uintptr_t lo = (uintptr_t)a.Ac[0], hi = lo;
+  for (int t = 0; t < a.n_targets; ++t) {
+    const uintptr_t p = (uintptr_t)a.Ac[t];
+    if (p & 15) return 0;
+    lo = p < lo ? p : lo; hi = p > hi ? p : hi;
+  }
+  if (hi - lo + (size_t)a.K * a.rank * 4 >= (size_t)1 << 31) return 0;       // one buffer (a layer's factors lie together)
+  const int64_t blocks = (int64_t)(a.T / a.rows_per_copy) * ((a.rows_per_copy + 63) / 64) * ((a.n_targets * a.rank + 15) / 16);
   return blocks * 256 > (int64_t)UINT32_MAX ? 0 : blocks;
 }
 
 bool launch_lora_down_ordered(hipStream_t st, const LoraDownArgs& a) {
   const int64_t blocks = lora_down_ordered_blocks(a);
   if (blocks == 0) return false;
-  const int tiles = (a.rows_per_copy + 63) / 64, cols = (a.rank + 15) / 16;
+  const int tiles = (a.rows_per_copy + 63) / 64, cols = (a.n_targets * a.rank + 15) / 16;
+  DownFactors fa{a.Ac[0], 0, {0, 0, 0, 0}};
+  for (int t = 1; t < a.n_targets; ++t) fa.first = a.Ac[t] < fa.first ? a.Ac[t] : fa.first;
+  for (int t = 0; t < a.n_targets; ++t) {
+    fa.off[t] = (uint32_t)((uintptr_t)a.Ac[t] - (uintptr_t)fa.first);
+    const uint32_t end = fa.off[t] + (uint32_t)a.K * (uint32_t)a.rank * 4u;
+    fa.bytes = end > fa.bytes ? end : fa.bytes;
+  }
   // few blocks: twice the bytes in flight and half the barriers (a block has the CU to itself)
-  if (blocks <= 256 && a.K % 128 == 0) launch_down<128, 6>(st, a, (unsigned)blocks, tiles, cols);
-  else launch_down<64, 6>(st, a, (unsigned)blocks, tiles, cols);
+  if (blocks <= 256 && a.K % 128 == 0) launch_down<128, 6>(st, a, fa, (unsigned)blocks, tiles, cols);
+  else launch_down<64, 6>(st, a, fa, (unsigned)blocks, tiles, cols);
   return true;
 }
 

@@ -58,6 +58,13 @@ def test_widths_of_half_a_k_tile_have_the_bits_of_the_shape_agnostic_kernels(d, 
     test_projection_has_the_bits_of_the_shape_agnostic_kernels(d, heads, kv, rank, q, E, S, targets)
 
 
+# columns of several targets in one tile of 16: all in one, a target that ends inside one, one that spans two, a last tile with 4 and 12
+# columns; outputs of the same columns as one target at a time
+@pytest.mark.parametrize("rank,targets", [(4, "qv"), (4, "qkv"), (8, "qkv"), (12, "qk"), (12, "qkv"), (20, "kv"), (28, "qkv")])
+def test_targets_in_one_tile_have_the_bits_of_the_shape_agnostic_kernels(rank, targets):
+    test_projection_has_the_bits_of_the_shape_agnostic_kernels(288, 4, 2, rank, 2, 3, 45, targets)
+
+
 # a block whose every other part takes the same kernels either way (d = 320, heads of 32) and whose feed-forward adds exact
 # zeros: norm, q/k/v with rotary staging or not, attention, output projection with residual; 4-bit weights once per pass
 @pytest.mark.parametrize("llama,rank,q,E,S,quant", [(True, 16, 4, 3, 77, "none"), (False, 8, 4, 3, 77, "none"), (True, 32, 2, 3, 33, "none"),

@@ -8,3 +8,9 @@ from dispatch_program import ask
 def test_widths(k, taken):
     """Whole pieces of 32 columns, 32 modulo 64 among them."""
     assert (ask([f"lora_down_ordered {k} 8 2 33 4"])[0] > 0) == taken
+
+
+@pytest.mark.parametrize("rank,targets", [(4, 1), (4, 2), (4, 3), (8, 2), (8, 3), (12, 3), (16, 1), (16, 3), (20, 2), (24, 3), (64, 3)])
+def test_targets_share_tiles_of_columns(rank, targets):
+    """16 columns a block, of all targets side by side: 4 copies of 77 rows are two tiles of rows each."""
+    assert ask([f"lora_down_ordered 768 {rank} {targets} 77 4"])[0] == 4 * 2 * ((rank * targets + 15) // 16)
