@@ -718,11 +718,15 @@ __global__ void __launch_bounds__(256, 1) lora_down_ring_kernel(MfmaLoraDownArgs
 }
 
 template <int RANK>
-void launch_lora_down_ring(hipStream_t st, const MfmaLoraDownArgs& a) {
+bool launch_lora_down_ring(hipStream_t st, const MfmaLoraDownArgs& a) {
   constexpr int lds = (RANK == 32 ? 3 : RANK == 16 ? 4 : 5) * (32 * 512 + RANK * 1024) + 3 * 16 * 64 * 4;
   static const hipError_t attr_status = hipFuncSetAttribute((const void*)lora_down_ring_kernel<RANK>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  (void)attr_status;                                       // (a refusal shows as the launch's error)
+  if (attr_status != hipSuccess) {                         // (the caller takes lora_down_mfma_kernel: same bits)
+    (void)hipGetLastError();
+    return false;
+  }
   lora_down_ring_kernel<RANK><<<dim3(a.T / 32, a.n_targets), 256, lds, st>>>(a);
+  return true;
 }
 
 // ---- pack the perturbed fp32 factors into the bf16 hi/lo operand layouts ---------------------------------
@@ -1231,10 +1235,7 @@ void launch_lora_down_mfma(hipStream_t st, const MfmaLoraDownArgs& a) {
   // at most a block per CU with one target each, and enough K to fetch: 32 tokens and one target per block (rows that begin on 16
   // bytes: they go straight into LDS in such pieces)
   if ((int)grid.x * a.n_targets <= 256 && a.K >= 1024 && ((uintptr_t)a.x & 15) == 0 && (a.rank == 8 || a.rank == 16 || a.rank == 32)) {
-    if (a.rank == 8) launch_lora_down_ring<8>(st, a);
-    else if (a.rank == 16) launch_lora_down_ring<16>(st, a);
-    else launch_lora_down_ring<32>(st, a);
-    return;
+    if (a.rank == 8 ? launch_lora_down_ring<8>(st, a) : a.rank == 16 ? launch_lora_down_ring<16>(st, a) : launch_lora_down_ring<32>(st, a)) return;
   }
   if (R <= 32) lora_down_mfma_kernel<1><<<grid, 256, 0, st>>>(a);
   else lora_down_mfma_kernel<2><<<grid, 256, 0, st>>>(a);

@@ -307,11 +307,15 @@ __global__ void __launch_bounds__(256) lora_down_ordered_kernel(LoraDownArgs a, 
 }
 
 template <int BK, int ST>
-void launch_down(hipStream_t st, const LoraDownArgs& a, const DownFactors& fa, unsigned blocks, int tiles, int cols) {
+bool launch_down(hipStream_t st, const LoraDownArgs& a, const DownFactors& fa, unsigned blocks, int tiles, int cols) {
   constexpr int lds = ST * (64 * BK * 2 + BK * 64);
   static const hipError_t attr_status = hipFuncSetAttribute((const void*)lora_down_ordered_kernel<BK, ST>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  (void)attr_status;                                       // (a refusal shows as the launch's error)
+  if (attr_status != hipSuccess) {                         // (the caller takes the shape-agnostic kernel: same bits)
+    (void)hipGetLastError();
+    return false;
+  }
   lora_down_ordered_kernel<BK, ST><<<blocks, 256, lds, st>>>(a, fa, tiles, cols);
+  return true;
 }
 
 }  // namespace
@@ -358,9 +362,8 @@ bool launch_lora_down_ordered(hipStream_t st, const LoraDownArgs& a) {
     fa.bytes = end > fa.bytes ? end : fa.bytes;
   }
   // few blocks: twice the bytes in flight and half the barriers (a block has the CU to itself)
-  if (blocks <= 256 && a.K % 128 == 0) launch_down<128, 6>(st, a, fa, (unsigned)blocks, tiles, cols);
-  else launch_down<64, 6>(st, a, fa, (unsigned)blocks, tiles, cols);
-  return true;
+  if (blocks <= 256 && a.K % 128 == 0) return launch_down<128, 6>(st, a, fa, (unsigned)blocks, tiles, cols);
+  return launch_down<64, 6>(st, a, fa, (unsigned)blocks, tiles, cols);
 }
 
 }  // namespace mpz

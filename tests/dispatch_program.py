@@ -17,13 +17,18 @@ using namespace mpz;
 int main() {
   char what[64];
   while (scanf("%63s", what) == 1) {
-    if (!strcmp(what, "lora_down_ordered")) {            // K, rank, targets, rows per copy, copies
+    if (!strncmp(what, "lora_down_ordered", 17)) {       // K, rank, targets, rows per copy, copies
       LoraDownArgs a{};
       int copies;
       if (scanf("%d %d %d %d %d", &a.K, &a.rank, &a.n_targets, &a.rows_per_copy, &copies) != 5) return 1;
       a.dtype = MPZ_DTYPE_BF16; a.T = copies * a.rows_per_copy; a.x = (const void*)4096; a.copy_stride = 16LL * a.K * a.rank;
       for (int t = 0; t < a.n_targets; ++t) a.Ac[t] = (const float*)4096 + 2LL * t * a.K * a.rank;
-      printf("%lld\n", (long long)lora_down_ordered_blocks(a));
+      if (!strcmp(what, "lora_down_ordered_launch")) {     // did it launch?  Asked only where there is no device to launch on
+        int devices = 0;
+        if (hipGetDeviceCount(&devices) == hipSuccess && devices > 0) return 1;
+        printf("%d\n", (int)launch_lora_down_ordered(nullptr, a));
+      } else
+        printf("%lld\n", (long long)lora_down_ordered_blocks(a));
     } else return 1;
   }
   return 0;
@@ -50,6 +55,7 @@ def _program():
 
 
 def ask(lines):
-    out = subprocess.run([_program()], input="\n".join(lines) + "\n", check=True, capture_output=True, text=True).stdout.split()
+    out = subprocess.run([_program()], input="\n".join(lines) + "\n", check=True, capture_output=True, text=True,
+                         env=dict(os.environ, HIP_VISIBLE_DEVICES="-1")).stdout.split()
     assert len(out) == len(lines)
     return [int(v) for v in out]

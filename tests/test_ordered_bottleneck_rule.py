@@ -14,3 +14,8 @@ def test_widths(k, taken):
 def test_targets_share_tiles_of_columns(rank, targets):
     """16 columns a block, of all targets side by side: 4 copies of 77 rows are two tiles of rows each."""
     assert ask([f"lora_down_ordered 768 {rank} {targets} 77 4"])[0] == 4 * 2 * ((rank * targets + 15) // 16)
+
+
+def test_a_refused_lds_limit_is_not_a_launch():
+    """Without a device the kernel's LDS limit cannot be raised: nothing is launched (the caller takes the shape-agnostic kernel)."""
+    assert ask(["lora_down_ordered_launch 768 8 2 77 4", "lora_down_ordered_launch 96 8 2 77 4"]) == [0, 0]
