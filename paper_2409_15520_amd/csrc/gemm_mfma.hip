@@ -922,7 +922,12 @@ int choose_cfg(const MfmaGemmArgs& a) {
   const bool forced_ok = a.w_scale == nullptr || a.tile_cfg == 1 || a.tile_cfg == 6 || a.tile_cfg == 11 || a.tile_cfg == 12 || a.tile_cfg == 15;   // int8: fewer instances
   if (forced_ok && known_cfg(a, a.tile_cfg) && cfg_ok(a, a.tile_cfg)) return a.tile_cfg;
   const long t5 = (long)((a.N + 255) / 256) * ((a.M + 255) / 256);
-  if (cfg_ok(a, 6) && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, a.K)) || (a.w_scale != nullptr && int8_large_tiles_pay(t5, a.K)))) return 6;
+  // Rotated columns that end inside a 256-wide tile: the 128-wide ones rotate them in their epilogue, the 256-wide ones leave that to a
+  // kernel of its own behind an fp32 staging buffer.  K = 2048, 2304 columns of which 2176 are rotated, a whole block of 6144 / 10240 /
+  // 24576 tokens: 630 / 983 / 2133 us with the wide tile, 617 / 957 / 2086 with the others (int8 691 / 1112 / 2392, 679 / 1083 / 2360); K = 4096,
+  // 4352 columns: 1966 / 2992 / 7133 against 1936 / 3059 / 7307, int8 2229 / 3446 / 8127 against 2257 / 3511 / 8310.
+  const bool rope256 = a.rope_cos == nullptr || a.rope_cols % 256 == 0 || a.K >= 4096;
+  if (cfg_ok(a, 6) && rope256 && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, a.K)) || (a.w_scale != nullptr && int8_large_tiles_pay(t5, a.K)))) return 6;
   // 128 x 128 tiles that fill between one and two blocks per CU leave half the chip with twice the work of the
   // other half; 192 x 128 tiles, one per CU, balance it (N = 768 projections of the 125M-class models; 2048 x 2560 with K = 2048 / 2560 /
   // 6912: 33 / 41 / 97 -> 29 / 35 / 75 us, the last column of tiles a third used)
@@ -996,6 +1001,8 @@ bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights, bool int8_wei
   const long t5 = (long)((N + 255) / 256) * ((M + 255) / 256);
   return t5 >= 512 || (bf16_weights && K % 128 == 0 && N % 8 == 0 && t5 * 8 >= (t5 + 255) / 256 * 256 * 5 && large_tiles_pay(t5, K)) || (int8_weights && int8_large_tiles_pay(t5, K));
 }
+
+int mfma_gemm_tile(const MfmaGemmArgs& a) { return choose_cfg(a); }
 
 int mfma_gemm_ce_slots(const MfmaGemmArgs& a0) {
   MfmaGemmArgs a = a0;

@@ -26,3 +26,24 @@ def test_block_has_the_bits_of_whole_tiles(heads, ffn, q, E, S, rank, targets):
         m.regen_noise(5, 0)
         hs.append(m.run_layers(m.embed(tokens), 0, 1, E, S).clone())
     assert torch.equal(hs[0], hs[1]) and torch.equal(hs[0], hs[2])
+
+
+# 2304 columns of which 2176 are rotated: by the 128-wide tiles, where the wide one would be chosen without a rotation
+@pytest.mark.parametrize("heads,kv,quant", [(32, 2, "none"), (32, 2, "int8"), (16, 1, "none"), (16, 1, "int8")])
+def test_rotated_columns_that_end_inside_a_wide_tile(heads, kv, quant):
+    import torch
+    import workloads as W
+    import paper_2409_15520_amd as M
+    w = W.Workload(name="mid", n_layers=1, d_model=2048, n_heads=heads, n_kv_heads=kv, d_ffn=256, vocab=600, max_seq=256, act="swiglu",
+                   norm="rmsnorm", pos="rope", has_bias=False, tie_embeddings=False, dtype="bf16", lora_rank=16, lora_targets=("q",),
+                   loss_mode="next_token_all_pos", q=10, E=2, S=256, steps=1, eps=1e-2, weight_quant=quant)
+    frozen = W.make_frozen_weights(w, 1)
+    masters = W.make_lora_masters(w, 2, b_std=0.05)
+    tokens = torch.from_numpy(W.make_tokens(w, 3)).cuda()
+    hs = []
+    for cfg in (0, 12, 1):
+        m = M.ZoModel(w, frozen, masters)
+        M.mpz_debug_set_tile_config(m.handle, cfg)
+        m.regen_noise(5, 0)
+        hs.append(m.run_layers(m.embed(tokens), 0, 1, 2, 256).clone())
+    assert torch.equal(hs[0], hs[1]) and torch.equal(hs[0], hs[2])

@@ -1,0 +1,14 @@
+"""Which tile a GEMM takes: the library's rules on sizes, asked without a GPU.  Tiles by number: 6 = 256 x 256, 11 = 192 x 128, 12 and 1 =
+128 x 128, 15 = the same for rotated heads of 128, 9 = 128 x 64, 10 = 64 x 64, 14 = 32 x 32; -1 = refused."""
+import pytest
+
+from dispatch_program import ask
+
+
+# one key-value head (two of 64): 128 rotated columns over.  K of 4096 keeps the wide tile, whose launch refuses the rotation
+@pytest.mark.parametrize("bits", [16, 8])
+@pytest.mark.parametrize("m,n,k,rope,dh,tile", [(10240, 2304, 2048, 2176, 128, 15), (10240, 2304, 2048, 2176, 64, 12), (5120, 2304, 2048, 2176, 64, 12),
+                                                (24576, 2304, 2048, 2176, 64, 12), (10240, 2304, 2048, 2048, 64, 6), (10240, 2560, 2048, 2304, 64, 6),
+                                                (10240, 4352, 4096, 4224, 128, -1), (10240, 4608, 4096, 4352, 128, 6)])
+def test_rotated_columns_that_end_inside_a_wide_tile(m, n, k, rope, dh, tile, bits):
+    assert ask([f"tile {m} {n} {k} {bits} {rope} {dh}"]) == [tile]
