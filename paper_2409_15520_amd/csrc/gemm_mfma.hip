@@ -891,14 +891,16 @@ bool cfg_ok(const MfmaGemmArgs& a, int cfg) {
 // 64-feature tiles (twice the blocks); a dual launch has one tile shape.
 int split_tile_bn(const MfmaGemmArgs& a) { return (a.dual || a.N >= 8192 || a.K >= 8192 || a.w_scale != nullptr || a.w_absmax != nullptr) ? 128 : 64; }
 
-// Do `tiles` 256 x 256 tiles (one per CU at a time) beat the 128-wide ones?  Always from two full rounds of 256 CUs on.  Below
-// that the persistent kernel of gemm_pipe.hip wins once one round is nine sixteenths full, two rounds together five eighths: K = 4096,
-// 128 / 144 / 192 / 256 / 384 tiles: 82 / 80 / 89 / 96 / 168 us against 72 / 90 / 107 / 138 / 208 us for the same product in 128 x 128 tiles;
-// K = 2048, 128 / 144 / 160 / 256 / 320: 47 / 45 / 47 / 55 / 89 against 39 / 49 / 53 / 74 / 92.  At K = 1024 a second round no longer pays
-// (352 tiles: 56 against 55, 176 tiles: 30 against 34), at K = 768 neither does the first (192 tiles: 28 against 27).
-bool large_tiles_pay(long tiles, int K) {
-  const long rounds = (tiles + 255) / 256;
-  return tiles >= 512 || (tiles * 16 >= rounds * 256 * (rounds == 1 ? 9 : 10) && K >= (rounds == 1 ? 1024 : 2048));
+// Do `tiles` 256 x 256 tiles (one per CU at a time) beat the `small` 128 x 128 ones of the same product (two per CU at a time)?  Always from
+// two full rounds of 256 CUs on.  Below that the time of either goes in steps, one per round: a round of the persistent kernel of
+// gemm_pipe.hip beats three half rounds of small tiles and not two (K = 1024 / 2048 / 4096, time of the small tiles over its own: up to
+// 512 small tiles 0.8 / 0.8 / 0.8, 513 to 640 1.02 - 1.08 / 1.03 - 1.10 / 1.03 - 1.15, 641 to 768 1.05 / 1.1 / 1.2), two rounds beat five half ones
+// from 1280 small tiles on (1152 / 1280 / 1408: 0.92 / 1.02 / 1.12 at K = 2048, 0.92 / 1.04 / 1.13 at K = 4096).  Counted in small tiles, because
+// rows that fill half a wide tile take half the small ones (12288 x 4096, 576 rows: 144 tiles, 79 us, against 480, 68).  At K = 1024 a
+// second round no longer pays (352 tiles: 56 against 55), at K = 768 neither does the first (192 tiles: 28 against 27).
+bool large_tiles_pay(long tiles, long small, int K) {
+  if (tiles >= 512) return true;
+  return tiles <= 256 ? small > 512 && K >= 1024 : small >= 1280 && K >= 2048;
 }
 // Gate and up together (2 x 128 features per tile), whose small tile fetches half lines: from half a round on (768 x 5632 x 2048, 132
 // tiles: 56 -> 44 us; 1536 x 2816 x 1024, 132: 33 -> 28; 768 x 11008 x 4096, 258: 179 -> 163; 512 x 5632 x 2048, 88: no gain)
@@ -921,17 +923,17 @@ int choose_cfg(const MfmaGemmArgs& a) {
   }
   const bool forced_ok = a.w_scale == nullptr || a.tile_cfg == 1 || a.tile_cfg == 6 || a.tile_cfg == 11 || a.tile_cfg == 12 || a.tile_cfg == 15;   // int8: fewer instances
   if (forced_ok && known_cfg(a, a.tile_cfg) && cfg_ok(a, a.tile_cfg)) return a.tile_cfg;
-  const long t5 = (long)((a.N + 255) / 256) * ((a.M + 255) / 256);
+  const long t5 = (long)((a.N + 255) / 256) * ((a.M + 255) / 256), t1 = (long)((a.N + 127) / 128) * ((a.M + 127) / 128);
   // Rotated columns that end inside a 256-wide tile: the 128-wide ones rotate them in their epilogue, the 256-wide ones leave that to a
   // kernel of its own behind an fp32 staging buffer.  K = 2048, 2304 columns of which 2176 are rotated, a whole block of 6144 / 10240 /
   // 24576 tokens: 630 / 983 / 2133 us with the wide tile, 617 / 957 / 2086 with the others (int8 691 / 1112 / 2392, 679 / 1083 / 2360); K = 4096,
   // 4352 columns: 1966 / 2992 / 7133 against 1936 / 3059 / 7307, int8 2229 / 3446 / 8127 against 2257 / 3511 / 8310.
   const bool rope256 = a.rope_cos == nullptr || a.rope_cols % 256 == 0 || a.K >= 4096;
-  if (cfg_ok(a, 6) && rope256 && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, a.K)) || (a.w_scale != nullptr && int8_large_tiles_pay(t5, a.K)))) return 6;
+  if (cfg_ok(a, 6) && rope256 && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, t1, a.K)) || (a.w_scale != nullptr && int8_large_tiles_pay(t5, a.K)))) return 6;
   // 128 x 128 tiles that fill between one and two blocks per CU leave half the chip with twice the work of the
   // other half; 192 x 128 tiles, one per CU, balance it (N = 768 projections of the 125M-class models; 2048 x 2560 with K = 2048 / 2560 /
   // 6912: 33 / 41 / 97 -> 29 / 35 / 75 us, the last column of tiles a third used)
-  const long t1 = (long)((a.N + 127) / 128) * ((a.M + 127) / 128), t11 = (long)((a.N + 191) / 192) * ((a.M + 127) / 128);
+  const long t11 = (long)((a.N + 191) / 192) * ((a.M + 127) / 128);
   const bool plain = a.rope_cos == nullptr && a.w_scale == nullptr && a.ce_max == nullptr;
   if (t1 > 256 && t1 < 512 && t11 <= 256 && a.K >= 1536 && a.rope_cos == nullptr && (a.N % 192 == 0 || plain) && cfg_ok(a, 11)) return 11;
   // heads of 128 columns rotated in the epilogue need a wave tile that holds one: four waves of 128 x 32 (1024 tokens of the
@@ -998,8 +1000,8 @@ __global__ void __launch_bounds__(1024) ce_combine_kernel(int slots, int M, cons
 // Does a pass whose Q|K|V projection this is take the 256-wide tiles?  Two halves on two streams with 128-wide ones beat the least filled
 // single round of them (d = 1024, 4608 tokens, 144 tiles, 12 layers: 2403 us in one pass, 2162 in two halves): from five eighths on.
 bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights, bool int8_weights) {
-  const long t5 = (long)((N + 255) / 256) * ((M + 255) / 256);
-  return t5 >= 512 || (bf16_weights && K % 128 == 0 && N % 8 == 0 && t5 * 8 >= (t5 + 255) / 256 * 256 * 5 && large_tiles_pay(t5, K)) || (int8_weights && int8_large_tiles_pay(t5, K));
+  const long t5 = (long)((N + 255) / 256) * ((M + 255) / 256), t1 = (long)((N + 127) / 128) * ((M + 127) / 128);
+  return t5 >= 512 || (bf16_weights && K % 128 == 0 && N % 8 == 0 && t5 * 8 >= (t5 + 255) / 256 * 256 * 5 && large_tiles_pay(t5, t1, K)) || (int8_weights && int8_large_tiles_pay(t5, K));
 }
 
 int mfma_gemm_tile(const MfmaGemmArgs& a) { return choose_cfg(a); }

@@ -12,3 +12,13 @@ from dispatch_program import ask
                                                 (10240, 4352, 4096, 4224, 128, -1), (10240, 4608, 4096, 4352, 128, 6)])
 def test_rotated_columns_that_end_inside_a_wide_tile(m, n, k, rope, dh, tile, bits):
     assert ask([f"tile {m} {n} {k} {bits} {rope} {dh}"]) == [tile]
+
+
+# 256 x 256 tiles, 128 x 128 ones of the same product: 144, 480 and 504 (rows that fill part of a wide tile); 130, 516; 144, 576; 256, 1024;
+# two rounds: 264, 1056; 305, 1210; 320, 1280; K of 1024 has no second round, K of 768 no first
+@pytest.mark.parametrize("m,n,k,wide", [(576, 12288, 4096, False), (640, 12288, 4096, False), (896, 9216, 3072, False), (2560, 3328, 4096, True),
+                                        (3072, 3072, 1024, True), (4096, 4096, 1024, True), (3072, 3072, 768, False),
+                                        (2816, 6144, 2048, False), (15616, 1280, 2048, False), (4096, 5120, 2048, True), (4096, 5120, 1024, False),
+                                        (8192, 4096, 768, True)])
+def test_wide_tiles_by_the_half_rounds_of_small_ones(m, n, k, wide):
+    assert (ask([f"tile {m} {n} {k} 16 0 0"])[0] == 6) == wide
