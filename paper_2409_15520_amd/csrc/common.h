@@ -217,7 +217,7 @@ long mfma_gemm_split_blocks(const MfmaGemmArgs& a, size_t partial_capacity);   /
 bool mfma_gemm_supported(const MfmaGemmArgs& a);
 // will a dense [M, K] x [N, K]^T take the 256 x 256 tile (which fills the chip by itself)?
 bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights, bool int8_weights);
-int mfma_gemm_tile(const MfmaGemmArgs& a);          // the tile configuration that a launch takes (not: gate and up together)
+int mfma_gemm_tile(const MfmaGemmArgs& a);          // the tile configuration that a launch takes (gate and up together: 6 or 1)
 int mfma_gemm_ce_slots(const MfmaGemmArgs& a);      // partial slots per row the launch will write (depends on the tile)
 // ce[m] = logsumexp over the slots - target logit (0 where ce_target[m] < 0)
 void launch_ce_combine(hipStream_t st, int slots, int M, const float* ce_max, const float* ce_sum, const float* ce_tlogit,

@@ -902,15 +902,26 @@ bool large_tiles_pay(long tiles, long small, int K) {
   if (tiles >= 512) return true;
   return tiles <= 256 ? small > 512 && K >= 1024 : small >= 1280 && K >= 2048;
 }
-// Gate and up together (2 x 128 features per tile), whose small tile fetches half lines: from half a round on (768 x 5632 x 2048, 132
-// tiles: 56 -> 44 us; 1536 x 2816 x 1024, 132: 33 -> 28; 768 x 11008 x 4096, 258: 179 -> 163; 512 x 5632 x 2048, 88: no gain)
-bool large_dual_tiles_pay(long tiles, int K) { return tiles >= 512 || (tiles >= 128 && K >= (tiles <= 256 ? 1024 : 2048)); }
+// Gate and up together (2 x 128 features per tile, one block per CU at a time for either size): when the small tiles need more rounds
+// (time of 128 tokens over 256 a tile, 1 / 2, 2 / 3 and 2 / 4 rounds against 1 / 1 and 2 / 2: K = 1024 1.03 - 1.21, 0.92 - 1.03, 1.17 - 1.22 against
+// 0.72 - 0.85, 0.70; K = 2048 1.13 - 1.36, 1.05 - 1.15, 1.28 - 1.35 against 0.73 - 0.89, 0.74; K = 4096 1.26 - 1.58, 1.08 - 1.28, 1.36 - 1.49 against
+// 0.74 - 0.99, 0.84; 768 x 5632 x 2048, 132 tiles: 56 -> 44 us, but 576 rows 34.8 against 42.4)
+bool large_dual_tiles_pay(long tiles, long small, int K) {
+  return tiles >= 512 || ((small + 255) / 256 > (tiles + 255) / 256 && K >= (tiles <= 256 ? 1024 : 2048));
+}
 
 // The same question for int8 weights, whose 256 x 256 tile is the register-staged one of this file: one and two part-filled rounds
 // pay from the same fill on (K = 4096, 128 / 192 / 256 / 288 / 384 tiles: 92 / 104 / 118 / 194 / 205 us against 78 / 116 / 150 / 179 / 222 in
 // 128 x 128 tiles; K = 2048, 128 / 160 / 256 / 384: 53 / 53 / 67 / 115 against 42 / 58 / 81 / 119; gate and up together, K = 4096, 172 / 344
 // tiles: 94 / 191 against 119 / 212).  Measured from K = 2048 on.
 bool int8_large_tiles_pay(long tiles, int K) { return tiles >= 512 || (tiles * 8 >= (tiles + 255) / 256 * 256 * 5 && K >= 2048); }
+
+bool dual_takes_large(const MfmaGemmArgs& a) {
+  if (a.tile_cfg != 0) return a.tile_cfg == 6;
+  const long tb = (long)((a.N + 127) / 128) * ((a.M + 255) / 256), t1 = (long)((a.N + 127) / 128) * ((a.M + 127) / 128);
+  if (tb >= 512) return true;
+  return a.w_scale != nullptr ? int8_large_tiles_pay(tb, a.K) : gemm_pipe_supported(a) && large_dual_tiles_pay(tb, t1, a.K);
+}
 
 int choose_cfg(const MfmaGemmArgs& a) {
   // split K (at most 256 stacked tokens): a block takes all the tokens it can (the weights are then fetched from HBM
@@ -1004,7 +1015,7 @@ bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights, bool int8_wei
   return t5 >= 512 || (bf16_weights && K % 128 == 0 && N % 8 == 0 && t5 * 8 >= (t5 + 255) / 256 * 256 * 5 && large_tiles_pay(t5, t1, K)) || (int8_weights && int8_large_tiles_pay(t5, K));
 }
 
-int mfma_gemm_tile(const MfmaGemmArgs& a) { return choose_cfg(a); }
+int mfma_gemm_tile(const MfmaGemmArgs& a) { return !a.dual || a.k_splits > 1 ? choose_cfg(a) : dual_takes_large(a) ? 6 : 1; }
 
 int mfma_gemm_ce_slots(const MfmaGemmArgs& a0) {
   MfmaGemmArgs a = a0;
@@ -1167,10 +1178,8 @@ hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a) {
     return hipSuccess;
   }
   if (a.dual) {
-    const long tb = (long)((a.N + 127) / 128) * ((a.M + 255) / 256);
-    const bool pipe = gemm_pipe_supported(a);
-    if ((a.tile_cfg == 0 && (tb >= 512 || (pipe && large_dual_tiles_pay(tb, a.K)) || (q8 && int8_large_tiles_pay(tb, a.K)))) || a.tile_cfg == 6) {               // 2 x 128 x 256
-      if (pipe) return launch_gemm_pipe(st, a);
+    if (dual_takes_large(a)) {                            // 2 x 128 x 256
+      if (gemm_pipe_supported(a)) return launch_gemm_pipe(st, a);
       return q8 ? launch_cfg<128, 256, 64, 2, 4, true, 0, true>(st, a) : launch_cfg<128, 256, 64, 2, 4, true>(st, a);
     }
     return q8 ? launch_cfg<128, 128, 32, 2, 2, true, 0, true>(st, a) : launch_cfg<128, 128, 32, 2, 2, true>(st, a);

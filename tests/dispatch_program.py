@@ -29,12 +29,13 @@ int main() {
         printf("%d\n", (int)launch_lora_down_ordered(nullptr, a));
       } else
         printf("%lld\n", (long long)lora_down_ordered_blocks(a));
-    } else if (!strcmp(what, "tile")) {                  // M, N, K, bits of a weight, rotated columns, their heads: tile, or -1 if refused
+    } else if (!strcmp(what, "tile")) {                  // M, N, K, bits of a weight, rotated columns (-1: gate and up), their heads: tile, or -1 if refused
       MfmaGemmArgs a{};
       int bits;
       if (scanf("%d %d %d %d %d %d", &a.M, &a.N, &a.K, &bits, &a.rope_cols, &a.rope_dh) != 6) return 1;
       a.w_rows = a.ldo = a.N; a.act = -1; a.rows_per_copy = a.M; a.x = a.w = a.out = (void*)4096;
       if (bits == 8) a.w_scale = (const float*)4096;
+      if (a.rope_cols < 0) { a.rope_cols = 0; a.dual = 1; a.dual_offset = a.N; a.w_rows = 2 * a.N; }
       if (a.rope_cols) { a.rope_cos = a.rope_sin = (const float*)4096; a.S = a.M; }
       printf("%d\n", mfma_gemm_supported(a) ? mfma_gemm_tile(a) : -1);
     } else return 1;

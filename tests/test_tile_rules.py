@@ -22,3 +22,11 @@ def test_rotated_columns_that_end_inside_a_wide_tile(m, n, k, rope, dh, tile, bi
                                         (8192, 4096, 768, True)])
 def test_wide_tiles_by_the_half_rounds_of_small_ones(m, n, k, wide):
     assert (ask([f"tile {m} {n} {k} 16 0 0"])[0] == 6) == wide
+
+
+# gate and up: wide tiles, 128 x 128 ones: 132, 220; 132, 264; 258, 430; 258, 516; 160, 240; 128, 256; 128, 224; 256, 512
+@pytest.mark.parametrize("m,n,k,wide", [(576, 5632, 2048, False), (768, 5632, 2048, True), (640, 11008, 4096, False), (768, 11008, 4096, True),
+                                        (384, 10240, 4096, False), (1024, 4096, 2048, False), (896, 4096, 1536, False), (1024, 8192, 1024, True),
+                                        (768, 11008, 1024, False), (768, 5632, 768, False), (4096, 11008, 768, True)])
+def test_gate_and_up_wide_where_small_tiles_need_more_rounds(m, n, k, wide):
+    assert (ask([f"tile {m} {n} {k} 16 -1 0"])[0] == 6) == wide
