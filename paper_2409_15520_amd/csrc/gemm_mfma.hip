@@ -910,17 +910,23 @@ bool large_dual_tiles_pay(long tiles, long small, int K) {
   return tiles >= 512 || ((small + 255) / 256 > (tiles + 255) / 256 && K >= (tiles <= 256 ? 1024 : 2048));
 }
 
-// The same question for int8 weights, whose 256 x 256 tile is the register-staged one of this file: one and two part-filled rounds
-// pay from the same fill on (K = 4096, 128 / 192 / 256 / 288 / 384 tiles: 92 / 104 / 118 / 194 / 205 us against 78 / 116 / 150 / 179 / 222 in
-// 128 x 128 tiles; K = 2048, 128 / 160 / 256 / 384: 53 / 53 / 67 / 115 against 42 / 58 / 81 / 119; gate and up together, K = 4096, 172 / 344
-// tiles: 94 / 191 against 119 / 212).  Measured from K = 2048 on.
-bool int8_large_tiles_pay(long tiles, int K) { return tiles >= 512 || (tiles * 8 >= (tiles + 255) / 256 * 256 * 5 && K >= 2048); }
+// The same questions for int8 weights, whose 256 x 256 tile is the register-staged one of this file: one round of them against three rounds
+// of 128 x 128 tiles, one per CU each, two against six (time of the small tiles over the wide ones', rounds wide / small 1 / 2, 1 / 3, 1 / 4, 2 / 5,
+// 2 / 6, 2 / 7: K = 2048 0.74, 1.03 - 1.08, 1.25, 0.87 - 0.92, 1.03 - 1.06, 1.16; K = 4096 0.74, 1.05 - 1.10, 1.28, 0.90 - 0.97, 1.04 - 1.09, 1.18).
+// Gate and up together as for bf16 (1 / 1, 1 / 2, 2 / 2, 2 / 3: K = 2048 0.90, 1.14 - 1.27, 0.71, 1.04 - 1.10; K = 4096 0.93, 1.19 - 1.33, 0.75,
+// 1.07 - 1.12).  K = 1024 and 1536 with three small rounds to a wide one: 0.96 - 1.03.
+bool int8_large_tiles_pay(long tiles, long small, int K) {
+  return tiles >= 512 || ((small + 255) / 256 >= 3 * ((tiles + 255) / 256) && K >= 2048);
+}
+bool int8_large_dual_tiles_pay(long tiles, long small, int K) {
+  return tiles >= 512 || ((small + 255) / 256 > (tiles + 255) / 256 && K >= 2048);
+}
 
 bool dual_takes_large(const MfmaGemmArgs& a) {
   if (a.tile_cfg != 0) return a.tile_cfg == 6;
   const long tb = (long)((a.N + 127) / 128) * ((a.M + 255) / 256), t1 = (long)((a.N + 127) / 128) * ((a.M + 127) / 128);
   if (tb >= 512) return true;
-  return a.w_scale != nullptr ? int8_large_tiles_pay(tb, a.K) : gemm_pipe_supported(a) && large_dual_tiles_pay(tb, t1, a.K);
+  return a.w_scale != nullptr ? int8_large_dual_tiles_pay(tb, t1, a.K) : gemm_pipe_supported(a) && large_dual_tiles_pay(tb, t1, a.K);
 }
 
 int choose_cfg(const MfmaGemmArgs& a) {
@@ -940,7 +946,7 @@ int choose_cfg(const MfmaGemmArgs& a) {
   // 24576 tokens: 630 / 983 / 2133 us with the wide tile, 617 / 957 / 2086 with the others (int8 691 / 1112 / 2392, 679 / 1083 / 2360); K = 4096,
   // 4352 columns: 1966 / 2992 / 7133 against 1936 / 3059 / 7307, int8 2229 / 3446 / 8127 against 2257 / 3511 / 8310.
   const bool rope256 = a.rope_cos == nullptr || a.rope_cols % 256 == 0 || a.K >= 4096;
-  if (cfg_ok(a, 6) && rope256 && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, t1, a.K)) || (a.w_scale != nullptr && int8_large_tiles_pay(t5, a.K)))) return 6;
+  if (cfg_ok(a, 6) && rope256 && (t5 >= 512 || (gemm_pipe_supported(a) && large_tiles_pay(t5, t1, a.K)) || (a.w_scale != nullptr && int8_large_tiles_pay(t5, t1, a.K)))) return 6;
   // 128 x 128 tiles that fill between one and two blocks per CU leave half the chip with twice the work of the
   // other half; 192 x 128 tiles, one per CU, balance it (N = 768 projections of the 125M-class models; 2048 x 2560 with K = 2048 / 2560 /
   // 6912: 33 / 41 / 97 -> 29 / 35 / 75 us, the last column of tiles a third used)
@@ -1012,7 +1018,7 @@ __global__ void __launch_bounds__(1024) ce_combine_kernel(int slots, int M, cons
 // single round of them (d = 1024, 4608 tokens, 144 tiles, 12 layers: 2403 us in one pass, 2162 in two halves): from five eighths on.
 bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights, bool int8_weights) {
   const long t5 = (long)((N + 255) / 256) * ((M + 255) / 256), t1 = (long)((N + 127) / 128) * ((M + 127) / 128);
-  return t5 >= 512 || (bf16_weights && K % 128 == 0 && N % 8 == 0 && t5 * 8 >= (t5 + 255) / 256 * 256 * 5 && large_tiles_pay(t5, t1, K)) || (int8_weights && int8_large_tiles_pay(t5, K));
+  return t5 >= 512 || (bf16_weights && K % 128 == 0 && N % 8 == 0 && t5 * 8 >= (t5 + 255) / 256 * 256 * 5 && large_tiles_pay(t5, t1, K)) || (int8_weights && int8_large_tiles_pay(t5, t1, K));
 }
 
 int mfma_gemm_tile(const MfmaGemmArgs& a) { return !a.dual || a.k_splits > 1 ? choose_cfg(a) : dual_takes_large(a) ? 6 : 1; }

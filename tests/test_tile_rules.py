@@ -30,3 +30,17 @@ def test_wide_tiles_by_the_half_rounds_of_small_ones(m, n, k, wide):
                                         (768, 11008, 1024, False), (768, 5632, 768, False), (4096, 11008, 768, True)])
 def test_gate_and_up_wide_where_small_tiles_need_more_rounds(m, n, k, wide):
     assert (ask([f"tile {m} {n} {k} 16 -1 0"])[0] == 6) == wide
+
+
+# int8: one round of wide tiles against two, three (513 to 768 small tiles) and four of small ones, two against five and six
+@pytest.mark.parametrize("m,n,k,wide", [(2048, 4096, 4096, False), (576, 12288, 4096, False), (1024, 12288, 4096, True), (2304, 4096, 2048, True),
+                                        (3072, 3072, 1536, False), (4096, 5120, 4096, False), (8192, 2560, 2048, False), (5632, 4096, 4096, True),
+                                        (3072, 7680, 2560, True), (8192, 4096, 1024, True)])
+def test_int8_wide_tiles_by_rounds(m, n, k, wide):
+    assert (ask([f"tile {m} {n} {k} 8 0 0"])[0] == 6) == wide
+
+
+@pytest.mark.parametrize("m,n,k,wide", [(384, 10240, 4096, False), (512, 11008, 4096, True), (640, 11008, 4096, False), (768, 11008, 4096, True),
+                                        (896, 4096, 2048, False), (768, 5632, 2048, True), (768, 5632, 1536, False)])
+def test_int8_gate_and_up_wide_where_small_tiles_need_more_rounds(m, n, k, wide):
+    assert (ask([f"tile {m} {n} {k} 8 -1 0"])[0] == 6) == wide
