@@ -959,14 +959,16 @@ int choose_cfg(const MfmaGemmArgs& a) {
   // fewer 128 x 128 tiles than CUs (single-copy and single-query passes): 128 x 64 tiles, twice the blocks, and
   // 64 x 64 tiles if that is still less than one block per CU (one pass per copy on the 125M-shaped workload:
   // 8.2 -> 7.4 ms per step; 2 x 64 tokens through the 7B-shaped model: 75 -> 67 ms), unless K is long (96 and 120 tiles, K = 8192 and 6912:
-  // 51 and 44 us against 44 and 41 in 128 x 64).  From 144 tiles on the whole ones are ahead again, a CU each instead of two halves on some
-  // (768 x 4096 x 11008, 192 tiles: 101 -> 81 us; 1024 x 2560 x 2048, 160: 22 -> 19; 3072 x 768 x 3072, 144: 31 -> 25).
+  // 51 and 44 us against 44 and 41 in 128 x 64).  From 144 tiles on, where their halves are more than the CUs, the whole ones are ahead again, a
+  // CU each instead of two halves on some (768 x 4096 x 11008, 192 tiles: 101 -> 81 us; 1024 x 2560 x 2048, 160: 22 -> 19; 3072 x 768 x 3072,
+  // 144: 31 -> 25; but 144 tiles of 240 halves, 288 x 6144 x 2048, 15.1 against 17.2, and 448 x 4608 x 1536, 12.5 against 14.5).
   // 32 x 32 tiles while three blocks per CU hold them all (768 x 768 x 3072, 576 tiles: 14.9 us against 16.9 in 64 x 64 tiles;
   // 384 x 2304 x 768, 864 tiles: 7.7 against 6.6), two per CU for wide outputs (288 x 2048 x 2048, 576 tiles: 12.3 against 9.9; 288 x 2560 x
   // 6912, 720: 35 against 32)
   const long t14 = (long)((a.N + 31) / 32) * ((a.M + 31) / 32);
   if (t14 <= (a.N >= 2048 ? 512 : 768) && cfg_ok(a, 14)) return 14;
-  if (t1 < 144 && plain && cfg_ok(a, 9))
+  const long t9 = (long)((a.N + 127) / 128) * ((a.M + 63) / 64);
+  if ((t1 < 144 || t9 <= 256) && plain && cfg_ok(a, 9))
     return ((t1 < 96 || (t1 < 128 && a.K < 4096)) && cfg_ok(a, 10)) ? 10 : 9;
   // otherwise the 128 x 128 tile with 8 waves of 64 x 32 (16 waves per CU): a block of a short-K problem lives for
   // a dozen K-tiles, and what hides its first loads and last stores is other waves (10 % over 4 waves of 64 x 64

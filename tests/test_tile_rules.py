@@ -44,3 +44,10 @@ def test_int8_wide_tiles_by_rounds(m, n, k, wide):
                                         (896, 4096, 2048, False), (768, 5632, 2048, True), (768, 5632, 1536, False)])
 def test_int8_gate_and_up_wide_where_small_tiles_need_more_rounds(m, n, k, wide):
     assert (ask([f"tile {m} {n} {k} 8 -1 0"])[0] == 6) == wide
+
+
+# 144 whole tiles of 240 and 252 halves, of 288; 192; 132 of 264
+@pytest.mark.parametrize("m,n,k,tile", [(288, 6144, 2048, 9), (300, 6144, 8192, 9), (448, 4608, 1536, 9), (384, 6144, 2048, 12), (512, 6144, 2048, 12),
+                                        (3072, 768, 3072, 12), (1408, 1536, 2048, 9)])
+def test_halves_of_tiles_that_fit_the_cus(m, n, k, tile):
+    assert ask([f"tile {m} {n} {k} 16 0 0"]) == [tile]
