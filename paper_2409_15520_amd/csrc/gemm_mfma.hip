@@ -964,9 +964,12 @@ int choose_cfg(const MfmaGemmArgs& a) {
   // 144: 31 -> 25; but 144 tiles of 240 halves, 288 x 6144 x 2048, 15.1 against 17.2, and 448 x 4608 x 1536, 12.5 against 14.5).
   // 32 x 32 tiles while three blocks per CU hold them all (768 x 768 x 3072, 576 tiles: 14.9 us against 16.9 in 64 x 64 tiles;
   // 384 x 2304 x 768, 864 tiles: 7.7 against 6.6), two per CU for wide outputs (288 x 2048 x 2048, 576 tiles: 12.3 against 9.9; 288 x 2560 x
-  // 6912, 720: 35 against 32)
+  // 6912, 720: 35 against 32), unless K is short or the rows are more than nine tiles and K is from 3072 to below 8192 (2048 columns: 320 rows
+  // of K = 512 / 768 / 2048 / 3072 / 4096 / 8192: 5.0 / 6.2 / 12.1 / 15.8 / 19.3 / 35.4 against 5.6 / 6.1 / 9.6 / 15.9 / 21.0 / 33.4; 288 rows:
+  // 5.1 / 6.3 / 12.0 / 16.9 / 21.3 / 40.7 against 5.5 / 6.1 / 9.5 / 15.7 / 20.8 / 33.0)
   const long t14 = (long)((a.N + 31) / 32) * ((a.M + 31) / 32);
-  if (t14 <= (a.N >= 2048 ? 512 : 768) && cfg_ok(a, 14)) return 14;
+  const bool two_per_cu = a.N >= 2048 && a.K >= 768 && (a.K < 3072 || a.K >= 8192 || a.M <= 288);
+  if (t14 <= (two_per_cu ? 512 : 768) && cfg_ok(a, 14)) return 14;
   const long t9 = (long)((a.N + 127) / 128) * ((a.M + 63) / 64);
   if ((t1 < 144 || t9 <= 256) && plain && cfg_ok(a, 9))
     return ((t1 < 96 || (t1 < 128 && a.K < 4096)) && cfg_ok(a, 10)) ? 10 : 9;

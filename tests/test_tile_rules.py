@@ -51,3 +51,9 @@ def test_int8_gate_and_up_wide_where_small_tiles_need_more_rounds(m, n, k, wide)
                                         (3072, 768, 3072, 12), (1408, 1536, 2048, 9)])
 def test_halves_of_tiles_that_fit_the_cus(m, n, k, tile):
     assert ask([f"tile {m} {n} {k} 16 0 0"]) == [tile]
+
+
+@pytest.mark.parametrize("m,n,k,tile", [(320, 2048, 512, 14), (384, 2048, 512, 14), (320, 2048, 768, 10), (320, 2048, 2048, 10), (320, 2048, 4096, 14),
+                                        (288, 2048, 4096, 10), (384, 2048, 5632, 14), (320, 2048, 8192, 10), (256, 2048, 2048, 14), (416, 2048, 4096, 10)])
+def test_the_smallest_tiles_of_wide_outputs(m, n, k, tile):
+    assert ask([f"tile {m} {n} {k} 16 0 0"]) == [tile]
