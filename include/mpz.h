@@ -368,7 +368,8 @@ mpz_status mpz_debug_dequant_nf4(const void* codes, const float* absmax, void* o
 mpz_status mpz_debug_set_kernel_path(mpz_model* m, int32_t simple_only);
 
 /* Test hook: allow (default) or forbid the two-halves schedule of mpz_forward_perturbed: for small models (every
- * GEMM on the 128-wide tiles, label-subset loss, d_model < 2048) and some thousand stacked tokens the pass is issued
+ * GEMM on the 128-wide tiles, label-subset loss, d_model < 2048) and some thousand stacked tokens, and for wider ones
+ * without gate and up whose Q|K|V and up projections are a little over one round of 256-wide tiles, the pass is issued
  * as two halves of q copies each on the caller's stream and on an internal second stream of the same priority, forked
  * from and joined to the caller's stream by events, so that the halves' kernels overlap.  Losses are bit-identical
  * either way. */

@@ -218,6 +218,7 @@ bool mfma_gemm_supported(const MfmaGemmArgs& a);
 // will a dense [M, K] x [N, K]^T take the 256 x 256 tile (which fills the chip by itself)?
 bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights, bool int8_weights);
 int mfma_gemm_tile(const MfmaGemmArgs& a);          // the tile configuration that a launch takes (gate and up together: 6 or 1)
+bool two_halves_pay(int d, int nqkv, int d_ffn, bool gate_up, int weight_quant, long T);   // mpz_api.hip: the sizes of the two-halves schedule
 int mfma_gemm_ce_slots(const MfmaGemmArgs& a);      // partial slots per row the launch will write (depends on the tile)
 // ce[m] = logsumexp over the slots - target logit (0 where ce_target[m] < 0)
 void launch_ce_combine(hipStream_t st, int slots, int M, const float* ce_max, const float* ce_sum, const float* ce_tlogit,

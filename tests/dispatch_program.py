@@ -38,6 +38,10 @@ int main() {
       if (a.rope_cols < 0) { a.rope_cols = 0; a.dual = 1; a.dual_offset = a.N; a.w_rows = 2 * a.N; }
       if (a.rope_cols) { a.rope_cos = a.rope_sin = (const float*)4096; a.S = a.M; }
       printf("%d\n", mfma_gemm_supported(a) ? mfma_gemm_tile(a) : -1);
+    } else if (!strcmp(what, "two_halves")) {            // d, columns of Q|K|V, d_ffn, gate and up, weight_quant, stacked tokens
+      int d, nqkv, ffn, gate, quant, T;
+      if (scanf("%d %d %d %d %d %d", &d, &nqkv, &ffn, &gate, &quant, &T) != 6) return 1;
+      printf("%d\n", (int)two_halves_pay(d, nqkv, ffn, gate != 0, quant, T));
     } else return 1;
   }
   return 0;

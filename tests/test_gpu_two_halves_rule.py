@@ -27,3 +27,23 @@ def test_streams_and_bits(heads, q, E, S, streams):
     one = m.forward_perturbed(tokens, labels).clone()
     assert M.mpz_debug_last_pass_streams(m.handle) == 1
     assert torch.equal(got.view(torch.int32), one.view(torch.int32))
+
+
+@pytest.mark.parametrize("quant,q,streams", [("none", 10, 2), ("none", 11, 1), ("int8", 13, 2), ("int8", 8, 1)])
+def test_wide_models(quant, q, streams):
+    """d = 2560, 256 tokens per query: both wide projections a little over one round of 256-wide tiles (300 and 270; int8 390 and 351)."""
+    import torch
+    import workloads as W
+    import paper_2409_15520_amd as M
+    w = W.Workload(name="halves", n_layers=1, d_model=2560, n_heads=40, n_kv_heads=40, d_ffn=6912, vocab=600, max_seq=128, act="relu",
+                   norm="layernorm", pos="learned", has_bias=True, tie_embeddings=True, dtype="bf16", lora_rank=8, lora_targets=("q", "v"),
+                   loss_mode="last_pos_label_subset", q=q, E=1, S=128, steps=1, eps=1e-2, weight_quant=quant)
+    m = M.ZoModel(w, W.make_frozen_weights(w, 1), W.make_lora_masters(w, 2, b_std=0.05))
+    tokens, labels = torch.from_numpy(W.make_tokens(w, 3)).cuda(), torch.from_numpy(W.make_labels(w, 3)).cuda()
+    m.regen_noise(5, 0)
+    got = m.forward_perturbed(tokens, labels).clone()
+    assert M.mpz_debug_last_pass_streams(m.handle) == streams
+    M.mpz_debug_set_two_halves(m.handle, False)
+    one = m.forward_perturbed(tokens, labels).clone()
+    assert M.mpz_debug_last_pass_streams(m.handle) == 1
+    assert torch.equal(got.view(torch.int32), one.view(torch.int32))

@@ -1,0 +1,22 @@
+"""Which sizes run as two halves on two streams (no GPU): weight_quant 0 = bf16, 1 = int8."""
+import pytest
+
+from dispatch_program import ask
+
+OPT = {768: "768 2304 3072 0", 2048: "2048 6144 8192 0", 2560: "2560 7680 6912 0", 3072: "3072 9216 12288 0"}
+LLAMA = {1024: "1024 2048 2816 1", 2048: "2048 2560 5632 1", 3072: "3072 5120 8192 1"}
+
+
+@pytest.mark.parametrize("shape,quant,tokens,halves", [
+    (OPT[768], 0, 5440, False), (OPT[768], 0, 5504, True), (LLAMA[1024], 0, 3008, False), (LLAMA[1024], 0, 3072, True),
+    (LLAMA[1024], 0, 4608, True), (LLAMA[1024], 0, 5120, False), (LLAMA[1024], 1, 5120, True),
+    # both wide projections a little over one round of 256-wide tiles; the tokens and widths next to them, and gate and up
+    (OPT[2560], 0, 2304, False), (OPT[2560], 0, 2560, True), (OPT[2560], 0, 2816, False), (OPT[2048], 0, 3072, False), (OPT[3072], 0, 2048, False),
+    (LLAMA[2048], 0, 3072, False), (LLAMA[3072], 0, 3328, False),
+    (OPT[2560], 1, 2048, False), (OPT[2560], 1, 2560, True), (OPT[2560], 1, 3328, True), (OPT[2560], 1, 3840, False), (OPT[2048], 1, 2560, True),
+    (OPT[2048], 1, 2816, True), (OPT[2048], 1, 3328, True), (OPT[2048], 1, 3584, False), (OPT[3072], 1, 1536, True), (OPT[3072], 1, 2560, False),
+    (LLAMA[2048], 1, 4608, False), (LLAMA[3072], 1, 2048, False),
+    # never so few tokens that a half would split K (widths that have many tiles all the same)
+    ("2048 6144 66048 0", 1, 512, False), ("2048 6144 33024 0", 1, 512, False)])
+def test_sizes(shape, quant, tokens, halves):
+    assert ask([f"two_halves {shape} {quant} {tokens}"]) == [halves]
