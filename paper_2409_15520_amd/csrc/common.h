@@ -215,8 +215,6 @@ inline bool fetch_aligned(const MfmaGemmArgs& a) { return (((uintptr_t)a.w | (ui
 int mfma_gemm_splits(const MfmaGemmArgs& a, size_t partial_capacity);
 long mfma_gemm_split_blocks(const MfmaGemmArgs& a, size_t partial_capacity);   // ... and the blocks it would have
 bool mfma_gemm_supported(const MfmaGemmArgs& a);
-// will a dense [M, K] x [N, K]^T take the 256 x 256 tile (which fills the chip by itself)?
-bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights, bool int8_weights);
 int mfma_gemm_tile(const MfmaGemmArgs& a);          // the tile configuration that a launch takes (gate and up together: 6 or 1)
 bool two_halves_pay(int d, int nqkv, int d_ffn, bool gate_up, int weight_quant, long T);   // mpz_api.hip: the sizes of the two-halves schedule
 int mfma_gemm_ce_slots(const MfmaGemmArgs& a);      // partial slots per row the launch will write (depends on the tile)

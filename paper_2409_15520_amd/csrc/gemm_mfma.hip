@@ -1019,13 +1019,6 @@ __global__ void __launch_bounds__(1024) ce_combine_kernel(int slots, int M, cons
 
 }  // namespace
 
-// Does a pass whose Q|K|V projection this is take the 256-wide tiles?  Two halves on two streams with 128-wide ones beat the least filled
-// single round of them (d = 1024, 4608 tokens, 144 tiles, 12 layers: 2403 us in one pass, 2162 in two halves): from five eighths on.
-bool mfma_gemm_large_tiles(int M, int N, int K, bool bf16_weights, bool int8_weights) {
-  const long t5 = (long)((N + 255) / 256) * ((M + 255) / 256), t1 = (long)((N + 127) / 128) * ((M + 127) / 128);
-  return t5 >= 512 || (bf16_weights && K % 128 == 0 && N % 8 == 0 && t5 * 8 >= (t5 + 255) / 256 * 256 * 5 && large_tiles_pay(t5, t1, K)) || (int8_weights && int8_large_tiles_pay(t5, t1, K));
-}
-
 int mfma_gemm_tile(const MfmaGemmArgs& a) { return !a.dual || a.k_splits > 1 ? choose_cfg(a) : dual_takes_large(a) ? 6 : 1; }
 
 int mfma_gemm_ce_slots(const MfmaGemmArgs& a0) {

@@ -873,8 +873,9 @@ void run_head(mpz_model* m, const float* h, const int32_t* tokens, const int32_t
 // Do T stacked tokens in two halves on two streams take less time than in one pass?  Twice the launches, each of half the work: that pays
 // once a launch is long enough to hide the next one's, and while blocks are short (12 layers, one pass / two halves, us; d = 768, 3072 /
 // 5120 / 6144 / 8192 tokens: 1270 / 1726 / 2101 / 2567 against 1358 / 1753 / 1998 / 2334; d = 1024, 2688 / 3072 / 4224: 1603 / 1847 / 2300 against
-// 1755 / 1769 / 2036; d = 1536, 1536 / 3072: 2335 / 3072 against 2467 / 2984), and not where Q|K|V takes the 256-wide tiles, which fill the
-// chip alone.  A half has more than the 256 tokens that split K, whose partial-sum buffer the halves would share.
+// 1755 / 1769 / 2036; d = 1536, 1536 / 3072: 2335 / 3072 against 2467 / 2984), and not where Q|K|V in 256-wide tiles fills the chip alone: from
+// two rounds on, and one round of bf16 weights from five eighths on (the least filled rounds are better in halves: d = 1024, 4608 tokens, 144 tiles,
+// 2403 us in one pass, 2162 in two halves).  A half has more than the 256 tokens that split K, whose partial-sum buffer the halves would share.
 // Wider models (d = 2048 to 3072, 4 layers, 1536 to 5120 tokens) lose 2 to 29 % by it, and more with gate and up, except where both wide
 // projections are a little over one round of 256-wide tiles, so that one pass leaves much of a second round idle (Q|K|V / up tiles, one
 // pass / two halves, us): bf16 300 / 270 1920 / 1745, but 288 / 384 1627 / 1614, 264 / 352 1525 / 1537, 330 / 297 1945 / 1867, 288 / 384 at
@@ -882,12 +883,13 @@ void run_head(mpz_model* m, const float* h, const int32_t* tokens, const int32_t
 // 216 / 288 at d = 3072 2127 / 1974, 312 / 416 1791 / 1793, but 360 / 480 1974 / 2049 and 240 / 216 1492 / 1561.
 bool mpz::two_halves_pay(int d, int nqkv, int d_ffn, bool gate_up, int weight_quant, long T) {
   const bool int8 = weight_quant == MPZ_WEIGHT_QUANT_INT8;
+  const long rows = (T + 255) / 256, qkv = (nqkv + 255) / 256 * rows;
   if (d < 2048) {
     if (T < 3072 || (double)T * d * d < 3.0 * (1 << 30)) return false;
-    return !(T <= INT32_MAX && mfma_gemm_large_tiles((int)T, nqkv, d, weight_quant == MPZ_WEIGHT_QUANT_NONE, int8));
+    return qkv < 512 && !(!int8 && d >= 1024 && d % 128 == 0 && nqkv % 8 == 0 && qkv >= 160 && qkv <= 256);
   }
   if (gate_up || T < 1536) return false;
-  const long rows = (T + 255) / 256, qkv = (nqkv + 255) / 256 * rows, up = (d_ffn + 255) / 256 * rows;
+  const long up = (d_ffn + 255) / 256 * rows;
   if (int8) return up > 256 && up <= 416 && qkv <= 416;
   return up > 256 && up < 320 && qkv > 256 && qkv < 320;
 }
