@@ -1,5 +1,5 @@
 // Few-token GEMM on 4-bit normal-float weights: out[M, N] = x w^T for M <= 256 stacked tokens, w = bf16(level[code] * max), for
-// projections with many weights (which: plan_stream in mpz_api.hip; the others look their codes up in gemm_bf16_kernel).
+// projections with many weights (which: gemm_codes_plan; the others look their codes up in gemm_bf16_kernel).
 //
 // What bounds it: the look-up (three vector instructions and an LDS read per weight), the matrix instructions and, where the runs
 // are short, the partial sums.  gemm_bf16_kernel looks every weight up once per 128 tokens and puts it into LDS, in turn with its
@@ -8,11 +8,12 @@
 //     of the wave that multiplies with it, and no dequantised weight goes through LDS;
 //   * the look-up of the next K-step stands between the matrix instructions of this one (written out: the compiler reads, waits
 //     and multiplies in turn);
-//   * the list of (feature tile, K-tile) pairs is dealt to one persistent block per CU in equal runs, as in gemm_stream.hip, and the
-//     raw sums go to the same reductions.
+//   * the list of (feature tile, K-tile) pairs is dealt to at most one persistent block per CU (three quarters of them where that ends
+//     runs with their tiles) in equal runs, as in gemm_stream.hip, and the raw sums go to the same reductions.
 // 7B shape, 192 tokens, in the model: gate and up 92 -> 61 us (their reduction 7.5 -> 12.6), Q|K|V 58 -> 45 (5.9 -> 9.1); two blocks
-// over 192 tokens 508 -> 454 us.  A K-tile takes 0.9 to 1.3 us of a CU (64 to 256 tokens; its matrix instructions 0.25 to 1.0), the
-// rest of a launch 6, the partial sums of 192 tokens 8.
+// over 192 tokens 508 -> 454 us.  Of whole runs from 32 to 128 K-tiles a K-tile takes a CU 1.1 / 1.3 / 1.6 / 2.0 us (64 / 128 / 192 / 256 tokens; its
+// matrix instructions 0.25 to 1.0), the rest of the launch with the partial sums and their reduction 15 / 20 / 22 / 31; a block that ends one
+// tile and begins the next stores two partial sums and ends some 8 us later.
 #include "gemm_tile.h"
 #include "fetch.h"
 #include <type_traits>
@@ -268,8 +269,10 @@ bool gemm_codes_supported(const MfmaGemmArgs& a) {
   return a.w_absmax != nullptr && a.M <= 256 && a.K % 64 == 0 && a.N % 4 == 0 && (a.dual ? 2 : 1) * (long)a.N < (1L << 20) && fetch_aligned(a) && !(a.dual && a.dual_offset != a.N);
 }
 
+namespace {
+
 // K-tiles per block: equal runs for 256 CUs, of at least four; 0 = the partial sums would not fit `capacity` floats
-int gemm_codes_units(const MfmaGemmArgs& a, size_t capacity) {
+int codes_units(const MfmaGemmArgs& a, size_t capacity) {
   const int nk = a.K / 64;
   const long units = (long)((a.N + kCodesTile - 1) / kCodesTile) * nk;
   long U = (units + 255) / 256;
@@ -279,6 +282,30 @@ int gemm_codes_units(const MfmaGemmArgs& a, size_t capacity) {
     if (nk % V == 0) { U = V; break; }
   while (U < nk && (size_t)stream_slots(nk, (int)U) * a.M * a.N > capacity) ++U;
   return (size_t)stream_slots(nk, (int)U) * a.M * a.N <= capacity ? (int)U : 0;
+}
+
+// Are runs of U K-tiles faster than shares of K in `share_blocks` blocks (two per CU) of gemm_bf16_kernel, which looks every code up once per
+// 128 tokens?  A run pays its partial sum of 256 features, 16 KB per 16 tokens, and the start of the stream with the look-ups it saves: those
+// of the second 128 tokens, and below that only what the look-up in the fragment registers saves.  Runs that do not end with their
+// tiles store more of them (see above), and shares that fill their rounds are at their best.  Shares / here, 64, 128, 192, 256 tokens:
+// whole runs of 8: 0.82 - 0.95, 0.83 - 0.98, 0.77 - 0.91, 0.75 - 0.84; 12: 0.92 - 0.93, 0.95 - 0.99, 1.09 - 1.13, 0.89 - 0.99; 14 to 17: 0.87 - 0.98, 0.93 - 1.03,
+// 1.08 - 1.19, 0.97 - 1.09; 18 to 24: 0.98 - 1.01, 1.03 - 1.06, 1.19 - 1.23, 1.07 - 1.12; 32 and more: 1.01 - 1.11, 1.03 - 1.15, 1.45 - 1.53, 1.29 - 1.35.
+// Runs that cross tiles, against full shares: 11 to 13: 0.85 - 0.89, 0.86 - 0.90, 0.94 - 1.11, 0.74 - 0.91; 17: 0.89, 0.93, 1.09, 0.95; 21: 0.91, 0.97;
+// against shares that leave CUs idle: 18 to 22: 1.00 - 1.16, 0.99 - 1.11, 1.20 - 1.56, 1.06 - 1.33.
+bool codes_pay(const MfmaGemmArgs& a, int U, long share_blocks) {
+  const int nk = a.K / 64;
+  const long units = (long)((a.N + kCodesTile - 1) / kCodesTile) * nk;
+  if (units <= 191L * U || U < (a.M <= 128 ? 18 : a.M <= 192 ? 12 : 14)) return false;       // (fewer blocks: only little room makes them)
+  const bool idle = share_blocks * 16 <= (share_blocks + 511) / 512 * 512 * 15;
+  return nk % U == 0 || idle || (a.M > 128 && a.M <= 192) || U >= (a.M <= 128 ? 32 : 18);
+}
+
+}  // namespace
+
+int gemm_codes_plan(const MfmaGemmArgs& a, size_t capacity, bool forced) {
+  if (!gemm_codes_supported(a)) return 0;
+  const int U = codes_units(a, capacity);
+  return U > 0 && (forced || codes_pay(a, U, mfma_gemm_split_blocks(a, capacity))) ? U : 0;
 }
 
 hipError_t launch_gemm_codes(hipStream_t st, const MfmaGemmArgs& a) {

@@ -392,13 +392,7 @@ bool plan_stream(MfmaGemmArgs& g, float* partial, size_t capacity, bool forced =
   MfmaGemmArgs b = g;
   if (g.dual) { b.dual = 0; b.N = 2 * g.N; }              // gate | up lie back to back: one product over 2 N rows
   if (g.w_absmax != nullptr) {
-    // 4-bit weights: gemm_codes.hip from twelve K-tiles of 256 features per CU on, sixteen up to 128 tokens.  Below, its partial sums
-    // (one of 256 features per CU at least) cost more than looking every weight up once saves; shares of K looked up in
-    // gemm_bf16_kernel -> here, us with the reduction: 12288 x 4096 64: 28 -> 32, 128: 38 -> 40, 192: 57 -> 46, 256: 60 -> 56;
-    // 22016 x 4096 64: 49 -> 42, 256: 93 -> 80; 4096 x 11008 (eleven) 128: 36 -> 39, 256: 51 -> 64; 11264 x 2048 (six) 192: 38 -> 43
-    if (!gemm_codes_supported(b)) return false;
-    if (!forced && (long)((b.N + kCodesTile - 1) / kCodesTile) * (b.K / 64) < 256 * (b.M <= 128 ? 16 : 12)) return false;
-    const int units = gemm_codes_units(b, capacity);
+    const int units = gemm_codes_plan(b, capacity, forced);
     if (units == 0) return false;
     const int slots = stream_slots(b.K / 64, units);
     g.stream_units = units; g.stream_bn = kCodesTile; g.k_splits = slots < 2 ? 2 : slots; g.partial = partial; g.ldp = b.N;

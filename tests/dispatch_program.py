@@ -38,6 +38,12 @@ int main() {
       if (a.rope_cols < 0) { a.rope_cols = 0; a.dual = 1; a.dual_offset = a.N; a.w_rows = 2 * a.N; }
       if (a.rope_cols) { a.rope_cos = a.rope_sin = (const float*)4096; a.S = a.M; }
       printf("%d\n", mfma_gemm_supported(a) ? mfma_gemm_tile(a) : -1);
+    } else if (!strcmp(what, "nf4_run")) {               // M, N, K of 4-bit weights, rows of partial sums there is room for: K-tiles per block of the streamed kernel
+      MfmaGemmArgs a{};
+      long rows;
+      if (scanf("%d %d %d %ld", &a.M, &a.N, &a.K, &rows) != 4) return 1;
+      a.w_rows = a.N; a.x = a.w = (const void*)4096; a.w_absmax = (const float*)4096; a.rows_per_copy = a.M;
+      printf("%d\n", gemm_codes_plan(a, (size_t)rows * a.N, false));
     } else if (!strcmp(what, "two_halves")) {            // d, columns of Q|K|V, d_ffn, gate and up, weight_quant, stacked tokens
       int d, nqkv, ffn, gate, quant, T;
       if (scanf("%d %d %d %d %d %d", &d, &nqkv, &ffn, &gate, &quant, &T) != 6) return 1;
