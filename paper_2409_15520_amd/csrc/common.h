@@ -203,8 +203,7 @@ __host__ __device__ inline int stream_slots_of(int tile, int nk, int units) { re
 __host__ __device__ inline int stream_slots(int nk, int units) { return nk % units == 0 ? nk / units : (nk + units - 2) / units + 1; }
 int gemm_stream_units(const MfmaGemmArgs& a, size_t capacity);
 hipError_t launch_gemm_stream(hipStream_t st, const MfmaGemmArgs& a);
-bool gemm_codes_supported(const MfmaGemmArgs& a);                            // gemm_codes.hip: 4-bit weights, few tokens
-// K-tiles per block of a plain product (gate and up: their 2 N rows); 0: not supported, no room, or (unless forced) shares of K are faster
+// gemm_codes.hip (4-bit weights, few tokens): K-tiles per block of a plain product (gate and up: their 2 N rows); 0: not supported, no room, or (unless forced) shares of K are faster
 int gemm_codes_plan(const MfmaGemmArgs& a, size_t capacity, bool forced);
 constexpr int kCodesTile = 256;                          // features of its tile
 hipError_t launch_gemm_codes(hipStream_t st, const MfmaGemmArgs& a);

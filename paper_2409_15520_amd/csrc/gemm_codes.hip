@@ -223,7 +223,7 @@ __global__ void __launch_bounds__(512, 1) gemm_codes_kernel(MfmaGemmArgs a) {
     if (u + 1 == u1 || kt + 1 == nk) {                   // the block's part of this tile ends here
       const int nw = tile * BN + wave * 32, first_u = tile * nk;
       if (u0 <= first_u) codes_low_rank<NJ>(a, acc, nw, lane);   // the block that began the tile adds the low-rank term
-      // (tokens past M fall outside the buffer, features past N are aimed outside: 256 rows stay below 2^31 bytes, gemm_codes_supported)
+      // (tokens past M fall outside the buffer, features past N are aimed outside: 256 rows stay below 2^31 bytes, codes_supported)
       const int slot = (int)blockIdx.x - first_u / U;
       const uint32_t row_p = (uint32_t)a.ldp * 4u;
       const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(a.partial + (size_t)slot * a.M * a.ldp, 0, (int)((uint32_t)a.M * row_p), 0x00020000);
@@ -263,13 +263,10 @@ hipError_t launch_codes(hipStream_t st, const MfmaGemmArgs& a, int grid) {
   return hipSuccess;
 }
 
-}  // namespace
-
-bool gemm_codes_supported(const MfmaGemmArgs& a) {
-  return a.w_absmax != nullptr && a.M <= 256 && a.K % 64 == 0 && a.N % 4 == 0 && (a.dual ? 2 : 1) * (long)a.N < (1L << 20) && fetch_aligned(a) && !(a.dual && a.dual_offset != a.N);
+// (gate and up come as one product over their 2 N rows)
+bool codes_supported(const MfmaGemmArgs& a) {
+  return !a.dual && a.w_absmax != nullptr && a.M <= 256 && a.K % 64 == 0 && a.N % 4 == 0 && a.N < 1 << 20 && fetch_aligned(a);
 }
-
-namespace {
 
 // K-tiles per block: equal runs for 256 CUs, of at least four; 0 = the partial sums would not fit `capacity` floats
 int codes_units(const MfmaGemmArgs& a, size_t capacity) {
@@ -303,7 +300,7 @@ bool codes_pay(const MfmaGemmArgs& a, int U, long share_blocks) {
 }  // namespace
 
 int gemm_codes_plan(const MfmaGemmArgs& a, size_t capacity, bool forced) {
-  if (!gemm_codes_supported(a)) return 0;
+  if (!codes_supported(a)) return 0;
   const int U = codes_units(a, capacity);
   return U > 0 && (forced || codes_pay(a, U, mfma_gemm_split_blocks(a, capacity))) ? U : 0;
 }
