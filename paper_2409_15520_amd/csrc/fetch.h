@@ -35,5 +35,10 @@ __device__ __forceinline__ i32x4 buffer_of(const void* p, size_t bytes) {
   return r;
 }
 
+// Stores through such a buffer (__builtin_amdgcn_raw_buffer_store_b128) keep the whole offset in the vector register and 0 in the
+// scalar one.  A store of 16 bytes reads its last registers some cycles after it was issued; the compiler waits for that before it
+// overwrites them, but not behind a store whose scalar offset is a register: sums that were cleared right behind such stores went to
+// memory as zeros, in one launch of a hundred.
+
 }  // namespace
 }  // namespace mpz

@@ -237,12 +237,7 @@ __global__ void __launch_bounds__(512, 1) gemm_codes_kernel(MfmaGemmArgs a) {
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), out, off[i] + (int)(j * 16 * row_p), 0, 0);
-      // a store reads its last registers some cycles after it was issued, and with a scalar offset the compiler does not wait for
-      // that: sums cleared right behind it were stored as zeros
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_nop 7\n\ts_nop 7" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), out, off[i] + (int)(j * 16 * row_p), 0, 0);   // (no scalar offset: fetch.h)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) acc[0][j] = acc[1][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       ++tile;

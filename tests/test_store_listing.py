@@ -1,0 +1,53 @@
+"""Stores of 16 bytes read their last registers some cycles after they were issued, and the compiler waits for that only where the scalar
+offset of the store is no register.  This test compiles the kernels that store accumulators through buffers and checks that form and
+the wait."""
+import os
+import re
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+from paper_2409_15520_amd import build
+
+WAIT_STATES = 2
+STORE = re.compile(r"buffer_store_dwordx([34]) v\[(\d+):(\d+)\], (?:v\d+|off), s\[\d+:\d+\], (\S+)")
+
+
+def _violations(lines):
+    data, found = [], []                                  # (registers of a store, wait states since)
+    for line in lines:
+        op, _, args = line.partition(" ")
+        if op.startswith("v_"):                            # (loads return long after)
+            dst = args.split(",")[0]
+            m = re.match(r"v\[(\d+):(\d+)\]|v(\d+)$", dst)
+            if m:
+                regs = {int(m[3])} if m[3] else set(range(int(m[1]), int(m[2]) + 1))
+                found += [line for r, age in data if age < WAIT_STATES and r & regs]
+        data = [(r, age + (int(args) + 1 if op == "s_nop" else 1)) for r, age in data if age < 8]
+        m = STORE.match(line)
+        if m:
+            if m[4] != "0":
+                found.append(line)
+            data.append((set(range(int(m[2]), int(m[3]) + 1)), 0))
+    return found
+
+
+def _lines(name, tmp_path):
+    out = tmp_path / f"{name}.s"
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *build.COMMON, "-S", "--cuda-device-only", "-o", str(out),
+                    os.path.join(build.CSRC, f"{name}.hip")], check=True, capture_output=True)
+    lines = [l.split(";")[0].strip() for l in out.read_text().splitlines()]
+    return [l for l in lines if l and not l.startswith(".") and not l.endswith(":")]
+
+
+def test_stores_wait_for_their_data(tmp_path):
+    with ThreadPoolExecutor(2) as ex:
+        for name, lines in zip(("gemm_codes", "gemm_pipe"), ex.map(lambda n: _lines(n, tmp_path), ("gemm_codes", "gemm_pipe"))):
+            assert sum(bool(STORE.match(l)) for l in lines) >= 64, name
+            assert not _violations(lines), (name, _violations(lines)[:3])
+
+
+def test_scan_sees_both_faults():
+    store = "buffer_store_dwordx4 v[4:7], v0, s[16:19], 0 offen"
+    assert not _violations([store, "s_nop 1", "v_mov_b32_e32 v7, 0"]) and not _violations([store, "v_mov_b32_e32 v8, 0"])
+    assert _violations([store, "v_mov_b32_e32 v7, 0"]) and _violations([store, "s_nop 0", "v_mov_b32_e32 v4, 0"])
+    assert _violations([store.replace(", 0 offen", ", s20 offen")])
