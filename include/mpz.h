@@ -328,6 +328,12 @@ mpz_status mpz_debug_set_split_k(mpz_model* m, int32_t enable);
 mpz_status mpz_debug_gemm_nf4_splitk(int32_t M, int32_t N, int32_t K, const void* x, const void* w_codes, const float* w_absmax,
                                      const float* bias, int32_t act, const float* residual, void* out, int32_t out_f32,
                                      int32_t k_splits, float* partial, size_t partial_elems, void* hip_stream);
+/* K-tiles of 64 that a block of the streamed kernel takes where the library would choose it for such weights, else 0. */
+int32_t mpz_debug_gemm_nf4_stream_units(int32_t M, int32_t N, int32_t K, int32_t dual, size_t partial_elems);
+/* The block-tile configuration that the library would choose for out[M, N] = x[M, K] w[N, K]^T with weights of weight_bits = 16 or 8 (bf16
+ * output, aligned operands, no low-rank terms): gate and up together (dual != 0), or the first rope_cols columns rotated in heads of
+ * rope_dh (0: none); -1 = no such launch. */
+int32_t mpz_debug_gemm_tile(int32_t M, int32_t N, int32_t K, int32_t dual, int32_t weight_bits, int32_t rope_cols, int32_t rope_dh);
 
 /* The same with weight-only int8 weights: w_codes [dev] int8 [N, K] (SwiGLU: [2N, K]), w_scale [dev] fp32 [N] ([2N]),
  * 16-byte aligned; out = act(x (codes * scale)^T + bias).  Tile configurations 1, 6, 11 and 12 only (others fall back to

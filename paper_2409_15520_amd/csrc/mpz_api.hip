@@ -1443,6 +1443,24 @@ int32_t mpz_debug_gemm_stream_units(int32_t M, int32_t N, int32_t K, int32_t dua
   return plan_stream(g, nullptr, partial_elems) ? g.stream_units : 0;
 }
 
+int32_t mpz_debug_gemm_nf4_stream_units(int32_t M, int32_t N, int32_t K, int32_t dual, size_t partial_elems) {
+  if (K % 64 || N % 4 || M < 1 || N < 1) return 0;
+  MfmaGemmArgs g{};
+  const void* some = (const void*)256;                     // (never read: alignment alone matters)
+  g.M = M; g.N = N; g.K = K; g.dual = dual != 0; g.dual_offset = dual ? N : 0; g.x = g.w = some; g.w_absmax = (const float*)some;
+  return plan_stream(g, nullptr, partial_elems) ? g.stream_units : 0;
+}
+
+int32_t mpz_debug_gemm_tile(int32_t M, int32_t N, int32_t K, int32_t dual, int32_t weight_bits, int32_t rope_cols, int32_t rope_dh) {
+  MfmaGemmArgs g{};
+  void* some = (void*)256;                                 // (never read: alignment alone matters)
+  g.M = M; g.N = N; g.K = K; g.dual = dual != 0; g.dual_offset = dual ? N : 0; g.w_rows = (dual ? 2 : 1) * N; g.x = g.w = g.out = some; g.ldo = N;
+  g.act = -1; g.rows_per_copy = M;
+  if (weight_bits == 8) g.w_scale = (const float*)some;
+  if (rope_cols > 0 && rope_dh > 0) { g.rope_cos = g.rope_sin = (const float*)some; g.rope_cols = rope_cols; g.rope_dh = rope_dh; g.S = M; }
+  return mfma_gemm_supported(g) ? mfma_gemm_tile(g) : -1;
+}
+
 mpz_status mpz_debug_gemm_int8(int32_t M, int32_t N, int32_t K, const void* x, const void* w_codes, const float* w_scale,
                                const float* bias, int32_t act, void* out, int32_t out_f32, int32_t tile_cfg,
                                void* hip_stream) {

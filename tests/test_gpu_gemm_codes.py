@@ -41,14 +41,22 @@ def test_streamed_codes(m, n, k, act, residual):
     assert err < (2e-6 if residual else 2.0 ** -8)         # fp32 sums of K products; bf16 rounding of the output
 
 
-@pytest.mark.parametrize("q,S,rank", [(1, 96, 16), (2, 64, 16), (4, 32, 8)])
-def test_block_with_low_rank_terms(q, S, rank):
-    """Q|K|V and gate, up of the 7B shape over 192 and 256 tokens of 2 to 8 copies, perturbed by as much as the adapters are large."""
+# Q|K|V and gate, up of the 7B shape, whose runs of Q|K|V (16 of 64 K-tiles) end with their tiles; a width of 5632, where a block ends one tile
+# (88 K-tiles in runs of 23) and begins the next one with its low-rank term
+@pytest.mark.parametrize("q,S,rank,d,run", [(1, 96, 16, 4096, 16), (2, 64, 16, 4096, 16), (4, 32, 8, 4096, 16), (1, 96, 16, 5632, 23), (4, 32, 8, 5632, 23)])
+def test_block_with_low_rank_terms(q, S, rank, d, run):
+    """192 and 256 tokens of 2 to 8 copies, perturbed by as much as the adapters are large."""
     import torch
     import workloads as W
     import paper_2409_15520_amd as M
     w = W.get_workload("c5_llama7b").with_(n_layers=1, q=q, E=1, S=S, weight_quant="nf4", lora_rank=rank, eps=0.05,
                                            lora_targets=("q", "k", "v"), loss_mode="last_pos_label_subset")
+    if d != w.d_model:
+        w = w.with_(d_model=d, n_heads=d // 128, n_kv_heads=d // 128, d_ffn=1024)
+    room = max(k * c for k, c in ((d // 4, 3 * d), (d // 4, 2 * w.d_ffn)))       # what a pass of 256 tokens has for its partial sums
+    assert M.mpz_debug_gemm_nf4_stream_units(2 * q * S, 3 * d, d, False, room) == run
+    if d == 4096:
+        assert M.mpz_debug_gemm_nf4_stream_units(2 * q * S, w.d_ffn, d, True, room) == 22
     frozen = M.device_random_weights(w, 1)
     masters = W.make_lora_masters(w, 2, b_std=0.05)
     tokens = torch.from_numpy(W.make_tokens(w, 3)).cuda()
