@@ -83,6 +83,7 @@ bool launch_lora_down_ordered(hipStream_t st, const LoraDownArgs& a);
 int64_t lora_down_ordered_blocks(const LoraDownArgs& a);                     // of its launch; 0: refused
 bool launch_linear_f64(hipStream_t st, const LinearArgs& a);
 bool launch_lora_down_f64(hipStream_t st, const LoraDownArgs& a);
+bool attention_f64_supported(const float* qkv, int qkv_stride, int n_seq, int S, int H, int dh);
 bool launch_attention_f64(hipStream_t st, const float* qkv, int qkv_stride, float* out, int n_seq, int S, int H, int Hkv, int dh, const int32_t* cu,
                           int E, int rows_per_copy);
 

@@ -289,12 +289,20 @@ __global__ void __launch_bounds__(256) attention_f64_kernel(const float* __restr
 
 }  // namespace
 
-// heads of 32 and 64 and up to 128 tokens (eight tiles of keys, which the registers hold); 16-byte rows
+// Heads of 32 and 64 and up to 128 tokens (eight tiles of keys, which the registers hold); 16-byte rows.  Eight tokens at least: of shorter
+// sequences most of a tile of queries is empty (2 / 4 tokens, 4 sequences of 12 heads: 4.3 / 4.4 us with a wave per query, 5.6 / 5.6 here; 256
+// sequences: 8.4 / 15.1 against 17.2 / 17.5).  From there to 16 many sequences gain what few lose (8 / 16 tokens, 4 sequences: 4.9 / 5.8 against
+// 5.7 / 5.9; 256: 29.9 / 68.1 against 18.7 / 20.9); the line is drawn by the tokens alone, so that a pass of one copy and a pass of all take the
+// same kernel and give the same bits.
+bool attention_f64_supported(const float* qkv, int qkv_stride, int n_seq, int S, int H, int dh) {
+  return (dh == 32 || dh == 64) && S >= 8 && S <= 128 && qkv_stride % 4 == 0 && qkv_stride < 1 << 24 && ((uintptr_t)qkv & 15) == 0 &&
+         (int64_t)n_seq * H * ((S + 15) / 16) * 256 <= (int64_t)UINT32_MAX;
+}
+
 bool launch_attention_f64(hipStream_t st, const float* qkv, int qkv_stride, float* out, int n_seq, int S, int H, int Hkv, int dh, const int32_t* cu,
                           int E, int rows_per_copy) {
-  if ((dh != 32 && dh != 64) || S > 128 || qkv_stride % 4 || qkv_stride >= 1 << 24 || ((uintptr_t)qkv & 15)) return false;
+  if (!attention_f64_supported(qkv, qkv_stride, n_seq, S, H, dh)) return false;
   const int64_t blocks = (int64_t)n_seq * H * ((S + 15) / 16);
-  if (blocks * 256 > (int64_t)UINT32_MAX) return false;
   const float scale = (float)(1.0 / sqrt((double)dh));
 #define MPZ_ATT(DH, MAXT) attention_f64_kernel<DH, MAXT><<<(unsigned)blocks, 256, 0, st>>>(qkv, qkv_stride, out, S, H, Hkv, scale, cu, E, rows_per_copy)
   if (dh == 64) { if (S <= 32) MPZ_ATT(64, 2); else if (S <= 64) MPZ_ATT(64, 4); else MPZ_ATT(64, 8); }

@@ -44,6 +44,10 @@ int main() {
       if (scanf("%d %d %d %ld", &a.M, &a.N, &a.K, &rows) != 4) return 1;
       a.w_rows = a.N; a.x = a.w = (const void*)4096; a.w_absmax = (const float*)4096; a.rows_per_copy = a.M;
       printf("%d\n", gemm_codes_plan(a, (size_t)rows * a.N, false));
+    } else if (!strcmp(what, "attention_f64")) {         // sequences, tokens, heads, columns of a head: taken?
+      int n, S, H, dh;
+      if (scanf("%d %d %d %d", &n, &S, &H, &dh) != 4) return 1;
+      printf("%d\n", (int)attention_f64_supported((const float*)4096, 3 * H * dh, n, S, H, dh));
     } else if (!strcmp(what, "two_halves")) {            // d, columns of Q|K|V, d_ffn, gate and up, weight_quant, stacked tokens
       int d, nqkv, ffn, gate, quant, T;
       if (scanf("%d %d %d %d %d %d", &d, &nqkv, &ffn, &gate, &quant, &T) != 6) return 1;

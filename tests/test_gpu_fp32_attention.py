@@ -43,6 +43,12 @@ def test_attention(H, Hkv, dh, S):
     assert (got != want).mean() < 1e-3
 
 
+# the first lengths that are taken, and the last that is not
+@pytest.mark.parametrize("S", [7, 8, 9])
+def test_short_sequences(S):
+    test_attention(6, 2, 64, S)
+
+
 @pytest.mark.parametrize("S,bad", [(16, 9), (33, 32), (70, 50)])
 def test_tokens_behind_a_query_do_not_reach_it(S, bad):
     H, dh = 2, 32
