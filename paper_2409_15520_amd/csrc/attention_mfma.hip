@@ -255,18 +255,27 @@ bool attention_mfma_supported(int dh, int qkv_stride, int d) {
   return (dh == 64 || dh == 128) && qkv_stride % 8 == 0 && d % 8 == 0;
 }
 
+// The scores of the only chunk stay in registers (ONE) unless operands and results together outgrow the last-level cache: then the
+// form that computes them twice is ahead (us, ONE / twice; 128 tokens, 32 heads of 64 over 4: 128 sequences, 151 MB, 46.8 / 50.0, 256, 302 MB,
+// 121 / 113.5; 96 tokens, 16 over 8: 151 MB 38.8 / 41.2, 302 MB 91.8 / 88.4; 32 over 32, 128 tokens: 268 MB 60.5 / 60.4, 537 MB 166 / 169; heads of 128: 64
+// tokens, 20 over 20: 168 MB 36.7 / 40.3, 335 MB 98.7 / 92.5; 16 over 2: 302 MB 111 / 123).  The same bits either way.
+bool attention_keeps_scores(int n_seq, int S, int qkv_stride, int d, int dh) {
+  return S <= (dh == 64 ? 128 : 64) && (size_t)n_seq * S * (qkv_stride + d) * 2 < (size_t)(dh == 64 ? 264 : 320) << 20;
+}
+
 void launch_attention_mfma(hipStream_t st, const void* qkv, int qkv_stride, void* out, int n_seq, int S, int H, int Hkv,
                            int dh, const int32_t* cu, int E, int rows_per_copy) {
   const int qblocks = (S + QB - 1) / QB;
   const unsigned blocks = (unsigned)((size_t)n_seq * H * qblocks);
   const float scale = (float)(1.0 / sqrt((double)dh));
+  const bool one = attention_keeps_scores(n_seq, S, qkv_stride, H * dh, dh);
   if (dh == 64 && S > 256)
     attention_mfma_kernel<64, 128, 4, false><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
-  else if (dh == 64 && S > 128)
+  else if (dh == 64 && !one)
     attention_mfma_kernel<64, 128, 2, false><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
   else if (dh == 64)
     attention_mfma_kernel<64, 128, 2, true><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
-  else if (S > 64)
+  else if (!one)
     attention_mfma_kernel<128, 64, 2, false><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
   else
     attention_mfma_kernel<128, 64, 2, true><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
