@@ -334,6 +334,9 @@ int32_t mpz_debug_gemm_nf4_stream_units(int32_t M, int32_t N, int32_t K, int32_t
  * output, aligned operands, no low-rank terms): gate and up together (dual != 0), or the first rope_cols columns rotated in heads of
  * rope_dh (0: none); -1 = no such launch. */
 int32_t mpz_debug_gemm_tile(int32_t M, int32_t N, int32_t K, int32_t dual, int32_t weight_bits, int32_t rope_cols, int32_t rope_dh);
+/* The fitted tile (20 to 26: 192 x 256, 256 x 192, 192 x 128, 128 x 192, 256 x 128, 128 x 128, int8 256 x 256 features x tokens) that takes the place of that
+ * configuration for the same launch, or -1: none does. */
+int32_t mpz_debug_gemm_fitted_tile(int32_t M, int32_t N, int32_t K, int32_t dual, int32_t weight_bits, int32_t rope_cols, int32_t rope_dh);
 
 /* The same with weight-only int8 weights: w_codes [dev] int8 [N, K] (SwiGLU: [2N, K]), w_scale [dev] fp32 [N] ([2N]),
  * 16-byte aligned; out = act(x (codes * scale)^T + bias).  Tile configurations 1, 6, 11 and 12 only (others fall back to
@@ -395,8 +398,8 @@ mpz_status mpz_debug_set_fused_norm_lora(mpz_model* m, int32_t enable);
  * kernel.  Same bits either way.  Invalidates the perturbed copies: call mpz_regen_noise again. */
 mpz_status mpz_debug_set_fused_perturb_pack(mpz_model* m, int32_t enable);
 
-/* Test hook: force one block-tile configuration (1, 6, 9, 10, 11, 12 or 15; 0 = chosen by shape) for every MFMA GEMM of the
- * model's passes that has it (15: rotated heads of 128), so that small test shapes can exercise the configurations large
+/* Test hook: force one block-tile configuration (1, 6, 9, 10, 11, 12, 15, or 20 to 26: the fitted tiles; 0 = chosen by shape) for every
+ * MFMA GEMM of the model's passes that has it (15: rotated heads of 128), so that small test shapes can exercise the configurations large
  * workloads select.  Errors: NULL, CONFIG. */
 mpz_status mpz_debug_set_tile_config(mpz_model* m, int32_t tile_cfg);
 

@@ -1181,6 +1181,7 @@ hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a) {
     splitk_reduce_kernel<<<(unsigned)((items + 255) / 256), 256, 0, st>>>(a);
     return hipSuccess;
   }
+  if (const int shape = gemm_fit_shape(a, mfma_gemm_tile(a)); shape >= 0) return launch_gemm_fit(st, a, shape);
   if (a.dual) {
     if (dual_takes_large(a)) {                            // 2 x 128 x 256
       if (gemm_pipe_supported(a)) return launch_gemm_pipe(st, a);

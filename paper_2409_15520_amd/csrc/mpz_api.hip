@@ -865,22 +865,24 @@ void run_head(mpz_model* m, const float* h, const int32_t* tokens, const int32_t
 }  // namespace
 
 // Do T stacked tokens in two halves on two streams take less time than in one pass?  Twice the launches, each of half the work: that pays
-// once a launch is long enough to hide the next one's, and while blocks are short (12 layers, one pass / two halves, us; d = 768, 3072 /
-// 5120 / 6144 / 8192 tokens: 1270 / 1726 / 2101 / 2567 against 1358 / 1753 / 1998 / 2334; d = 1024, 2688 / 3072 / 4224: 1603 / 1847 / 2300 against
-// 1755 / 1769 / 2036; d = 1536, 1536 / 3072: 2335 / 3072 against 2467 / 2984), and not where Q|K|V in 256-wide tiles fills the chip alone: from
-// two rounds on, and one round of bf16 weights from five eighths on (the least filled rounds are better in halves: d = 1024, 4608 tokens, 144 tiles,
-// 2403 us in one pass, 2162 in two halves).  A half has more than the 256 tokens that split K, whose partial-sum buffer the halves would share.
+// once a launch is long enough to hide the next one's, while blocks are short, and only where one pass leaves many CUs idle in the last
+// rounds of its tiles, which the other half's blocks then fill.  bf16 below d = 2048: from 3072 tokens and 3 x 2^30 of tokens x d^2 on (below,
+// twice the launches cost more: 12 layers of d = 768, 3072 tokens, 1270 us in one pass, 1358 in halves), where the tiles' work is less than 0.72 (d < 1024:
+// 0.73) of what their rounds hold (gemm_fit_filled; share, one pass / two halves of 4 layers, us: d = 768, 5504 / 6144 / 7168 / 8192 tokens 0.69 / 0.74 /
+// 0.81 / 0.82, 630 / 637 / 696 / 762 against 633 / 660 / 744 / 792; d = 1024, 3584 / 4096 / 4608 / 4864 tokens 0.72 / 0.80 / 0.72 / 0.79, 571 / 601 /
+// 729 / 1443 against 626 / 675 / 687 / 1456; but 3072 tokens, 0.69: 518 against 553).  int8 weights below d = 2048: while Q|K|V is below two rounds of
+// 256-wide tiles.  A half has more than the 256 tokens that split K, whose partial-sum buffer the halves would share.
 // Wider models (d = 2048 to 3072, 4 layers, 1536 to 5120 tokens) lose 2 to 29 % by it, and more with gate and up, except where both wide
-// projections are a little over one round of 256-wide tiles, so that one pass leaves much of a second round idle (Q|K|V / up tiles, one
-// pass / two halves, us): bf16 300 / 270 1920 / 1745, but 288 / 384 1627 / 1614, 264 / 352 1525 / 1537, 330 / 297 1945 / 1867, 288 / 384 at
-// d = 3072 2243 / 2391; int8, whose small tiles are nearer to its large ones, 264 / 352 1703 / 1593, 300 / 270 1938 / 1754, 390 / 351 2424 / 2241,
-// 216 / 288 at d = 3072 2127 / 1974, 312 / 416 1791 / 1793, but 360 / 480 1974 / 2049 and 240 / 216 1492 / 1561.
+// projections are a little over one round of 256-wide tiles (Q|K|V / up tiles, one pass / two halves, us): bf16 300 / 270 1746 / 1691,
+// but 288 / 384 1627 / 1614, 264 / 352 1525 / 1537, 288 / 384 at d = 3072 2243 / 2391; int8, whose small tiles are nearer to its large ones,
+// 264 / 352 1703 / 1593, 300 / 270 1938 / 1754, 390 / 351 2424 / 2241, 216 / 288 at d = 3072 2127 / 1974, 312 / 416 1791 / 1793, but 360 / 480
+// 1974 / 2049 and 240 / 216 1492 / 1561.
 bool mpz::two_halves_pay(int d, int nqkv, int d_ffn, bool gate_up, int weight_quant, long T) {
   const bool int8 = weight_quant == MPZ_WEIGHT_QUANT_INT8;
   const long rows = (T + 255) / 256, qkv = (nqkv + 255) / 256 * rows;
   if (d < 2048) {
     if (T < 3072 || (double)T * d * d < 3.0 * (1 << 30)) return false;
-    return qkv < 512 && !(!int8 && d >= 1024 && d % 128 == 0 && nqkv % 8 == 0 && qkv >= 160 && qkv <= 256);
+    return qkv < 512 && (int8 || gemm_fit_filled(d, nqkv, d_ffn, gate_up, T) < (d < 1024 ? 0.73 : 0.72));
   }
   if (gate_up || T < 1536) return false;
   const long up = (d_ffn + 255) / 256 * rows;
@@ -1078,11 +1080,11 @@ void forward_two_halves(mpz_model* m, const int32_t* tokens, const int32_t* labe
   (void)hipEventRecord(m->ev_fork, main);                   // the perturbed factors are ready on the caller's stream
   (void)hipStreamWaitEvent(m->stream2, m->ev_fork, 0);
   const size_t rows = (size_t)half * E * S;
-  // With the other half's kernels filling a block's first-load and last-store edges, the 128 x 128 tile does better
-  // with 4 waves of 64 x 64 (a third fewer LDS fragment reads) than with the 8 waves of 64 x 32 that hide those edges
-  // when a GEMM runs alone: 2.44 -> 2.37 ms per step on the 125M-shaped workload, 2.62 -> 2.77 without the halves.
+  // int8: with the other half's kernels filling a block's first-load and last-store edges, the 128 x 128 tile does better with 4 waves
+  // of 64 x 64 (a third fewer LDS fragment reads) than with the 8 waves of 64 x 32 that hide those edges when a GEMM runs alone.
+  // (bf16 halves take the tiles that fit half the tokens: 4 layers of d = 1024, 4608 tokens, 687 us against 781 with that tile.)
   const int saved_cfg = m->force_tile_cfg;
-  if (saved_cfg == 0) m->force_tile_cfg = 1;
+  if (saved_cfg == 0 && m->cfg.weight_quant == MPZ_WEIGHT_QUANT_INT8) m->force_tile_cfg = 1;
   for (int step = -1; step <= m->cfg.n_layers; ++step)       // embedding, the blocks one by one, the head
     for (int hf = 0; hf < 2; ++hf) {
       m->stream = streams[hf]; m->cb = hf * half; m->nc = half;
@@ -1451,14 +1453,25 @@ int32_t mpz_debug_gemm_nf4_stream_units(int32_t M, int32_t N, int32_t K, int32_t
   return plan_stream(g, nullptr, partial_elems) ? g.stream_units : 0;
 }
 
-int32_t mpz_debug_gemm_tile(int32_t M, int32_t N, int32_t K, int32_t dual, int32_t weight_bits, int32_t rope_cols, int32_t rope_dh) {
+static MfmaGemmArgs launch_of_shape(int32_t M, int32_t N, int32_t K, int32_t dual, int32_t weight_bits, int32_t rope_cols, int32_t rope_dh) {
   MfmaGemmArgs g{};
   void* some = (void*)256;                                 // (never read: alignment alone matters)
   g.M = M; g.N = N; g.K = K; g.dual = dual != 0; g.dual_offset = dual ? N : 0; g.w_rows = (dual ? 2 : 1) * N; g.x = g.w = g.out = some; g.ldo = N;
   g.act = -1; g.rows_per_copy = M;
   if (weight_bits == 8) g.w_scale = (const float*)some;
   if (rope_cols > 0 && rope_dh > 0) { g.rope_cos = g.rope_sin = (const float*)some; g.rope_cols = rope_cols; g.rope_dh = rope_dh; g.S = M; }
+  return g;
+}
+
+int32_t mpz_debug_gemm_tile(int32_t M, int32_t N, int32_t K, int32_t dual, int32_t weight_bits, int32_t rope_cols, int32_t rope_dh) {
+  const MfmaGemmArgs g = launch_of_shape(M, N, K, dual, weight_bits, rope_cols, rope_dh);
   return mfma_gemm_supported(g) ? mfma_gemm_tile(g) : -1;
+}
+
+int32_t mpz_debug_gemm_fitted_tile(int32_t M, int32_t N, int32_t K, int32_t dual, int32_t weight_bits, int32_t rope_cols, int32_t rope_dh) {
+  const MfmaGemmArgs g = launch_of_shape(M, N, K, dual, weight_bits, rope_cols, rope_dh);
+  const int shape = mfma_gemm_supported(g) ? gemm_fit_shape(g, mfma_gemm_tile(g)) : -1;
+  return shape < 0 ? -1 : 20 + shape;
 }
 
 mpz_status mpz_debug_gemm_int8(int32_t M, int32_t N, int32_t K, const void* x, const void* w_codes, const float* w_scale,
@@ -1545,8 +1558,8 @@ mpz_status mpz_debug_set_fused_perturb_pack(mpz_model* m, int32_t enable) {
 
 mpz_status mpz_debug_set_tile_config(mpz_model* m, int32_t tile_cfg) {
   if (!m) return fail(nullptr, MPZ_ERR_NULL, "mpz_debug_set_tile_config: NULL model");
-  if (!(tile_cfg == 0 || tile_cfg == 1 || tile_cfg == 6 || (tile_cfg >= 9 && tile_cfg <= 12) || tile_cfg == 15))
-    return fail(m, MPZ_ERR_CONFIG, "tile configuration must be 0 (by shape), 1, 6, 9, 10, 11, 12 or 15");
+  if (!(tile_cfg == 0 || tile_cfg == 1 || tile_cfg == 6 || (tile_cfg >= 9 && tile_cfg <= 12) || tile_cfg == 15 || (tile_cfg >= 20 && tile_cfg <= 26)))
+    return fail(m, MPZ_ERR_CONFIG, "tile configuration must be 0 (by shape), 1, 6, 9, 10, 11, 12, 15 or 20 to 26");
   m->force_tile_cfg = tile_cfg;
   return MPZ_OK;
 }

@@ -328,6 +328,13 @@ def mpz_debug_gemm_tile(M: int, N: int, K: int, dual: bool = False, weight_bits:
     return int(lib.mpz_debug_gemm_tile(M, N, K, int(dual), weight_bits, rope_cols, rope_dh))
 
 
+def mpz_debug_gemm_fitted_tile(M: int, N: int, K: int, dual: bool = False, weight_bits: int = 16, rope_cols: int = 0, rope_dh: int = 0) -> int:
+    lib = load_library()
+    lib.mpz_debug_gemm_fitted_tile.restype = C.c_int32
+    lib.mpz_debug_gemm_fitted_tile.argtypes = [C.c_int32] * 7
+    return int(lib.mpz_debug_gemm_fitted_tile(M, N, K, int(dual), weight_bits, rope_cols, rope_dh))
+
+
 def mpz_debug_set_split_k(handle, enable: bool):
     lib = load_library()
     lib.mpz_debug_set_split_k.restype = C.c_int
