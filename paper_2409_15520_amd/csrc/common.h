@@ -215,6 +215,7 @@ bool gemm_fit_supported(const MfmaGemmArgs& a, int shape);
 int gemm_fit_shape(const MfmaGemmArgs& a, int tile);
 double gemm_fit_filled(int d, int nqkv, int d_ffn, bool gate_up, long T);   // work of a block's four products over what the rounds of their tiles hold
 hipError_t launch_gemm_fit(hipStream_t st, const MfmaGemmArgs& a, int shape);
+hipError_t launch_gemm_fit_int8(hipStream_t st, const MfmaGemmArgs& a, int shape);   // gemm_fit_int8.hip
 // operands that may be fetched straight into LDS, 16 bytes at a time
 inline bool fetch_aligned(const MfmaGemmArgs& a) { return (((uintptr_t)a.w | (uintptr_t)a.x) & 15) == 0; }
 // k_splits a launch of these arguments would use given room for `partial_capacity` floats (1 = no split)

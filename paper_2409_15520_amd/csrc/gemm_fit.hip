@@ -14,17 +14,18 @@ hipError_t launch_fit_lr(hipStream_t st, const MfmaGemmArgs& a) {
 // shapes: 0 = 192 features x 256 tokens, 1 = 256 x 192, 2 = 192 x 128, 3 = 128 x 192, 4 = 256 x 128, 5 = 128 x 128; int8 weights: 1, 3, 4, 5 and
 // 6 = 256 x 256
 bool gemm_fit_supported(const MfmaGemmArgs& a, int shape) {
-  if (a.w_scale != nullptr || a.w_absmax != nullptr || a.k_splits > 1 || a.ce_max != nullptr || a.K % 64 || !fetch_aligned(a)) return false;
+  if (a.w_absmax != nullptr || a.k_splits > 1 || a.ce_max != nullptr || a.K % 64 || !fetch_aligned(a)) return false;
   if (a.act >= 0 && a.act != MPZ_ACT_RELU) return false;
   const int es = a.out_f32 ? 4 : 2;
   if (((uintptr_t)a.out | (uintptr_t)a.residual) & 15 || a.N * es % 16 || a.ldo * es % 16 || a.ldo > (1 << 21) || (uintptr_t)a.bias & 3) return false;
   if (!a.out_f32 && a.residual != nullptr) return false;
+  if ((uintptr_t)a.w_scale & 3) return false;
   const bool wide192 = shape == 0 || shape == 2, rope = a.rope_cos != nullptr;
   if (a.dual) { if (a.out_f32 || a.n_seg || a.act >= 0 || rope || wide192 || a.dual_offset % 4) return false; }
   if (rope) {
     if (a.out_f32 || a.act >= 0 || wide192 || (a.rope_dh != 64 && a.rope_dh != 128) || a.rope_cols % a.rope_dh) return false;
   }
-  if (shape == 6 || (a.out_f32 && a.act >= 0)) return false;
+  if ((a.out_f32 && a.act >= 0) || (a.w_scale != nullptr ? wide192 : shape == 6)) return false;
   if (a.n_seg) {
     if (a.act >= 0 || a.rows_per_copy % 32 || a.M % 32) return false;
     const int cols = rope ? a.rope_dh : wide192 ? 96 : 64;    // a wave's
@@ -111,6 +112,7 @@ double gemm_fit_filled(int d, int nqkv, int d_ffn, bool gate_up, long T) {
 }
 
 hipError_t launch_gemm_fit(hipStream_t st, const MfmaGemmArgs& a, int shape) {
+  if (a.w_scale != nullptr) return launch_gemm_fit_int8(st, a, shape);
 #define SHAPES(EPI)                                              \
   switch (shape) {                                               \
     case 1: return launch_fit_lr<4, 2, 4, 6, 2, EPI>(st, a);     \

@@ -31,7 +31,30 @@ def test_equals_the_staged_tile(m, n, k, act, f32, bias):
         assert torch.equal(out, outs[0]), cfg
 
 
-@pytest.mark.parametrize("quant", ["none"])
+@pytest.mark.parametrize("m,n,k", [(32, 256, 64), (300, 264, 192), (256, 256, 5504), (4640, 4360, 128), (6000, 4616, 64)])
+@pytest.mark.parametrize("act,f32,bias", [(-1, False, False), (0, False, True), (-1, True, True), (2, False, False), (2, False, True)])
+def test_int8_equals_the_staged_tile(m, n, k, act, f32, bias):
+    import torch
+    import paper_2409_15520_amd as M
+    g = torch.Generator(device="cuda").manual_seed(m * 7 + n + k + act)
+    nw = 2 * n if act == 2 else n
+    x = torch.randn(m, k, generator=g, device="cuda").bfloat16()
+    w = torch.randint(-127, 128, (nw, k), generator=g, device="cuda", dtype=torch.int8)
+    scale = torch.rand(nw, generator=g, device="cuda") * 1e-3 + 1e-4
+    b = torch.randn(nw, generator=g, device="cuda") if bias else None
+    st = torch.cuda.current_stream().cuda_stream
+    outs = []
+    for cfg in (1, 21, 23, 24, 25, 26):
+        out = torch.full((m + 1, n), -7.0, device="cuda", dtype=torch.float32 if f32 else torch.bfloat16)
+        M.mpz_debug_gemm_int8(m, n, k, x.data_ptr(), w.data_ptr(), scale.data_ptr(), None if b is None else b.data_ptr(), act, out.data_ptr(),
+                              f32, st, cfg)
+        assert bool((out[m] == -7.0).all())
+        outs.append(out[:m])
+    for out in outs[1:]:
+        assert torch.equal(out, outs[0])
+
+
+@pytest.mark.parametrize("quant", ["none", "int8"])
 @pytest.mark.parametrize("kind,heads,q,E,S,rank", [("rope64", 8, 4, 1, 64, 8), ("rope64", 8, 2, 3, 96, 16), ("rope128", 4, 2, 2, 64, 16),
                                                    ("rope128", 4, 5, 1, 32, 8), ("plain", 12, 4, 1, 64, 8), ("plain", 12, 3, 1, 160, 16)])
 def test_model_pass_with_a_fitted_tile_forced(kind, heads, q, E, S, rank, quant):
