@@ -5,12 +5,13 @@
 // Rounding P against the exact maximum makes the result independent of the key tiling, which a running
 // ("online") maximum would not be.
 //
-// One block = one (sequence, head) and 128 queries, 4 waves x 32 queries.  MFMA orientation: rows = keys
+// One block = one (sequence, head) and 128 or 256 queries, 32 per wave.  MFMA orientation: rows = keys
 // (A operand), columns = queries (B operand): a lane owns ONE query, so max / sum are in-lane plus one
 // cross-half shuffle, and the score registers are directly the B operand of the P V product
 // D[dv, q] = sum_key Vt[dv, key] P[key, q] (the key order inside an MFMA K-step is permuted identically
 // on both operands).
 #include "common.h"
+#include "fetch.h"
 
 namespace mpz {
 namespace {
@@ -20,31 +21,35 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-constexpr int QB = 128;   // queries per block
-
-// The softmax is VALU-bound at these head sizes (16 scores per lane and tile against 12 MFMAs), so the score
-// path is kept to one fma and one hardware exp2 per element: exp(scale (s - max)) = exp2(s c - max c) with
-// c = scale log2(e); masking only on tiles that touch the diagonal; bf16 rounding in hardware.
-
-// KC = keys per LDS chunk.  When every key the block can see fits one chunk, K and V are loaded once and both
-// passes run from LDS; otherwise each pass streams the chunks.
-// MINB = blocks per CU the register allocation is held to: 2 leaves 134 registers (3 waves per SIMD), 4 squeezes the
-// same code into 128 (4 waves per SIMD, no spills), which pays once a block streams several key chunks (S = 512:
-// 11.9 -> 11.1 ms per step on the 1.1B-shaped workload) and costs 3 % at S = 256, where a block lives for two.
-// ONE: no sequence is longer than a chunk (the launcher knows); the scores of pass 1 stay in registers and pass 2 takes them from
-// there instead of computing them again (4 sequences of 128, 12 heads of 64: 5.9 -> 5.1 us; 2 of 64, 32 heads of 128: 7.5 -> 5.5).
-template <int DH, int KC, int MINB, bool ONE>
-__global__ void __launch_bounds__(256, MINB) attention_mfma_kernel(const uint16_t* __restrict__ qkv, int qkv_stride,
+// The score path is one fma and one hardware exp2 per element: exp(scale (s - max)) = exp2(s c - max c) with c = scale log2(e); masking
+// only on tiles that touch the diagonal; bf16 rounding in hardware.
+//
+// K and V go straight into LDS as they lie in memory, in pieces of KC keys that take turns in a ring of NS slots: pass 1 takes the pieces of K,
+// pass 2 pairs of K and V.  V is read transposed
+// (ds_read_b64_tr_b16: lane i of 16 gets element i of four rows), so the operand V^T of the second product needs neither a transposition
+// through registers nor loads that touch a row with 16 bytes.  16-byte chunk c of row r lies at c ^ f(r), where f
+// keeps the reads of either operand out of each other's banks (K: 32 rows at one chunk; V: four rows at four chunks).
+// WV waves of 32 queries per block.  ONE: all keys fit half the ring (the launcher knows): each piece is fetched once, all at the start, and
+// the scores of pass 1 stay in registers.
+// What bounds it: instruction issue (a SIMD issues 63 % of the time, vector instructions 36 %: one fma and one exp2 at a quarter
+// of the rate per score) beside waits for the chain scores -> exp2 -> P V; the matrix cores are busy 27 % of it.  Few scalar instructions
+// matter therefore: constant waits, no bookkeeping of what is on its way (61 a tile instead of 114: 363 -> 343 us).  Against the form that moved K
+// and V through registers, with the same bits (us; sequences x tokens, heads over key-value heads of columns): 128 x 512, 32 / 4 of 64 397 -> 330,
+// 64 x 256 74 -> 54, 64 x 96 21.6 -> 15.9, 64 x 128, 12 / 12 of 64 14.0 -> 10.8, 16 x 512, 32 / 32 of 128 127 -> 93, 8 x 480, 20 / 20 of 128 51 -> 34.
+template <int DH, int KC, int NS, int WV, int MINB, bool ONE>
+__global__ void __launch_bounds__(64 * WV, MINB) attention_mfma_kernel(const uint16_t* __restrict__ qkv, int qkv_stride,
                                                              uint16_t* __restrict__ out, int S_grid, int H, int Hkv,
                                                              float scale, const int32_t* __restrict__ cu, int E,
                                                              int rows_per_copy) {
-  constexpr int KS = DH + 8;        // K chunk row stride (elements)
-  constexpr int VS = KC + 8;        // V^T chunk row stride
+  constexpr int QB = 32 * WV;       // queries per block
   constexpr int NJ = DH / 16;       // MFMA K-steps over the head dimension
   constexpr int NT = DH / 32;       // 32-row output tiles over the head dimension
-  __shared__ __align__(16) uint16_t sK[KC * KS];
-  __shared__ __align__(16) uint16_t sVt[DH * VS];
+  constexpr int CPR = DH / 8, RPF = 64 / CPR, PER = KC / RPF / WV;           // 16-byte chunks of a row, rows of a fetch, fetches of a wave per piece
+  constexpr uint32_t RB = DH * 2, PIECE = KC * RB;
+  static_assert(KC % (RPF * WV) == 0 && KC % 32 == 0, "pieces deal out evenly");
+  __shared__ __align__(256) unsigned char smem[NS * PIECE];
 
   // Hardware deals consecutive workgroups round-robin to the 8 XCDs; give each XCD a contiguous range of the
   // (sequence, head, query block) order instead, so that the blocks that read one sequence's K and V (all query
@@ -81,8 +86,39 @@ __global__ void __launch_bounds__(256, MINB) attention_mfma_kernel(const uint16_
   const int q0 = qb * QB + wave * 32;             // first query of this wave
   const int qi = q0 + lrow;                       // this lane's query
   const int qi_c = qi < S ? qi : S - 1;
-  const uint16_t* kbase = qkv + row0 * qkv_stride + d + kvh * DH;
-  const uint16_t* vbase = qkv + row0 * qkv_stride + d + dkv + kvh * DH;
+  const int last_q_block = qb * QB + QB - 1 < S ? qb * QB + QB - 1 : S - 1;
+  const int n = __builtin_amdgcn_readfirstlane(last_q_block / KC + 1);       // pieces of K (and of V) that any query of the block can see
+  const int wave_last_q = q0 + 31;
+
+  // this head's K as a buffer of S rows, its V dkv columns to the right in it: rows past the end read as zeros (their keys are masked)
+  const uint32_t stride_b = (uint32_t)qkv_stride * 2u, v_b = (uint32_t)dkv * 2u;
+  const i32x4 rsrc = buffer_of(qkv + row0 * qkv_stride + d + kvh * DH, (size_t)(S - 1) * stride_b + v_b + RB);
+  auto swizzle = [](int r) { return DH == 64 ? (r >> 1 & 1) * 4 + (r >> 2 & 1) * 2 + (r >> 3 & 1) : (r & 3) * 4 + (r >> 2 & 3); };
+  uint32_t voff[PER];
+#pragma unroll
+  for (int t = 0; t < PER; ++t) {
+    const int r = (wave * PER + t) * RPF + lane / CPR;
+    voff[t] = (uint32_t)r * stride_b + (uint32_t)(lane % CPR ^ swizzle(r)) * 16u;
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + (uint32_t)wave * (PER * 1024u);
+  auto fetch = [&](uint32_t soff, uint32_t slot) {
+#pragma unroll
+    for (int t = 0; t < PER; ++t) fetch_rows(rsrc, voff[t], soff, lds0 + slot + (uint32_t)t * 1024u);
+  };
+  // Pieces in the order of their use: ONE K_0 K_1 V_0 V_1 (all of them, at once), else K_0 .. K_n-1 and then K_0 V_0 K_1 V_1 ...; past the end
+  // nothing is read (an offset outside the buffer), so that the waits need not know where the end is
+  const uint32_t piece_b = (uint32_t)KC * stride_b;
+  auto piece_at = [&](int p) {
+    const int q = p - n;
+    return q < 0 ? (uint32_t)p * piece_b : q < 2 * n ? (uint32_t)(q >> 1) * piece_b + (q & 1 ? v_b : 0u) : 0x7fffff00u;
+  };
+  if constexpr (ONE) {
+#pragma unroll
+    for (int c = 0; c < NS; ++c) fetch((c % (NS / 2) < n ? (uint32_t)(c % (NS / 2)) * piece_b : 0x7ff00000u) + (c >= NS / 2 ? v_b : 0u), c * PIECE);
+  } else {
+#pragma unroll
+    for (int c = 0; c < NS - 1; ++c) fetch(piece_at(c), c * PIECE);
+  }
 
   // Q fragments (B operand): query qi, head-dim elements j*16 + lhalf*8 .. +7
   bf16x8 fq[NJ];
@@ -90,91 +126,66 @@ __global__ void __launch_bounds__(256, MINB) attention_mfma_kernel(const uint16_
     const uint16_t* qp = qkv + (row0 + qi_c) * qkv_stride + head * DH + lhalf * 8;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) fq[j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + j * 16));
+    // (used here, so that the wait for them stands here: inside the loops it would wait for the pieces on their way as well)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(fq[j]));
   }
 
-  const int last_q_block = (qb * QB + QB - 1 < S ? qb * QB + QB - 1 : S - 1);
-  const int n_chunks = ONE ? 1 : last_q_block / KC + 1;     // key chunks any query of the block can see
-  const int wave_last_q = q0 + 31;
-  constexpr int CPR = DH / 8;                     // 16-byte chunks per key row
+  // byte of this lane's first chunk in a piece of K (row lrow), and of its quarter of four rows of V (row 4 lhalf + i / 4, i = lane % 16; then
+  // eight rows on)
+  const uint32_t kaddr = (uint32_t)lrow * RB + (uint32_t)(lhalf ^ swizzle(lrow)) * 16u;
+  const int ti = lane & 15, vrow = lhalf * 4 + (ti >> 2), vchunk = (lane >> 4 & 1) * 2 + (ti >> 1 & 1);
+  const uint32_t vaddr0 = (uint32_t)vrow * RB + (uint32_t)(vchunk ^ swizzle(vrow)) * 16u + (uint32_t)(ti & 1) * 8u;
+  const uint32_t vaddr8 = (uint32_t)(vrow + 8) * RB + (uint32_t)(vchunk ^ swizzle(vrow + 8)) * 16u + (uint32_t)(ti & 1) * 8u;
 
-  // K / V chunks travel global -> registers -> LDS: the fetch of chunk c + 1 is issued right after chunk c has
-  // been published, so its latency hides behind the MFMAs on chunk c.
-  constexpr int KL = KC * CPR / 256;              // 16-byte pieces of a K chunk per thread
-  constexpr int VL = (KC / 2) * CPR / 256;        // key pairs x 8 head-dim elements per thread
-  static_assert(KC * CPR % 256 == 0 && (KC / 2) * CPR % 256 == 0, "chunks must deal out evenly");
-  u32x4 rk[KL], rv0[VL], rv1[VL];
-#define MPZ_FETCH_K(c)                                                             \
-  _Pragma("unroll") for (int it = 0; it < KL; ++it) {                              \
-    const int i = tid + 256 * it, key = i / CPR, ch = i % CPR;                     \
-    int kg = (c) * KC + key; kg = kg < S ? kg : S - 1;                             \
-    rk[it] = *(const u32x4*)(kbase + (size_t)kg * qkv_stride + ch * 8);            \
-  }
-#define MPZ_PUT_K()                                                                \
-  _Pragma("unroll") for (int it = 0; it < KL; ++it) {                              \
-    const int i = tid + 256 * it, key = i / CPR, ch = i % CPR;                     \
-    *(u32x4*)(sK + key * KS + ch * 8) = rk[it];                                    \
-  }
-  // V^T into LDS: a thread takes two consecutive keys and 8 head-dim elements and writes 8 words
-  // {V[key][dv], V[key+1][dv]}; consecutive lanes hold consecutive key pairs, so the 32-bit writes of a wave fall
-  // into consecutive banks (a per-element 16-bit scatter would serialise on a handful of banks).  Inside every
-  // group of 16 keys the pairs are stored in the order 0 1 4 5 2 3 6 7: the 8 keys of one MFMA K-step that a lane
-  // half needs (k + 4 lhalf + (0..3) and k + 8 + 4 lhalf + (0..3)) are then 16 contiguous bytes.
-#define MPZ_FETCH_V(c)                                                             \
-  _Pragma("unroll") for (int it = 0; it < VL; ++it) {                              \
-    const int i = tid + 256 * it, kp = i % (KC / 2), ch = i / (KC / 2);            \
-    int k0 = (c) * KC + 2 * kp, k1 = k0 + 1;                                       \
-    k0 = k0 < S ? k0 : S - 1; k1 = k1 < S ? k1 : S - 1;                            \
-    rv0[it] = *(const u32x4*)(vbase + (size_t)k0 * qkv_stride + ch * 8);           \
-    rv1[it] = *(const u32x4*)(vbase + (size_t)k1 * qkv_stride + ch * 8);           \
-  }
-#define MPZ_PUT_V()                                                                \
-  _Pragma("unroll") for (int it = 0; it < VL; ++it) {                              \
-    const int i = tid + 256 * it, kp = i % (KC / 2), ch = i / (KC / 2);            \
-    const int pp = kp & 7;                                                         \
-    uint32_t* dst = (uint32_t*)sVt + (kp & ~7) + ((pp & 1) | ((pp & 2) << 1) | ((pp & 4) >> 1)); \
-    _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                \
-      dst[(ch * 8 + 2 * e) * (VS / 2)] = (rv0[it][e] & 0xFFFFu) | (rv1[it][e] << 16);        \
-      dst[(ch * 8 + 2 * e + 1) * (VS / 2)] = (rv0[it][e] >> 16) | (rv1[it][e] & 0xFFFF0000u); \
-    }                                                                              \
-  }
   // raw scores (q . k, unscaled) of one 32-key tile against this wave's 32 queries; lane: query qi,
   // keys kt0 + (e/4)*8 + lhalf*4 + e%4.  Tiles that reach past the diagonal get -inf on the masked entries.
-#define MPZ_SCORE_TILE(t_local, kt0, sacc)                                         \
-  {                                                                                \
-    _Pragma("unroll") for (int e = 0; e < 16; ++e) sacc[e] = 0.f;                  \
-    _Pragma("unroll") for (int j = 0; j < NJ; ++j) {                               \
-      bf16x8 fk = __builtin_bit_cast(bf16x8, *(const u32x4*)(sK + ((t_local) * 32 + lrow) * KS + j * 16 + lhalf * 8)); \
-      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk, fq[j], sacc, 0, 0, 0);    \
-    }                                                                              \
-    if ((kt0) + 31 > q0) {                                                         \
-      _Pragma("unroll") for (int e = 0; e < 16; ++e) {                             \
-        int key = (kt0) + (e >> 2) * 8 + lhalf * 4 + (e & 3);                      \
-        sacc[e] = key <= qi ? sacc[e] : -INFINITY;                                 \
-      }                                                                            \
-    }                                                                              \
-  }
+  auto score_tile = [&](f32x16& sacc, const unsigned char* piece, int t, int kt0) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const bf16x8 fk = __builtin_bit_cast(bf16x8, *(const u32x4*)(piece + t * 32 * RB + (kaddr ^ (j * 32u))));
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk, fq[j], sacc, 0, 0, 0);
+    }
+    if (kt0 + 31 > q0) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int key = kt0 + (e >> 2) * 8 + lhalf * 4 + (e & 3);
+        sacc[e] = key <= qi ? sacc[e] : -INFINITY;
+      }
+    }
+  };
 
   // ---- pass 1: exact row maximum ----
   float mx = -1e30f;
-  f32x16 kept[ONE ? KC / 32 : 1];                 // ONE: the scores of the only chunk, for pass 2
-  MPZ_FETCH_K(0)
-  if (n_chunks == 1) { MPZ_FETCH_V(0) }
-  for (int c = 0; c < n_chunks; ++c) {
-    __syncthreads();                              // every wave is done with the previous chunk
-    MPZ_PUT_K()
-    if (n_chunks == 1) { MPZ_PUT_V() }
-    __syncthreads();
-    if (n_chunks > 1) {                           // next chunk of this pass, or the first one of pass 2
-      if (c + 1 < n_chunks) { MPZ_FETCH_K(c + 1) } else { MPZ_FETCH_K(0) MPZ_FETCH_V(0) }
-    }
+  constexpr int KEPT = ONE ? NS / 2 * (KC / 32) : 1;
+  f32x16 kept[KEPT];                              // ONE: the scores of all tiles, for pass 2
+  auto pass1 = [&](int c, uint32_t slot) {
+    const unsigned char* piece = smem + slot;
 #pragma unroll
     for (int t = 0; t < KC / 32; ++t) {
-      int kt0 = c * KC + t * 32;
+      const int kt0 = c * KC + t * 32;
       if (kt0 > wave_last_q) continue;            // tile entirely in this wave's future
-      f32x16& sc = kept[ONE ? t : 0];
-      MPZ_SCORE_TILE(t, kt0, sc)
+      f32x16& sc = kept[ONE ? (c * (KC / 32) + t) % KEPT : 0];
+      score_tile(sc, piece, t, kt0);
 #pragma unroll
       for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sc[e]);
+    }
+  };
+  uint32_t slot = 0;                              // byte of the slot of the piece in use
+  if constexpr (ONE) {
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NS / 2 * PER) : "memory");
+#pragma unroll
+    for (int c = 0; c < NS / 2; ++c)
+      if (c < n) pass1(c, c * PIECE);
+  } else {
+    for (int c = 0; c < n; ++c) {
+      // piece c has landed for the block and every wave is done with the piece before, whose slot is requested again
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * PER) : "memory");
+      fetch(piece_at(c + NS - 1), slot == 0 ? (NS - 1) * PIECE : slot - PIECE);
+      pass1(c, slot);
+      slot = slot + PIECE == NS * PIECE ? 0 : slot + PIECE;
     }
   }
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
@@ -189,20 +200,15 @@ __global__ void __launch_bounds__(256, MINB) attention_mfma_kernel(const uint16_
     for (int e = 0; e < 16; ++e) oacc[t][e] = 0.f;
   float lsum = 0.f;
   const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
-  for (int c = 0; c < n_chunks; ++c) {
-    if (n_chunks > 1) {
-      __syncthreads();
-      MPZ_PUT_K()
-      MPZ_PUT_V()
-      __syncthreads();
-      if (c + 1 < n_chunks) { MPZ_FETCH_K(c + 1) MPZ_FETCH_V(c + 1) }
-    }
+  auto pass2 = [&](int c, uint32_t kslot, uint32_t vslot) {
+    const unsigned char* piece = smem + kslot;
+    const unsigned char* vpiece = smem + vslot;
 #pragma unroll
     for (int t = 0; t < KC / 32; ++t) {
-      int kt0 = c * KC + t * 32;
+      const int kt0 = c * KC + t * 32;
       if (kt0 > wave_last_q) continue;
-      f32x16& sc = kept[ONE ? t : 0];
-      if constexpr (!ONE) MPZ_SCORE_TILE(t, kt0, sc)
+      f32x16& sc = kept[ONE ? (c * (KC / 32) + t) % KEPT : 0];
+      if constexpr (!ONE) score_tile(sc, piece, t, kt0);
       uint32_t pw[8];                             // 16 probabilities as bf16 pairs
 #pragma unroll
       for (int e = 0; e < 16; e += 2) {
@@ -216,35 +222,54 @@ __global__ void __launch_bounds__(256, MINB) attention_mfma_kernel(const uint16_
       // kt0 + 16h + lhalf*4 + (0..3) and kt0 + 16h + 8 + lhalf*4 + (0..3)
 #pragma unroll
       for (int hstep = 0; hstep < 2; ++hstep) {
-        u32x4 pfrag = {pw[hstep * 4], pw[hstep * 4 + 1], pw[hstep * 4 + 2], pw[hstep * 4 + 3]};
-        bf16x8 fp = __builtin_bit_cast(bf16x8, pfrag);
-        const int kl = t * 32 + hstep * 16 + lhalf * 8;   // this half's 8 keys of the step, as stored
+        const u32x4 pfrag = {pw[hstep * 4], pw[hstep * 4 + 1], pw[hstep * 4 + 2], pw[hstep * 4 + 3]};
+        const bf16x8 fp = __builtin_bit_cast(bf16x8, pfrag);
 #pragma unroll
         for (int vt = 0; vt < NT; ++vt) {
-          const u32x4 vfrag = *(const u32x4*)(sVt + (vt * 32 + lrow) * VS + kl);
+          typedef __attribute__((address_space(3))) s16x4 lds4;
+          const unsigned char* p = vpiece + (t * 32 + hstep * 16) * RB;
+          const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)(p + (vaddr0 ^ (vt * 64u)))));
+          const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4*)(p + (vaddr8 ^ (vt * 64u)))));
+          const u32x4 vfrag = {lo[0], lo[1], hi[0], hi[1]};
           oacc[vt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vfrag), fp, oacc[vt], 0, 0, 0);
         }
       }
     }
+  };
+  if constexpr (ONE) {
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int c = 0; c < NS / 2; ++c)
+      if (c < n) pass2(c, c * PIECE, (NS / 2 + c) * PIECE);
+  } else {
+    static_assert(NS == 4, "two pairs of pieces");
+    for (int c = 0; c < n; ++c) {
+      // the pair has landed and every wave is done with the pair before, whose slots take the next one (its K is on its way since pass 1
+      // when c = 0)
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      const uint32_t vslot = slot == 3 * PIECE ? 0 : slot + PIECE, next = vslot == 3 * PIECE ? 0 : vslot + PIECE, next_v = next == 3 * PIECE ? 0 : next + PIECE;
+      if (c > 0) fetch(piece_at(n + 2 * c + 2), next);
+      fetch(piece_at(n + 2 * c + 3), next_v);
+      pass2(c, slot, vslot);
+      slot = next;
+    }
   }
-#undef MPZ_FETCH_K
-#undef MPZ_PUT_K
-#undef MPZ_FETCH_V
-#undef MPZ_PUT_V
-#undef MPZ_SCORE_TILE
   lsum += __shfl_xor(lsum, 32, 64);
 
+  // a lane has four elements of every eight of its query's row, its partner (lane ^ 32) the others: they exchange halves of neighbouring
+  // eights, so that each stores 16 bytes
   if (qi < S) {
     const float inv = 1.0f / lsum;
     uint16_t* op = out + (row0 + qi) * (size_t)d + head * DH;
 #pragma unroll
     for (int vt = 0; vt < NT; ++vt)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        int dv = vt * 32 + g * 8 + lhalf * 4;
-        u32x2 pk = {pack_bf16x2(oacc[vt][g * 4] * inv, oacc[vt][g * 4 + 1] * inv),
-                    pack_bf16x2(oacc[vt][g * 4 + 2] * inv, oacc[vt][g * 4 + 3] * inv)};
-        *(u32x2*)(op + dv) = pk;
+      for (int g = 0; g < 4; g += 2) {
+        const auto a = __builtin_amdgcn_permlane32_swap(pack_bf16x2(oacc[vt][g * 4] * inv, oacc[vt][g * 4 + 1] * inv),
+                                                        pack_bf16x2(oacc[vt][g * 4 + 4] * inv, oacc[vt][g * 4 + 5] * inv), false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap(pack_bf16x2(oacc[vt][g * 4 + 2] * inv, oacc[vt][g * 4 + 3] * inv),
+                                                        pack_bf16x2(oacc[vt][g * 4 + 6] * inv, oacc[vt][g * 4 + 7] * inv), false, false);
+        *(u32x4*)(op + vt * 32 + (g + lhalf) * 8) = u32x4{a[0], b[0], a[1], b[1]};
       }
   }
 }
@@ -255,30 +280,33 @@ bool attention_mfma_supported(int dh, int qkv_stride, int d) {
   return (dh == 64 || dh == 128) && qkv_stride % 8 == 0 && d % 8 == 0;
 }
 
-// The scores of the only chunk stay in registers (ONE) unless operands and results together outgrow the last-level cache: then the
-// form that computes them twice is ahead (us, ONE / twice; 128 tokens, 32 heads of 64 over 4: 128 sequences, 151 MB, 46.8 / 50.0, 256, 302 MB,
-// 121 / 113.5; 96 tokens, 16 over 8: 151 MB 38.8 / 41.2, 302 MB 91.8 / 88.4; 32 over 32, 128 tokens: 268 MB 60.5 / 60.4, 537 MB 166 / 169; heads of 128: 64
-// tokens, 20 over 20: 168 MB 36.7 / 40.3, 335 MB 98.7 / 92.5; 16 over 2: 302 MB 111 / 123).  The same bits either way.
+// Heads of 128 that share no keys: the scores stay in registers (ONE) unless operands and results together outgrow the last-level cache
+// (64 tokens, 20 heads over 20, ONE / twice: 128 sequences, 168 MB, 26.1 / 28; 256, 335 MB, 77.9 / 76.3; 512 153.3 / 152.6).  Everywhere else ONE is
+// ahead whatever the size (16 over 2 heads of 128, 920 sequences 149.5 / 173; heads of 64: 32 over 4, 256 x 128 tokens 87.7 / 99.7, 32 over 32 128.1 /
+// 139.8, 16 over 8, 768 x 96 100.3 / 116.1).  The same bits either way.
 bool attention_keeps_scores(int n_seq, int S, int qkv_stride, int d, int dh) {
   return S <= (dh == 64 ? 128 : 64) && (size_t)n_seq * S * (qkv_stride + d) * 2 < (size_t)(dh == 64 ? 264 : 320) << 20;
 }
 
 void launch_attention_mfma(hipStream_t st, const void* qkv, int qkv_stride, void* out, int n_seq, int S, int H, int Hkv,
                            int dh, const int32_t* cu, int E, int rows_per_copy) {
-  const int qblocks = (S + QB - 1) / QB;
-  const unsigned blocks = (unsigned)((size_t)n_seq * H * qblocks);
   const float scale = (float)(1.0 / sqrt((double)dh));
-  const bool one = attention_keeps_scores(n_seq, S, qkv_stride, H * dh, dh);
-  if (dh == 64 && S > 256)
-    attention_mfma_kernel<64, 128, 4, false><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
-  else if (dh == 64 && !one)
-    attention_mfma_kernel<64, 128, 2, false><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
-  else if (dh == 64)
-    attention_mfma_kernel<64, 128, 2, true><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
-  else if (!one)
-    attention_mfma_kernel<128, 64, 2, false><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
-  else
-    attention_mfma_kernel<128, 64, 2, true><<<blocks, 256, 0, st>>>((const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy);
+  const bool one = S <= (dh == 64 ? 128 : 64) && (dh == 64 || H > Hkv || attention_keeps_scores(n_seq, S, qkv_stride, H * dh, dh));
+  // eight waves fetch a key once for 256 queries: heads of 64 whose last 256 are at least three quarters there (128 x 512, 32 over 4 345 -> 330 us, 64 x
+  // 256 58.8 -> 53.8; 416 tokens 43.3 -> 44.3, 288 11.4 -> 16.6; heads of 128, 512 tokens 93 -> 107)
+  const bool eight = dh == 64 && S > 128 && (S - 1) % 256 >= 191;
+#define LAUNCH(DH, KC, NS, WV, MINB, ONE)                                                                                    \
+  attention_mfma_kernel<DH, KC, NS, WV, MINB, ONE><<<(unsigned)((size_t)n_seq * H * ((S + 32 * WV - 1) / (32 * WV))), 64 * WV, 0, st>>>( \
+      (const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy)
+  if (dh == 64) {
+    if (one) LAUNCH(64, 64, 4, 4, 2, true);
+    else if (eight) LAUNCH(64, 64, 4, 8, 4, false);
+    else LAUNCH(64, 64, 4, 4, 4, false);
+  } else {
+    if (one) LAUNCH(128, 32, 4, 4, 2, true);
+    else LAUNCH(128, 32, 4, 4, 2, false);
+  }
+#undef LAUNCH
 }
 
 }  // namespace mpz
