@@ -891,6 +891,12 @@ bool cfg_ok(const MfmaGemmArgs& a, int cfg) {
 // 64-feature tiles (twice the blocks); a dual launch has one tile shape.
 int split_tile_bn(const MfmaGemmArgs& a) { return (a.dual || a.N >= 8192 || a.K >= 8192 || a.w_scale != nullptr || a.w_absmax != nullptr) ? 128 : 64; }
 
+// 4-bit codes, 129 to 192 tokens: one tile of all tokens looks a code up once instead of twice, on half the blocks (one per CU where two of 128
+// tokens stand): ahead while those are most of the CUs (feature tiles x splits 144 to 192: 12288 x 4096 60.6 -> 55.1 us, 4096 x 11008 51.0 -> 46.6, 4096 x 4096
+// 32.5 -> 29.9, 6144 x 2048, 160 tokens, 28.9 -> 27.1; 128: 2048 x 5632 24.2 -> 26.9, 8192 x 2048 27.3 -> 30.4; and tiles of 256 tokens, 193 to 256 tokens, 3 - 45 %
+// behind).  The cuts of K and so the sums stay.
+bool nf4_all_tokens(const MfmaGemmArgs& a) { return a.M > 128 && a.M <= 192 && (long)((a.N + 127) / 128) * a.k_splits >= 144; }
+
 // Do `tiles` 256 x 256 tiles (one per CU at a time) beat the `small` 128 x 128 ones of the same product (two per CU at a time)?  Always from
 // two full rounds of 256 CUs on.  Below that the time of either goes in steps, one per round: a round of the persistent kernel of
 // gemm_pipe.hip beats three half rounds of small tiles and not two (K = 1024 / 2048 / 4096, time of the small tiles over its own: up to
@@ -1165,8 +1171,10 @@ hipError_t launch_gemm_mfma(hipStream_t st, const MfmaGemmArgs& a) {
     if (a.dual && a.dual_offset == a.N) { b.dual = 0; b.N = 2 * a.N; }
     if (a.stream_units > 0) e = a.w_absmax != nullptr ? launch_gemm_codes(st, b) : launch_gemm_stream(st, b);
     else if (b.dual) e = q8 ? launch_cfg<128, 128, 32, 2, 2, true, 0, true>(st, a) : launch_cfg<128, 128, 32, 2, 2, true>(st, a);
-    else if (a.w_absmax != nullptr)          // 4-bit codes looked up in the operand load: the two 128-feature tiles
-      e = choose_cfg(b) == 9 ? launch_cfg<128, 64, 64, 2, 2, false, 0, 2>(st, b) : launch_cfg<128, 128, 64, 2, 2, false, 0, 2>(st, b);
+    else if (a.w_absmax != nullptr)          // 4-bit codes looked up in the operand load: the 128-feature tiles
+      e = choose_cfg(b) == 9 ? launch_cfg<128, 64, 64, 2, 2, false, 0, 2>(st, b)
+          : nf4_all_tokens(b)  ? launch_cfg<128, 192, 64, 2, 2, false, 0, 2>(st, b)
+                               : launch_cfg<128, 128, 64, 2, 2, false, 0, 2>(st, b);
     else
       switch (choose_cfg(b)) {
         case 9: e = q8 ? launch_cfg<128, 64, 64, 2, 2, false, 0, true>(st, b) : launch_cfg<128, 64, 64, 2, 2, false>(st, b); break;
