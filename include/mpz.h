@@ -300,7 +300,8 @@ mpz_status mpz_debug_attention(mpz_model* m, const void* qkv, int32_t n_seq, int
 
 /* Test / measurement hook: the bf16 MFMA GEMM alone, out[M, N] = act(x[M, K] w[N, K]^T + bias), all [dev], x and w bf16,
  * out bf16 or fp32 (out_f32), act = -1 (none), MPZ_ACT_RELU, MPZ_ACT_GELU_ERF, or MPZ_ACT_SWIGLU (then w has 2N rows,
- * gate then up, bias 2N, out = SiLU(gate) * up); tile_cfg 0 = chosen by shape; 1, 6, 9, 10, 11, 12, 14 = that block-tile configuration (other numbers fall back to the choice by shape).  Errors: NULL, SHAPE (K % 64, N % 4). */
+ * gate then up, bias 2N, out = SiLU(gate) * up); tile_cfg 0 = chosen by shape; 1, 6, 9, 10, 11, 12, 14 = that block-tile configuration, 20 to 25 = that
+ * fitted tile where it takes the launch (otherwise, and other numbers: the choice by shape).  Errors: NULL, SHAPE (K % 64, N % 4). */
 mpz_status mpz_debug_gemm_bf16(int32_t M, int32_t N, int32_t K, const void* x, const void* w, const float* bias,
                                int32_t act, void* out, int32_t out_f32, int32_t tile_cfg, void* hip_stream);
 /* The same GEMM through the split-K path that passes over at most 256 stacked tokens take (k_splits blocks per output
@@ -339,7 +340,7 @@ int32_t mpz_debug_gemm_tile(int32_t M, int32_t N, int32_t K, int32_t dual, int32
 int32_t mpz_debug_gemm_fitted_tile(int32_t M, int32_t N, int32_t K, int32_t dual, int32_t weight_bits, int32_t rope_cols, int32_t rope_dh);
 
 /* The same with weight-only int8 weights: w_codes [dev] int8 [N, K] (SwiGLU: [2N, K]), w_scale [dev] fp32 [N] ([2N]),
- * 16-byte aligned; out = act(x (codes * scale)^T + bias).  Tile configurations 1, 6, 11 and 12 only (others fall back to
+ * 16-byte aligned; out = act(x (codes * scale)^T + bias).  Tile configurations 1, 6, 11, 12, 21 and 23 to 26 only (others fall back to
  * the choice by shape). */
 mpz_status mpz_debug_gemm_int8(int32_t M, int32_t N, int32_t K, const void* x, const void* w_codes, const float* w_scale,
                                const float* bias, int32_t act, void* out, int32_t out_f32, int32_t tile_cfg,

@@ -179,7 +179,7 @@ struct MfmaGemmArgs {
   const float* residual;        // [M, ldo] fp32 or null
   int out_f32; void* out; int ldo;
   int tile_cfg;                 // 0 = choose by shape; 1, 6, 9 .. 15 force that tile configuration (tests; 13: split K only, 14: what
-                                // gemm_ring_supported takes, 15: rotated heads of 128)
+                                // gemm_ring_supported takes, 15: rotated heads of 128), 20 .. 26 shape 0 .. 6 of gemm_fit.hip
   // fused rotary embedding (bf16 output only): columns [0, rope_cols) are heads of width rope_dh rotated by the
   // position m % S with tables [max_seq, rope_dh / 2]; packed batches: position rope_pos[m % S] (S = rows per copy)
   const float* rope_cos; const float* rope_sin; int rope_cols, rope_dh, S;

@@ -3,9 +3,9 @@
 //
 // What bounds it.  The time of such a product is its number of rounds of 256 tiles times the time of a tile: with 128 x 128 and 256 x 256
 // tiles alone the last round is often nearly empty.  Inside the K loop the shapes differ little (ns per K-tile of 64 with every CU
-// busy: 256 x 192 and 192 x 256 1080, 256 x 128 800, 192 x 128 590, 128 x 128 400: 1300 to 1460 TFLOP/s), because all of them keep two or
+// busy, fitted: 192 x 256 1034, 256 x 192 1060, 256 x 128 725, 192 x 128 580, 128 x 128 434: 1240 to 1560 TFLOP/s), because all of them keep two or
 // more K-tiles in flight without registers to stage them and meet at one barrier per K-tile; what a smaller tile loses is the operand
-// traffic of its CU (90 GB/s at most).  So there are five shapes, and gemm_fit_tile takes the one that fills its rounds.
+// traffic of its CU (90 GB/s at most).  So there are five shapes, and gemm_fit_shape takes the one that fills its rounds.
 //   * A K-tile (64) of BN + BM rows of 128 bytes lies in one of ST stages, 16-byte chunk c of row r at c ^ ((r / 2) % 8) (the fetch
 //     applies that order through each lane's global address; fragment reads then meet no bank twice).
 //   * A K-tile is two K-steps of 32.  Each step's matrix instructions cover the fragment reads of the next.  Behind the first
