@@ -181,52 +181,54 @@ __global__ void __launch_bounds__(256) splitk_reduce_norm_kernel(MfmaGemmArgs a,
 }
 
 // ---- pre-norm fused with the LoRA bottleneck of the projections that read its output ------------------------
-// One block = 32 token rows.  Phase A is norm_rows_kernel's arithmetic (each wave takes 8 of the rows, RB at a time
+// One block = 32 token rows.  Phase A is norm_rows_kernel's arithmetic (each wave takes 32 / WV of the rows, RB at a time
 // so that their loads travel together); the bf16 row goes to global memory for the GEMM and to an LDS tile.  Phase B
-// is lora_down_mfma_kernel's arithmetic on that tile - same K split over the 4 waves, same order of the partial sums,
+// is lora_down_mfma_kernel's arithmetic on that tile - same K split over 4 waves, same order of the partial sums,
 // so t has the same bits - without reading x again, without chunk staging and without its launch.  A block's life is a chain of
 // round trips to memory: gains and factors are requested with the rows (d = 768, 512 rows: 14.3 -> 11.4 us; 4096 rows beside
-// the other half's GEMMs: 24.2 -> 16.9 us).
+// the other half's GEMMs: 24.2 -> 16.9 us).  At d = 2048 the x tile leaves room for one block per CU: eight waves, so that all 32 rows travel
+// at once, and waves 4 to 7 take the second 32 bottleneck columns (three targets of rank 16, four waves -> eight: 65536 rows 235 -> 223 us; a 1.1B block
+// of 1024 / 1152 / 8192 tokens 161.6 -> 159.0 / 175.0 -> 171.8 / 698.6 -> 694.4).
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-template <int NV, int JT>   // d = 256 NV; JT 32-row MFMA tiles cover n_targets * rank bottleneck columns
-__global__ void __launch_bounds__(256, NV <= 4 ? 2 : 1) norm_lora_kernel(int kind, float eps, const float* __restrict__ h,
+template <int NV, int JT, int WV>   // d = 256 NV; JT 32-row MFMA tiles cover n_targets * rank bottleneck columns; WV waves
+__global__ void __launch_bounds__(WV * 64, NV <= 4 || WV == 8 ? 2 : 1) norm_lora_kernel(int kind, float eps, const float* __restrict__ h,
                                                                        const float* __restrict__ g,
                                                                        const float* __restrict__ b,
                                                                        uint16_t* __restrict__ out, MfmaLoraDownArgs a) {
-  constexpr int D = 256 * NV, XS = D + 8, RB = NV <= 4 ? 8 : 4;
+  constexpr int D = 256 * NV, XS = D + 8, RB = NV <= 4 ? 8 : 4, ROWS = 32 / WV, JW = WV == 8 ? 1 : JT;
   extern __shared__ __align__(16) unsigned char smem[];
   uint16_t* xs = (uint16_t*)smem;                      // [32][XS]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lrow = lane & 31, lhalf = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, share = wave & 3, t0 = wave >> 2, lrow = lane & 31, lhalf = lane >> 5;
   const int m0 = blockIdx.x * 32;
 
   // phase B: t = scale * x (A_hi + A_lo) for the block's copy; wave w owns K-elements 256 ch + 64 w + (0..63).  Its first factors
   // (all of them if the row is short) are requested behind the rows of phase A and travel during it
   const int copy = m0 / a.rows_per_copy;
   const int R = a.n_targets * a.rank;
-  const uint16_t* Ah[JT];
-  const uint16_t* Al[JT];
-  bool valid[JT];
+  const uint16_t* Ah[JW];
+  const uint16_t* Al[JW];
+  bool valid[JW];
 #pragma unroll
-  for (int t = 0; t < JT; ++t) {
-    int j = t * 32 + lrow;
+  for (int t = 0; t < JW; ++t) {
+    int j = (t0 + t) * 32 + lrow;
     valid[t] = j < R;
     int jj = valid[t] ? j : 0;
     int tgt = jj / a.rank, jr = jj % a.rank;
     const uint16_t* base = (const uint16_t*)a.ap[tgt] + (size_t)copy * a.copy_stride;
-    Ah[t] = base + ((size_t)(wave * 8 + lhalf) * a.rank + jr) * 8;      // [2][K / 8][rank][8], as in lora_down_mfma_kernel
+    Ah[t] = base + ((size_t)(share * 8 + lhalf) * a.rank + jr) * 8;      // [2][K / 8][rank][8], as in lora_down_mfma_kernel
     Al[t] = Ah[t] + (size_t)D * a.rank;
   }
   constexpr int PF = NV <= 3 && JT == 1 ? NV : 1, NS = PF == NV ? NV : 2;   // chunks requested ahead, register sets
   const u32x4 zero = {0u, 0u, 0u, 0u};
-  u32x4 fh[NS][4][JT], fl[NS][4][JT];
+  u32x4 fh[NS][4][JW], fl[NS][4][JW];
   auto request = [&](int ch) {
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4)
 #pragma unroll
-      for (int t = 0; t < JT; ++t) {
+      for (int t = 0; t < JW; ++t) {
         fh[ch % NS][s4][t] = *(const u32x4*)(Ah[t] + (size_t)(ch * 256 + s4 * 16) * a.rank);
         fl[ch % NS][s4][t] = *(const u32x4*)(Al[t] + (size_t)(ch * 256 + s4 * 16) * a.rank);
       }
@@ -235,11 +237,11 @@ __global__ void __launch_bounds__(256, NV <= 4 ? 2 : 1) norm_lora_kernel(int kin
 
   // ---- phase A: rows m0 + 8 wave + (0..7), RB at a time
 #pragma unroll 1
-  for (int r0 = 0; r0 < 8; r0 += RB) {
+  for (int r0 = 0; r0 < ROWS; r0 += RB) {
     f32x4 v[RB][NV];
 #pragma unroll
     for (int rr = 0; rr < RB; ++rr) {
-      const f32x4* hr = (const f32x4*)(h + (int64_t)(m0 + wave * 8 + r0 + rr) * D);
+      const f32x4* hr = (const f32x4*)(h + (int64_t)(m0 + wave * ROWS + r0 + rr) * D);
 #pragma unroll
       for (int i = 0; i < NV; ++i) v[rr][i] = hr[i * 64 + lane];
     }
@@ -268,7 +270,7 @@ __global__ void __launch_bounds__(256, NV <= 4 ? 2 : 1) norm_lora_kernel(int kin
 #pragma unroll
         for (int e = 0; e < 4; ++e) { float c = v[rr][i][e] - mean; q += c * c; }
       const float rstd = 1.0f / sqrtf(wave_sum_f32(q) / (float)D + eps);
-      const int row = wave * 8 + r0 + rr;
+      const int row = wave * ROWS + r0 + rr;
       u32x2* orow = (u32x2*)(out + (int64_t)(m0 + row) * D);
       u32x2* lrow_p = (u32x2*)(xs + row * XS);
 #pragma unroll
@@ -289,24 +291,24 @@ __global__ void __launch_bounds__(256, NV <= 4 ? 2 : 1) norm_lora_kernel(int kin
   __syncthreads();
 
   // ---- phase B
-  f32x16 acc[JT];
+  f32x16 acc[JW];
 #pragma unroll
-  for (int t = 0; t < JT; ++t)
+  for (int t = 0; t < JW; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
 #pragma unroll
   for (int ch = 0; ch < NV; ++ch) {
-    u32x4 ch_h[4][JT], ch_l[4][JT];
+    u32x4 ch_h[4][JW], ch_l[4][JW];
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4)
 #pragma unroll
-      for (int t = 0; t < JT; ++t) { ch_h[s4][t] = valid[t] ? fh[ch % NS][s4][t] : zero; ch_l[s4][t] = valid[t] ? fl[ch % NS][s4][t] : zero; }
+      for (int t = 0; t < JW; ++t) { ch_h[s4][t] = valid[t] ? fh[ch % NS][s4][t] : zero; ch_l[s4][t] = valid[t] ? fl[ch % NS][s4][t] : zero; }
     if (ch + PF < NV) request(ch + PF);                  // later factors travel during this chunk's MFMAs
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4) {
-      const bf16x8 fx = __builtin_bit_cast(bf16x8, *(const u32x4*)(xs + lrow * XS + ch * 256 + wave * 64 + s4 * 16 + lhalf * 8));
+      const bf16x8 fx = __builtin_bit_cast(bf16x8, *(const u32x4*)(xs + lrow * XS + ch * 256 + share * 64 + s4 * 16 + lhalf * 8));
 #pragma unroll
-      for (int t = 0; t < JT; ++t) {
+      for (int t = 0; t < JW; ++t) {
         acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ch_h[s4][t]), fx, acc[t], 0, 0, 0);
         acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ch_l[s4][t]), fx, acc[t], 0, 0, 0);
       }
@@ -314,26 +316,26 @@ __global__ void __launch_bounds__(256, NV <= 4 ? 2 : 1) norm_lora_kernel(int kin
   }
   __syncthreads();                                       // every wave is done with the x tile: its memory takes the sums
   float* part = (float*)smem;                            // [3][JT][16][64]: partial sums of waves 1..3
-  if (wave > 0) {
+  if (share > 0) {
 #pragma unroll
-    for (int t = 0; t < JT; ++t)
+    for (int t = 0; t < JW; ++t)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) part[(((wave - 1) * JT + t) * 16 + e) * 64 + lane] = acc[t][e];
+      for (int e = 0; e < 16; ++e) part[(((share - 1) * JT + t0 + t) * 16 + e) * 64 + lane] = acc[t][e];
   }
   __syncthreads();
-  if (wave != 0) return;
+  if (share != 0) return;
 #pragma unroll
-  for (int t = 0; t < JT; ++t)
+  for (int t = 0; t < JW; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e)
-      acc[t][e] = ((acc[t][e] + part[((0 * JT + t) * 16 + e) * 64 + lane]) + part[((1 * JT + t) * 16 + e) * 64 + lane]) +
-                  part[((2 * JT + t) * 16 + e) * 64 + lane];
+      acc[t][e] = ((acc[t][e] + part[((0 * JT + t0 + t) * 16 + e) * 64 + lane]) + part[((1 * JT + t0 + t) * 16 + e) * 64 + lane]) +
+                  part[((2 * JT + t0 + t) * 16 + e) * 64 + lane];
   const int m = m0 + lrow;
 #pragma unroll
-  for (int t = 0; t < JT; ++t)
+  for (int t = 0; t < JW; ++t)
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
-      const int j = t * 32 + gq * 8 + lhalf * 4;
+      const int j = (t0 + t) * 32 + gq * 8 + lhalf * 4;
       if (j >= R) continue;
       const int tgt = j / a.rank, jr = j % a.rank;
       const u32x2 pk = {pack_bf16x2(acc[t][gq * 4] * a.scale, acc[t][gq * 4 + 1] * a.scale),
@@ -342,21 +344,21 @@ __global__ void __launch_bounds__(256, NV <= 4 ? 2 : 1) norm_lora_kernel(int kin
       *(u32x2*)(row + jr) = pk;
       *(u32x2*)(row + a.rank + jr) = pk;
     }
-  if (lhalf == 0)
+  if (lhalf == 0 && t0 == 0)
     for (int tgt = 0; tgt < a.n_targets; ++tgt)
       for (int c = 2 * a.rank; c < a.rp; ++c) ((uint16_t*)a.tp[tgt])[(size_t)m * a.rp + c] = 0;
 }
 
-template <int NV, int JT>
+template <int NV, int JT, int WV = 4>
 void launch_norm_lora_t(hipStream_t st, int kind, float eps, const float* h, const float* g, const float* b, void* out,
                         const MfmaLoraDownArgs& a) {
   constexpr size_t lds = (size_t)32 * (256 * NV + 8) * 2;
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)norm_lora_kernel<NV, JT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipFuncSetAttribute((const void*)norm_lora_kernel<NV, JT, WV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     attr_set = true;
   }
-  norm_lora_kernel<NV, JT><<<a.T / 32, 256, lds, st>>>(kind, eps, h, g, b, (uint16_t*)out, a);
+  norm_lora_kernel<NV, JT, WV><<<a.T / 32, WV * 64, lds, st>>>(kind, eps, h, g, b, (uint16_t*)out, a);
 }
 
 }  // namespace
@@ -377,7 +379,7 @@ void launch_norm_lora(hipStream_t st, int kind, float eps, const float* h, const
   switch (a.K / 256) {
     case 3: if (two) launch_norm_lora_t<3, 2>(st, kind, eps, h, g, b, out, a); else launch_norm_lora_t<3, 1>(st, kind, eps, h, g, b, out, a); break;
     case 4: if (two) launch_norm_lora_t<4, 2>(st, kind, eps, h, g, b, out, a); else launch_norm_lora_t<4, 1>(st, kind, eps, h, g, b, out, a); break;
-    default: if (two) launch_norm_lora_t<8, 2>(st, kind, eps, h, g, b, out, a); else launch_norm_lora_t<8, 1>(st, kind, eps, h, g, b, out, a); break;
+    default: launch_norm_lora_t<8, 2, 8>(st, kind, eps, h, g, b, out, a); break;
   }
 }
 
