@@ -38,7 +38,9 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 // matter therefore: constant waits, no bookkeeping of what is on its way (61 a tile instead of 114: 363 -> 343 us).  Against the form that moved K
 // and V through registers, with the same bits (us; sequences x tokens, heads over key-value heads of columns): 128 x 512, 32 / 4 of 64 397 -> 330,
 // 64 x 256 74 -> 54, 64 x 96 21.6 -> 15.9, 64 x 128, 12 / 12 of 64 14.0 -> 10.8, 16 x 512, 32 / 32 of 128 127 -> 93, 8 x 480, 20 / 20 of 128 51 -> 34.
-template <int DH, int KC, int NS, int WV, int MINB, bool ONE>
+// FAR: the rows of a sequence span more than the 31 bits that the offsets into one buffer have (attention_far): each piece gets a buffer of its
+// own, whose base is computed in 64 bits.  The pieces, their order and the sums are the same.
+template <int DH, int KC, int NS, int WV, int MINB, bool ONE, bool FAR = false>
 __global__ void __launch_bounds__(64 * WV, MINB) attention_mfma_kernel(const uint16_t* __restrict__ qkv, int qkv_stride,
                                                              uint16_t* __restrict__ out, int S_grid, int H, int Hkv,
                                                              float scale, const int32_t* __restrict__ cu, int E,
@@ -49,6 +51,7 @@ __global__ void __launch_bounds__(64 * WV, MINB) attention_mfma_kernel(const uin
   constexpr int CPR = DH / 8, RPF = 64 / CPR, PER = KC / RPF / WV;           // 16-byte chunks of a row, rows of a fetch, fetches of a wave per piece
   constexpr uint32_t RB = DH * 2, PIECE = KC * RB;
   static_assert(KC % (RPF * WV) == 0 && KC % 32 == 0, "pieces deal out evenly");
+  static_assert(!(ONE && FAR), "a sequence of two pieces is near");
   __shared__ __align__(256) unsigned char smem[NS * PIECE];
 
   // Hardware deals consecutive workgroups round-robin to the 8 XCDs; give each XCD a contiguous range of the
@@ -92,7 +95,8 @@ __global__ void __launch_bounds__(64 * WV, MINB) attention_mfma_kernel(const uin
 
   // this head's K as a buffer of S rows, its V dkv columns to the right in it: rows past the end read as zeros (their keys are masked)
   const uint32_t stride_b = (uint32_t)qkv_stride * 2u, v_b = (uint32_t)dkv * 2u;
-  const i32x4 rsrc = buffer_of(qkv + row0 * qkv_stride + d + kvh * DH, (size_t)(S - 1) * stride_b + v_b + RB);
+  const uint16_t* const kbase = qkv + row0 * qkv_stride + d + kvh * DH;
+  const i32x4 rsrc = buffer_of(kbase, (size_t)(S - 1) * stride_b + v_b + RB);
   auto swizzle = [](int r) { return DH == 64 ? (r >> 1 & 1) * 4 + (r >> 2 & 1) * 2 + (r >> 3 & 1) : (r & 3) * 4 + (r >> 2 & 3); };
   uint32_t voff[PER];
 #pragma unroll
@@ -106,18 +110,26 @@ __global__ void __launch_bounds__(64 * WV, MINB) attention_mfma_kernel(const uin
     for (int t = 0; t < PER; ++t) fetch_rows(rsrc, voff[t], soff, lds0 + slot + (uint32_t)t * 1024u);
   };
   // Pieces in the order of their use: ONE K_0 K_1 V_0 V_1 (all of them, at once), else K_0 .. K_n-1 and then K_0 V_0 K_1 V_1 ...; past the end
-  // nothing is read (an offset outside the buffer), so that the waits need not know where the end is
+  // nothing is read (an offset outside the buffer, or a buffer of no bytes), so that the waits need not know where the end is
   const uint32_t piece_b = (uint32_t)KC * stride_b;
-  auto piece_at = [&](int p) {
+  auto fetch_piece = [&](int p, uint32_t slot) {
     const int q = p - n;
-    return q < 0 ? (uint32_t)p * piece_b : q < 2 * n ? (uint32_t)(q >> 1) * piece_b + (q & 1 ? v_b : 0u) : 0x7fffff00u;
+    if constexpr (FAR) {
+      const int rows = __builtin_amdgcn_readfirstlane(S), c = q < 0 ? p : q >> 1, left = c < n ? rows - c * KC : 0;   // (n pieces begin inside the sequence)
+      const i32x4 piece = buffer_of(kbase + (size_t)c * KC * qkv_stride + (q >= 0 && (q & 1) ? dkv : 0),
+                                    left > 0 ? (size_t)((left < KC ? left : KC) - 1) * stride_b + RB : 0);
+#pragma unroll
+      for (int t = 0; t < PER; ++t) fetch_rows<4>(piece, voff[t], 0, lds0 + slot + (uint32_t)t * 1024u);
+    } else {
+      fetch(q < 0 ? (uint32_t)p * piece_b : q < 2 * n ? (uint32_t)(q >> 1) * piece_b + (q & 1 ? v_b : 0u) : 0x7fffff00u, slot);
+    }
   };
   if constexpr (ONE) {
 #pragma unroll
     for (int c = 0; c < NS; ++c) fetch((c % (NS / 2) < n ? (uint32_t)(c % (NS / 2)) * piece_b : 0x7ff00000u) + (c >= NS / 2 ? v_b : 0u), c * PIECE);
   } else {
 #pragma unroll
-    for (int c = 0; c < NS - 1; ++c) fetch(piece_at(c), c * PIECE);
+    for (int c = 0; c < NS - 1; ++c) fetch_piece(c, c * PIECE);
   }
 
   // Q fragments (B operand): query qi, head-dim elements j*16 + lhalf*8 .. +7
@@ -183,7 +195,7 @@ __global__ void __launch_bounds__(64 * WV, MINB) attention_mfma_kernel(const uin
     for (int c = 0; c < n; ++c) {
       // piece c has landed for the block and every wave is done with the piece before, whose slot is requested again
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * PER) : "memory");
-      fetch(piece_at(c + NS - 1), slot == 0 ? (NS - 1) * PIECE : slot - PIECE);
+      fetch_piece(c + NS - 1, slot == 0 ? (NS - 1) * PIECE : slot - PIECE);
       pass1(c, slot);
       slot = slot + PIECE == NS * PIECE ? 0 : slot + PIECE;
     }
@@ -248,8 +260,8 @@ __global__ void __launch_bounds__(64 * WV, MINB) attention_mfma_kernel(const uin
       // when c = 0)
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
       const uint32_t vslot = slot == 3 * PIECE ? 0 : slot + PIECE, next = vslot == 3 * PIECE ? 0 : vslot + PIECE, next_v = next == 3 * PIECE ? 0 : next + PIECE;
-      if (c > 0) fetch(piece_at(n + 2 * c + 2), next);
-      fetch(piece_at(n + 2 * c + 3), next_v);
+      if (c > 0) fetch_piece(n + 2 * c + 2, next);
+      fetch_piece(n + 2 * c + 3, next_v);
       pass2(c, slot, vslot);
       slot = next;
     }
@@ -280,6 +292,11 @@ bool attention_mfma_supported(int dh, int qkv_stride, int d) {
   return (dh == 64 || dh == 128) && qkv_stride % 8 == 0 && d % 8 == 0;
 }
 
+// Do the rows of a sequence span more than the offsets into one buffer reach?  Offsets are 32 bits of which the ones from 0x7ff00000 on mean
+// "past the end" (attention_mfma_kernel), and the last piece's run up to 64 rows past the sequence.  (A piece's own offsets always fit: 64
+// rows of 32 MB would be the rows of a model whose Q|K|V weights alone outgrow the memory.)
+bool attention_far(int S, int qkv_stride, int dkv) { return ((size_t)S + 64) * qkv_stride * 2 + (size_t)dkv * 2 >= 0x7ff00000u; }
+
 // Heads of 128 that share no keys: the scores stay in registers (ONE) unless operands and results together outgrow the last-level cache
 // (64 tokens, 20 heads over 20, ONE / twice: 128 sequences, 168 MB, 26.1 / 28; 256, 335 MB, 77.9 / 76.3; 512 153.3 / 152.6).  Everywhere else ONE is
 // ahead whatever the size (16 over 2 heads of 128, 920 sequences 149.5 / 173; heads of 64: 32 over 4, 256 x 128 tokens 87.7 / 99.7, 32 over 32 128.1 /
@@ -295,10 +312,13 @@ void launch_attention_mfma(hipStream_t st, const void* qkv, int qkv_stride, void
   // eight waves fetch a key once for 256 queries: heads of 64 whose last 256 are at least three quarters there (128 x 512, 32 over 4 345 -> 330 us, 64 x
   // 256 58.8 -> 53.8; 416 tokens 43.3 -> 44.3, 288 11.4 -> 16.6; heads of 128, 512 tokens 93 -> 107)
   const bool eight = dh == 64 && S > 128 && (S - 1) % 256 >= 191;
-#define LAUNCH(DH, KC, NS, WV, MINB, ONE)                                                                                    \
-  attention_mfma_kernel<DH, KC, NS, WV, MINB, ONE><<<(unsigned)((size_t)n_seq * H * ((S + 32 * WV - 1) / (32 * WV))), 64 * WV, 0, st>>>( \
+#define LAUNCH(DH, KC, NS, WV, MINB, ...)                                                                                    \
+  attention_mfma_kernel<DH, KC, NS, WV, MINB, __VA_ARGS__><<<(unsigned)((size_t)n_seq * H * ((S + 32 * WV - 1) / (32 * WV))), 64 * WV, 0, st>>>( \
       (const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy)
-  if (dh == 64) {
+  if (attention_far(S, qkv_stride, Hkv * dh)) {
+    if (dh == 64) LAUNCH(64, 64, 4, 4, 4, false, true);
+    else LAUNCH(128, 32, 4, 4, 2, false, true);
+  } else if (dh == 64) {
     if (one) LAUNCH(64, 64, 4, 4, 2, true);
     else if (eight) LAUNCH(64, 64, 4, 8, 4, false);
     else LAUNCH(64, 64, 4, 4, 4, false);

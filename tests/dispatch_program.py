@@ -52,6 +52,10 @@ int main() {
       int n, S, H, kv, dh;
       if (scanf("%d %d %d %d %d", &n, &S, &H, &kv, &dh) != 5) return 1;
       printf("%d\n", (int)attention_keeps_scores(n, S, (H + 2 * kv) * dh, H * dh, dh));
+    } else if (!strcmp(what, "attention_far")) {         // tokens of a sequence, heads, key-value heads, columns of a head
+      int S, H, kv, dh;
+      if (scanf("%d %d %d %d", &S, &H, &kv, &dh) != 4) return 1;
+      printf("%d\n", (int)attention_far(S, (H + 2 * kv) * dh, kv * dh));
     } else if (!strcmp(what, "two_halves")) {            // d, columns of Q|K|V, d_ffn, gate and up, weight_quant, stacked tokens
       int d, nqkv, ffn, gate, quant, T;
       if (scanf("%d %d %d %d %d %d", &d, &nqkv, &ffn, &gate, &quant, &T) != 6) return 1;

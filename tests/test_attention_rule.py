@@ -1,5 +1,5 @@
-"""Where the attention of one key chunk keeps its scores and where it computes them twice (no GPU): chunks of 128 keys with heads of 64, of 64
-with heads of 128, and operands and results of some 300 MB."""
+"""Rules of the attention kernel (no GPU).  Where the attention of one key chunk keeps its scores and where it computes them twice (no GPU): chunks of 128 keys with heads of 64, of 64
+with heads of 128, and operands and results of some 300 MB.  From which length on a sequence's rows are more than the offsets into one buffer reach."""
 import pytest
 
 from dispatch_program import ask
@@ -10,3 +10,18 @@ from dispatch_program import ask
                                                (128, 64, 20, 20, 128, True), (256, 64, 20, 20, 128, False), (512, 64, 16, 2, 128, True)])
 def test_sizes(n, S, H, kv, dh, keeps):
     assert ask([f"attention_keeps {n} {S} {H} {kv} {dh}"]) == [keeps]
+
+
+@pytest.mark.parametrize("H,kv,dh", [(32, 32, 128), (32, 4, 64), (128, 128, 64), (128, 8, 128)])
+def test_sequences_that_one_buffer_does_not_reach(H, kv, dh):
+    row = (H + 2 * kv) * dh * 2
+    lo, hi = 2, 1 << 24                                    # the longest near sequence, the first far one
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if ask([f"attention_far {mid} {H} {kv} {dh}"])[0] else (mid, hi)
+    piece = 64 if dh == 64 else 32
+    past = -(-lo // piece) * piece - 1                     # the last row that a piece begins to ask for
+    assert (lo - 1) * row + kv * dh * 2 + dh * 2 <= 0x7ff00000, "the size of the buffer, below the offsets that mean past the end"
+    assert past * row + kv * dh * 2 + dh * 2 < 1 << 31, "offsets of the last piece"
+    assert (lo + 70) * row > 0x7ff00000                    # and no sooner than that asks for
+    assert ask([f"attention_far {s} {H} {kv} {dh}" for s in (2, 512, lo - 1, lo, hi, hi + 1, 174764 * 24576 // row, 1 << 24)]) == [0] * 4 + [1] * 4
