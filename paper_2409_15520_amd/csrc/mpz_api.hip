@@ -865,12 +865,15 @@ void run_head(mpz_model* m, const float* h, const int32_t* tokens, const int32_t
 }  // namespace
 
 // Do T stacked tokens in two halves on two streams take less time than in one pass?  Twice the launches, each of half the work: that pays
-// once a launch is long enough to hide the next one's, while blocks are short, and only where one pass leaves many CUs idle in the last
-// rounds of its tiles, which the other half's blocks then fill.  bf16 below d = 2048: from 3072 tokens and 3 x 2^30 of tokens x d^2 on (below,
-// twice the launches cost more: 12 layers of d = 768, 3072 tokens, 1270 us in one pass, 1358 in halves), where the tiles' work is less than 0.72 (d < 1024:
-// 0.73) of what their rounds hold (gemm_fit_filled; share, one pass / two halves of 4 layers, us: d = 768, 5504 / 6144 / 7168 / 8192 tokens 0.69 / 0.74 /
-// 0.81 / 0.82, 630 / 637 / 696 / 762 against 633 / 660 / 744 / 792; d = 1024, 3584 / 4096 / 4608 / 4864 tokens 0.72 / 0.80 / 0.72 / 0.79, 571 / 601 /
-// 729 / 1443 against 626 / 675 / 687 / 1456; but 3072 tokens, 0.69: 518 against 553).  int8 weights below d = 2048: while Q|K|V is below two rounds of
+// once a launch is long enough to hide the next one's, while blocks are short, and only where one pass leaves so many CUs idle in the last
+// rounds of its tiles that the other half's blocks, which then fill them, make up for the halves' own part-filled rounds (gemm_fit_halves_gain).
+// bf16 below d = 2048: from 3072 tokens and 3 x 2^30 of tokens x d^2 on, while Q|K|V is below two rounds of 256-wide tiles, where that gain is
+// above 1.02.  Timed both ways at 270 sizes (d 768 to 1536, with and without gate and up, 4 layers) the rule takes the faster way or one within
+// 3 % of it, but for four sizes (up to 8.7 %); one pass at all of them would cost 3.7 % on average, the rule 0.3 %.  Gain, one pass / two
+// halves, us: d = 768, 5632 / 8192 / 8704 / 10240 / 11264 / 12288 tokens 1.05 / 1.01 / 1.09 / 1.03 / 1.06 / 1.03, 628 / 713 / 830 / 874 / 1078 / 1148 against
+// 620 / 745 / 788 / 887 / 970 / 1036; d = 1024 with gate and up, 3072 / 4096 / 4608 / 6144 / 6656 / 9216 tokens 0.96 / 0.95 / 1.06 / 0.96 / 1.06 / 1.08, 505 / 582 /
+// 717 / 762 / 986 / 1264 against 527 / 637 / 671 / 830 / 920 / 1114; d = 1536, 3072 / 4096 / 5632 tokens 1.00 / 1.08 / 1.08, 1037 / 1229 / 1861 against 1069 /
+// 1269 / 1651.  int8 weights below d = 2048: while Q|K|V is below two rounds of
 // 256-wide tiles.  A half has more than the 256 tokens that split K, whose partial-sum buffer the halves would share.
 // Wider models (d = 2048 to 3072, 4 layers, 1536 to 5120 tokens) lose 2 to 29 % by it, and more with gate and up, except where both wide
 // projections are a little over one round of 256-wide tiles (Q|K|V / up tiles, one pass / two halves, us): bf16 300 / 270 1746 / 1691,
@@ -882,7 +885,7 @@ bool mpz::two_halves_pay(int d, int nqkv, int d_ffn, bool gate_up, int weight_qu
   const long rows = (T + 255) / 256, qkv = (nqkv + 255) / 256 * rows;
   if (d < 2048) {
     if (T < 3072 || (double)T * d * d < 3.0 * (1 << 30)) return false;
-    return qkv < 512 && (int8 || gemm_fit_filled(d, nqkv, d_ffn, gate_up, T) < (d < 1024 ? 0.73 : 0.72));
+    return qkv < 512 && (int8 || gemm_fit_halves_gain(d, nqkv, d_ffn, gate_up, T) > 1.02);
   }
   if (gate_up || T < 1536) return false;
   const long up = (d_ffn + 255) / 256 * rows;

@@ -4,12 +4,13 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("heads,q,E,S,streams", [(16, 8, 2, 96, 2),      # 1024 wide, 3072 tokens: the first that does
-                                                 (16, 8, 1, 188, 1),     # 3008 tokens
+@pytest.mark.parametrize("heads,q,E,S,streams", [(16, 8, 2, 96, 1),      # 1024 wide, 3072 tokens: one pass fills its rounds as well
+                                                 (16, 9, 2, 128, 2),     # 4608
+                                                 (16, 16, 1, 144, 2),    # the same in copies of 144 rows
+                                                 (16, 10, 2, 128, 1),    # 5120
                                                  (12, 8, 2, 170, 1),     # 768 wide, 5440 tokens: below 3 x 2^30
-                                                 (12, 8, 2, 172, 2),     # 5504
-                                                 (16, 9, 2, 128, 2),     # 4608 tokens: 144 tiles of 256 x 256 for Q|K|V
-                                                 (16, 10, 2, 128, 1),    # 160
+                                                 (12, 8, 4, 128, 1),     # 8192
+                                                 (12, 8, 4, 136, 2),     # 8704
                                                  (32, 8, 2, 96, 1)])     # 2048 wide
 def test_streams_and_bits(heads, q, E, S, streams):
     import torch
