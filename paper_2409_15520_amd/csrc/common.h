@@ -213,7 +213,7 @@ hipError_t launch_gemm_ring(hipStream_t st, const MfmaGemmArgs& a);
 // gemm_fit.hip: shapes 0 .. 5 (see there); the one that a product chosen by size takes, or -1
 bool gemm_fit_supported(const MfmaGemmArgs& a, int shape);
 int gemm_fit_shape(const MfmaGemmArgs& a, int tile);
-double gemm_fit_halves_gain(int d, int nqkv, int d_ffn, bool gate_up, long T);   // a block's four products in one pass over what two halves should take
+double gemm_fit_halves_gain(int d, int nqkv, int d_ffn, bool gate_up, bool int8, long T);   // a block's four products in one pass over what two halves should take
 hipError_t launch_gemm_fit(hipStream_t st, const MfmaGemmArgs& a, int shape);
 hipError_t launch_gemm_fit_int8(hipStream_t st, const MfmaGemmArgs& a, int shape);   // gemm_fit_int8.hip
 // operands that may be fetched straight into LDS, 16 bytes at a time

@@ -89,8 +89,8 @@ int gemm_fit_shape(const MfmaGemmArgs& a, int tile) {
 }
 
 // A block's four products of T tokens in one pass, over the mean of two sums between which two halves at the same time lie: the halves
-// one behind the other, each in rounds of its own, and the halves as if no CU were ever idle.  (All by the costs above.  At 55 sizes of six other models, 4 layers: the faster way or one within 2 % of it but at five, up to 5 %.)
-double gemm_fit_halves_gain(int d, int nqkv, int d_ffn, bool gate_up, long T) {
+// one behind the other, each in rounds of its own, and the halves as if no CU were ever idle.  (All by the costs above.  At 54 sizes of six other models, 4 layers, the faster way or one within 3 % of it but at five, up to 5 %; int8 at all 54.)
+double gemm_fit_halves_gain(int d, int nqkv, int d_ffn, bool gate_up, bool int8, long T) {
   const int shapes[4][4] = {{nqkv, d, 0, 0}, {d, d, 1, 0}, {d_ffn, d, 0, gate_up}, {d, d_ffn, 1, 0}};   // columns, K, fp32 output, gate and up
   double whole = 0.0, apart = 0.0, filled = 0.0;
   for (const auto& g : shapes) {
@@ -99,8 +99,8 @@ double gemm_fit_halves_gain(int d, int nqkv, int d_ffn, bool gate_up, long T) {
     double w = 0.0, p = 0.0, f = 0.0;
     auto least = [](double& m, double c) { m = m == 0.0 || c < m ? c : m; };
     for (int s = 0; s <= 6; ++s) {
-      const FitCost& c = s < 6 ? kFitCost[s] : kPipeCost;
-      if (c.bn == 192 && (a.dual || d >= 1024)) continue;
+      const FitCost& c = int8 ? kFitCost8[s] : s < 6 ? kFitCost[s] : kPipeCost;
+      if (c.bn == 0 || (c.bn == 192 && (a.dual || d >= 1024))) continue;
       a.M = (int)T;
       least(w, cost_of(a, c));
       a.M = (int)(T / 2);

@@ -867,30 +867,29 @@ void run_head(mpz_model* m, const float* h, const int32_t* tokens, const int32_t
 // Do T stacked tokens in two halves on two streams take less time than in one pass?  Twice the launches, each of half the work: that pays
 // once a launch is long enough to hide the next one's, while blocks are short, and only where one pass leaves so many CUs idle in the last
 // rounds of its tiles that the other half's blocks, which then fill them, make up for the halves' own part-filled rounds (gemm_fit_halves_gain).
-// bf16 below d = 2048: from 3072 tokens and 3 x 2^30 of tokens x d^2 on, while Q|K|V is below two rounds of 256-wide tiles, where that gain is
-// above 1.02.  Timed both ways at 270 sizes (d 768 to 1536, with and without gate and up, 4 layers) the rule takes the faster way or one within
-// 3 % of it, but for four sizes (up to 8.7 %); one pass at all of them would cost 3.7 % on average, the rule 0.3 %.  Gain, one pass / two
+// Below d = 2048: from 3072 tokens and 3 x 2^30 of tokens x d^2 on, while Q|K|V is below two rounds of 256-wide tiles, where that gain is
+// above 1.02.  bf16, timed both ways at 270 sizes (d 768 to 1536, with and without gate and up, 4 layers): the rule takes the faster way or one
+// within 3 % of it, but for four sizes (up to 8.7 %); one pass at all of them would cost 3.7 % on average, the rule 0.3 %.  Gain, one pass / two
 // halves, us: d = 768, 5632 / 8192 / 8704 / 10240 / 11264 / 12288 tokens 1.05 / 1.01 / 1.09 / 1.03 / 1.06 / 1.03, 628 / 713 / 830 / 874 / 1078 / 1148 against
 // 620 / 745 / 788 / 887 / 970 / 1036; d = 1024 with gate and up, 3072 / 4096 / 4608 / 6144 / 6656 / 9216 tokens 0.96 / 0.95 / 1.06 / 0.96 / 1.06 / 1.08, 505 / 582 /
 // 717 / 762 / 986 / 1264 against 527 / 637 / 671 / 830 / 920 / 1114; d = 1536, 3072 / 4096 / 5632 tokens 1.00 / 1.08 / 1.08, 1037 / 1229 / 1861 against 1069 /
-// 1269 / 1651.  int8 weights below d = 2048: while Q|K|V is below two rounds of
-// 256-wide tiles.  A half has more than the 256 tokens that split K, whose partial-sum buffer the halves would share.
-// Wider models (d = 2048 to 3072, 4 layers, 1536 to 5120 tokens) lose 2 to 29 % by it, and more with gate and up, except where both wide
-// projections are a little over one round of 256-wide tiles (Q|K|V / up tiles, one pass / two halves, us): bf16 300 / 270 1746 / 1691,
-// but 288 / 384 1627 / 1614, 264 / 352 1525 / 1537, 288 / 384 at d = 3072 2243 / 2391; int8, whose small tiles are nearer to its large ones,
-// 264 / 352 1703 / 1593, 300 / 270 1938 / 1754, 390 / 351 2424 / 2241, 216 / 288 at d = 3072 2127 / 1974, 312 / 416 1791 / 1793, but 360 / 480
-// 1974 / 2049 and 240 / 216 1492 / 1561.
+// 1269 / 1651.  int8, 128 sizes: one pass at all would cost 1.9 %, the rule 0.5 %, up to 5 % (d = 768, 7168 / 8192 tokens 0.96 / 1.13, 688 / 820 against
+// 760 / 775; d = 1024 with gate and up, 4096 / 9216 tokens 0.97 / 1.06, 619 / 1261 against 702 / 1106).
+// A half has more than the 256 tokens that split K, whose partial-sum buffer the halves would share.
+// Wider models (d = 2048 to 3072, 4 layers, 1536 to 5120 tokens): with the gain, and where both wide projections are a little over one round of
+// 256-wide tiles (Q|K|V / up tiles, one pass / two halves, us): bf16 300 / 270 1727 / 1668, but 288 / 384 1384 / 1414 and at d = 3072 2005 / 2168; int8,
+// whose large tile's rounds are longer, 300 / 270 1734 / 1641, 390 / 351 2094 / 1984, 312 / 416 1693 / 1613, 288 / 384 at d = 3072 2254 / 2084, but
+// without the gain 216 / 288 1183 / 1238, 288 / 384 1414 / 1466, 252 / 336 at d = 3072 1813 / 2077.
 bool mpz::two_halves_pay(int d, int nqkv, int d_ffn, bool gate_up, int weight_quant, long T) {
   const bool int8 = weight_quant == MPZ_WEIGHT_QUANT_INT8;
-  const long rows = (T + 255) / 256, qkv = (nqkv + 255) / 256 * rows;
+  const long rows = (T + 255) / 256, qkv = (nqkv + 255) / 256 * rows, up = (d_ffn + 255) / 256 * rows;
   if (d < 2048) {
-    if (T < 3072 || (double)T * d * d < 3.0 * (1 << 30)) return false;
-    return qkv < 512 && (int8 || gemm_fit_halves_gain(d, nqkv, d_ffn, gate_up, T) > 1.02);
+    if (T < 3072 || (double)T * d * d < 3.0 * (1 << 30) || qkv >= 512) return false;
+  } else {
+    const long most = int8 ? 416 : 319;
+    if (gate_up || T < 1536 || up <= 256 || up > most || qkv > most || (!int8 && qkv <= 256)) return false;
   }
-  if (gate_up || T < 1536) return false;
-  const long up = (d_ffn + 255) / 256 * rows;
-  if (int8) return up > 256 && up <= 416 && qkv <= 416;
-  return up > 256 && up < 320 && qkv > 256 && qkv < 320;
+  return gemm_fit_halves_gain(d, nqkv, d_ffn, gate_up, int8, T) > 1.02;
 }
 
 extern "C" {
@@ -1083,11 +1082,6 @@ void forward_two_halves(mpz_model* m, const int32_t* tokens, const int32_t* labe
   (void)hipEventRecord(m->ev_fork, main);                   // the perturbed factors are ready on the caller's stream
   (void)hipStreamWaitEvent(m->stream2, m->ev_fork, 0);
   const size_t rows = (size_t)half * E * S;
-  // int8: with the other half's kernels filling a block's first-load and last-store edges, the 128 x 128 tile does better with 4 waves
-  // of 64 x 64 (a third fewer LDS fragment reads) than with the 8 waves of 64 x 32 that hide those edges when a GEMM runs alone.
-  // (bf16 halves take the tiles that fit half the tokens: 4 layers of d = 1024, 4608 tokens, 687 us against 781 with that tile.)
-  const int saved_cfg = m->force_tile_cfg;
-  if (saved_cfg == 0 && m->cfg.weight_quant == MPZ_WEIGHT_QUANT_INT8) m->force_tile_cfg = 1;
   for (int step = -1; step <= m->cfg.n_layers; ++step)       // embedding, the blocks one by one, the head
     for (int hf = 0; hf < 2; ++hf) {
       m->stream = streams[hf]; m->cb = hf * half; m->nc = half;
@@ -1097,7 +1091,6 @@ void forward_two_halves(mpz_model* m, const int32_t* tokens, const int32_t* labe
       else run_head(m, h, tokens, labels, E, S, losses_out + hf * half);
     }
   m->stream = main; m->cb = 0; m->nc = n;
-  m->force_tile_cfg = saved_cfg;
   (void)hipEventRecord(m->ev_join, m->stream2);
   (void)hipStreamWaitEvent(main, m->ev_join, 0);
 }

@@ -72,14 +72,14 @@ def test_copy_range_errors():
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("name", ["c2_2layers", "c2_int8"])
-def test_two_halves_schedule_changes_no_bit(name):
+@pytest.mark.parametrize("name,E,S", [("c2_2layers", 17, 64), ("c2_int8", 8, 128)])     # 8704 and 8192 tokens: sizes that run in halves
+def test_two_halves_schedule_changes_no_bit(name, E, S):
     """Small models run the pass as two halves of q copies on two streams; with the hook off it is one pass on the
     caller's stream.  Losses of three consecutive steps (update in between) are bit-identical, also when the caller's
     stream is not the default one."""
     import torch
     import paper_2409_15520_amd as M
-    w = CASES[name]
+    w = CASES[name].with_(E=E, S=S)
     b = make_bundle(w, b_std=0.01)
     side = torch.cuda.Stream()
     runs = []
@@ -94,6 +94,7 @@ def test_two_halves_schedule_changes_no_bit(name):
             for step in range(3):
                 m.regen_noise(3456, step)
                 out.append(m.forward_perturbed(tok, lab).clone())
+                assert M.mpz_debug_last_pass_streams(m.handle) == (2 if enable else 1)
                 m.zo_update()
             torch.cuda.current_stream().synchronize()
             runs.append(torch.stack(out).cpu().numpy())
