@@ -1058,11 +1058,13 @@ bool mfma_gemm_supported(const MfmaGemmArgs& a) {
     return true;                                         // the rotation is the reduction kernel's: no tile constraints
   }
   if (a.rope_cos != nullptr) {
-    // the rotated column range must end on a block-tile boundary, and a wave tile must hold whole heads
+    // the rotated column range must end on a block-tile boundary, and a wave tile must hold whole heads (a fitted tile that is asked for by
+    // number has rules of its own)
+    if (a.dual || a.out_f32 || a.act >= 0 || a.residual != nullptr || !a.rope_sin || a.S < 1 || a.rope_cols > a.N) return false;
+    if ((a.rope_dh != 64 && a.rope_dh != 128) || a.N % a.rope_dh) return false;
+    if (a.tile_cfg >= 20 && gemm_fit_shape(a, 0) >= 0) return true;
     const int cfg = choose_cfg(a), bn = tile_bn(cfg), tn = wave_cols(cfg);
-    if (a.dual || a.out_f32 || a.act >= 0 || a.residual != nullptr || !a.rope_sin || a.S < 1) return false;
-    if ((cfg != 6 && cfg != 1 && cfg != 12 && cfg != 15) || (a.rope_dh != 64 && a.rope_dh != 128) || a.rope_dh > tn) return false;
-    if (a.rope_cols % bn || a.rope_cols > a.N || a.N % a.rope_dh) return false;
+    if ((cfg != 6 && cfg != 1 && cfg != 12 && cfg != 15) || a.rope_dh > tn || a.rope_cols % bn) return false;
   }
   return true;
 }

@@ -59,7 +59,9 @@ def test_int8_equals_the_staged_tile(m, n, k, act, f32, bias):
                                                    ("rope128", 4, 5, 1, 32, 8), ("plain", 12, 4, 1, 64, 8), ("plain", 12, 3, 1, 160, 16)])
 def test_model_pass_with_a_fitted_tile_forced(kind, heads, q, E, S, rank, quant):
     """Two blocks with low-rank terms (rank 8 and 16), rotary embedding, residual and SwiGLU / ReLU epilogues, every bit of the residual
-    stream.  Copies of 32 to 288 rows: a wave's tokens span several.  768 wide: segments that the 192-wide tiles take."""
+    stream.  Copies of 32 to 288 rows: a wave's tokens span several.  768 wide: segments that the 192-wide tiles take.  Heads of 128 columns: the
+fitted tiles rotate them, the staged one (and what stands in for the 192-wide shapes and, bf16, 26, which rotate nothing) leaves that to a kernel
+of its own, one launch a block."""
     import torch
     import workloads as W
     import paper_2409_15520_amd as M
@@ -72,12 +74,16 @@ def test_model_pass_with_a_fitted_tile_forced(kind, heads, q, E, S, rank, quant)
     frozen = W.make_frozen_weights(w, 1)
     masters = W.make_lora_masters(w, 2, b_std=0.05)
     tokens = torch.from_numpy(W.make_tokens(w, 3)).cuda()
-    hs = []
+    hs, rotary = [], []
     for cfg in (1,) + FITTED + (26,):
         m = M.ZoModel(w, frozen, masters)
         M.mpz_debug_set_tile_config(m.handle, cfg)
         m.regen_noise(5, 0)
+        M.mpz_profile_begin(m.handle)
         hs.append(m.run_layers(m.embed(tokens), 0, 2, E, S).clone())
+        rotary.append(M.mpz_profile_end(m.handle)["rope"]["launches"])
+    if kind == "rope128":
+        assert rotary == [2, 2, 0, 2, 0, 0, 0, 0 if quant == "int8" else 2]
     for cfg, h in zip(FITTED + (26,), hs[1:]):
         assert torch.equal(h.view(torch.int32), hs[0].view(torch.int32)), cfg
 
