@@ -297,18 +297,19 @@ bool attention_mfma_supported(int dh, int qkv_stride, int d) {
 // rows of 32 MB would be the rows of a model whose Q|K|V weights alone outgrow the memory.)
 bool attention_far(int S, int qkv_stride, int dkv) { return ((size_t)S + 64) * qkv_stride * 2 + (size_t)dkv * 2 >= 0x7ff00000u; }
 
-// Heads of 128 that share no keys: the scores stay in registers (ONE) unless operands and results together outgrow the last-level cache
-// (64 tokens, 20 heads over 20, ONE / twice: 128 sequences, 168 MB, 26.1 / 28; 256, 335 MB, 77.9 / 76.3; 512 153.3 / 152.6).  Everywhere else ONE is
-// ahead whatever the size (16 over 2 heads of 128, 920 sequences 149.5 / 173; heads of 64: 32 over 4, 256 x 128 tokens 87.7 / 99.7, 32 over 32 128.1 /
-// 139.8, 16 over 8, 768 x 96 100.3 / 116.1).  The same bits either way.
-bool attention_keeps_scores(int n_seq, int S, int qkv_stride, int d, int dh) {
-  return S <= (dh == 64 ? 128 : 64) && (size_t)n_seq * S * (qkv_stride + d) * 2 < (size_t)(dh == 64 ? 264 : 320) << 20;
+// Do the scores of the first pass stay in registers (ONE)?  Where all keys fit half the ring; heads of 128 that share no keys only unless
+// operands and results together outgrow the last-level cache (64 tokens, 20 heads over 20, ONE / twice: 128 sequences, 168 MB, 26.1 / 28; 256, 335 MB,
+// 77.9 / 76.3; 512 153.3 / 152.6).  Everywhere else ONE is ahead whatever the size (16 over 2 heads of 128, 920 sequences 149.5 / 173; heads of 64: 32 over
+// 4, 256 x 128 tokens 87.7 / 99.7, 32 over 32 128.1 / 139.8, 16 over 8, 768 x 96 100.3 / 116.1).  The same bits either way.
+bool attention_keeps_scores(int n_seq, int S, int H, int Hkv, int dh) {
+  if (S > (dh == 64 ? 128 : 64)) return false;
+  return dh == 64 || H > Hkv || (size_t)n_seq * S * (2 * H + 2 * Hkv) * dh * 2 < (size_t)320 << 20;
 }
 
 void launch_attention_mfma(hipStream_t st, const void* qkv, int qkv_stride, void* out, int n_seq, int S, int H, int Hkv,
                            int dh, const int32_t* cu, int E, int rows_per_copy) {
   const float scale = (float)(1.0 / sqrt((double)dh));
-  const bool one = S <= (dh == 64 ? 128 : 64) && (dh == 64 || H > Hkv || attention_keeps_scores(n_seq, S, qkv_stride, H * dh, dh));
+  const bool one = attention_keeps_scores(n_seq, S, H, Hkv, dh);
   // eight waves fetch a key once for 256 queries: heads of 64 whose last 256 are at least three quarters there (128 x 512, 32 over 4 345 -> 330 us, 64 x
   // 256 58.8 -> 53.8; 416 tokens 43.3 -> 44.3, 288 11.4 -> 16.6; heads of 128, 512 tokens 93 -> 107)
   const bool eight = dh == 64 && S > 128 && (S - 1) % 256 >= 191;

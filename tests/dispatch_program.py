@@ -51,7 +51,7 @@ int main() {
     } else if (!strcmp(what, "attention_keeps")) {       // sequences, tokens, heads, key-value heads, columns of a head
       int n, S, H, kv, dh;
       if (scanf("%d %d %d %d %d", &n, &S, &H, &kv, &dh) != 5) return 1;
-      printf("%d\n", (int)attention_keeps_scores(n, S, (H + 2 * kv) * dh, H * dh, dh));
+      printf("%d\n", (int)attention_keeps_scores(n, S, H, kv, dh));
     } else if (!strcmp(what, "attention_far")) {         // tokens of a sequence, heads, key-value heads, columns of a head
       int S, H, kv, dh;
       if (scanf("%d %d %d %d", &S, &H, &kv, &dh) != 4) return 1;

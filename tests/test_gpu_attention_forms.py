@@ -1,5 +1,6 @@
-"""Attention of one key chunk: the form that keeps its scores (few sequences) has the bits of the one that computes them twice (more than
-the last-level cache holds)."""
+"""Attention of all keys in half the ring: the form that keeps its scores (few sequences) and the one
+that computes them twice (heads of 128 that share no keys, more than the last-level cache holds; heads of 64 keep them in any batch)
+have the same bits."""
 import pytest
 
 pytestmark = pytest.mark.gpu
