@@ -306,13 +306,22 @@ bool attention_keeps_scores(int n_seq, int S, int H, int Hkv, int dh) {
   return dh == 64 || H > Hkv || (size_t)n_seq * S * (2 * H + 2 * Hkv) * dh * 2 < (size_t)320 << 20;
 }
 
+// Eight waves fetch a key once for 256 queries: heads of 64 whose last 256 are at least three quarters there (128 x 512, 32 over 4 345 -> 330 us, 64 x
+// 256 58.8 -> 53.8; 416 tokens 43.3 -> 44.3, 288 11.4 -> 16.6; heads of 128, 512 tokens 93 -> 107).  Not where the blocks are few and the last of every 256 of
+// them (one a CU; a CU holds two) are at most half there: twice the blocks of four waves then take as many rounds, of half the work (four waves / eight,
+// us, 200 and 512 tokens, 12 over 12: 96 blocks 7.6 / 9.0 and 12.7 / 15.5, 312 12.0 / 13.0 and 20.6 / 22.9, 600 18.7 / 19.7 and 31.7 / 33.4; but 192 9.7 / 9.4 and
+// 16.4 / 15.9, 504 15.6 / 14.4 and 26.3 / 24.9; from 768 on it hangs on the keys that the heads share: 832 blocks of 256 tokens 32 over 4 25.4 / 24.5, 852 12
+// over 12 27.1 / 27.8).  The same bits either way.
+bool attention_eight_waves(int n_seq, int S, int H, int dh) {
+  if (dh != 64 || S <= 128 || (S - 1) % 256 < 191) return false;
+  const long blocks = (long)n_seq * H * ((S + 255) / 256);
+  return blocks > 640 || (blocks - 1) % 256 >= 128;
+}
+
 void launch_attention_mfma(hipStream_t st, const void* qkv, int qkv_stride, void* out, int n_seq, int S, int H, int Hkv,
                            int dh, const int32_t* cu, int E, int rows_per_copy) {
   const float scale = (float)(1.0 / sqrt((double)dh));
-  const bool one = attention_keeps_scores(n_seq, S, H, Hkv, dh);
-  // eight waves fetch a key once for 256 queries: heads of 64 whose last 256 are at least three quarters there (128 x 512, 32 over 4 345 -> 330 us, 64 x
-  // 256 58.8 -> 53.8; 416 tokens 43.3 -> 44.3, 288 11.4 -> 16.6; heads of 128, 512 tokens 93 -> 107)
-  const bool eight = dh == 64 && S > 128 && (S - 1) % 256 >= 191;
+  const bool one = attention_keeps_scores(n_seq, S, H, Hkv, dh), eight = attention_eight_waves(n_seq, S, H, dh);
 #define LAUNCH(DH, KC, NS, WV, MINB, ...)                                                                                    \
   attention_mfma_kernel<DH, KC, NS, WV, MINB, __VA_ARGS__><<<(unsigned)((size_t)n_seq * H * ((S + 32 * WV - 1) / (32 * WV))), 64 * WV, 0, st>>>( \
       (const uint16_t*)qkv, qkv_stride, (uint16_t*)out, S, H, Hkv, scale, cu, E, rows_per_copy)

@@ -257,6 +257,7 @@ void launch_pack_factors(hipStream_t st, const float* pert, int64_t P, int n_cop
 bool attention_mfma_supported(int dh, int qkv_stride, int d);
 bool attention_far(int S, int qkv_stride, int dkv);        // rows of a sequence past the offsets into one buffer
 bool attention_keeps_scores(int n_seq, int S, int H, int Hkv, int dh);
+bool attention_eight_waves(int n_seq, int S, int H, int dh);
 // cu / E / rows_per_copy: as for launch_attention_simple
 void launch_attention_mfma(hipStream_t st, const void* qkv, int qkv_stride, void* out, int n_seq, int S, int H, int Hkv,
                            int dh, const int32_t* cu, int E, int rows_per_copy);

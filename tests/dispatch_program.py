@@ -52,6 +52,10 @@ int main() {
       int n, S, H, kv, dh;
       if (scanf("%d %d %d %d %d", &n, &S, &H, &kv, &dh) != 5) return 1;
       printf("%d\n", (int)attention_keeps_scores(n, S, H, kv, dh));
+    } else if (!strcmp(what, "attention_eight")) {       // sequences, tokens, heads, columns of a head
+      int n, S, H, dh;
+      if (scanf("%d %d %d %d", &n, &S, &H, &dh) != 4) return 1;
+      printf("%d\n", (int)attention_eight_waves(n, S, H, dh));
     } else if (!strcmp(what, "attention_far")) {         // tokens of a sequence, heads, key-value heads, columns of a head
       int S, H, kv, dh;
       if (scanf("%d %d %d %d", &S, &H, &kv, &dh) != 4) return 1;

@@ -12,6 +12,17 @@ def test_sizes(n, S, H, kv, dh, keeps):
     assert ask([f"attention_keeps {n} {S} {H} {kv} {dh}"]) == [keeps]
 
 
+# blocks of 256 queries (sequences x heads x blocks of one): few, the last 256 of them half there and a little more, many; lengths around
+# three quarters of a block
+@pytest.mark.parametrize("n,S,H,dh,eight", [(2, 256, 32, 64, False), (4, 256, 32, 64, False), (5, 256, 32, 64, True), (8, 256, 32, 64, True), (9, 256, 32, 64, False),
+                                            (12, 256, 32, 64, False), (13, 256, 32, 64, True), (16, 256, 32, 64, True), (20, 200, 32, 64, False), (21, 200, 32, 64, True),
+                                            (2, 512, 32, 64, False), (3, 512, 32, 64, True), (6, 512, 32, 64, False), (12, 512, 32, 64, True), (128, 512, 32, 64, True),
+                                            (40, 191, 4, 64, False), (40, 192, 4, 64, True), (40, 257, 4, 64, False), (20, 447, 4, 64, False), (20, 448, 4, 64, True),
+                                            (8, 128, 32, 64, False), (8, 256, 32, 128, False)])
+def test_eight_waves(n, S, H, dh, eight):
+    assert ask([f"attention_eight {n} {S} {H} {dh}"]) == [eight]
+
+
 @pytest.mark.parametrize("H,kv,dh", [(32, 32, 128), (32, 4, 64), (128, 128, 64), (128, 8, 128)])
 def test_sequences_that_one_buffer_does_not_reach(H, kv, dh):
     row = (H + 2 * kv) * dh * 2
