@@ -63,7 +63,8 @@ double cost_of(const MfmaGemmArgs& a, const FitCost& c, bool filled = false) {  
 //     tile has two weight operands to an activation: 66 to 132 small tiles 1.2 - 1.7, int8 1.6 - 1.9;
 //   * 128 x 128, 192 x 128 and 128 x 64 tiles beyond that: 0.99 - 1.5, 1.14 on average; gate and up in 128 x 128: 1.31 (int8 1.15, 1.43);
 //   * the 256 x 256 tile of gemm_pipe.hip: where its rounds are part-filled 1.0 - 1.45, else down to 0.77, so the sums decide, with 4 % in
-//     its favour (K = 11008, whose many K-tiles the smaller shapes fetch more slowly than the sums say, 0.90 - 0.97 at that margin: 13 %);
+//     its favour (K = 11008, whose many K-tiles the smaller shapes fetch more slowly than the sums say, 0.90 - 0.97 at that margin: 13 %;
+//     weights that outgrow the last-level cache, whatever K: 0.83 - 1.1 at 0.82 to 0.88 by the sums, 1.0 - 1.26 below: 18 %);
 //     from four of its rounds on it stays (0.9 - 1.03 beyond), and for gate and up of up to 384 tokens, which are a stream of weights
 //     (0.87 - 0.94).  The staged 256 x 256 tile of int8 weights: 1.0 - 1.35, 1.13 on average, two rounds and more included.
 int gemm_fit_shape(const MfmaGemmArgs& a, int tile) {
@@ -77,7 +78,8 @@ int gemm_fit_shape(const MfmaGemmArgs& a, int tile) {
   if (tile == 6 && !int8) {
     const int cn = a.dual ? 128 : 256;
     if ((long)((a.N + cn - 1) / cn) * ((a.M + 255) / 256) > 1024 || (a.dual && a.M <= 384)) return -1;
-    least = (a.K > 8192 ? 0.87 : 0.96) * cost_of(a, kPipeCost);
+    const size_t weights = (size_t)(a.dual ? 2 : 1) * a.N * a.K * 2;
+    least = (weights >= (size_t)240 << 20 ? 0.82 : a.K > 8192 ? 0.87 : 0.96) * cost_of(a, kPipeCost);
   }
   int shape = -1;
   for (int s = 0; s < 7; ++s) {

@@ -2,6 +2,7 @@
 128 x 128, 15 = the same for rotated heads of 128, 9 = 128 x 64, 10 = 64 x 64, 14 = 32 x 32; -1 = refused."""
 import pytest
 
+import paper_2409_15520_amd as M
 from dispatch_program import ask
 
 
@@ -57,3 +58,12 @@ def test_halves_of_tiles_that_fit_the_cus(m, n, k, tile):
                                         (288, 2048, 4096, 10), (384, 2048, 5632, 14), (320, 2048, 8192, 10), (256, 2048, 2048, 14), (416, 2048, 4096, 10)])
 def test_the_smallest_tiles_of_wide_outputs(m, n, k, tile):
     assert ask([f"tile {m} {n} {k} 16 0 0"]) == [tile]
+
+
+# weights that the last-level cache holds and that it does not (256 MiB, 250, 449; gate and up 224 and 432): the 256 x 256 tile (-1) stays unless the
+# fitted ones (20 + shape) gain much; not where the 128 x 128 ones were the other choice
+@pytest.mark.parametrize("m,n,k,dual,tile", [(576, 16384, 4096, False, 21), (576, 16384, 8192, False, -1), (768, 16384, 8192, False, -1), (1152, 16384, 8192, False, 23),
+                                             (384, 16384, 8192, False, 23), (288, 32000, 4096, False, -1), (1152, 32000, 4096, False, -1), (320, 28672, 8192, False, -1),
+                                             (1152, 28672, 8192, False, 24), (576, 14336, 4096, True, 23), (640, 16384, 6912, True, -1)])
+def test_fitted_tiles_and_weights_past_the_last_level_cache(m, n, k, dual, tile):
+    assert M.mpz_debug_gemm_fitted_tile(m, n, k, dual) == tile
