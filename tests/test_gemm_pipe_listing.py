@@ -1,12 +1,16 @@
 """The large GEMM writes its accumulators from inline assembly, whose latency the compiler does not know.  This test compiles
 the kernel and checks, instruction by instruction, that the compiled code keeps the wait states the hardware asks for: no
 accumulator is touched by anything but an MFMA before the MFMA that wrote it is done, no MFMA reads a register right behind
-the vector instruction that wrote it, and no fetch reads a scalar register right behind a vector write of it."""
-import os
+the vector instruction that wrote it, and no fetch reads a scalar register right behind a vector write of it.  The last holds for every kernel
+that fetches straight into LDS from inline assembly."""
 import re
-import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
-from paper_2409_15520_amd import build
+import pytest
+
+from listing import listing
+
+FETCHING = ("attention_mfma", "gemm_codes", "gemm_fit", "gemm_fit_int8", "gemm_ring", "gemm_stream", "ordered_kernels")
 
 MFMA = "v_mfma_f32_16x16x32_bf16"
 RESULT_STATES = 12          # 8-pass MFMA result -> vector ALU or LDS read: 11 wait states
@@ -22,7 +26,7 @@ def _regs(text, kind):
 
 
 def _kernels(text):
-    for m in re.finditer(r"^(_Z\S*gemm_pipe_kernel\S*):", text, re.M):
+    for m in re.finditer(r"^(_Z\S*kernel\S*):", text, re.M):
         body = text[m.end():]
         lines, inline = [], False
         for raw in body[:body.index(".Lfunc_end")].splitlines():
@@ -60,14 +64,28 @@ def _violations(lines):
     return found
 
 
-def test_compiled_gemm_keeps_its_wait_states(tmp_path):
-    out = tmp_path / "gemm_pipe.s"
-    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *build.COMMON, "-S", "--cuda-device-only", "-o", str(out),
-                    os.path.join(build.CSRC, "gemm_pipe.hip")], check=True, capture_output=True)
-    kernels = list(_kernels(out.read_text()))
+@pytest.fixture(scope="module", autouse=True)
+def _compiled():
+    with ThreadPoolExecutor(4) as ex:
+        list(ex.map(listing, ("gemm_pipe",) + FETCHING))
+
+
+def test_compiled_gemm_keeps_its_wait_states():
+    kernels = [k for k in _kernels(listing("gemm_pipe")) if "gemm_pipe_kernel" in k[0]]
     assert len(kernels) >= 20
     for name, lines in kernels:
         assert sum(l.startswith("asm " + MFMA) for l in lines) >= 256, name
+        assert not _violations(lines), (name, _violations(lines)[:3])
+
+
+@pytest.mark.parametrize("source", FETCHING)
+def test_fetches_wait_for_their_scalars(source):
+    fetching = [(n, lines) for n, lines in _kernels(listing(source)) if any("offen lds" in l for l in lines)]
+    assert fetching
+    for name, lines in fetching:
+        for i, line in enumerate(lines):
+            if "offen lds" in line:                        # the LDS address, one wait state or more, the fetch
+                assert lines[i - 1].startswith("s_nop") and lines[i - 2].startswith("s_mov_b32 m0,"), (name, lines[i - 2:i + 1])
         assert not _violations(lines), (name, _violations(lines)[:3])
 
 

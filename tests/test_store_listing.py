@@ -1,13 +1,14 @@
 """Stores of 16 bytes read their last registers some cycles after they were issued, and the compiler waits for that only where the scalar
 offset of the store is no register.  This test compiles the kernels that store accumulators through buffers and checks that form and
 the wait."""
-import os
 import re
-import subprocess
 from concurrent.futures import ThreadPoolExecutor
 
-from paper_2409_15520_amd import build
+import pytest
 
+from listing import listing
+
+SOURCES = ("gemm_codes", "gemm_pipe", "gemm_fit", "gemm_fit_int8")
 WAIT_STATES = 2
 STORE = re.compile(r"buffer_store_dwordx([34]) v\[(\d+):(\d+)\], (?:v\d+|off), s\[\d+:\d+\], (\S+)")
 
@@ -31,19 +32,18 @@ def _violations(lines):
     return found
 
 
-def _lines(name, tmp_path):
-    out = tmp_path / f"{name}.s"
-    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *build.COMMON, "-S", "--cuda-device-only", "-o", str(out),
-                    os.path.join(build.CSRC, f"{name}.hip")], check=True, capture_output=True)
-    lines = [l.split(";")[0].strip() for l in out.read_text().splitlines()]
-    return [l for l in lines if l and not l.startswith(".") and not l.endswith(":")]
+@pytest.fixture(scope="module", autouse=True)
+def _compiled():
+    with ThreadPoolExecutor(4) as ex:
+        list(ex.map(listing, SOURCES))
 
 
-def test_stores_wait_for_their_data(tmp_path):
-    with ThreadPoolExecutor(2) as ex:
-        for name, lines in zip(("gemm_codes", "gemm_pipe"), ex.map(lambda n: _lines(n, tmp_path), ("gemm_codes", "gemm_pipe"))):
-            assert sum(bool(STORE.match(l)) for l in lines) >= 64, name
-            assert not _violations(lines), (name, _violations(lines)[:3])
+@pytest.mark.parametrize("name", SOURCES)
+def test_stores_wait_for_their_data(name):
+    lines = [l.split(";")[0].strip() for l in listing(name).splitlines()]
+    lines = [l for l in lines if l and not l.startswith(".") and not l.endswith(":")]
+    assert sum(bool(STORE.match(l)) for l in lines) >= 64
+    assert not _violations(lines), _violations(lines)[:3]
 
 
 def test_scan_sees_both_faults():
