@@ -138,7 +138,9 @@ __global__ void __launch_bounds__(64 * WV, MINB) attention_mfma_kernel(const uin
     const uint16_t* qp = qkv + (row0 + qi_c) * qkv_stride + head * DH + lhalf * 8;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) fq[j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + j * 16));
-    // (used here, so that the wait for them stands here: inside the loops it would wait for the pieces on their way as well)
+    // (used here, so that the wait for them stands here: inside the loops it would wait for the pieces on their way as well.  They are the
+    // youngest requests: what has been fetched so far has landed behind this wait, so that the first counted wait below, and the second of
+    // ONE, are barriers only.  ONE with one barrier for both passes: 512 sequences of 128 tokens 154 -> 157 us, 32 over 32 heads 250 -> 256)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(fq[j]));
   }

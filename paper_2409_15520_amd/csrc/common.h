@@ -210,7 +210,7 @@ constexpr int kCodesTile = 256;                          // features of its tile
 hipError_t launch_gemm_codes(hipStream_t st, const MfmaGemmArgs& a);
 bool gemm_ring_supported(const MfmaGemmArgs& a);                             // gemm_ring.hip: 32 x 32 tiles, bf16 weights
 hipError_t launch_gemm_ring(hipStream_t st, const MfmaGemmArgs& a);
-// gemm_fit.hip: shapes 0 .. 5 (see there); the one that a product chosen by size takes, or -1
+// gemm_fit.hip: shapes 0 .. 6 (see there; 6: int8 256 x 256); the one that a product chosen by size takes, or -1
 bool gemm_fit_supported(const MfmaGemmArgs& a, int shape);
 int gemm_fit_shape(const MfmaGemmArgs& a, int tile);
 double gemm_fit_halves_gain(int d, int nqkv, int d_ffn, bool gate_up, bool int8, long T);   // a block's four products in one pass over what two halves should take

@@ -12,7 +12,8 @@
 //     step the block meets: all its fragments of this stage are in registers, so the stage may be fetched into again (K-tile kt + ST), and
 //     K-tile kt + 1, whose fetches were issued ST - 1 K-tiles ago, has landed and may be read.
 //   * The stream of K-tiles does not stop at a tile's end: its last ST K-tiles fetch the next tile's first ones, and the epilogue's stores
-//     are not waited for.
+//     are not waited for.  What an epilogue reads comes back in order behind those fetches: the residual, low-rank operands, rotary tables, and in
+//     nine of the 89 instances 2 to 26 spilled registers (192 x 256 with fp32 output, int8 256 x 256; none in a K loop).
 //   * The outputs leave the accumulators without LDS: two neighbouring 16-feature tiles exchange halves between lanes (one lane swap per
 //     dword), so that a lane holds 8 features of a token, and an instruction writes 64 contiguous bytes per token.
 // v_mfma_f32_16x16x32_bf16 gives the bits of two chained 32 x 32 x 16 ones and K runs upwards: the sums are those of every other tile.

@@ -204,8 +204,8 @@ __global__ void __launch_bounds__(WV * 64, NV <= 4 || WV == 8 ? 2 : 1) norm_lora
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, share = wave & 3, t0 = wave >> 2, lrow = lane & 31, lhalf = lane >> 5;
   const int m0 = blockIdx.x * 32;
 
-  // phase B: t = scale * x (A_hi + A_lo) for the block's copy; wave w owns K-elements 256 ch + 64 w + (0..63).  Its first factors
-  // (all of them if the row is short) are requested behind the rows of phase A and travel during it
+  // phase B: t = scale * x (A_hi + A_lo) for the block's copy; a wave owns K-elements 256 ch + 64 share + (0..63), of eight waves for the 32
+  // columns from 32 t0 on.  Its first factors (all of them if the row is short) are requested behind the rows of phase A and travel during it
   const int copy = m0 / a.rows_per_copy;
   const int R = a.n_targets * a.rank;
   const uint16_t* Ah[JW];
@@ -235,7 +235,7 @@ __global__ void __launch_bounds__(WV * 64, NV <= 4 || WV == 8 ? 2 : 1) norm_lora
   };
   f32x4 gg[NV], bb[NV];
 
-  // ---- phase A: rows m0 + 8 wave + (0..7), RB at a time
+  // ---- phase A: rows m0 + ROWS wave + (0 .. ROWS - 1), RB at a time
 #pragma unroll 1
   for (int r0 = 0; r0 < ROWS; r0 += RB) {
     f32x4 v[RB][NV];
@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(WV * 64, NV <= 4 || WV == 8 ? 2 : 1) norm_lora
     }
   }
   __syncthreads();                                       // every wave is done with the x tile: its memory takes the sums
-  float* part = (float*)smem;                            // [3][JT][16][64]: partial sums of waves 1..3
+  float* part = (float*)smem;                            // [3][JT][16][64]: partial sums of shares 1..3
   if (share > 0) {
 #pragma unroll
     for (int t = 0; t < JW; ++t)
