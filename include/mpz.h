@@ -377,9 +377,9 @@ mpz_status mpz_debug_dequant_nf4(const void* codes, const float* absmax, void* o
  * Invalidates the perturbed copies: call mpz_regen_noise again. */
 mpz_status mpz_debug_set_kernel_path(mpz_model* m, int32_t simple_only);
 
-/* Test hook: allow (default) or forbid the two-halves schedule of mpz_forward_perturbed: for small models (every
- * GEMM on the 128-wide tiles, label-subset loss, d_model < 2048) and some thousand stacked tokens, and for wider ones
- * without gate and up whose Q|K|V and up projections are a little over one round of 256-wide tiles, the pass is issued
+/* Test hook: allow (default) or forbid the two-halves schedule of mpz_forward_perturbed: label-subset loss, some thousand
+ * stacked tokens, and GEMM tiles whose last rounds would leave many CUs idle in one pass (d_model < 2048, or wider without gate
+ * and up where Q|K|V and up are a little over one round of 256-wide tiles; not 4-bit weights): the pass is issued
  * as two halves of q copies each on the caller's stream and on an internal second stream of the same priority, forked
  * from and joined to the caller's stream by events, so that the halves' kernels overlap.  Losses are bit-identical
  * either way. */

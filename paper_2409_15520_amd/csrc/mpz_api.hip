@@ -1049,10 +1049,10 @@ mpz_status mpz_regen_noise(mpz_model* m, uint64_t seed, uint32_t step, int32_t q
 
 namespace {
 
-// Small models (every GEMM of the pass stays on the 128-wide tiles) leave the chip part-empty around each kernel's
-// first loads and last stores.  The copies are independent (Section 3), so the pass is issued as two halves of
-// n/2 copies on two streams, layer by layer: the halves' kernels overlap and fill each other's edges (12 layers of d = 768, 8192 tokens, on 128 x 128 tiles:
-// 2.98 -> 2.68 ms per step).  Every copy's numbers are what the one-stream pass gives (a copy's rows never mix
+// Products of a few rounds of CUs leave the chip part-empty around each kernel's first loads and last stores and in their last
+// round.  The copies are independent (Section 3), so the pass is issued as two halves of
+// n/2 copies on two streams, layer by layer: the halves' kernels overlap and fill each other's edges (two_halves_pay has the sizes
+// and times).  Every copy's numbers are what the one-stream pass gives (a copy's rows never mix
 // with another's).  The second stream forks from and joins the caller's stream through events, so the call keeps
 // its ordering guarantees; it is not used while kernels are being timed one by one.
 bool use_two_halves(mpz_model* m, int E, int S) {
