@@ -33,8 +33,9 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 // keeps the reads of either operand out of each other's banks (K: 32 rows at one chunk; V: four rows at four chunks).
 // WV waves of 32 queries per block.  ONE: all keys fit half the ring (the launcher knows): each piece is fetched once, all at the start, and
 // the scores of pass 1 stay in registers.
-// What bounds it: instruction issue (a SIMD issues 63 % of the time, vector instructions 36 %: one fma and one exp2 at a quarter
-// of the rate per score) beside waits for the chain scores -> exp2 -> P V; the matrix cores are busy 27 % of it.  Few scalar instructions
+// What bounds it: no unit by itself.  128 x 512 tokens, heads of 64: a SIMD issues 65 % of the time (vector instructions 37 %: one fma and one
+// exp2 at a quarter of the rate per score; scalar 18 %), the matrix cores are busy 28 %, and a wave stands at waits for half of its
+// time (256 tokens: 47 %, 15 %; heads of 128: 37 %, 22 %): the chain scores -> exp2 -> P V of the waves that are there.  Few scalar instructions
 // matter therefore: constant waits, no bookkeeping of what is on its way (61 a tile instead of 114: 363 -> 343 us).  Against the form that moved K
 // and V through registers, with the same bits (us; sequences x tokens, heads over key-value heads of columns): 128 x 512, 32 / 4 of 64 397 -> 330,
 // 64 x 256 74 -> 54, 64 x 96 21.6 -> 15.9, 64 x 128, 12 / 12 of 64 14.0 -> 10.8, 16 x 512, 32 / 32 of 128 127 -> 93, 8 x 480, 20 / 20 of 128 51 -> 34.
